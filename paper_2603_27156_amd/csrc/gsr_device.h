@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
+#include <utility>
 
 namespace gsr {
 
@@ -249,6 +250,7 @@ struct CsrView {
     const int32_t* rp;
     const int32_t* ci;
     const float* av;
+    const uint8_t* er;            // row of the entry modulo 16: its row in its 16-row tile
     // split plan of very long rows
     const int32_t* hub_rows;
     const int32_t* hub_cptr;
@@ -259,6 +261,7 @@ struct CsrView {
     const int32_t* heavy;
     int32_t n_heavy;
     int32_t heavy_edges;
+    int32_t heavy_ptr[9];         // the entries of the list in every eighth of the tiles (an XCD's share of a sweep)
 };
 
 __device__ __forceinline__ int find_hub(const CsrView& g, int row) {
@@ -270,24 +273,65 @@ __device__ __forceinline__ int find_hub(const CsrView& g, int row) {
     return lo;
 }
 
+// acc + partial rows q .. q1 - 1 of column c, added in chunk order, sixteen requested at a time.  The last batch is a
+// whole one too, with zeros in the places past the end: one partial row after the other it was a round trip to memory
+// each (30k nodes, eight nets of 5,000 sinks in one tile: 54 -> 38 us per launch of a tile kernel).
+template <int DG>
+__device__ __forceinline__ float hub_chunks_sum(const float* __restrict__ part, int q, int q1, int c, float acc) {
+    for (; q < q1; q += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(q + u < q1 ? q + u : q1 - 1) * DG + c];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc += q + u < q1 ? v[u] : 0.f;
+    }
+    return acc;
+}
+
 // sum of the first-pass partial rows of hub row `row`, in chunk order
 template <int DG>
 __device__ __forceinline__ float hub_row_sum(const CsrView& g, const float* __restrict__ part, int row, int c) {
     const int h = find_hub(g, row);
-    // sixteen partial rows in flight at a time; added in chunk order, so the sum does not depend
-    // on the unrolling
-    const int q1 = g.hub_cptr[h + 1];
-    int q = g.hub_cptr[h];
-    float acc = 0.f;
-    for (; q + 16 <= q1; q += 16) {
-        float v[16];
+    return hub_chunks_sum<DG>(part, g.hub_cptr[h], g.hub_cptr[h + 1], c, 0.f);
+}
+
+// ---- 16-row tiles in LDS ---------------------------------------------------------------------------------
+// Row stride of a tile of 16 x DG floats: a multiple of four words, so that adjacent columns move as 16-byte pieces, and
+// four more than DG, which spreads the rows of a column over the banks.
+template <int DG>
+constexpr int tile_ld() { return DG + 4; }
+typedef float f32v2 __attribute__((ext_vector_type(2)));
+typedef float f32v4 __attribute__((ext_vector_type(4)));
+// CPL adjacent columns (the first a multiple of CPL) between an LDS tile and registers
+template <int CPL>
+__device__ __forceinline__ void lds_load(const float* p, float (&v)[CPL]) {
+    if constexpr (CPL == 1) {
+        v[0] = *p;
+    } else if constexpr (CPL == 2) {
+        const f32v2 t = *reinterpret_cast<const f32v2*>(p);
+        v[0] = t[0]; v[1] = t[1];
+    } else {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(q + u) * DG + c];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) acc += v[u];
+        for (int c = 0; c < CPL; c += 4) {
+            const f32v4 t = *reinterpret_cast<const f32v4*>(p + c);
+            v[c] = t[0]; v[c + 1] = t[1]; v[c + 2] = t[2]; v[c + 3] = t[3];
+        }
     }
-    for (; q < q1; ++q) acc += part[(size_t)q * DG + c];
-    return acc;
+}
+template <int CPL>
+__device__ __forceinline__ void lds_store(float* p, const float (&v)[CPL]) {
+    if constexpr (CPL == 1) {
+        *p = v[0];
+    } else if constexpr (CPL == 2) {
+        f32v2 t; t[0] = v[0]; t[1] = v[1];
+        *reinterpret_cast<f32v2*>(p) = t;
+    } else {
+#pragma unroll
+        for (int c = 0; c < CPL; c += 4) {
+            f32v4 t; t[0] = v[c]; t[1] = v[c + 1]; t[2] = v[c + 2]; t[3] = v[c + 3];
+            *reinterpret_cast<f32v4*>(p + c) = t;
+        }
+    }
 }
 
 // ---- tile gathers on the matrix cores ------------------------------------------------------------------
@@ -763,7 +807,7 @@ __device__ __forceinline__ void gather_records_rows(const CsrView& g, const floa
                                                     int e_b, const int* s_rp, RecEdge* ebuf, uint8_t* rbuf, int lane,
                                                     float* st, const DealLutF* lut = nullptr) {
     using M = typename MaskOf<DG>::type;
-    constexpr int CPL = DG / 16, LR = DG + 1;
+    constexpr int CPL = DG / 16, LR = tile_ld<DG>();
     const int i16 = lane & 15, kk = lane >> 4, bp = CPL * i16;
     const uint32_t sh = bp & 31;
     const bool upper = bp >= 32;
@@ -876,71 +920,203 @@ __device__ __forceinline__ void gather_records_rows(const CsrView& g, const floa
     }
 }
 
-// The same for a dense float32 plane X (row stride ld): st += P * X over the edges [e_a, e_b) of ordinary rows.
+// The same sums for float32 records with a lane per kept value (Section 4.1, eq. (10)).  Beside its k values a record
+// holds the column of each as a byte; the value of slot t of a neighbour belongs to lane t of a group of sixteen, which
+// adds a_ij * value to that column of the destination row's sums in LDS: read, fused multiply-add, written back.  (A lane
+// that owns columns instead has to find the window of slots that may hold them from the neighbour's mask - a round trip to
+// memory before the values can be requested -, load four times the record's bytes and deal them out: some 24 vector
+// instructions per four edges and five round trips per 64 edges where this takes about eight and one: 1M nodes, D/C = 64,
+// k = 16: forward kernel 280 -> 223 us, inverse 298 -> 246, vector instructions per tile 1,490 -> 950.  What is left is
+// latency: a wave waits for two thirds of its time, and LDS holds no more waves.)
+// The staged edges of a round are cut into four equal runs, one per lane group; a run's edges add straight into the rows
+// of the tile, except those of the run's first row, which the run before may share: they add into a row of the group's
+// own (tile rows 16 .. 19 of st), and those four rows join the tile at the end of the round, the rows that end inside
+// their run before the rows that fill one.  So no two groups touch one row in the same step, the values of one record
+// are in different columns, and the order of the additions is fixed by the edge list alone.
+// Lane s of a group holds edge s of the group's run, and a step takes its edge from there by a row broadcast of the
+// lanes (through LDS it took as much of the LDS pipe as the additions themselves).
+// st: 20 rows, zeroed by the caller (rows 16 .. 19 are left zero), and 64 words behind them where lanes without a value
+// add.  A run is a whole number of ROUND steps; the places past the last edge hold that edge once more with a_ij = 0.
+// k above 16 takes ceil(k / 16) passes over the edges of a round.  FEW: four steps' loads in flight instead of a whole
+// run's (for kernels without registers to spare).
+constexpr int GATHER_ROWS = 20;
+template <int DG>
+constexpr int gather_floats() { return GATHER_ROWS * tile_ld<DG>() + 64; }
+typedef __attribute__((address_space(3))) float lds_float;
+
+// v of lane S of this lane's row of sixteen
+template <int S>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + S, 0xF, 0xF, true);
+}
+
+// steps S0 .. S0 + NB - 1 of a run, value t of every record: all loads first, then the additions in edge order
+template <int S0, int NB, typename T, int... U>
+__device__ __forceinline__ void values_run(const T* __restrict__ vals, const uint8_t* __restrict__ cols, uint32_t off0, float a,
+                                           uint32_t row, uint32_t t, bool has, uint32_t dump, std::integer_sequence<int, U...>) {
+    T v[NB];
+    uint32_t col[NB];
+    ((v[U] = vals[(size_t)(row_lane<S0 + U>(off0) + t)], col[U] = cols[(size_t)(row_lane<S0 + U>(off0) + t)]), ...);
+    wave_sync();
+    (([&] {
+         const uint32_t at = row_lane<S0 + U>(row) + 4u * col[U];
+         lds_float* s = (lds_float*)(uintptr_t)(has ? at : dump);
+         *s = __builtin_fmaf(__uint_as_float(row_lane<S0 + U>(__float_as_uint(a))), to_float(v[U]), *s);
+         wave_sync();
+     }()),
+     ...);
+}
+
+// The edges of one round as the lanes hold them: lane s of group kk the s-th edge of the kk-th of four equal runs of the
+// (up to 64) edges from eb on.
+struct RunEdges {
+    int j, r;        // neighbour, row of the tile
+    float a;         // a_ij (of the last edge in the places past it)
+    int steps;       // edges per run, at most 16 (wave-uniform)
+};
+template <int ROUND>
+__device__ __forceinline__ RunEdges run_edges(const CsrView& g, int eb, int e_b, int lane) {
+    RunEdges d;
+    const int cnt = e_b - eb < 64 ? e_b - eb : 64, slot = lane & 15;
+    d.steps = (((cnt + 3) >> 2) + ROUND - 1) / ROUND * ROUND;
+    const int e = eb + (lane >> 4) * d.steps + (slot < d.steps ? slot : d.steps - 1);
+    const int ec = e < e_b ? e : e_b - 1;
+    d.j = __builtin_nontemporal_load(g.ci + ec);
+    d.a = __builtin_nontemporal_load(g.av + ec);
+    d.r = __builtin_nontemporal_load(g.er + ec);
+    return d;
+}
+
+template <int DG, int ROUND, bool FEW, typename T>
+__device__ __forceinline__ void gather_values_rows(const CsrView& g, const T* __restrict__ vals, const uint8_t* __restrict__ cols,
+                                                   int k, int e_a, int e_b, int lane, float* st) {
+    constexpr int LR = tile_ld<DG>();
+    static_assert(ROUND == 4 || ROUND == 8, "a run must fit the sixteen lanes of a group");
+    const int slot = lane & 15, kk = lane >> 4;
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_float*)st, dump = base + 4u * (uint32_t)(GATHER_ROWS * LR + lane);
+    RunEdges next = run_edges<ROUND>(g, e_a, e_b, lane);
+    for (int eb = e_a; eb < e_b; eb += 64) {
+        const int steps = next.steps, j = next.j, r = next.r;
+        const float a = eb + kk * steps + slot < e_b ? next.a : 0.f;      // (lanes past the run: not used)
+        int head[4], tail[4];                              // first and last row of every run
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            head[q] = __builtin_amdgcn_readlane(r, 16 * q);
+            tail[q] = __builtin_amdgcn_readlane(r, 16 * q + steps - 1);
+        }
+        const uint32_t off0 = (uint32_t)j * (uint32_t)k;
+        const uint32_t row = base + 4u * (uint32_t)((r == (int)row_lane<0>((uint32_t)r) ? 16 + kk : r) * LR);
+        if (eb + 64 < e_b) next = run_edges<ROUND>(g, eb + 64, e_b, lane);     // arrives while this round is added
+        for (int t0 = 0; t0 < k; t0 += 16) {
+            const bool has = t0 + slot < k;
+            const uint32_t t = (uint32_t)(has ? t0 + slot : t0);
+            auto run = [&](auto nbc, auto s0c) {
+                constexpr int NB = decltype(nbc)::value;
+                // (keeps the variants apart: folded together, every load is waited for before the next)
+                asm volatile("; %0 steps" ::"n"(NB));
+                values_run<decltype(s0c)::value, NB>(vals, cols, off0, a, row, t, has, dump, std::make_integer_sequence<int, NB>{});
+            };
+            constexpr std::integral_constant<int, 0> s0{};
+            if constexpr (FEW) {
+                run(std::integral_constant<int, 4>{}, s0);
+                if (steps > 4) run(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+                if (steps > 8) run(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
+                if (steps > 12) run(std::integral_constant<int, 4>{}, std::integral_constant<int, 12>{});
+            } else if constexpr (ROUND == 4) {
+                if (steps == 4) run(std::integral_constant<int, 4>{}, s0);
+                else if (steps == 8) run(std::integral_constant<int, 8>{}, s0);
+                else if (steps == 12) run(std::integral_constant<int, 12>{}, s0);
+                else run(std::integral_constant<int, 16>{}, s0);
+            } else {
+                if (steps == 8) run(std::integral_constant<int, 8>{}, s0);
+                else run(std::integral_constant<int, 16>{}, s0);
+            }
+        }
+        // the groups' own rows join the tile
+        if (lane < DG) {
+            float sum[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sum[q] = st[(16 + q) * LR + lane];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) st[(16 + q) * LR + lane] = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (head[q] != tail[q]) st[head[q] * LR + lane] += sum[q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (head[q] == tail[q]) st[head[q] * LR + lane] += sum[q];
+        }
+        wave_sync();
+    }
+}
+
+// The same for a dense float32 plane X (row stride ld): st += P * X over the edges [e_a, e_b) of ordinary rows, lane j of
+// a group keeping a running sum of its CPL columns for the run's present row in registers and adding it to the row of the
+// tile when the row changes and at the end of the round.  Two groups never add to one row in the same instruction: inside
+// a round only the last run that holds a row sees it end; the sums left at the end of the round are added group by group.
+// Lane s of a group holds edge s of the run (row_lane hands it to the others).
+template <int DG, int S0, int... U>
+__device__ __forceinline__ void dense_run(const float* __restrict__ xl, uint32_t ldu, uint32_t j, uint32_t a, uint32_t r, float* mine,
+                                          uint32_t& cur, float (&run)[DG / 16], std::integer_sequence<int, U...>) {
+    constexpr int CPL = DG / 16, LR = tile_ld<DG>();
+    uint32_t w[sizeof...(U)][CPL];
+    (load_words<CPL>(xl + (size_t)row_lane<S0 + U>(j) * ldu, w[U]), ...);
+    (([&] {
+         const uint32_t row = row_lane<S0 + U>(r);
+         if (row != cur) {
+             float was[CPL];
+             lds_load<CPL>(mine + cur * LR, was);
+#pragma unroll
+             for (int cb = 0; cb < CPL; ++cb) {
+                 was[cb] += run[cb];
+                 run[cb] = 0.f;
+             }
+             lds_store<CPL>(mine + cur * LR, was);
+             cur = row;
+         }
+         const float p = __uint_as_float(row_lane<S0 + U>(a));
+#pragma unroll
+         for (int cb = 0; cb < CPL; ++cb) run[cb] = __builtin_fmaf(p, __uint_as_float(w[U][cb]), run[cb]);
+     }()),
+     ...);
+}
+
 template <int DG, int GB>
 __device__ __forceinline__ void gather_dense_rows(const CsrView& g, const float* __restrict__ x, int64_t ld, int e_a, int e_b,
-                                                  const int* s_rp, EdgeRec* ebuf, int lane, float* st) {
-    constexpr int CPL = DG / 16, LR = DG + 1;
+                                                  int lane, float* st) {
+    constexpr int CPL = DG / 16, LR = tile_ld<DG>();
+    static_assert(GB == 8, "a run is one or two batches");
     const int i16 = lane & 15, kk = lane >> 4;
     const float* xl = x + CPL * i16;
     const uint32_t ldu = (uint32_t)ld;
     float* mine = st + CPL * i16;
     for (int eb = e_a; eb < e_b; eb += 64) {
-        const int e = eb + lane;
-        const bool ok = e < e_b;
-        EdgeRec me;
-        const int ec = ok ? e : e_b - 1;                 // (places past the last edge: the last edge once more with a_ij = 0)
-        me.j = __builtin_nontemporal_load(g.ci + ec);
-        me.a = ok ? __builtin_nontemporal_load(g.av + ec) : 0.f;
-        me.r = tile_row_of(s_rp, ec);
-        me.pad = 0;
-        wave_sync();          // readers of the previous round are done
-        ebuf[lane] = me;
-        wave_sync();
-        const int cnt = e_b - eb < 64 ? e_b - eb : 64;
-        const int steps = (((cnt + 3) >> 2) + GB - 1) / GB * GB;
-        static_assert(16 % GB == 0, "a run must end inside the 64 staged places");
-        const int first = kk * steps;
-        int cur = ebuf[first].r;
+        const int cnt = e_b - eb < 64 ? e_b - eb : 64;     // wave-uniform
+        const int steps = (((cnt + 3) >> 2) + GB - 1) / GB * GB;      // edges per run: 8 or 16
+        const int e = eb + kk * steps + (i16 < steps ? i16 : steps - 1);
+        const int ec = e < e_b ? e : e_b - 1;              // (places past the last edge: the last edge once more with a_ij = 0)
+        const uint32_t j = (uint32_t)__builtin_nontemporal_load(g.ci + ec);
+        const float av = __builtin_nontemporal_load(g.av + ec);
+        const uint32_t r = __builtin_nontemporal_load(g.er + ec);
+        const uint32_t a = __float_as_uint(e < e_b ? av : 0.f);
+        uint32_t cur = row_lane<0>(r);
         float run[CPL];
 #pragma unroll
         for (int cb = 0; cb < CPL; ++cb) run[cb] = 0.f;
-        for (int s0 = 0; s0 < steps; s0 += GB) {
-            uint32_t w[GB][CPL];
-            float p[GB];
-            int row[GB];
-#pragma unroll
-            for (int u = 0; u < GB; ++u) {
-                const EdgeRec er = ebuf[first + s0 + u];
-                load_words<CPL>(xl + (size_t)(uint32_t)er.j * ldu, w[u]);
-                p[u] = er.a;
-                row[u] = er.r;
-            }
-#pragma unroll
-            for (int u = 0; u < GB; ++u) {
-                if (row[u] != cur) {
-                    float was[CPL];            // (all reads before the writes: one LDS round trip, not one per pair)
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) was[cb] = mine[cur * LR + cb];
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) {
-                        mine[cur * LR + cb] = was[cb] + run[cb];
-                        run[cb] = 0.f;
-                    }
-                    cur = row[u];
-                }
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) run[cb] = __builtin_fmaf(p[u], __uint_as_float(w[u][cb]), run[cb]);
-            }
-        }
+        dense_run<DG, 0>(xl, ldu, j, a, r, mine, cur, run, std::make_integer_sequence<int, GB>{});
+        if (steps > GB) dense_run<DG, GB>(xl, ldu, j, a, r, mine, cur, run, std::make_integer_sequence<int, GB>{});
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
             wave_sync();
             if (kk == gq) {
+                float was[CPL];
+                lds_load<CPL>(mine + cur * LR, was);
 #pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) mine[cur * LR + cb] += run[cb];
+                for (int cb = 0; cb < CPL; ++cb) was[cb] += run[cb];
+                lds_store<CPL>(mine + cur * LR, was);
             }
         }
+        wave_sync();
     }
 }
 
@@ -948,12 +1124,13 @@ template <int DG, bool FAST = true>
 __device__ __forceinline__ void hub_rows_fill(const CsrView& g, const float* __restrict__ hub_part, int r0, const int* s_rp,
                                               float* st, int lane);
 
-// H of the tile into st through gather_records_rows: st is cleared, the runs of ordinary rows are added into it,
+// H of the tile into st through a row-wise gather: st (ROWS rows of it) is cleared, the runs of ordinary rows are added into it,
 // split rows receive the sum of their first-pass partial rows afterwards.
-template <int DG, bool FAST = true, typename Range>
+template <int DG, bool FAST = true, int ROWS = 16, typename Range>
 __device__ __forceinline__ void tile_gather_rows(const CsrView& g, const float* __restrict__ hub_part, bool has_hub, int r0,
                                                  const int* s_rp, float* st, int lane, Range range) {
-    for (int i = lane; i < 16 * (DG + 1); i += 64) st[i] = 0.f;
+    static_assert(ROWS * tile_ld<DG>() % 4 == 0, "cleared in pieces of 16 bytes");
+    for (int i = 4 * lane; i < ROWS * tile_ld<DG>(); i += 256) *reinterpret_cast<f32v4*>(st + i) = f32v4{0.f, 0.f, 0.f, 0.f};
     wave_sync();
     tile_ranges(g, has_hub, s_rp, range);
     wave_sync();
@@ -984,20 +1161,10 @@ __device__ __forceinline__ void hub_rows_fill(const CsrView& g, const float* __r
             q1s = g.hub_cptr[h + 1];
         }
         for (int r = 0; r < 16; ++r) {
-            int q = __builtin_amdgcn_readlane(q0s, r);
-            const int q1 = __builtin_amdgcn_readlane(q1s, r);
+            const int q = __builtin_amdgcn_readlane(q0s, r), q1 = __builtin_amdgcn_readlane(q1s, r);
             if (q1 <= q) continue;                 // not a split row
-            const int cc = lane < DG ? lane : 0;
-            float acc = 0.f;
-            for (; q + 16 <= q1; q += 16) {
-                float v[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) v[u] = hub_part[(size_t)(q + u) * DG + cc];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) acc += v[u];
-            }
-            for (; q < q1; ++q) acc += hub_part[(size_t)q * DG + cc];
-            if (lane < DG) st[r * (DG + 1) + lane] = acc;
+            const float acc = hub_chunks_sum<DG>(hub_part, q, q1, lane < DG ? lane : 0, 0.f);
+            if (lane < DG) st[r * tile_ld<DG>() + lane] = acc;
         }
         return;
     }
@@ -1025,25 +1192,16 @@ __device__ __forceinline__ void hub_rows_fill(const CsrView& g, const float* __r
             for (int u = 0; u < HUB_FILL_ROWS; ++u) {
                 const int r = rb + u;
                 const int q = __builtin_amdgcn_readlane(q0v, r) + j, q1 = __builtin_amdgcn_readlane(q1v, r);
-                if (q < q1 && lane < DG) st[r * (DG + 1) + lane] = (j == 0 ? 0.f : st[r * (DG + 1) + lane]) + v[u];
+                if (q < q1 && lane < DG) st[r * tile_ld<DG>() + lane] = (j == 0 ? 0.f : st[r * tile_ld<DG>() + lane]) + v[u];
             }
         }
     }
     // rows of more chunks than that go on one by one, sixteen loads in flight
     for (int r = 0; r < 16; ++r) {
-        int q = __builtin_amdgcn_readlane(q0v, r) + HUB_FILL_DEPTH;
-        const int q1 = __builtin_amdgcn_readlane(q1v, r);
+        const int q = __builtin_amdgcn_readlane(q0v, r) + HUB_FILL_DEPTH, q1 = __builtin_amdgcn_readlane(q1v, r);
         if (q1 <= q) continue;
-        float acc = st[r * (DG + 1) + c];
-        for (; q + 16 <= q1; q += 16) {
-            float v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = hub_part[(size_t)(q + u) * DG + c];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) acc += v[u];
-        }
-        for (; q < q1; ++q) acc += hub_part[(size_t)q * DG + c];
-        if (lane < DG) st[r * (DG + 1) + lane] = acc;
+        const float acc = hub_chunks_sum<DG>(hub_part, q, q1, c, st[r * tile_ld<DG>() + c]);
+        if (lane < DG) st[r * tile_ld<DG>() + lane] = acc;
     }
 }
 
@@ -1064,25 +1222,28 @@ __device__ __forceinline__ void tile_ranges(const CsrView& g, bool has_hub, cons
     }
 }
 
-// H of the tile into st (16 rows of DG+1 floats): the runs of ordinary rows go through
+// H of the tile into st (16 rows, row stride tile_ld): the runs of ordinary rows go through
 // `range(e_a, e_b)`, which accumulates into acc (D[4 (lane / 16) + reg][j] of column block cb,
 // column = CPL j + cb); split rows receive the sum of their first-pass partial rows afterwards.
 template <int DG, bool FAST = true, typename Range>
 __device__ __forceinline__ void tile_gather(const CsrView& g, const float* __restrict__ hub_part, bool has_hub, int r0,
                                             const int* s_rp, float* st, int lane, f32x4 (&acc)[DG / 16], Range range) {
-    constexpr int CPL = DG / 16, LR = DG + 1;
+    constexpr int CPL = DG / 16, LR = tile_ld<DG>();
 #pragma unroll
     for (int cb = 0; cb < CPL; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     tile_ranges(g, has_hub, s_rp, range);
 #pragma unroll
-    for (int cb = 0; cb < CPL; ++cb)
+    for (int r = 0; r < 4; ++r) {
+        float v[CPL];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) st[(4 * (lane >> 4) + r) * LR + CPL * (lane & 15) + cb] = acc[cb][r];
+        for (int cb = 0; cb < CPL; ++cb) v[cb] = acc[cb][r];
+        lds_store<CPL>(st + (4 * (lane >> 4) + r) * LR + CPL * (lane & 15), v);
+    }
     if (has_hub) hub_rows_fill<DG, FAST>(g, hub_part, r0, s_rp, st, lane);
 }
 
 // ---- 16-row MFMA tiles -------------------------------------------------------------------------
-// A wave multiplies its 16 x DG tile (staged in LDS, row stride DG+1) by a DG x DG matrix with
+// A wave multiplies its 16 x DG tile (staged in LDS, row stride tile_ld) by a DG x DG matrix with
 // v_mfma_f32_16x16x4_f32:
 //   A[i][kk]: lane = kk*16 + i;  B[kk][j]: lane = kk*16 + j;  D[4*(lane/16)+r][lane%16] in reg r.
 // The DG x DG weight matrix (row stride ldw in memory: DG, or more when it is a block of a wider matrix) sits in LDS (odd row stride DG + 1, which spreads the four k-rows of a
@@ -1123,7 +1284,7 @@ __device__ __forceinline__ void load_w_lds(const float* __restrict__ w, int ldw,
     __syncthreads();
 }
 
-// acc = tile (16 x DG, LDS, row stride DG+1) * B (DG x DG, LDS), left in the tile register
+// acc = tile (16 x DG, LDS, row stride tile_ld) * B (DG x DG, LDS), left in the tile register
 // layout: acc[cb][reg] = product[row 4 reg + lane / 16][column CPL (lane % 16) + cb].
 template <int DG>
 __device__ __forceinline__ void mfma_tile(const float* st, const WLds<DG>& wl, f32x4 (&acc)[DG / 16]) {
@@ -1134,7 +1295,7 @@ __device__ __forceinline__ void mfma_tile(const float* st, const WLds<DG>& wl, f
     for (int cb = 0; cb < CPL; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < DG / 4; ++s) {
-        const float a = st[arow * (DG + 1) + 4 * s + kk];
+        const float a = st[arow * tile_ld<DG>() + 4 * s + kk];
 #pragma unroll
         for (int cb = 0; cb < CPL; ++cb) {
             const float b = wl.w[(4 * s + kk) * WLds<DG>::WP + CPL * i + cb];
@@ -1212,7 +1373,7 @@ __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int l
     __syncthreads();
 }
 
-// acc = tile (16 x DG float32, LDS, row stride DG+1) * W, in the tile register layout of mfma_tile.
+// acc = tile (16 x DG float32, LDS, row stride tile_ld) * W, in the tile register layout of mfma_tile.
 template <int DG>
 __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& wl, f32x4 (&acc)[DG / 16]) {
     constexpr int CPL = DG / 16;
@@ -1223,8 +1384,7 @@ __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& 
 #pragma unroll
     for (int s = 0; s < DG / 16; ++s) {
         float a[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = st[arow * (DG + 1) + 16 * s + 4 * kk + u];
+        lds_load<4>(st + arow * tile_ld<DG>() + 16 * s + 4 * kk, a);
         bf16x4 ah, am, al;
         split_p4(a, ah, am, al);
 #pragma unroll
@@ -1258,7 +1418,7 @@ __device__ __forceinline__ void mfma_outer_b3(const float* st_h, const float (&g
     for (int mb = 0; mb < DG / 16; ++mb) {
         float a[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = st_h[(4 * u + kk) * (DG + 1) + 16 * mb + j];
+        for (int u = 0; u < 4; ++u) a[u] = st_h[(4 * u + kk) * tile_ld<DG>() + 16 * mb + j];
         bf16x4 ah, am, al;
         split_p4(a, ah, am, al);
 #pragma unroll
@@ -1285,7 +1445,7 @@ __device__ __forceinline__ void mfma_outer(const float* st_h, const float (&gy)[
         const int nrow = 4 * ks + (lane >> 4);
 #pragma unroll
         for (int mb = 0; mb < DG / 16; ++mb) {
-            const float a = st_h[nrow * (DG + 1) + 16 * mb + (lane & 15)];
+            const float a = st_h[nrow * tile_ld<DG>() + 16 * mb + (lane & 15)];
 #pragma unroll
             for (int ob = 0; ob < DG / 16; ++ob)
                 acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, gy[ks][ob], acc[mb][ob], 0, 0, 0);
@@ -1301,6 +1461,7 @@ struct Record {
     using M = typename MaskOf<DG>::type;
     T* vals;        // [n][k]
     M* mask;        // [n]
+    uint8_t* cols;  // [n][k]: column of every value (NULL: not kept)
 };
 
 // ---- the k-th largest key of a row when k is a quarter of its width -------------------------------
@@ -1486,7 +1647,7 @@ __device__ __forceinline__ float record_scale(const float (&x)[DG / 4], int norm
 }
 
 // GS of the 16 rows of an LDS tile and their records (Section 4.1; record layout of Section 4.3).
-// st holds the rows as they read back from memory (16 x (DG+1) floats, rows past the end zero).
+// st holds the rows as they read back from memory (16 x tile_ld floats, rows past the end zero).
 // Lane (r, q) takes the quarter q of row r into registers, so the 16 searches for the k-th largest
 // key run side by side in vector registers on an order-preserving integer image of the values
 // (select_quarter): a selection network when k is a quarter of the width, else interval bisection,
@@ -1500,18 +1661,21 @@ __device__ __forceinline__ float record_scale(const float (&x)[DG / 4], int norm
 // application selected (Section 4.2 keeps the indices of the forward pass) and only the values
 // are taken, from the present rows.  st is overwritten.  With idx_out (and ist, 16 * DG words of
 // LDS scratch) the kept column numbers are written as well, [n][k] in ascending order, and
-// out.mask may be NULL.
-template <int DG, typename T>
+// out.mask may be NULL.  With COLS the kept columns are written as bytes too, [n][k] like the values.
+// Floats of LDS emit_tile works with: the tile, 64 dump words, and with COLS a byte for every one of those.
+template <int DG, bool COLS>
+constexpr int emit_floats() { return (16 * tile_ld<DG>() + 64) + (COLS ? (16 * tile_ld<DG>() + 64) / 4 : 0); }
+
+template <int DG, typename T, bool COLS = false>
 __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int norm, float eps, const Record<DG, T>& out,
                                           bool given, int lane, int32_t* idx_out = nullptr, int* ist = nullptr,
                                           TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}) {
     using M = typename MaskOf<DG>::type;
-    constexpr int QW = DG / 4, LR = DG + 1;
+    constexpr int QW = DG / 4, LR = tile_ld<DG>();
     constexpr int KS = sizeof(T) == 2 ? 16 : 0;   // bf16 values: the low 16 key bits are zero
     const int r = lane & 15, q = lane >> 4;
     float x[QW];
-#pragma unroll
-    for (int j = 0; j < QW; ++j) x[j] = st[r * LR + q * QW + j];
+    lds_load<QW>(st + r * LR + q * QW, x);
     uint32_t msel;
     if (given) {
         const M m = out.mask[r0 + r < n ? r0 + r : n - 1];
@@ -1551,11 +1715,14 @@ __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int n
     wave_sync();   // every lane holds its quarter: the tile can be reused for the compacted values
     // a kept value goes to its slot, a dropped one to the lane's dump word: word number = dump + bit * (slot - dump)
     const int dump = 16 * LR + lane;
+    uint8_t* cst = reinterpret_cast<uint8_t*>(st + 16 * LR + 64);      // (COLS: the column beside every word)
     int ahead = slot - dump;
 #pragma unroll
     for (int j = 0; j < QW; ++j) {
         const int bit = (int)((msel >> j) & 1u);
-        st[dump + __mul24(bit, ahead)] = x[j] * scale;
+        const int at = dump + __mul24(bit, ahead);
+        st[at] = x[j] * scale;
+        if constexpr (COLS) cst[at] = (uint8_t)(q * QW + j);
         if (idx_out && bit) ist[dump + ahead] = q * QW + j;
         ahead += bit;
     }
@@ -1563,6 +1730,10 @@ __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int n
     const int rows = min(16, n - r0), total = rows * k;
     T* dst = out.vals + (size_t)r0 * k;
     for (int i = lane; i < total; i += 64) dst[i] = from_float<T>(st[i]);
+    if constexpr (COLS) {        // whole words: the array is padded, and 16 k bytes per tile keep r0 * k a multiple of four
+        uint32_t* dc = reinterpret_cast<uint32_t*>(out.cols + (size_t)r0 * k);
+        for (int i = lane; 4 * i < total; i += 64) dc[i] = reinterpret_cast<const uint32_t*>(cst)[i];
+    }
     if (idx_out)
         for (int i = lane; i < total; i += 64) idx_out[(size_t)r0 * k + i] = ist[i];
     if (!given && out.mask && q == 0 && r < rows) out.mask[r0 + r] = mask;
@@ -1653,20 +1824,28 @@ __device__ __forceinline__ void tile_finish(const TileDraws& d) {
 // ---- the long tiles first -----------------------------------------------------------------------------
 // A tile with many stored entries takes many times longer than a median one.  Met late in a sweep it makes
 // the kernel's tail; met twice by one wave of a fixed sweep it makes that wave the last.  The layer kernels
-// therefore deal the listed heavy tiles out first, wave w of the grid taking entries w, w + waves, .. of the
-// list, and pass them over in the sweep that follows (a tile is heavy by its row pointers alone, so the sweep
-// needs no flag; the check sits after the tile's own rows have been requested, which costs a few wasted loads).  The assignment is the same on every run.
+// therefore deal such tiles out first, an XCD's waves taking the listed tiles of the XCD's own eighth in turn, and
+// pass them over in the sweep that follows (a tile is heavy by its row pointers alone, so the sweep
+// needs no flag; the check sits after the tile's own rows have been requested, which costs a few wasted loads).
+// The assignment is the same on every run.
 struct TileDeal {
     int at;        // this wave's next entry of the list
-    int waves;     // waves of the grid
+    int step;      // waves of the XCD
+    int end;       // one past the XCD's last entry
     bool on;       // still dealing
 };
 __device__ __forceinline__ TileDeal tile_deal(const CsrView& g) {
+    const int xcd = blockIdx.x & 7, wpw = (int)(blockDim.x >> 6);
     TileDeal d;
-    d.waves = (int)(gridDim.x * (blockDim.x >> 6));
-    d.at = (int)(blockIdx.x * (blockDim.x >> 6)) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    d.on = d.at < g.n_heavy;
+    d.step = (int)(gridDim.x >> 3) * wpw;
+    d.at = g.heavy_ptr[xcd] + (int)(blockIdx.x >> 3) * wpw + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    d.end = g.heavy_ptr[xcd + 1];
+    d.on = d.at < d.end;
     return d;
+}
+__device__ __forceinline__ void tile_deal_next(TileDeal& d) {
+    d.at += d.step;
+    d.on = d.at < d.end;
 }
 // s_rp: the tile's row pointers as tile_begin published them.  Rows that are split do not count: their
 // neighbours are summed by the first pass.
@@ -1699,7 +1878,7 @@ struct TileWalk {
     int requested, t, t_end;
     __device__ __forceinline__ TileWalk(const CsrView& g, int tiles, int* set, int* done) {
         td = tile_draws(tiles, set, done);
-        deal = TileDeal{0, 0, false};
+        deal = TileDeal{0, 0, 0, false};
         if constexpr (DEAL) deal = tile_deal(g);
         requested = tile_request(td);
         if (DEAL && deal.on) { t = g.heavy[deal.at]; t_end = tiles; }
@@ -1715,8 +1894,7 @@ struct TileWalk {
     }
     __device__ __forceinline__ void next(const CsrView& g) {
         if (DEAL && deal.on) {
-            deal.at += deal.waves;
-            deal.on = deal.at < g.n_heavy;
+            tile_deal_next(deal);
             if (deal.on) { t = g.heavy[deal.at]; return; }
             t_end = td.end;
         }

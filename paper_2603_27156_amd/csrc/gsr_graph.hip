@@ -129,6 +129,7 @@ static void free_csr(Csr& c) {
     if (c.rp) (void)hipFree(c.rp);
     if (c.ci) (void)hipFree(c.ci);
     if (c.av) (void)hipFree(c.av);
+    if (c.er) (void)hipFree(c.er);
     if (c.hub.rows) (void)hipFree(c.hub.rows);
     if (c.hub.cptr) (void)hipFree(c.hub.cptr);
     if (c.hub.tile0) (void)hipFree(c.hub.tile0);
@@ -158,10 +159,14 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
         if (e > kHeavyTileEdges) heavy.push_back((int32_t)(t0 / 16));
     }
     out->n_heavy = (int32_t)heavy.size();
+    split_heavy(heavy, (int)((n + 15) / 16), out);
     GSR_TRY(upload(heavy, &out->heavy));
     GSR_TRY(upload(h.rp, &out->rp));
     GSR_TRY(upload(h.ci, &out->ci));
     GSR_TRY(upload(h.av, &out->av));
+    std::vector<uint8_t> er(h.ci.size());
+    for (int64_t i = 0; i < n; ++i) std::fill(er.begin() + h.rp[i], er.begin() + h.rp[i + 1], (uint8_t)(i & 15));
+    GSR_TRY(upload(er, &out->er));
     std::vector<int32_t> rows, cptr, crow, ce0, ce1, tile0;
     cptr.push_back(0);
     for (int64_t i = 0; i < n; ++i) {
@@ -251,6 +256,8 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
         off += align_up(n * (size_t)cfg->k * b + 16);   // the record gather loads up to 16 bytes past a record
         w.rec_mask[s] = off;
         off += align_up(n * (dgs == 32 ? 4 : 8));
+        w.rec_cols[s] = off;
+        if (S == 1 && b == 4) off += align_up(n * (size_t)cfg->k + 16);
     }
     w.y0 = off;
     off += align_up(n * dg * b);

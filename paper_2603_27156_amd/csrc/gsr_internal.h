@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <vector>
+
 #include "gsr.h"
 
 namespace gsr {
@@ -86,9 +88,11 @@ struct Csr {
     int32_t* rp = nullptr;  // device [n+1]
     int32_t* ci = nullptr;  // device [nnz]
     float* av = nullptr;    // device [nnz]
+    uint8_t* er = nullptr;  // device [nnz]  row of the entry modulo 16
     HubPlan hub;
     int32_t* heavy = nullptr;  // device [n_heavy]: the heavy tiles, ascending
     int32_t n_heavy = 0;
+    int32_t heavy_ptr[9] = {};   // where the entries of every eighth of the tiles start in the list
 };
 
 }  // namespace gsr
@@ -115,6 +119,9 @@ struct gsr_graph {
 
 namespace gsr {
 
+// gsr_ops.hip: fills c->heavy_ptr for a list of heavy tiles
+void split_heavy(const std::vector<int32_t>& heavy, int tiles, Csr* c);
+
 // gsr_graph.hip
 gsr_status_t validate_config(const gsr_config_t* cfg, const gsr_graph_t* g, bool need_l);
 
@@ -122,6 +129,7 @@ gsr_status_t validate_config(const gsr_config_t* cfg, const gsr_graph_t* g, bool
 constexpr int kMaxRecordSlots = 32;   // groups (at most 8) x sub-planes of a group (at most 4)
 struct LayerWs {
     size_t rec_vals[kMaxRecordSlots];  // per slot and sub-plane: compressed values  [n][k] of T
+    size_t rec_cols[kMaxRecordSlots];  // per slot, float32 and groups of at most 64 columns: column of every value [n][k] bytes
     size_t rec_mask[kMaxRecordSlots];  // per slot and sub-plane: column bit mask    [n] of uint32 (32 columns) / uint64 (64)
     size_t y0;           // Y_0 plane [n][dg] of T (C > 2); wide groups: [S][n][64]
     size_t h;            // [n][min(dg, 64)] float: H of the block being inverted, for the weight-gradient kernel

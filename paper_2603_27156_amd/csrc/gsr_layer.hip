@@ -22,13 +22,14 @@ namespace gsr {
 
 CsrView make_view(const gsr_graph_t* g, bool transpose);
 
-// per-wave LDS: tile(s) of 16 x (DG+1) floats, 64 staged edges, 17 row pointers
-template <int DG, int TILES>
+// per-wave LDS: a tile of 16 x tile_ld floats, 64 staged edges, 17 row pointers
+template <int DG, bool COLS = false>
 struct WaveLds {
-    float st[TILES][16 * (DG + 1) + 64];   // tile + 64 dump words for contributions that must not count
-    EdgeRec ebuf[64];                      // 64 staged edges (RecEdge has the same size)
+    // the tile, with what emit_tile and (COLS) gather_values_rows need behind it
+    alignas(16) float st[COLS && gather_floats<DG>() > emit_floats<DG, COLS>() ? gather_floats<DG>() : emit_floats<DG, COLS>()];
+    EdgeRec ebuf[COLS ? 1 : 64];           // 64 staged edges (RecEdge has the same size; not with gather_values_rows)
     int rp[20];                            // row pointers of the tile's 17 row boundaries
-    uint8_t rbuf[64];                      // tile row of every staged edge
+    uint8_t rbuf[COLS ? 4 : 64];           // tile row of every staged edge
 };
 
 // ---- block: forward / inverse (+ weight gradient) ------------------------------------------------
@@ -81,15 +82,17 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         if (a.draws) { a.draws += ob * a.y_draws; a.draws_done += ob * a.y_draws; }
         if (ob > 0) a.h_out = nullptr;          // (the same rows for every column block written)
     }
-    constexpr int LR = DG + 1, CPL = DG / 16;
-    __shared__ WaveLds<DG, 1> lds[block_waves(WITH_DW, B3)];
+    constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
+    // float32 records carry their columns (gather_values_rows, emit_tile)
+    constexpr bool COLS = sizeof(T) == 4 && !YG;
+    __shared__ WaveLds<DG, COLS> lds[block_waves(WITH_DW, B3)];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
-    WaveLds<DG, 1>& L = lds[wave];
-    float* st_h = L.st[0];
+    WaveLds<DG, COLS>& L = lds[wave];
+    float* st_h = L.st;
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
     __shared__ typename std::conditional<sizeof(T) == 2, DealLut, DealLutF>::type dlut;
     if constexpr (sizeof(T) == 2) deal_lut_fill(dlut);
-    else deal_lutf_fill(dlut);
+    else if constexpr (!COLS) deal_lutf_fill(dlut);
     if constexpr (B3) load_w_lds_b3<DG>(a.w, a.ldw, false, wl);
     else load_w_lds<DG>(a.w, a.ldw, false, wl);
     f32x4 dw[WITH_DW ? DG / 16 : 1][WITH_DW ? DG / 16 : 1];
@@ -102,7 +105,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
     // the weight gradient sums over the tiles a wave has seen: fixed sweep there, drawn tiles otherwise
     const TileSweep ts = tile_sweep(a.tiles);
     TileDraws td;
-    TileDeal deal{0, 0, false};      // DEAL: the heavy tiles first (a variant of its own: the bookkeeping costs
+    TileDeal deal{0, 0, 0, false};      // DEAL: the heavy tiles first (a variant of its own: the bookkeeping costs
     if constexpr (DEAL) deal = tile_deal(a.g);   // 3 % on a graph with 120 short tiles per wave even when it never fires)
     int requested = 0;     // the draw that is outstanding (dynamic sweep)
     int t = ts.first, t_end = ts.end;
@@ -115,19 +118,39 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
     if constexpr (DEAL) {
         if (deal.on) { t = a.g.heavy[deal.at]; t_end = a.tiles; }
     }
+    // the tile after the present one: its row pointers are requested while the present one is finished (1M nodes: forward
+    // 232 -> 223 us, inverse 257 -> 246; its first edges as well: slower, their registers live through the record)
+    int t_next = 0, t_end_next = t_end;
+    auto advance = [&]() {
+        t_end_next = t_end;
+        if (DEAL && deal.on) {
+            tile_deal_next(deal);
+            if (deal.on) {
+                t_next = a.g.heavy[deal.at];
+            } else if constexpr (WITH_DW) {
+                t_next = ts.first; t_end_next = ts.end;
+            } else {
+                t_next = tile_drawn(td, requested); t_end_next = td.end;
+            }
+        } else {
+            if constexpr (WITH_DW) t_next = t + ts.step;
+            else t_next = tile_drawn(td, requested);
+        }
+    };
+    int rpv = tile_rp_load(a.g, t * 16, a.n, lane);
+
     while (t < t_end) {
         if constexpr (!WITH_DW) {
             if (!DEAL || !deal.on) requested = tile_request(td);
         }
         const int r0 = t * 16;
         wave_sync();
-        const int rpv = tile_rp_load(a.g, r0, a.n, lane);
         // The tile's own rows (X_i, and dY_i for the weight gradient), in the tile register layout.  Requested before
-        // the gather they arrive while it runs, but hold sixteen registers through it; where the gather is short of
-        // registers they are requested after it and arrive during the weight product (1M-node workload, float32:
-        // forward 291 -> 274 us, inverse 326 -> 309 us, spilled registers 14 -> 4; measured per variant: the fused
-        // inverse + dW kernel gains at D/C = 32 and loses at 64, the 16-bit forward kernel the other way round).
-        constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 || DG == 64);
+        // the gather they arrive while it runs, but hold sixteen registers through it; requested after it they arrive
+        // during the weight product.  Measured per variant (1M-node workload, float32: forward 232 us early against 241
+        // late, inverse 264 against 257; the fused inverse + dW kernel gains from late rows at D/C = 32 and loses at 64,
+        // the 16-bit forward kernel the other way round).
+        constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
         float xy[4][CPL], gy[WITH_DW ? 4 : 1][CPL];
         auto own_rows = [&]() {
 #pragma unroll
@@ -142,15 +165,20 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         const bool has_hub = tile_begin(a.g, rpv, L.rp, lane);
         if constexpr (DEAL) {
             if (!deal.on && tile_is_heavy(a.g, rpv, L.rp, has_hub)) {      // dealt out before the sweep
-                if constexpr (WITH_DW) t += ts.step;
-                else t = tile_drawn(td, requested);
+                advance();
+                t = t_next;
+                rpv = tile_rp_load(a.g, t * 16, a.n, lane);
                 continue;
             }
         }
-        // float32: the sums in ordinary arithmetic (forward 329 us against 370 through the matrix cores on the 1M-node
-        // workload), in the forward and in both inverse kernels alike, so that f_i is recomputed by the instructions that
-        // computed it; four window loads in flight per lane group (eight cost registers: inverse 310 us against 297).
-        if constexpr (sizeof(T) == 4) {
+        // float32: the sums in ordinary arithmetic, in the forward and in both inverse kernels alike, so that f_i is
+        // recomputed by the instructions that computed it.
+        if constexpr (COLS) {
+            tile_gather_rows<DG, true, GATHER_ROWS>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
+                gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, __builtin_amdgcn_readfirstlane(e_a),
+                                          __builtin_amdgcn_readfirstlane(e_b), lane, st_h);
+            });
+        } else if constexpr (sizeof(T) == 4) {
             tile_gather_rows<DG>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
                 gather_records_rows<DG, 4, true>(a.g, a.in.vals, a.in.mask, a.k, __builtin_amdgcn_readfirstlane(e_a),
                                                  __builtin_amdgcn_readfirstlane(e_b), L.rp, reinterpret_cast<RecEdge*>(L.ebuf),
@@ -164,6 +192,8 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
                                               lane, hacc, &dlut);
             });
         }
+        advance();
+        rpv = tile_rp_load(a.g, t_next * 16, a.n, lane);
         if constexpr (OWN_LATE) own_rows();
         if constexpr (WITH_DW) {
 #pragma unroll
@@ -178,8 +208,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
                 for (int reg = 0; reg < 4; ++reg) {
                     const int rr = 4 * reg + tg, row = r0 + rr;
                     float hv[CPL];
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) hv[cb] = st_h[rr * LR + CPL * tj + cb];
+                    lds_load<CPL>(st_h + rr * LR + CPL * tj, hv);
                     if (row < a.n) store_cols<CPL, float>(a.h_out + (size_t)row * DG + CPL * tj, hv);
                 }
             }
@@ -204,26 +233,15 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
             for (int cb = 0; cb < CPL; ++cb) y[cb] = stored<T>(SIGN > 0 ? xy[reg][cb] + acc[cb][reg] : xy[reg][cb] - acc[cb][reg]);
             if (ok) store_cols<CPL, T>(p, y);
 #pragma unroll
-            for (int cb = 0; cb < CPL; ++cb) st_h[rr * LR + CPL * tj + cb] = ok ? y[cb] : 0.f;
+            for (int cb = 0; cb < CPL; ++cb) y[cb] = ok ? y[cb] : 0.f;
+            lds_store<CPL>(st_h + rr * LR + CPL * tj, y);
         }
         if (a.out.mask) {
             wave_sync();
-            emit_tile<DG, T>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+            emit_tile<DG, T, COLS>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
         }
-        if (DEAL && deal.on) {
-            deal.at += deal.waves;
-            deal.on = deal.at < a.g.n_heavy;
-            if (deal.on) {
-                t = a.g.heavy[deal.at];
-            } else if constexpr (WITH_DW) {
-                t = ts.first; t_end = ts.end;
-            } else {
-                t = tile_drawn(td, requested); t_end = td.end;
-            }
-        } else {
-            if constexpr (WITH_DW) t += ts.step;
-            else t = tile_drawn(td, requested);
-        }
+        t = t_next;
+        t_end = t_end_next;
     }
     if constexpr (!WITH_DW) tile_finish(td);
     if constexpr (WITH_DW) {
@@ -280,7 +298,10 @@ __device__ __forceinline__ void tie_fixup_rows(const TieSeg<DG>& tie, const T* _
 #pragma unroll
         for (int j = 0; j < QW; ++j) {
             const bool bit = (msel >> j) & 1u;
-            if (ok && bit) out.vals[slot] = from_float<T>(x[j] * scale);
+            if (ok && bit) {
+                out.vals[slot] = from_float<T>(x[j] * scale);
+                if constexpr (sizeof(T) == 4) out.cols[slot] = (uint8_t)(q * QW + j);
+            }
             slot += bit ? 1 : 0;
         }
         if (ok && q == 0) out.mask[row] = m;
@@ -368,8 +389,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (a.tie.count)
         tie_fixup_rows<DG, T>(a.tie, a.fix_plane, a.fix_ld, a.k, a.norm, a.eps, a.fix_out, (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6),
                               (int)((gridDim.x * blockDim.x) >> 6));
-    constexpr int LR = DG + 1, CPL = DG / 16;
-    __shared__ float tile[4][16 * LR];
+    constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
+    __shared__ __attribute__((aligned(16))) float tile[4][16 * LR];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     float* st = tile[wave];
     f32x4 dw[DG / 16][DG / 16];
@@ -398,11 +419,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
         for (int reg = 0; reg < 4; ++reg) {
             const bool ok = r0 + 4 * reg + tg < a.n;
+            float h[CPL];
 #pragma unroll
             for (int cb = 0; cb < CPL; ++cb) {
-                st[(4 * reg + tg) * LR + CPL * tj + cb] = ok ? hv[reg][cb] : 0.f;
+                h[cb] = ok ? hv[reg][cb] : 0.f;
                 g[reg][cb] = ok ? gy[reg][cb] : 0.f;          // rows past the end
             }
+            lds_store<CPL>(st + (4 * reg + tg) * LR + CPL * tj, h);
         }
         t += ts.step;
         if (t < ts.end) request(t);
@@ -525,17 +548,17 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
     // the partial rows of a tile's split rows requested together (hub_rows_fill) only where that spills no register:
     // these kernels sit at their 128 registers
     constexpr bool FILL_FAST = ACC || (!DEAL && sizeof(T) == 4 && DG == 64);
-    __shared__ WaveLds<DG, 1> lds[GRAD_WAVES];
+    __shared__ WaveLds<DG> lds[GRAD_WAVES];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
-    WaveLds<DG, 1>& L = lds[wave];
-    float* st = L.st[0];
+    WaveLds<DG>& L = lds[wave];
+    float* st = L.st;
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
     static_assert(GRAD_WAVES >= 4 && sizeof(lds) >= 256 * sizeof(float), "dw_reduce_slices works with the first 256 threads");
     if (a.dw_out) dw_reduce_slices<DG * DG>(a.dw_partial, a.dw_parts, a.dw_out, reinterpret_cast<float*>(lds));
     if constexpr (B3) load_w_lds_b3<DG>(a.w, a.ldw, true, wl);
     else load_w_lds<DG>(a.w, a.ldw, true, wl);
     TileDraws td = tile_draws(a.tiles, a.draws, a.draws_done);
-    TileDeal deal{0, 0, false};
+    TileDeal deal{0, 0, 0, false};
     if constexpr (DEAL) deal = tile_deal(a.gt);
     int requested = tile_request(td);      // the draw that is outstanding
     int t_end = td.end;
@@ -571,7 +594,7 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         if constexpr (sizeof(T) == 4) {
             tile_gather_rows<DG, FILL_FAST>(a.gt, a.hub_part, has_hub, r0, L.rp, st, lane, [&](int e_a, int e_b) {
                 gather_dense_rows<DG, 8>(a.gt, a.dy, a.ldg, __builtin_amdgcn_readfirstlane(e_a),
-                                               __builtin_amdgcn_readfirstlane(e_b), L.rp, L.ebuf, lane, st);
+                                               __builtin_amdgcn_readfirstlane(e_b), lane, st);
             });
         } else {
             f32x4 qacc[DG / 16];
@@ -636,8 +659,9 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
             }
         } else {
             // JC planes at a time: all their rows are requested before the first is written back (block 1 updates C - 1
-            // planes; one plane after the other took 3.2 ms against 1.2 ms for a one-plane launch at 8M rows, C = 8)
-            constexpr int JC = CPL <= 2 ? 4 : 2;
+            // planes; one plane after the other took 3.2 ms against 1.2 ms for a one-plane launch at 8M rows, C = 8, 16-bit
+            // rows of 32 columns).  float32 at 64 columns: two planes spill registers, 285 us per launch against 273
+                        constexpr int JC = CPL <= 2 ? 4 : sizeof(T) == 4 ? 1 : 2;
             if (a.ndst == 1) {          // the common case on its own, so that it requests nothing twice
                 float g[4][CPL];
 #pragma unroll
@@ -680,8 +704,7 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
             }
         }
         if (DEAL && deal.on) {
-            deal.at += deal.waves;
-            deal.on = deal.at < a.gt.n_heavy;
+            tile_deal_next(deal);
             if (deal.on) t = a.gt.heavy[deal.at];
             else { t = tile_drawn(td, requested); t_end = td.end; }
         } else {
@@ -713,8 +736,9 @@ __global__ void k_zero_ints(int* p, int count) {
 
 template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
-    constexpr int LR = DG + 1, CPL = DG / 16;
-    __shared__ float tile[4][16 * LR + 64];
+    constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
+    constexpr bool COLS = sizeof(T) == 4;
+    __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, COLS>()];
     const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
     float* st = tile[threadIdx.x >> 6];
     const int nwaves = (gridDim.x * blockDim.x) >> 6, tiles = (a.n + 15) / 16;
@@ -747,10 +771,11 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
             for (int cb = 0; cb < CPL; ++cb) y[reg][cb] = stored<T>(y[reg][cb]);
             if (ok && a.y0) store_cols<CPL, T>(a.y0 + (size_t)row * DG + CPL * tj, y[reg]);
 #pragma unroll
-            for (int cb = 0; cb < CPL; ++cb) st[rr * LR + CPL * tj + cb] = ok ? y[reg][cb] : 0.f;
+            for (int cb = 0; cb < CPL; ++cb) y[reg][cb] = ok ? y[reg][cb] : 0.f;
+            lds_store<CPL>(st + rr * LR + CPL * tj, y[reg]);
         }
         wave_sync();
-        emit_tile<DG, T>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+        emit_tile<DG, T, COLS>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
     }
 }
 
@@ -1114,8 +1139,9 @@ struct Ctx {
     // the mask in the slot, or in the kept store when indices are saved.
     Record<DG, T> rec(int slot, int layer = 0, int sub = 0) const {
         Record<DG, T> r;
-        if (slot < 0) { r.vals = nullptr; r.mask = nullptr; return r; }
+        if (slot < 0) { r.vals = nullptr; r.mask = nullptr; r.cols = nullptr; return r; }
         r.vals = (T*)(ws + lw.rec_vals[slot * S + sub]);
+        r.cols = sizeof(T) == 4 && S == 1 ? (uint8_t*)(ws + lw.rec_cols[slot]) : nullptr;
         r.mask = saved ? saved + (((size_t)layer * cfg->c + slot) * S + sub) * (size_t)cfg->n : (M*)(ws + lw.rec_mask[slot * S + sub]);
         return r;
     }

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <vector>
 
 namespace gsr {
 
@@ -12,13 +13,18 @@ static_assert(TILE_COUNTERS == kTileCounters, "host and device disagree on the s
 static_assert(TIE_SUB == kTieSub && TIE_COUNTER_STRIDE == kTieCounterStride, "host and device disagree on the near-tie sub-lists");
 
 CsrView make_view(const gsr_graph_t* g, bool transpose);
+void split_heavy(const std::vector<int32_t>& heavy, int tiles, Csr* c) {
+    for (int x = 0; x < 9; ++x)
+        c->heavy_ptr[x] = (int32_t)(std::lower_bound(heavy.begin(), heavy.end(), (int32_t)((int64_t)tiles * x / 8)) - heavy.begin());
+}
 CsrView make_view(const gsr_graph_t* g, bool transpose) {
     const Csr& c = transpose ? g->at : g->a;
     CsrView v;
-    v.rp = c.rp; v.ci = c.ci; v.av = c.av;
+    v.rp = c.rp; v.ci = c.ci; v.av = c.av; v.er = c.er;
     v.hub_rows = c.hub.rows; v.hub_cptr = c.hub.cptr; v.hub_tile0 = c.hub.tile0; v.n_hub = c.hub.n_hub;
     v.hub_threshold = g->hub_threshold;
     v.heavy = c.heavy; v.n_heavy = c.n_heavy; v.heavy_edges = kHeavyTileEdges;
+    for (int x = 0; x < 9; ++x) v.heavy_ptr[x] = c.heavy_ptr[x];
     return v;
 }
 
@@ -178,11 +184,11 @@ template <int W, bool DEAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_spmm_tile(CsrView g, int n, int tiles, const float* __restrict__ x, int64_t ldx,
                                                    float* __restrict__ y, int64_t ldy, const float* __restrict__ hub_part,
                                                    int* draws, int* draws_done) {
-    constexpr int LR = W + 1, CPL = W / 16;
+    constexpr int LR = tile_ld<W>(), CPL = W / 16;
     constexpr bool ROWS = W >= 32;
     struct Wave {
         TileLds t;
-        float st[ROWS ? 16 * LR : 1];
+        alignas(16) float st[ROWS ? 16 * LR : 4];
     };
     __shared__ Wave lds[4];
     Wave& Wv = lds[threadIdx.x >> 6];
@@ -198,8 +204,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         if (walk.dealt(g, rpv, L.rp, has_hub)) { walk.next(g); continue; }
         if constexpr (ROWS) {
             tile_gather_rows<W>(g, hub_part, has_hub, r0, L.rp, Wv.st, lane, [&](int e_a, int e_b) {
-                gather_dense_rows<W, 8>(g, x, ldx, __builtin_amdgcn_readfirstlane(e_a), __builtin_amdgcn_readfirstlane(e_b), L.rp,
-                                        L.ebuf, lane, Wv.st);
+                gather_dense_rows<W, 8>(g, x, ldx, __builtin_amdgcn_readfirstlane(e_a), __builtin_amdgcn_readfirstlane(e_b),
+                                        lane, Wv.st);
             });
             wave_sync();
             // four rows per store instruction, CPL adjacent columns per lane
@@ -207,8 +213,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             for (int reg = 0; reg < 4; ++reg) {
                 const int rr = 4 * reg + (lane >> 4), row = r0 + rr;
                 float v[CPL];
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) v[cb] = Wv.st[rr * LR + CPL * (lane & 15) + cb];
+                lds_load<CPL>(Wv.st + rr * LR + CPL * (lane & 15), v);
                 if (row < n) store_cols<CPL, float>(y + (size_t)row * ldy + CPL * (lane & 15), v);
             }
         } else {
@@ -233,10 +238,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                                                         const typename MaskOf<DG>::type* __restrict__ masks, int k,
                                                         const float* __restrict__ hub_part, float* __restrict__ h_out,
                                                         int* draws, int* draws_done) {
-    constexpr int LR = DG + 1;
+    constexpr int LR = tile_ld<DG>();
     struct Wave {
         TileLds t;
-        float st[sizeof(T) == 4 ? 16 * LR : 1];
+        alignas(16) float st[sizeof(T) == 4 ? 16 * LR : 4];
     };
     __shared__ Wave lds[4];
     __shared__ typename std::conditional<sizeof(T) == 2, DealLut, DealLutF>::type dlut;
@@ -283,9 +288,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_gs_tile(const T* __restrict__ x, int n, int64_t ld, int k, int norm, float eps,
                                                  T* __restrict__ vals, int32_t* __restrict__ idx) {
-    constexpr int LR = DG + 1, CPL = DG / 16;
+    constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     struct Wave {
-        float st[16 * LR + 64];
+        alignas(16) float st[emit_floats<DG, false>()];
         int ist[16 * DG];
     };
     __shared__ Wave lds[4];
@@ -295,6 +300,7 @@ __global__ __launch_bounds__(256) void k_gs_tile(const T* __restrict__ x, int n,
     Record<DG, T> out;
     out.vals = vals;
     out.mask = nullptr;
+    out.cols = nullptr;
     for (int t = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; t < tiles; t += nwaves) {
         const int r0 = t * 16;
         float v[4][CPL];
@@ -305,10 +311,11 @@ __global__ __launch_bounds__(256) void k_gs_tile(const T* __restrict__ x, int n,
         }
         wave_sync();          // the previous tile's results have left the scratch
 #pragma unroll
-        for (int reg = 0; reg < 4; ++reg)
+        for (int reg = 0; reg < 4; ++reg) {
 #pragma unroll
-            for (int cb = 0; cb < CPL; ++cb)
-                L.st[(4 * reg + tg) * LR + CPL * tj + cb] = r0 + 4 * reg + tg < n ? v[reg][cb] : 0.f;
+            for (int cb = 0; cb < CPL; ++cb) v[reg][cb] = r0 + 4 * reg + tg < n ? v[reg][cb] : 0.f;
+            lds_store<CPL>(L.st + (4 * reg + tg) * LR + CPL * tj, v[reg]);
+        }
         wave_sync();
         emit_tile<DG, T>(L.st, r0, n, k, norm, eps, out, false, lane, idx, L.ist);
     }
