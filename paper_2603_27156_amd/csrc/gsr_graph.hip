@@ -148,7 +148,22 @@ static gsr_status_t upload(const std::vector<V>& h, V** d) {
     return GSR_OK;
 }
 
-static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, int64_t chunk, Csr* out) {
+// Neighbours per first-pass partial of a row of `len` > kLongChunks x chunk neighbours (`grow`; else every row is cut at
+// `chunk`).  A partial costs the first pass a round of `chunk` edges after the other, and the tile that owns the row a
+// place in its chain of partial rows, sixteen per round trip to memory; the nets that reach thousands of nodes are
+// adjacent rows of one tile (clock, reset), some eight of them.  On a graph with few tiles per wave a launch is as long as
+// that tile: 30k nodes, eight nets of 5,000 sinks: 80 partials per row, 640 in the tile, 38 us per tile-kernel launch
+// against 23 us with partials of 320 (first pass 5 -> 11 us; forward layer of eight groups on 57k nodes 392 -> 321 us).  Rounds per partial r and trips of the tile 8 (len / 64 r) / 16
+// balance at r = sqrt(len / 128); half of that many trips for r = sqrt(len / 256), taken since nets stand alone as often.
+constexpr int64_t kLongChunks = 16;
+static int64_t row_chunk(int64_t len, int64_t chunk, bool grow) {
+    if (!grow || len <= kLongChunks * chunk) return chunk;
+    int64_t r = 1;
+    while (r * r * 4 * chunk < len) ++r;
+    return r * chunk;
+}
+
+static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, int64_t base_chunk, bool grow, Csr* out) {
     std::vector<int32_t> heavy;
     for (int64_t t0 = 0; t0 < n; t0 += 16) {
         int64_t e = 0;      // stored entries of the tile's rows that are not split
@@ -174,6 +189,7 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
         int64_t len = h.rp[i + 1] - h.rp[i];
         if (len <= threshold) continue;
         rows.push_back((int32_t)i);
+        const int64_t chunk = row_chunk(len, base_chunk, grow);
         for (int64_t e = h.rp[i]; e < h.rp[i + 1]; e += chunk) {
             crow.push_back((int32_t)i);
             ce0.push_back((int32_t)e);
@@ -528,13 +544,15 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
                                   : long_rows ? 1 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
     const int64_t hub_chunk = options().hub_chunk > 0 ? options().hub_chunk : (long_rows ? 512 : 64);      // (Table-1-shaped graph, rows of up to 390 entries: 289 / 274 / 263 / 263 ms per step with chunks of 128 / 256 / 512 / 1,024)
     g->hub_threshold = (int32_t)hub_threshold;
+    // (with more tiles per wave the tile with the long nets starts early and is hidden: there the first pass is better short)
+    const bool grow = few_tiles && !long_rows && options().hub_chunk == 0;
     g->hub_values = options().hub_values == 1 ? 2 : (options().hub_values == 0 && long_rows) ? 1 : 0;
     g->split_backward = !(long_rows || (n + 15) / 16 < (int64_t)8 * full_grid);    // (not with fewer than two tiles per resident wave)
 
-    gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, &g->a);
+    gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, grow, &g->a);
     if (st == GSR_OK) {
         if (symmetric) g->at = g->a;
-        else st = upload_csr(t, n, hub_threshold, hub_chunk, &g->at);
+        else st = upload_csr(t, n, hub_threshold, hub_chunk, grow, &g->at);
     }
     if (st == GSR_OK) {
         const size_t chunks = (size_t)std::max(std::max(g->a.hub.n_chunks, g->at.hub.n_chunks), 1);
