@@ -257,6 +257,7 @@ struct CsrView {
     const int32_t* hub_tile0;     // [tiles + 1]: split rows before row 16 t
     int32_t n_hub;
     int32_t hub_threshold;
+    int32_t hub_chunk;            // a split row of at most this many entries is one chunk
     // tiles with more than heavy_edges stored entries, ascending (see TileDeal)
     const int32_t* heavy;
     int32_t n_heavy;
@@ -614,32 +615,6 @@ __device__ __forceinline__ void deal_lut_fill(DealLut& l) {
     __syncthreads();
 }
 
-// The same for float32 records and four columns per lane: the window is four words, column c takes word
-// popcount(mask bits below c) if its bit is set.  A word moves whole, so a v_perm_b32 over two words of the window
-// with a selector that copies the lower word, the upper word or zeros does it: column 0 from word 0, column 1 from
-// words (0, 1), columns 2 and 3 from words (0, 1) or-ed with (2, -) and (2, 3).  Six selectors per value of the four
-// mask bits, eight instructions per staged edge and lane instead of a chain of some twenty-five bitwise selects.
-struct alignas(32) DealLutF {
-    uint32_t sel[16][8];      // s0, s1, s2 over (0,1), s2 over (2,-), s3 over (0,1), s3 over (2,3), unused
-};
-__device__ __forceinline__ void deal_lutf_fill(DealLutF& l) {
-    if (threadIdx.x < 16) {
-        constexpr uint32_t LOW = 0x03020100u, HIGH = 0x07060504u, ZERO = 0x0c0c0c0cu;
-        const uint32_t nib = threadIdx.x;
-        const uint32_t p1 = nib & 1u, p2 = (uint32_t)__popc(nib & 3u), p3 = (uint32_t)__popc(nib & 7u);
-        const bool b0 = nib & 1u, b1 = nib & 2u, b2 = nib & 4u, b3 = nib & 8u;
-        uint32_t* e = l.sel[nib];
-        e[0] = b0 ? LOW : ZERO;
-        e[1] = b1 ? (p1 ? HIGH : LOW) : ZERO;
-        e[2] = (b2 && p2 < 2u) ? (p2 ? HIGH : LOW) : ZERO;
-        e[3] = (b2 && p2 == 2u) ? LOW : ZERO;
-        e[4] = (b3 && p3 < 2u) ? (p3 ? HIGH : LOW) : ZERO;
-        e[5] = (b3 && p3 >= 2u) ? (p3 == 3u ? HIGH : LOW) : ZERO;
-        e[6] = ZERO; e[7] = ZERO;
-    }
-    __syncthreads();
-}
-
 // acc += P * scatter(V, I) over the edges [e_a, e_b) of ordinary rows (Section 4.1, eq. (10)).
 // The record of neighbour j is its k kept values in ascending column order plus a DG-bit column
 // mask.  A lane's CPL adjacent columns occupy adjacent slots of the record, starting at
@@ -651,10 +626,9 @@ template <int DG, typename T, int MAXB, bool ONE_ROW = false>
 __device__ __forceinline__ void gather_records_mfma(const CsrView& g, const T* __restrict__ vals,
                                                     const typename MaskOf<DG>::type* __restrict__ masks, int k, int e_a,
                                                     int e_b, const int* s_rp, RecEdge* ebuf, uint8_t* rbuf, int lane,
-                                                    f32x4 (&acc)[DG / 16], const DealLut* lut = nullptr,
-                                                    const DealLutF* lutf = nullptr) {
-    constexpr bool PERM = sizeof(T) == 2 && !ONE_ROW;     // (callers of that case pass the table)
-    constexpr bool PERMF = sizeof(T) == 4 && ONE_ROW && DG == 64;   // float32 chunk sums: the table of DealLutF (passed too)
+                                                    f32x4 (&acc)[DG / 16], const DealLut* lut = nullptr) {
+    static_assert(sizeof(T) == 2, "float32 records are summed value by value");
+    constexpr bool PERM = !ONE_ROW;                       // (callers of that case pass the table)
     using M = typename MaskOf<DG>::type;
     constexpr int CPL = DG / 16, NW = sizeof(T) == 4 ? CPL : CPL / 2 + 1;
     const int i16 = lane & 15, kk = lane >> 4, bp = CPL * i16;
@@ -730,22 +704,6 @@ __device__ __forceinline__ void gather_records_mfma(const CsrView& g, const T* _
                 }
                 return;
             }
-            if constexpr (PERMF) {
-#pragma unroll
-                for (int u = 0; u < GB; ++u) {
-                    const uint4 sa = *reinterpret_cast<const uint4*>(lutf->sel[nib[u]]);
-                    const uint2 sb = *reinterpret_cast<const uint2*>(lutf->sel[nib[u]] + 4);
-                    const uint32_t b0 = __builtin_amdgcn_perm(0u, w[u][0], sa.x);
-                    const uint32_t b1 = __builtin_amdgcn_perm(w[u][1], w[u][0], sa.y);
-                    const uint32_t b2 = __builtin_amdgcn_perm(w[u][1], w[u][0], sa.z) | __builtin_amdgcn_perm(0u, w[u][2], sa.w);
-                    const uint32_t b3 = __builtin_amdgcn_perm(w[u][1], w[u][0], sb.x) | __builtin_amdgcn_perm(w[u][3], w[u][2], sb.y);
-                    acc[0][0] = __builtin_fmaf(p[u], __uint_as_float(b0), acc[0][0]);
-                    acc[1][0] = __builtin_fmaf(p[u], __uint_as_float(b1), acc[1][0]);
-                    acc[2][0] = __builtin_fmaf(p[u], __uint_as_float(b2), acc[2][0]);
-                    acc[3][0] = __builtin_fmaf(p[u], __uint_as_float(b3), acc[3][0]);
-                }
-                return;
-            }
             uint32_t bq[sizeof(T) == 4 ? 1 : GB][CPL];   // dealt-out values (float bits) of the 16-bit variant
 #pragma unroll
             for (int u = 0; u < GB; ++u) {
@@ -793,134 +751,9 @@ __device__ __forceinline__ void gather_records_mfma(const CsrView& g, const T* _
     }
 }
 
-// The same sums in ordinary arithmetic, for float32 records (Section 4.1, eq. (10)): on this chip float32 matrix
-// instructions do not hide under vector work, and a 16-row product spends fifteen rows of every edge on zeros.
-// The staged edges of a round are cut into four equal runs, one per group of sixteen lanes; a group walks its run
-// in order (rows do not decrease along it), lane j of the group keeping a running sum of its CPL columns for the
-// run's present row and adding it to the row of the LDS tile `st` (zeroed by the caller, row stride DG + 1) when
-// the row changes and at the end of the round.  Two groups never add to one row in the same instruction: inside a
-// round only the last run that holds a row sees it end; the sums left at the end of the round are added group by
-// group.  The order of the additions is fixed by the edge list alone.
-template <int DG, int GB, bool LUT = false>
-__device__ __forceinline__ void gather_records_rows(const CsrView& g, const float* __restrict__ vals,
-                                                    const typename MaskOf<DG>::type* __restrict__ masks, int k, int e_a,
-                                                    int e_b, const int* s_rp, RecEdge* ebuf, uint8_t* rbuf, int lane,
-                                                    float* st, const DealLutF* lut = nullptr) {
-    using M = typename MaskOf<DG>::type;
-    constexpr int CPL = DG / 16, LR = tile_ld<DG>();
-    const int i16 = lane & 15, kk = lane >> 4, bp = CPL * i16;
-    const uint32_t sh = bp & 31;
-    const bool upper = bp >= 32;
-    const uint32_t below_lo = upper ? 0xFFFFFFFFu : (1u << sh) - 1u, below_hi = upper ? (1u << sh) - 1u : 0u;
-    float* mine = st + bp;
-    for (int eb = e_a; eb < e_b; eb += 64) {
-        const int e = eb + lane;
-        const bool ok = e < e_b;
-        const int ec = ok ? e : e_b - 1;
-        const int j = __builtin_nontemporal_load(g.ci + ec);
-        RecEdge me;
-        me.a = ok ? __builtin_nontemporal_load(g.av + ec) : 0.f;
-        const M m = masks[j];
-        me.off0 = (uint32_t)j * (uint32_t)k;
-        me.mlo = (uint32_t)m;
-        if constexpr (DG == 64) me.mhi = (uint32_t)(m >> 32);
-        else me.mhi = 0u;
-        // The places of the round past its last edge are staged too: the last edge once more with a_ij = 0.
-        // A run is a whole number of batches, so every place a lane group reads is staged and adds what it should: no
-        // test per edge for the end of the run or of the round.
-        const int r = tile_row_of(s_rp, ec);
-        wave_sync();          // readers of the previous round are done
-        ebuf[lane] = me;
-        rbuf[lane] = (uint8_t)r;
-        wave_sync();
-        const int cnt = e_b - eb < 64 ? e_b - eb : 64;     // wave-uniform
-        const int steps = (((cnt + 3) >> 2) + GB - 1) / GB * GB;      // edges per run (at most 16: GB divides 16)
-        static_assert(16 % GB == 0, "a run must end inside the 64 staged places");
-        const int first = kk * steps;
-        int cur = (int)rbuf[first];
-        float run[CPL];
-#pragma unroll
-        for (int cb = 0; cb < CPL; ++cb) run[cb] = 0.f;
-        for (int s0 = 0; s0 < steps; s0 += GB) {
-            uint32_t w[GB][CPL], nib[GB];
-            float p[GB];
-            int row[GB];
-#pragma unroll
-            for (int u = 0; u < GB; ++u) {
-                const int ei = first + s0 + u;
-                const RecEdge er = ebuf[ei];
-                const uint32_t word = upper ? er.mhi : er.mlo;
-                const uint32_t at = er.off0 + (uint32_t)__popc(er.mlo & below_lo) + (uint32_t)__popc(er.mhi & below_hi);
-                nib[u] = (word >> sh) & ((1u << CPL) - 1u);
-                load_words<CPL>(vals + (size_t)at, w[u]);
-                p[u] = er.a;
-                row[u] = (int)rbuf[ei];
-            }
-            constexpr bool PERM = LUT && CPL == 4;
-            uint4 sa_next = make_uint4(0u, 0u, 0u, 0u);      // selectors of the edge after the present one
-            uint2 sb_next = make_uint2(0u, 0u);
-            if constexpr (PERM) {
-                sa_next = *reinterpret_cast<const uint4*>(lut->sel[nib[0]]);
-                sb_next = *reinterpret_cast<const uint2*>(lut->sel[nib[0]] + 4);
-            }
-#pragma unroll
-            for (int u = 0; u < GB; ++u) {
-                const uint4 sa = sa_next;
-                const uint2 sb = sb_next;
-                if constexpr (PERM) {
-                    if (u + 1 < GB) {
-                        sa_next = *reinterpret_cast<const uint4*>(lut->sel[nib[u + 1 < GB ? u + 1 : u]]);
-                        sb_next = *reinterpret_cast<const uint2*>(lut->sel[nib[u + 1 < GB ? u + 1 : u]] + 4);
-                    }
-                }
-                if (row[u] != cur) {     // the row of this run has ended: its sum joins the tile
-                    float was[CPL];            // (all reads before the writes: one LDS round trip, not one per pair)
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) was[cb] = mine[cur * LR + cb];
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) {
-                        mine[cur * LR + cb] = was[cb] + run[cb];
-                        run[cb] = 0.f;
-                    }
-                    cur = row[u];
-                }
-                if constexpr (PERM) {
-                    const uint32_t b0 = __builtin_amdgcn_perm(0u, w[u][0], sa.x);
-                    const uint32_t b1 = __builtin_amdgcn_perm(w[u][1], w[u][0], sa.y);
-                    const uint32_t b2 = __builtin_amdgcn_perm(w[u][1], w[u][0], sa.z) | __builtin_amdgcn_perm(0u, w[u][2], sa.w);
-                    const uint32_t b3 = __builtin_amdgcn_perm(w[u][1], w[u][0], sb.x) | __builtin_amdgcn_perm(w[u][3], w[u][2], sb.y);
-                    run[0] = __builtin_fmaf(p[u], __uint_as_float(b0), run[0]);
-                    run[1] = __builtin_fmaf(p[u], __uint_as_float(b1), run[1]);
-                    run[2] = __builtin_fmaf(p[u], __uint_as_float(b2), run[2]);
-                    run[3] = __builtin_fmaf(p[u], __uint_as_float(b3), run[3]);
-                    continue;
-                }
-                uint32_t q[CPL];
-#pragma unroll
-                for (int t = 0; t < CPL; ++t) q[t] = w[u][t];
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) {
-                    const uint32_t mbit = (uint32_t)__builtin_amdgcn_sbfe((int)nib[u], cb, 1);
-                    const uint32_t b = q[0] & mbit;
-#pragma unroll
-                    for (int t = 0; t + 1 < CPL - cb; ++t) q[t] = bit_select(mbit, q[t + 1], q[t]);
-                    run[cb] = __builtin_fmaf(p[u], __uint_as_float(b), run[cb]);
-                }
-            }
-        }
-        // what the runs still hold, one group after the other (neighbouring runs may end in the same row)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            wave_sync();
-            if (kk == gq) {
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) mine[cur * LR + cb] += run[cb];
-            }
-        }
-    }
-}
-
-// The same sums for float32 records with a lane per kept value (Section 4.1, eq. (10)).  Beside its k values a record
+// The same sums in ordinary arithmetic with a lane per kept value, for float32 records and for groups of more than 64
+// columns (Section 4.1, eq. (10)): on this chip float32 matrix instructions do not hide under vector work, and a 16-row
+// product spends fifteen rows of every edge on zeros.  Beside its k values a record
 // holds the column of each as a byte; the value of slot t of a neighbour belongs to lane t of a group of sixteen, which
 // adds a_ij * value to that column of the destination row's sums in LDS: read, fused multiply-add, written back.  (A lane
 // that owns columns instead has to find the window of slots that may hold them from the neighbour's mask - a round trip to
@@ -930,18 +763,18 @@ __device__ __forceinline__ void gather_records_rows(const CsrView& g, const floa
 // latency: a wave waits for two thirds of its time, and LDS holds no more waves.)
 // The staged edges of a round are cut into four equal runs, one per lane group; a run's edges add straight into the rows
 // of the tile, except those of the run's first row, which the run before may share: they add into a row of the group's
-// own (tile rows 16 .. 19 of st), and those four rows join the tile at the end of the round, the rows that end inside
+// own (the four rows of st behind the tile), and those four rows join the tile at the end of the round, the rows that end inside
 // their run before the rows that fill one.  So no two groups touch one row in the same step, the values of one record
 // are in different columns, and the order of the additions is fixed by the edge list alone.
 // Lane s of a group holds edge s of the group's run, and a step takes its edge from there by a row broadcast of the
 // lanes (through LDS it took as much of the LDS pipe as the additions themselves).
-// st: 20 rows, zeroed by the caller (rows 16 .. 19 are left zero), and 64 words behind them where lanes without a value
+// st: TR + 4 rows, zeroed by the caller (the last four are left zero), and 64 words behind them where lanes without a value
 // add.  A run is a whole number of ROUND steps; the places past the last edge hold that edge once more with a_ij = 0.
 // k above 16 takes ceil(k / 16) passes over the edges of a round.  FEW: four steps' loads in flight instead of a whole
 // run's (for kernels without registers to spare).
-constexpr int GATHER_ROWS = 20;
-template <int DG>
-constexpr int gather_floats() { return GATHER_ROWS * tile_ld<DG>() + 64; }
+// The tile has TR rows (16, or 8 where a group is wider than 64 columns and LDS would hold too few waves).
+template <int DG, int TR = 16>
+constexpr int gather_floats() { return (TR + 4) * tile_ld<DG>() + 64; }
 typedef __attribute__((address_space(3))) float lds_float;
 
 // v of lane S of this lane's row of sixteen
@@ -987,16 +820,16 @@ __device__ __forceinline__ RunEdges run_edges(const CsrView& g, int eb, int e_b,
     return d;
 }
 
-template <int DG, int ROUND, bool FEW, typename T>
+template <int DG, int ROUND, bool FEW, int TR = 16, typename T>
 __device__ __forceinline__ void gather_values_rows(const CsrView& g, const T* __restrict__ vals, const uint8_t* __restrict__ cols,
                                                    int k, int e_a, int e_b, int lane, float* st) {
     constexpr int LR = tile_ld<DG>();
     static_assert(ROUND == 4 || ROUND == 8, "a run must fit the sixteen lanes of a group");
     const int slot = lane & 15, kk = lane >> 4;
-    const uint32_t base = (uint32_t)(uintptr_t)(lds_float*)st, dump = base + 4u * (uint32_t)(GATHER_ROWS * LR + lane);
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_float*)st, dump = base + 4u * (uint32_t)((TR + 4) * LR + lane);
     RunEdges next = run_edges<ROUND>(g, e_a, e_b, lane);
     for (int eb = e_a; eb < e_b; eb += 64) {
-        const int steps = next.steps, j = next.j, r = next.r;
+        const int steps = next.steps, j = next.j, r = next.r & (TR - 1);
         const float a = eb + kk * steps + slot < e_b ? next.a : 0.f;      // (lanes past the run: not used)
         int head[4], tail[4];                              // first and last row of every run
 #pragma unroll
@@ -1005,7 +838,7 @@ __device__ __forceinline__ void gather_values_rows(const CsrView& g, const T* __
             tail[q] = __builtin_amdgcn_readlane(r, 16 * q + steps - 1);
         }
         const uint32_t off0 = (uint32_t)j * (uint32_t)k;
-        const uint32_t row = base + 4u * (uint32_t)((r == (int)row_lane<0>((uint32_t)r) ? 16 + kk : r) * LR);
+        const uint32_t row = base + 4u * (uint32_t)((r == (int)row_lane<0>((uint32_t)r) ? TR + kk : r) * LR);
         if (eb + 64 < e_b) next = run_edges<ROUND>(g, eb + 64, e_b, lane);     // arrives while this round is added
         for (int t0 = 0; t0 < k; t0 += 16) {
             const bool has = t0 + slot < k;
@@ -1033,18 +866,19 @@ __device__ __forceinline__ void gather_values_rows(const CsrView& g, const T* __
             }
         }
         // the groups' own rows join the tile
-        if (lane < DG) {
+#pragma unroll
+        for (int c = lane; c < DG; c += 64) {
             float sum[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sum[q] = st[(16 + q) * LR + lane];
+            for (int q = 0; q < 4; ++q) sum[q] = st[(TR + q) * LR + c];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) st[(16 + q) * LR + lane] = 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (head[q] != tail[q]) st[head[q] * LR + lane] += sum[q];
+            for (int q = 0; q < 4; ++q) st[(TR + q) * LR + c] = 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (head[q] == tail[q]) st[head[q] * LR + lane] += sum[q];
+                if (head[q] != tail[q]) st[head[q] * LR + c] += sum[q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (head[q] == tail[q]) st[head[q] * LR + c] += sum[q];
         }
         wave_sync();
     }
@@ -1373,6 +1207,18 @@ __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int l
     __syncthreads();
 }
 
+// acc += the six products of one 16-deep step with W's block cb, smallest terms first
+template <int DG>
+__device__ __forceinline__ void mfma_b3(bf16x4 ah, bf16x4 am, bf16x4 al, const WLdsB3<DG>& wl, int s, int cb, int lane, f32x4& acc) {
+    const bf16x4 bh = as_bf16x4(wl.w[0][s][cb][lane]), bm = as_bf16x4(wl.w[1][s][cb][lane]), bl = as_bf16x4(wl.w[2][s][cb][lane]);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bm, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bh, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bm, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, acc, 0, 0, 0);
+}
+
 // acc = tile (16 x DG float32, LDS, row stride tile_ld) * W, in the tile register layout of mfma_tile.
 template <int DG>
 __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& wl, f32x4 (&acc)[DG / 16]) {
@@ -1388,17 +1234,7 @@ __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& 
         bf16x4 ah, am, al;
         split_p4(a, ah, am, al);
 #pragma unroll
-        for (int cb = 0; cb < CPL; ++cb) {
-            const bf16x4 bh = as_bf16x4(wl.w[0][s][cb][lane]), bm = as_bf16x4(wl.w[1][s][cb][lane]),
-                         bl = as_bf16x4(wl.w[2][s][cb][lane]);
-            // smallest terms first
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, acc[cb], 0, 0, 0);
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bm, acc[cb], 0, 0, 0);
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, acc[cb], 0, 0, 0);
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bh, acc[cb], 0, 0, 0);
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bm, acc[cb], 0, 0, 0);
-            acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, acc[cb], 0, 0, 0);
-        }
+        for (int cb = 0; cb < CPL; ++cb) mfma_b3<DG>(ah, am, al, wl, s, cb, lane, acc[cb]);
     }
 }
 
@@ -1915,6 +1751,7 @@ struct HubChunks {
     const int32_t* ce1;
     int32_t n_chunks;
     int32_t banded = 0;      // every XCD takes a contiguous eighth of the list (hub_sweep)
+    const int32_t* row = nullptr;    // the row that is all this chunk, or -1 (hub_out)
 };
 
 // Which chunks a wave takes; what a chunk's partial row holds does not depend on the wave that sums it.  The chunks
@@ -1967,11 +1804,21 @@ __device__ __forceinline__ void hub_chunk_store(const f32x4 (&acc)[DG / 16], flo
     }
 }
 
+// Where the sums of chunk q go: its partial row, or, with `rows`, straight to the row itself if that is all one chunk
+// (h.row).  Arrays of sums are [blocks of 64 columns][chunks or n][64].
+__device__ __forceinline__ float* hub_out(const HubChunks& h, float* part, float* rows, int n, int q, int block, int cols) {
+    if (rows) {
+        const int r = h.row[q];
+        if (r >= 0) return rows + ((size_t)block * n + r) * cols;
+    }
+    return part + ((size_t)block * h.n_chunks + q) * cols;
+}
+
+// 16-bit records of at most 64 columns
 template <int DG, typename T>
 __device__ __forceinline__ void hub_records_pass(const CsrView& g, const HubChunks& h, const T* __restrict__ vals,
                                                  const typename MaskOf<DG>::type* __restrict__ masks, int k,
-                                                 float* __restrict__ part, HubLds& L, const HubSweep w,
-                                                 const DealLutF* lutf) {
+                                                 float* __restrict__ part, HubLds& L, const HubSweep w) {
     const int lane = lane_id();
     for (int q = w.q; q < w.end; q += w.step) {
         const int e0 = __builtin_amdgcn_readfirstlane(h.ce0[q]), e1 = __builtin_amdgcn_readfirstlane(h.ce1[q]);
@@ -1979,16 +1826,66 @@ __device__ __forceinline__ void hub_records_pass(const CsrView& g, const HubChun
         f32x4 acc[DG / 16];
 #pragma unroll
         for (int cb = 0; cb < DG / 16; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        gather_records_mfma<DG, T, 16, true>(g, vals, masks, k, e0, e1, L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf, lane, acc,
-                                             nullptr, lutf);
+        gather_records_mfma<DG, T, 16, true>(g, vals, masks, k, e0, e1, L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf, lane, acc);
 #pragma unroll
         for (int cb = 0; cb < DG / 16; ++cb) acc[cb][0] = quarter_sum(acc[cb][0]);
         hub_chunk_store<DG>(acc, part + (size_t)q * DG, lane);
     }
 }
+
+// Records with the column of every value, any k and any width: a lane per value (gather_values_rows), lane group kk taking
+// the edges kk, kk + 4, .. of the chunk into a row of sums of its own; the four rows are added at the end of the chunk.
+template <int DG>
+struct HubRowsLds {
+    float rows[4][DG];
+    float dump[64];
+};
+template <int DG, typename T>
+__device__ __forceinline__ void hub_value_rows_pass(const CsrView& g, const HubChunks& h, const T* __restrict__ vals,
+                                                    const uint8_t* __restrict__ cols, int k, int n, float* __restrict__ part,
+                                                    float* __restrict__ rows, HubRowsLds<DG>& L, const HubSweep w) {
+    constexpr int BC = DG < 64 ? DG : 64;
+    const int lane = lane_id(), slot = lane & 15, kk = lane >> 4;
+    const uint32_t row = (uint32_t)(uintptr_t)(lds_float*)&L.rows[kk][0], dump = (uint32_t)(uintptr_t)(lds_float*)&L.dump[lane];
+    for (int i = lane; i < 4 * DG; i += 64) (&L.rows[0][0])[i] = 0.f;
+    wave_sync();
+    for (int q = w.q; q < w.end; q += w.step) {
+        const int e0 = __builtin_amdgcn_readfirstlane(h.ce0[q]), e1 = __builtin_amdgcn_readfirstlane(h.ce1[q]);
+        for (int eb = e0; eb < e1; eb += 64) {
+            const int e = eb + 4 * slot + kk, ec = e < e1 ? e : e1 - 1;
+            const uint32_t off0 = (uint32_t)__builtin_nontemporal_load(g.ci + ec) * (uint32_t)k;
+            const float av = __builtin_nontemporal_load(g.av + ec);
+            const float a = e < e1 ? av : 0.f;
+            const int steps = (min(e1 - eb, 64) + 3) >> 2;
+            for (int t0 = 0; t0 < k; t0 += 16) {
+                const bool has = t0 + slot < k;
+                const uint32_t t = (uint32_t)(has ? t0 + slot : t0);
+                if (steps > 8) {
+                    asm volatile("; 16 steps");       // (keeps the two apart, see gather_values_rows)
+                    values_run<0, 16>(vals, cols, off0, a, row, t, has, dump, std::make_integer_sequence<int, 16>{});
+                } else {
+                    asm volatile("; 8 steps");
+                    values_run<0, 8>(vals, cols, off0, a, row, t, has, dump, std::make_integer_sequence<int, 8>{});
+                }
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int c0 = 0; c0 < DG; c0 += 64) {
+            if (lane < BC) {
+                const int c = c0 + lane;
+                const float s = (L.rows[0][c] + L.rows[1][c]) + (L.rows[2][c] + L.rows[3][c]);
+#pragma unroll
+                for (int p = 0; p < 4; ++p) L.rows[p][c] = 0.f;
+                hub_out(h, part, rows, n, q, c0 >> 6, BC)[lane] = s;
+            }
+        }
+        wave_sync();
+    }
+}
 template <int DG, typename T>
 __device__ __forceinline__ void hub_dense_pass(const CsrView& g, const HubChunks& h, const T* __restrict__ x, int64_t ld,
-                                               float* __restrict__ part, HubLds& L, const HubSweep w) {
+                                               float* __restrict__ part, HubLds& L, const HubSweep w, float* __restrict__ rows = nullptr) {
     const int lane = lane_id();
     for (int q = w.q; q < w.end; q += w.step) {
         const int e0 = __builtin_amdgcn_readfirstlane(h.ce0[q]), e1 = __builtin_amdgcn_readfirstlane(h.ce1[q]);
@@ -1999,111 +1896,63 @@ __device__ __forceinline__ void hub_dense_pass(const CsrView& g, const HubChunks
         gather_dense_mfma<DG, T, 16, true>(g, x, ld, e0, e1, L.rp, L.ebuf, lane, acc);
 #pragma unroll
         for (int cb = 0; cb < DG / 16; ++cb) acc[cb][0] = quarter_sum(acc[cb][0]);
-        hub_chunk_store<DG>(acc, part + (size_t)q * DG, lane);
+        hub_chunk_store<DG>(acc, hub_out(h, part, rows, 0, q, 0, DG), lane);
     }
 }
 
+// cols != NULL: records with columns (float32), else 16-bit records with masks
 template <int DG, typename T>
-__global__ __launch_bounds__(256) void k_hub_records(CsrView g, HubChunks h, const T* __restrict__ vals,
-                                                     const typename MaskOf<DG>::type* __restrict__ masks, int k,
-                                                     float* __restrict__ part) {
-    __shared__ HubLds lds[4];
-    __shared__ DealLutF dlut;
-    deal_lutf_fill(dlut);
-    hub_records_pass<DG, T>(g, h, vals, masks, k, part, lds[threadIdx.x >> 6], hub_sweep(h), &dlut);
+__device__ __forceinline__ void hub_any_records_pass(const CsrView& g, const HubChunks& h, const Record<DG, T>& in, int k,
+                                                     float* __restrict__ part, void* lds, const HubSweep w) {
+    if constexpr (sizeof(T) == 4)
+        hub_value_rows_pass<DG, T>(g, h, in.vals, in.cols, k, 0, part, nullptr, reinterpret_cast<HubRowsLds<DG>*>(lds)[threadIdx.x >> 6], w);
+    else
+        hub_records_pass<DG, T>(g, h, in.vals, in.mask, k, part, reinterpret_cast<HubLds*>(lds)[threadIdx.x >> 6], w);
+}
+constexpr int hub_lds_bytes(int a, int b) { return 4 * (a > b ? a : b); }
+
+template <int DG, typename T>
+__global__ __launch_bounds__(256) void k_hub_records(CsrView g, HubChunks h, Record<DG, T> in, int k, float* __restrict__ part) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[hub_lds_bytes(sizeof(HubLds), sizeof(HubRowsLds<DG>))];
+    hub_any_records_pass<DG, T>(g, h, in, k, part, lds, hub_sweep(h));
 }
 
 template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_hub_dense(CsrView g, HubChunks h, const T* __restrict__ x, int64_t ld,
-                                                   float* __restrict__ part) {
+                                                   float* __restrict__ part, float* __restrict__ rows = nullptr) {
     __shared__ HubLds lds[4];
-    hub_dense_pass<DG, T>(g, h, x, ld, part, lds[threadIdx.x >> 6], hub_sweep(h));
+    hub_dense_pass<DG, T>(g, h, x, ld, part, lds[threadIdx.x >> 6], hub_sweep(h), rows);
 }
 
 // Both first passes of one block's backward in one launch: blockIdx.y = 0 takes the records over A (for the
 // inverse), blockIdx.y = 1 the dense gradient rows over A^T (for the data gradient).
 template <int DG, typename T>
-__global__ __launch_bounds__(256) void k_hub_both(CsrView ga, HubChunks ha, const T* __restrict__ vals,
-                                                  const typename MaskOf<DG>::type* __restrict__ masks, int k,
-                                                  float* __restrict__ part_a, CsrView gt, HubChunks ht,
-                                                  const T* __restrict__ x, int64_t ld, float* __restrict__ part_t) {
-    __shared__ HubLds lds[4];
-    __shared__ DealLutF dlut;
-    deal_lutf_fill(dlut);
-    if (blockIdx.y == 0) hub_records_pass<DG, T>(ga, ha, vals, masks, k, part_a, lds[threadIdx.x >> 6], hub_sweep(ha), &dlut);
-    else hub_dense_pass<DG, T>(gt, ht, x, ld, part_t, lds[threadIdx.x >> 6], hub_sweep(ht));
+__global__ __launch_bounds__(256) void k_hub_both(CsrView ga, HubChunks ha, Record<DG, T> in, int k, float* __restrict__ part_a,
+                                                  CsrView gt, HubChunks ht, const T* __restrict__ x, int64_t ld,
+                                                  float* __restrict__ part_t) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[hub_lds_bytes(sizeof(HubLds), sizeof(HubRowsLds<DG>))];
+    if (blockIdx.y == 0) hub_any_records_pass<DG, T>(ga, ha, in, k, part_a, lds, hub_sweep(ha));
+    else hub_dense_pass<DG, T>(gt, ht, x, ld, part_t, reinterpret_cast<HubLds*>(lds)[threadIdx.x >> 6], hub_sweep(ht));
 }
 
-// ---- first pass over the chunks, value by value (float32 records) ---------------------------------
-// On graphs where nearly every row is split the first pass is the step, and dealing a record to the lanes that own
-// its columns (sixteen lanes, a four-slot window each: four times the record's bytes through the vector cache, some
-// thirty instructions per four edges) is what it spends.  Here a lane owns a *value* instead: LPE = 2^LG lanes per
-// edge, lane t of them loads value t (+ LPE, + 2 LPE .. below k) of the record and the number of its column - one
-// byte per value, written from the column mask by k_record_columns before the pass (0xFF for a slot the record does
-// not use: a column block of a wide group keeps between 0 and k values) - and adds a_ij * value to that
-// column of its edge place's row in LDS (64 / LPE places, each a row of DG floats; the places of one instruction are
-// different rows and the values of one record different columns, so no two lanes meet): the sum is read, added to
-// and written back by the lane, and stays in the row for the whole chunk.  Even and odd instructions of a batch keep
-// rows of their own, so two such chains are in flight.  At the end of a chunk the rows of the places are added in
+// The records of a group of S column blocks
+template <int S, typename T>
+__global__ __launch_bounds__(256) void k_hub_records_wide(CsrView g, HubChunks h, const T* __restrict__ vals, const uint8_t* __restrict__ cols,
+                                                          int k, int n, float* __restrict__ part, float* __restrict__ rows) {
+    __shared__ HubRowsLds<64 * S> lds[4];
+    hub_value_rows_pass<64 * S, T>(g, h, vals, cols, k, n, part, rows, lds[threadIdx.x >> 6], hub_sweep(h));
+}
+
+// ---- first pass over the chunks of a graph of long rows, value by value (float32 records) -----------------
+// There nearly every row is split and the first pass is the step.  As hub_value_rows_pass, but with as many lanes per edge
+// as the record has values, LPE = 2^LG: lane t of them loads value t (+ LPE, + 2 LPE .. below k) and its column and adds
+// a_ij * value to that column of its edge place's row in LDS (64 / LPE places, each a row of DG floats; the places of one
+// instruction are different rows and the values of one record different columns, so no two lanes meet): the sum is read,
+// added to and written back by the lane, and stays in the row for the whole chunk.  Even and odd instructions of a batch
+// keep rows of their own, so two such chains are in flight.  At the end of a chunk the rows of the places are added in
 // place order and cleared.  Scattering into zeroed rows, reading them back sixteen bytes wide into running sums and
-// clearing them again was 3 % slower; LDS float atomics were four times slower than the dealing (one such
-// instruction takes some 140 cycles).  The order of the additions is fixed by the edge list and the lane layout.
-template <int DG>
-__global__ __launch_bounds__(256) void k_record_columns(int n, int k, const typename MaskOf<DG>::type* __restrict__ masks,
-                                                        uint8_t* __restrict__ cols) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
-    uint64_t m = (uint64_t)masks[j];
-    uint8_t* o = cols + (size_t)j * k;
-    if ((k & 3) == 0) {
-        for (int t = 0; t < k; t += 4) {
-            uint32_t w = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const uint32_t c = m ? (uint32_t)__builtin_ctzll(m) : 0xFFu;
-                m &= m - 1;
-                w |= c << (8 * b);
-            }
-            *reinterpret_cast<uint32_t*>(o + t) = w;
-        }
-    } else {
-        for (int t = 0; t < k; ++t) {
-            o[t] = m ? (uint8_t)__builtin_ctzll(m) : (uint8_t)0xFF;
-            m &= m - 1;
-        }
-    }
-}
-
-// The same for a group of S column blocks of 64 (S = 2 or 3: a column number must fit a byte beside the 0xFF of an
-// unused slot): the k values a row keeps over its whole width, taken out of the S records of its column blocks into
-// one list [n][k] with the column in the whole row beside each, so that one first pass serves all S blocks and every
-// lane of it has a value (a pass per column block walks the edges S times with room for k values in each).
-template <int S>
-struct WideRecords {
-    const float* vals[S];
-    const uint64_t* mask[S];
-};
-template <int S>
-__global__ __launch_bounds__(256) void k_record_columns_wide(int n, int k, WideRecords<S> r, float* __restrict__ vals,
-                                                             uint8_t* __restrict__ cols) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
-    float* v = vals + (size_t)j * k;
-    uint8_t* o = cols + (size_t)j * k;
-    int pos = 0;
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        uint64_t m = r.mask[s][j];
-        const float* src = r.vals[s] + (size_t)j * k;
-        for (int t = 0; m && pos < k; ++t, ++pos) {
-            v[pos] = src[t];
-            o[pos] = (uint8_t)(64 * s + __builtin_ctzll(m));
-            m &= m - 1;
-        }
-    }
-    for (; pos < k; ++pos) { v[pos] = 0.f; o[pos] = (uint8_t)0xFF; }
-}
-
+// clearing them again was 3 % slower; LDS float atomics were four times slower (one such instruction takes some 140
+// cycles).  The order of the additions is fixed by the edge list and the lane layout.
 template <int DG, int LG>
 struct HubValLds {
     uint2 ebuf[64];                   // (j * k, a_ij) of the staged edges
@@ -2113,8 +1962,8 @@ struct HubValLds {
 
 template <int DG, int LG, int KQ>
 __device__ __forceinline__ void hub_values_pass(const CsrView& g, const HubChunks& h, const float* __restrict__ vals,
-                                                const uint8_t* __restrict__ cols, int k, float* __restrict__ part,
-                                                HubValLds<DG, LG>& L, const HubSweep w) {
+                                                const uint8_t* __restrict__ cols, int k, int n, float* __restrict__ part,
+                                                float* __restrict__ rows, HubValLds<DG, LG>& L, const HubSweep w) {
     constexpr int LPE = 1 << LG, NE = 64 >> LG;          // lanes per edge, edges per instruction
     constexpr int MAXS = 64 / NE;                        // instructions per round of 64 staged edges
     constexpr int GB = KQ == 1 ? (MAXS < 8 ? MAXS : 8) : KQ == 2 ? 4 : 2;
@@ -2165,21 +2014,19 @@ __device__ __forceinline__ void hub_values_pass(const CsrView& g, const HubChunk
 #pragma unroll
                     for (int w = 0; w < KQ; ++w) {
                         const bool has = KQ == 1 || t + w * LPE < k;      // (else slot 0 once more: not added again)
-                        const bool h0 = has && c[u][w] != 0xFFu, h1 = has && c[u + 1][w] != 0xFFu;
-                        const int i0 = h0 ? place * DG + (int)c[u][w] : spare;
-                        const int i1 = h1 ? TOT + place * DG + (int)c[u + 1][w] : spare;
+                        const int i0 = has ? place * DG + (int)c[u][w] : spare;
+                        const int i1 = has ? TOT + place * DG + (int)c[u + 1][w] : spare;
                         const float o0 = base[i0];
                         const float o1 = base[i1];
                         wave_sync();
-                        base[i0] = o0 + (h0 ? v[u][w] : 0.f);
-                        base[i1] = o1 + (h1 ? v[u + 1][w] : 0.f);
+                        base[i0] = o0 + (has ? v[u][w] : 0.f);
+                        base[i1] = o1 + (has ? v[u + 1][w] : 0.f);
                         wave_sync();
                     }
                 }
             }
         }
         // the sums of the places are added in place order, even rows before odd rows, and the rows cleared
-        // (DG > 64, a group of column blocks: part is [DG / 64][n_chunks][64], one array of partial rows per block)
         wave_sync();
 #pragma unroll
         for (int c0 = 0; c0 < DG; c0 += 64) {
@@ -2191,8 +2038,7 @@ __device__ __forceinline__ void hub_values_pass(const CsrView& g, const HubChunk
                     s += base[pl * DG + c];
                     base[pl * DG + c] = 0.f;
                 }
-                if (DG > 64) part[((size_t)(c0 >> 6) * h.n_chunks + q) * 64 + lane] = s;
-                else part[(size_t)q * DG + lane] = s;
+                hub_out(h, part, rows, n, q, c0 >> 6, DG < 64 ? DG : 64)[lane] = s;
             }
         }
         wave_sync();
@@ -2220,9 +2066,10 @@ inline void hub_values_variant_wide(int k, F&& f) {
 
 template <int DG, int LG, int KQ>
 __global__ __launch_bounds__(256) void k_hub_values(CsrView g, HubChunks h, const float* __restrict__ vals,
-                                                    const uint8_t* __restrict__ cols, int k, float* __restrict__ part) {
+                                                    const uint8_t* __restrict__ cols, int k, int n, float* __restrict__ part,
+                                                    float* __restrict__ rows) {
     __shared__ HubValLds<DG, LG> lds[4];
-    hub_values_pass<DG, LG, KQ>(g, h, vals, cols, k, part, lds[threadIdx.x >> 6], hub_sweep(h));
+    hub_values_pass<DG, LG, KQ>(g, h, vals, cols, k, n, part, rows, lds[threadIdx.x >> 6], hub_sweep(h));
 }
 
 }  // namespace gsr

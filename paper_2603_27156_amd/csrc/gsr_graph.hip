@@ -136,6 +136,7 @@ static void free_csr(Csr& c) {
     if (c.hub.crow) (void)hipFree(c.hub.crow);
     if (c.hub.ce0) (void)hipFree(c.hub.ce0);
     if (c.hub.ce1) (void)hipFree(c.hub.ce1);
+    if (c.hub.single) (void)hipFree(c.hub.single);
     if (c.heavy) (void)hipFree(c.heavy);
     c = Csr();
 }
@@ -182,7 +183,7 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
     std::vector<uint8_t> er(h.ci.size());
     for (int64_t i = 0; i < n; ++i) std::fill(er.begin() + h.rp[i], er.begin() + h.rp[i + 1], (uint8_t)(i & 15));
     GSR_TRY(upload(er, &out->er));
-    std::vector<int32_t> rows, cptr, crow, ce0, ce1, tile0;
+    std::vector<int32_t> rows, cptr, crow, ce0, ce1, tile0, single;
     cptr.push_back(0);
     for (int64_t i = 0; i < n; ++i) {
         if ((i & 15) == 0) tile0.push_back((int32_t)rows.size());
@@ -195,6 +196,7 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
             ce0.push_back((int32_t)e);
             ce1.push_back((int32_t)std::min<int64_t>(e + chunk, h.rp[i + 1]));
         }
+        for (size_t q = cptr.back(); q < crow.size(); ++q) single.push_back(crow.size() - cptr.back() == 1 ? (int32_t)i : -1);
         cptr.push_back((int32_t)crow.size());
     }
     tile0.push_back((int32_t)rows.size());
@@ -206,6 +208,7 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
     GSR_TRY(upload(crow, &out->hub.crow));
     GSR_TRY(upload(ce0, &out->hub.ce0));
     GSR_TRY(upload(ce1, &out->hub.ce1));
+    GSR_TRY(upload(single, &out->hub.single));
     return GSR_OK;
 }
 
@@ -267,13 +270,16 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
     const int S = sub_planes(cfg);
     const size_t dgs = dg / S;                       // columns of a tile: 32 or 64
     size_t off = 0;
-    for (int s = 0; s < cfg->c * S && s < kMaxRecordSlots; ++s) {
+    // (groups of S column blocks: one list of values and columns per group, a mask per block)
+    for (int s = 0; s < cfg->c; ++s) {
         w.rec_vals[s] = off;
         off += align_up(n * (size_t)cfg->k * b + 16);   // the record gather loads up to 16 bytes past a record
+        w.rec_cols[s] = off;
+        if (S > 1 || b == 4) off += align_up(n * (size_t)cfg->k + 16);
+    }
+    for (int s = 0; s < cfg->c * S && s < kMaxRecordSlots; ++s) {
         w.rec_mask[s] = off;
         off += align_up(n * (dgs == 32 ? 4 : 8));
-        w.rec_cols[s] = off;
-        if (S == 1 && b == 4) off += align_up(n * (size_t)cfg->k + 16);
     }
     w.y0 = off;
     off += align_up(n * dg * b);
@@ -283,17 +289,12 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
     off += align_up((size_t)g->grid * dgs * dgs * sizeof(float) * (size_t)(S * S));      // (wide groups: a set per block of dW_i)
     w.hub_partial = off;
     size_t chunks = (size_t)std::max(g->a.hub.n_chunks, g->at.hub.n_chunks);
-    // (wide groups summed value by value: the partial rows of all S column blocks from one pass, [S][chunks][64])
-    const bool wide_values = S > 1 && b == 4 && g->hub_values;
-    off += align_up(std::max<size_t>(chunks, 1) * dgs * (wide_values ? S : 1) * sizeof(float));
+    off += align_up(std::max<size_t>(chunks, 1) * dgs * S * sizeof(float));
     w.hub_partial2 = off;
-    off += align_up(std::max<size_t>(chunks, 1) * dgs * sizeof(float));
-    w.hub_cols = off;
-    if (b == 4 && g->hub_values) off += align_up(n * (size_t)cfg->k + 16);
-    w.hub_vals = off;
-    if (wide_values) off += align_up(n * (size_t)cfg->k * sizeof(float) + 16);
+    if (S == 1) off += align_up(std::max<size_t>(chunks, 1) * dgs * sizeof(float));
     w.h = off;               // (not for 16-bit storage at 32 columns: that backward keeps H on chip)
-    if ((b == 4 || dgs == 64) && g->split_backward) off += align_up(n * dgs * sizeof(float));
+    if (S > 1) off += align_up(n * dg * sizeof(float));
+    else if ((b == 4 || dgs == 64) && g->split_backward) off += align_up(n * dgs * sizeof(float));
     w.total = off;
     return w;
 }
@@ -544,6 +545,7 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
                                   : long_rows ? 1 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
     const int64_t hub_chunk = options().hub_chunk > 0 ? options().hub_chunk : (long_rows ? 512 : 64);      // (Table-1-shaped graph, rows of up to 390 entries: 289 / 274 / 263 / 263 ms per step with chunks of 128 / 256 / 512 / 1,024)
     g->hub_threshold = (int32_t)hub_threshold;
+    g->hub_chunk = (int32_t)hub_chunk;
     // (with more tiles per wave the tile with the long nets starts early and is hidden: there the first pass is better short)
     const bool grow = few_tiles && !long_rows && options().hub_chunk == 0;
     g->hub_values = options().hub_values == 1 ? 2 : (options().hub_values == 0 && long_rows) ? 1 : 0;

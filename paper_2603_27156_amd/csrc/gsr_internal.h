@@ -76,6 +76,7 @@ struct HubPlan {
     int32_t* crow = nullptr;  // device [n_chunks] row of the chunk
     int32_t* ce0 = nullptr;   // device [n_chunks] first edge
     int32_t* ce1 = nullptr;   // device [n_chunks] one past the last edge
+    int32_t* single = nullptr; // device [n_chunks] the row if the chunk is all of it, else -1
 };
 
 // 16-row tiles with more than this many stored entries in rows that are not split are listed per matrix; the
@@ -109,6 +110,7 @@ struct gsr_graph {
                              // 2 k <= D/C (beyond that the dealing of the tile kernels is faster: 650 against 490 ms per step
                              // at k = D/C = 64 on the Table-1-shaped graph, 464 against 473 at k = 32), 2 always
     int32_t hub_threshold = 512;
+    int32_t hub_chunk = 64;
     int device = 0;
     int num_cus = 256;
     int grid = 512;          // workgroups of the persistent row-tile kernels (multiple of 8)
@@ -128,17 +130,15 @@ gsr_status_t validate_config(const gsr_config_t* cfg, const gsr_graph_t* g, bool
 // Workspace carving shared by gsr_workspace_size and the layer / step calls.
 constexpr int kMaxRecordSlots = 32;   // groups (at most 8) x sub-planes of a group (at most 4)
 struct LayerWs {
-    size_t rec_vals[kMaxRecordSlots];  // per slot and sub-plane: compressed values  [n][k] of T
-    size_t rec_cols[kMaxRecordSlots];  // per slot, float32 and groups of at most 64 columns: column of every value [n][k] bytes
+    size_t rec_vals[kMaxRecordSlots];  // per slot: compressed values  [n][k] of T
+    size_t rec_cols[kMaxRecordSlots];  // per slot (float32, or groups of more than 64 columns): column of every value [n][k] bytes
     size_t rec_mask[kMaxRecordSlots];  // per slot and sub-plane: column bit mask    [n] of uint32 (32 columns) / uint64 (64)
     size_t y0;           // Y_0 plane [n][dg] of T (C > 2); wide groups: [S][n][64]
-    size_t h;            // [n][min(dg, 64)] float: H of the block being inverted, for the weight-gradient kernel
-    size_t dh;           // wide groups only: [S][n][64] float, the block gradient summed over column blocks
+    size_t h;            // [n][dg] float: H of the block being inverted, for the weight-gradient kernel; wide groups: [S][n][64], H
+    size_t dh;           // wide groups only: [S][n][64] float, Q = A^T dY_i
     size_t dw_partial;   // [grid][dg*dg] float; wide groups: [S*S][grid][64*64]
-    size_t hub_partial;  // [max(n_chunks A, n_chunks A^T)][dg] float
-    size_t hub_partial2; // same size: the backward's two first passes of a block run as one launch
-    size_t hub_cols;     // [n][k] bytes: column of every record value, for the value-by-value first pass (float32)
-    size_t hub_vals;     // wide groups, same pass: [n][k] float, the kept values of a whole row side by side
+    size_t hub_partial;  // [max(n_chunks A, n_chunks A^T)][dg] float; wide groups: [S][chunks][64]
+    size_t hub_partial2; // same size: the backward's two first passes of a block run as one launch (not wide groups)
     size_t total;
 };
 struct StepWs {

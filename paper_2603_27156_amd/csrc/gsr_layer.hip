@@ -55,10 +55,6 @@ struct BlockArgs {
     int* draws_done;
     TieSeg<DG> tie;         // where rows that select at a near-tie are listed (count == NULL: nowhere)
     float* h_out;           // [n][DG] float32: receives H = A scatter(V, I) of the block for k_dw (NULL: not kept)
-    // YG (groups wider than a tile): blockIdx.y is the column block written, ob: W_i's block 64 columns on, the plane
-    // and dY 64 elements on, the dW partials and the tile counters a set on
-    size_t y_dw_partial;
-    int y_draws;
 };
 
 // B3: the H W_i (and dW_i) products on the bf16 matrix pipe from three-term splits (mfma_tile_b3), with W_i kept
@@ -70,29 +66,20 @@ struct BlockArgs {
 // always use the split form: the plain and the fused inverse must rebuild the same bits.
 constexpr int block_waves(bool with_dw, bool b3) { return (!with_dw && b3) ? 8 : 4; }
 
-template <int DG, typename T, int SIGN, bool WITH_DW, bool DEAL, bool B3 = true, bool YG = false>
+template <int DG, typename T, int SIGN, bool WITH_DW, bool DEAL, bool B3 = true>
 __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgpu_waves_per_eu(WITH_DW ? 2 : 4))) void k_block(BlockArgs<DG, T> a) {
     static_assert(B3 || (SIGN > 0 && !WITH_DW), "only the forward kernel has a float32 variant");
-    if constexpr (YG) {
-        const int ob = blockIdx.y;
-        a.w += 64 * ob;
-        a.plane += 64 * ob;
-        if (a.dy) a.dy += 64 * ob;
-        a.dw_partial += (size_t)ob * a.y_dw_partial;
-        if (a.draws) { a.draws += ob * a.y_draws; a.draws_done += ob * a.y_draws; }
-        if (ob > 0) a.h_out = nullptr;          // (the same rows for every column block written)
-    }
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     // float32 records carry their columns (gather_values_rows, emit_tile)
-    constexpr bool COLS = sizeof(T) == 4 && !YG;
+    constexpr bool COLS = sizeof(T) == 4;
     __shared__ WaveLds<DG, COLS> lds[block_waves(WITH_DW, B3)];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     WaveLds<DG, COLS>& L = lds[wave];
     float* st_h = L.st;
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
-    __shared__ typename std::conditional<sizeof(T) == 2, DealLut, DealLutF>::type dlut;
+    struct None {};
+    __shared__ typename std::conditional<sizeof(T) == 2, DealLut, None>::type dlut;
     if constexpr (sizeof(T) == 2) deal_lut_fill(dlut);
-    else if constexpr (!COLS) deal_lutf_fill(dlut);
     if constexpr (B3) load_w_lds_b3<DG>(a.w, a.ldw, false, wl);
     else load_w_lds<DG>(a.w, a.ldw, false, wl);
     f32x4 dw[WITH_DW ? DG / 16 : 1][WITH_DW ? DG / 16 : 1];
@@ -174,15 +161,9 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         // float32: the sums in ordinary arithmetic, in the forward and in both inverse kernels alike, so that f_i is
         // recomputed by the instructions that computed it.
         if constexpr (COLS) {
-            tile_gather_rows<DG, true, GATHER_ROWS>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
+            tile_gather_rows<DG, true, 20>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
                 gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, __builtin_amdgcn_readfirstlane(e_a),
                                           __builtin_amdgcn_readfirstlane(e_b), lane, st_h);
-            });
-        } else if constexpr (sizeof(T) == 4) {
-            tile_gather_rows<DG>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
-                gather_records_rows<DG, 4, true>(a.g, a.in.vals, a.in.mask, a.k, __builtin_amdgcn_readfirstlane(e_a),
-                                                 __builtin_amdgcn_readfirstlane(e_b), L.rp, reinterpret_cast<RecEdge*>(L.ebuf),
-                                                 L.rbuf, lane, st_h, &dlut);
             });
         } else {
             f32x4 hacc[DG / 16];
@@ -371,6 +352,10 @@ template <int DG, typename T>
 struct DwArgs {
     int n, tiles;
     const float* h;         // [n][DG]
+    // groups of S column blocks: blockIdx.y = mb S + ob takes H_mb (planes of [n][64]) and dY's columns 64 ob on, into a set
+    // of partials of its own, y_set floats on (S = 0: one set)
+    int S;
+    size_t y_set;
     const T* dy;            // row stride ldg
     int64_t ldg;
     float* dw_partial;      // [gridDim.x][DG*DG]
@@ -386,6 +371,11 @@ struct DwArgs {
 
 template <int DG, typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_dw(DwArgs<DG, T> a) {
+    if (a.S) {
+        a.h += (size_t)(blockIdx.y / a.S) * a.n * DG;
+        a.dy += 64 * (blockIdx.y % a.S);
+        a.dw_partial += (size_t)blockIdx.y * a.y_set;
+    }
     if (a.tie.count)
         tie_fixup_rows<DG, T>(a.tie, a.fix_plane, a.fix_ld, a.k, a.norm, a.eps, a.fix_out, (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6),
                               (int)((gridDim.x * blockDim.x) >> 6));
@@ -489,12 +479,6 @@ struct GradArgs {
     const float* dw_partial;
     int dw_parts;
     float* dw_out;
-    // ACC (groups wider than one tile: the gradient of a block is summed over its column blocks before the epilogue):
-    // dh [n][DG] float32 receives dH = Q W^T (dh_first) or has it added
-    float* dh;
-    bool dh_first;
-    // ACC: blockIdx.y is the block mb of dH written: W_i's block 64 rows on, dh a plane of [n][64] on, the tile counters a set on
-    int y_draws;
 };
 
 // dW_i[e] = sum over the workgroup partials, in a fixed order: a workgroup takes 64 entries at a time; its four
@@ -534,20 +518,13 @@ __device__ __forceinline__ void dw_reduce_slices(const float* __restrict__ parti
 // against 132).
 constexpr int grad_waves(bool b3) { return b3 ? 8 : 4; }
 
-template <int DG, typename T, bool DEAL, bool B3, bool ACC = false>
+template <int DG, typename T, bool DEAL, bool B3>
 __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_per_eu(4))) void k_grad(GradArgs<DG, T> a) {
     constexpr int CPL = DG / 16;
     constexpr int GRAD_WAVES = grad_waves(B3);
-    if constexpr (ACC) {
-        const int mb = blockIdx.y;
-        a.w += (size_t)mb * 64 * a.ldw;
-        a.dh += (size_t)mb * a.n * 64;
-        a.draws += mb * a.y_draws;
-        a.draws_done += mb * a.y_draws;
-    }
     // the partial rows of a tile's split rows requested together (hub_rows_fill) only where that spills no register:
     // these kernels sit at their 128 registers
-    constexpr bool FILL_FAST = ACC || (!DEAL && sizeof(T) == 4 && DG == 64);
+    constexpr bool FILL_FAST = !DEAL && sizeof(T) == 4 && DG == 64;
     __shared__ WaveLds<DG> lds[GRAD_WAVES];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     WaveLds<DG>& L = lds[wave];
@@ -577,10 +554,8 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         for (int reg = 0; reg < 4; ++reg) {
             const int row = r0 + 4 * reg + tg;
             const size_t rowc = (size_t)(row < a.n ? row : a.n - 1);
-            if constexpr (!ACC) {
-                own[reg] = a.own_mask[rowc];
-                if (a.norm == GSR_NORM_RMS) load_cols<CPL, T>(a.z + rowc * a.ldz + CPL * tj, z[reg]);
-            }
+            own[reg] = a.own_mask[rowc];
+            if (a.norm == GSR_NORM_RMS) load_cols<CPL, T>(a.z + rowc * a.ldz + CPL * tj, z[reg]);
         }
         const bool has_hub = tile_begin(a.gt, rpv, L.rp, lane);
         if constexpr (DEAL) {
@@ -613,11 +588,6 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         for (int reg = 0; reg < 4; ++reg) {
             const int row = r0 + 4 * reg + tg;
             const bool ok = row < a.n;
-            if constexpr (ACC) {
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) dz[reg][cb] = acc[cb][reg];
-                continue;
-            }
             const uint32_t bits = ok ? (uint32_t)(own[reg] >> (CPL * tj)) & ((1u << CPL) - 1u) : 0u;
             if (a.norm == GSR_NORM_RMS) {
                 // V = Z[I] * rinv, rinv = (mean Z^2 + eps)^-1/2:
@@ -639,25 +609,8 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
                 for (int cb = 0; cb < CPL; ++cb) dz[reg][cb] = ((bits >> cb) & 1u) ? acc[cb][reg] : 0.f;
             }
         }
-        // the planes that receive dZ (or the float32 sum of dH): the four rows of a plane are requested together
-        if constexpr (ACC) {
-            float g[4][CPL];
-#pragma unroll
-            for (int reg = 0; reg < 4; ++reg) {
-                const int row = r0 + 4 * reg + tg;
-                const int rowc = row < a.n ? row : a.n - 1;
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) g[reg][cb] = 0.f;
-                if (!a.dh_first) load_cols<CPL, float>(a.dh + (size_t)rowc * DG + CPL * tj, g[reg]);
-            }
-#pragma unroll
-            for (int reg = 0; reg < 4; ++reg) {
-                const int row = r0 + 4 * reg + tg;
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) g[reg][cb] += dz[reg][cb];
-                if (row < a.n) store_cols<CPL, float>(a.dh + (size_t)row * DG + CPL * tj, g[reg]);
-            }
-        } else {
+        // the planes that receive dZ: the four rows of a plane are requested together
+        {
             // JC planes at a time: all their rows are requested before the first is written back (block 1 updates C - 1
             // planes; one plane after the other took 3.2 ms against 1.2 ms for a one-plane launch at 8M rows, C = 8, 16-bit
             // rows of 32 columns).  float32 at 64 columns: two planes spill registers, 285 us per launch against 273
@@ -780,11 +733,311 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
 }
 
 // ---- groups wider than one tile: D/C = 64 S, S = 2, 3 or 4 ---------------------------------------------------
-// Such a group is handled as S column blocks of 64 ("sub-planes": block s of a row starts 64 s elements into it).  The
-// aggregation is column-wise, so every sub-plane has a record of its own in the 64-column format (the kept values that
-// fall into it, at most k, and its 64-bit mask) and the 64-column block kernels compute Y_i[:, ob] (+)= H_mb W_i[mb][ob]
-// one pair (mb, ob) per launch.  What couples the sub-planes is GS, which selects over the whole row (Section 4.1),
-// and the scale and the backward through it: those are the two kernels below.
+// A block of such a group runs as separate passes over planes of 64 columns: H = A scatter(V, I) for the whole row at once
+// (k_gather_wide; a row that is one first-pass chunk gets its sums straight from that pass), X_i +- H W_i
+// (k_wide_product), GS over the whole row (k_gs_wide), and for the gradient Q = A^T dY_i (k_dense_planes), then dH = Q W_i^T
+// and back through GS (k_wide_grad).  W_i, up to 256 x 256, does not fit the LDS beside the tiles of a gather, and a kernel
+// per pair of 64-column blocks has to gather every input block S times and to read and write the plane S times (as it was
+// before: 200k nodes, two groups of 128, backward 1,523 us; 50k nodes of mean degree 236, two groups of 192, forward 690).
+
+template <int S, typename T>
+struct WideGatherArgs {
+    CsrView g;
+    int n, tiles;           // tiles of eight rows
+    const T* vals;          // the record: [n][k] values and columns of the whole row
+    const uint8_t* cols;
+    int k;
+    const float* hub_part;  // [S][chunks][64]
+    int n_chunks;
+    float* h;               // [S][n][64]
+    int* draws;
+    int* draws_done;
+};
+
+// Eight rows per wave: their sums, twelve rows of 64 S floats, leave LDS for sixteen waves per compute unit at S = 3.
+template <int S, typename T>
+__global__ __launch_bounds__(256) void k_gather_wide(WideGatherArgs<S, T> a) {
+    constexpr int DGW = 64 * S, LR = tile_ld<DGW>();
+    struct Wave {
+        alignas(16) float st[gather_floats<DGW, 8>()];
+        int rp[20];
+    };
+    __shared__ Wave lds[4];
+    Wave& L = lds[threadIdx.x >> 6];
+    const int lane = lane_id();
+    TileWalk<false> walk(a.g, a.tiles, a.draws, a.draws_done);
+    while (walk.more()) {
+        walk.ahead();
+        const int r0 = walk.t * 8, up = r0 & 8;            // up: the second half of a 16-row tile
+        wave_sync();
+        const int rpv = tile_rp_load(a.g, r0 - up, a.n, lane);
+        if (lane < 17) L.rp[lane] = rpv;
+        for (int i = 4 * lane; i < 12 * LR; i += 256) *reinterpret_cast<f32v4*>(L.st + i) = f32v4{0.f, 0.f, 0.f, 0.f};
+        wave_sync();
+        const int len = lane < 16 ? L.rp[lane + 1] - rpv : 0;
+        const uint64_t splits = ballot(len > a.g.hub_threshold);
+        // rows the first pass has written already (h.row of HubChunks)
+        const uint32_t done = (uint32_t)(ballot(len > a.g.hub_threshold && len <= a.g.hub_chunk) >> up) & 255u;
+        const uint32_t split = (uint32_t)(splits >> up) & 255u;
+        int run = 0;
+        for (int r = 0; r <= 8; ++r) {
+            const bool hub = r < 8 && ((split >> r) & 1u);
+            if (r == 8 || hub) {
+                const int e_a = __builtin_amdgcn_readfirstlane(L.rp[up + run]), e_b = __builtin_amdgcn_readfirstlane(L.rp[up + r]);
+                if (e_b > e_a) gather_values_rows<DGW, 4, false, 8>(a.g, a.vals, a.cols, a.k, e_a, e_b, lane, L.st);
+                run = r + 1;
+            }
+        }
+        for (int r = 0; r < 8; ++r) {
+            if (!((split & ~done) >> r & 1u)) continue;    // a row of several chunks
+            const int hrow = a.g.hub_tile0[r0 >> 4] + __popcll(splits & (((uint64_t)1 << (up + r)) - 1));
+            const int q = a.g.hub_cptr[hrow], q1 = a.g.hub_cptr[hrow + 1];
+            for (int s = 0; s < S; ++s)
+                L.st[r * LR + 64 * s + lane] = hub_chunks_sum<64>(a.hub_part + (size_t)s * a.n_chunks * 64, q, q1, lane, 0.f);
+        }
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            if (r0 + r >= a.n || ((done >> r) & 1u)) continue;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                __builtin_nontemporal_store(L.st[r * LR + 64 * s + lane], a.h + ((size_t)s * a.n + r0 + r) * 64 + lane);
+        }
+        walk.next(a.g);
+    }
+    walk.finish();
+}
+
+// Q = A^T dY, blockIdx.y a block of 64 columns: planes q [S][n][64]
+template <typename T>
+struct DensePlanesArgs {
+    CsrView g;
+    int n, tiles;
+    const T* x;             // row stride ld; block y 64 y columns on
+    int64_t ld;
+    const float* hub_part;  // [S][chunks][64]
+    int n_chunks;
+    float* q;
+    int* draws;             // a counter set per block
+    int* draws_done;
+    int y_draws;
+};
+template <typename T, bool DEAL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_dense_planes(DensePlanesArgs<T> a) {
+    constexpr int LR = tile_ld<64>();
+    const int block = blockIdx.y;
+    const T* x = a.x + 64 * block;
+    const float* part = a.hub_part + (size_t)block * a.n_chunks * 64;
+    float* q = a.q + (size_t)block * a.n * 64;
+    __shared__ WaveLds<64> lds[4];
+    WaveLds<64>& L = lds[threadIdx.x >> 6];
+    const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
+    TileWalk<DEAL> walk(a.g, a.tiles, a.draws + block * a.y_draws, a.draws_done + block * a.y_draws);
+    while (walk.more()) {
+        walk.ahead();
+        const int r0 = walk.t * 16;
+        wave_sync();
+        const int rpv = tile_rp_load(a.g, r0, a.n, lane);
+        const bool has_hub = tile_begin(a.g, rpv, L.rp, lane);
+        if (walk.dealt(a.g, rpv, L.rp, has_hub)) { walk.next(a.g); continue; }
+        if constexpr (sizeof(T) == 4) {
+            // (rows of one chunk are in q already: nothing to fill where no row has more)
+            const int len = lane < 16 ? L.rp[lane + 1] - rpv : 0;
+            const bool many = has_hub && ballot(len > a.g.hub_threshold && len > a.g.hub_chunk) != 0ull;
+            for (int i = 4 * lane; i < 16 * LR; i += 256) *reinterpret_cast<f32v4*>(L.st + i) = f32v4{0.f, 0.f, 0.f, 0.f};
+            wave_sync();
+            tile_ranges(a.g, has_hub, L.rp, [&](int e_a, int e_b) {
+                gather_dense_rows<64, 8>(a.g, x, a.ld, __builtin_amdgcn_readfirstlane(e_a), __builtin_amdgcn_readfirstlane(e_b), lane, L.st);
+            });
+            wave_sync();
+            if (many) hub_rows_fill<64, true>(a.g, part, r0, L.rp, L.st, lane);
+        } else {
+            f32x4 acc[4];
+            tile_gather<64>(a.g, part, has_hub, r0, L.rp, L.st, lane, acc, [&](int e_a, int e_b) {
+                gather_dense_mfma<64, T, 8>(a.g, x, a.ld, __builtin_amdgcn_readfirstlane(e_a), __builtin_amdgcn_readfirstlane(e_b), L.rp,
+                                            L.ebuf, lane, acc);
+            });
+        }
+        wave_sync();
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) {
+            const int rr = 4 * reg + tg, row = r0 + rr, len = L.rp[rr + 1] - L.rp[rr];
+            float v[4];
+            lds_load<4>(L.st + rr * LR + 4 * tj, v);
+            if (row < a.n && !(len > a.g.hub_threshold && len <= a.g.hub_chunk)) store_cols<4, float>(q + (size_t)row * 64 + 4 * tj, v);
+        }
+        walk.next(a.g);
+    }
+    walk.finish();
+}
+
+// The A operands of a 16-row tile's product, straight from a plane of [n][64] floats: row arow, columns 16 s + 4 kk .. of
+// step s, split in three terms (mfma_tile_b3).
+struct PlaneOperand {
+    bf16x4 hi[4], mid[4], lo[4];
+};
+__device__ __forceinline__ void plane_request(const float* __restrict__ plane, int r0, int n, float (&v)[4][4]) {
+    const int lane = lane_id(), i = lane & 15, kk = lane >> 4;
+    const int row = min(r0 + 4 * (i & 3) + (i >> 2), n - 1);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) load_cols<4, float>(plane + (size_t)row * 64 + 16 * s + 4 * kk, v[s]);
+}
+__device__ __forceinline__ void plane_product(const PlaneOperand& p, const WLdsB3<64>& wl, f32x4 (&acc)[4]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) mfma_b3(p.hi[s], p.mid[s], p.lo[s], wl, s, cb, lane, acc[cb]);
+}
+
+// Workgroups of eight waves, a 16-row tile each, sharing W_i's blocks: row mb of blocks (of the transpose: column ob) at a
+// time, S x 24.6 KB of LDS.  The row is rounded to its storage type after every block mb of the sum.
+template <int S, typename T>
+struct WideProductArgs {
+    int n, tiles;
+    const float* h;         // [S][n][64]
+    const float* w;         // W_i, row stride 64 S
+    T* plane;               // X_i on entry / Y_i on return (or the reverse), row stride ld
+    int64_t ld;
+};
+template <int S, typename T, int SIGN>
+__global__ __launch_bounds__(512) void k_wide_product(WideProductArgs<S, T> a) {
+    __shared__ WLdsB3<64> wl[S];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
+    const int t = (int)blockIdx.x * 8 + wave, r0 = t * 16;
+    float y[S][4][4];
+#pragma unroll
+    for (int ob = 0; ob < S; ++ob)
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) load_cols<4, T>(a.plane + (size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ld + 64 * ob + 4 * tj, y[ob][reg]);
+#pragma unroll 1
+    for (int mb = 0; mb < S; ++mb) {
+        float v[4][4];
+        plane_request(a.h + (size_t)mb * a.n * 64, r0, a.n, v);
+        __syncthreads();        // the blocks before have been read
+#pragma unroll 1
+        for (int ob = 0; ob < S; ++ob) load_w_lds_b3<64>(a.w + (size_t)mb * 64 * (64 * S) + 64 * ob, 64 * S, false, wl[ob]);
+        PlaneOperand p;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) split_p4(v[s], p.hi[s], p.mid[s], p.lo[s]);
+#pragma unroll
+        for (int ob = 0; ob < S; ++ob) {
+            f32x4 acc[4];
+            plane_product(p, wl[ob], acc);
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) y[ob][reg][cb] = stored<T>(SIGN > 0 ? y[ob][reg][cb] + acc[cb][reg] : y[ob][reg][cb] - acc[cb][reg]);
+        }
+    }
+#pragma unroll
+    for (int ob = 0; ob < S; ++ob)
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) {
+            const int row = r0 + 4 * reg + tg;
+            if (row < a.n) store_cols<4, T>(a.plane + (size_t)row * a.ld + 64 * ob + 4 * tj, y[ob][reg]);
+        }
+}
+
+// dH = Q W_i^T, then back through GS and its scale: dZ_c = [c in I] g_c / r - Z_c (sum_t g_t Z_{I_t}) / (D/C r^3) with g = dH
+// at the recorded positions (eq. (11): only those are read); dst planes += dZ.
+template <int S, typename T>
+struct WideGradArgs {
+    int n, tiles;
+    const float* q;                     // [S][n][64]
+    const float* w;                     // W_i, row stride 64 S
+    const uint64_t* mask[S];            // column sets recorded for the block's input
+    const T* z;                         // rows of the block's input (RMS only): row stride ldz, sub-plane s at + s * z_sub
+    int64_t ldz, z_sub;
+    int norm;
+    float eps;
+    T* dst;                             // ndst groups, dst_gs apart, row stride ldd
+    int64_t ldd, dst_gs;
+    int ndst;
+};
+template <int S, typename T>
+__global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
+    constexpr int DGW = 64 * S;
+    __shared__ WLdsB3<64> wl[S];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
+    const int t = (int)blockIdx.x * 8 + wave, r0 = t * 16;
+    float g[S][4][4];
+#pragma unroll
+    for (int mb = 0; mb < S; ++mb)
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) g[mb][reg][cb] = 0.f;
+#pragma unroll 1
+    for (int ob = 0; ob < S; ++ob) {
+        float v[4][4];
+        plane_request(a.q + (size_t)ob * a.n * 64, r0, a.n, v);
+        __syncthreads();
+#pragma unroll 1
+        for (int mb = 0; mb < S; ++mb) load_w_lds_b3<64>(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
+        PlaneOperand p;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) split_p4(v[s], p.hi[s], p.mid[s], p.lo[s]);
+#pragma unroll
+        for (int mb = 0; mb < S; ++mb) {
+            f32x4 acc[4];
+            plane_product(p, wl[mb], acc);
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) g[mb][reg][cb] += acc[cb][reg];
+        }
+    }
+#pragma unroll
+    for (int reg = 0; reg < 4; ++reg) {
+        const int row = r0 + 4 * reg + tg, rowc = min(row, a.n - 1);
+        uint32_t bits[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) bits[s] = (uint32_t)(a.mask[s][rowc] >> (4 * tj)) & 15u;
+        if (a.norm == GSR_NORM_RMS) {
+            float z[S][4], ss = 0.f, dot = 0.f;
+#pragma unroll
+            for (int s = 0; s < S; ++s) load_cols<4, T>(a.z + (size_t)rowc * a.ldz + (size_t)s * a.z_sub + 4 * tj, z[s]);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) {
+                    ss += z[s][cb] * z[s][cb];
+                    dot += ((bits[s] >> cb) & 1u) ? g[s][reg][cb] * z[s][cb] : 0.f;
+                }
+            ss = group16_sum(ss);
+            dot = group16_sum(dot);
+            const float rinv = __builtin_amdgcn_rsqf(ss * (1.0f / (float)DGW) + a.eps);
+            const float coef = dot * (rinv * rinv * rinv) * (1.0f / (float)DGW);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) g[s][reg][cb] = (((bits[s] >> cb) & 1u) ? g[s][reg][cb] * rinv : 0.f) - z[s][cb] * coef;
+        } else {
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) g[s][reg][cb] = ((bits[s] >> cb) & 1u) ? g[s][reg][cb] : 0.f;
+        }
+    }
+    for (int j = 0; j < a.ndst; ++j)
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            float d[4][4];
+            T* p = a.dst + (size_t)j * a.dst_gs + 64 * s + 4 * tj;
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) load_cols<4, T>(p + (size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ldd, d[reg]);
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) {
+                const int row = r0 + 4 * reg + tg;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) d[reg][cb] = stored<T>(d[reg][cb] + g[s][reg][cb]);
+                if (row < a.n) store_cols<4, T>(p + (size_t)row * a.ldd, d[reg]);
+            }
+        }
+}
 
 template <int S, typename T>
 struct WideGsArgs {
@@ -795,76 +1048,86 @@ struct WideGsArgs {
     T* y0;                  // [S][n][64]: the sum, sub-plane by sub-plane (NULL: not kept)
     int k, norm;
     float eps;
-    Record<64, T> out[S];
-    bool out_given;         // out[s].mask hold the column sets to use
+    T* vals;                // the record: [n][k] values of the whole row in column order and their columns
+    uint8_t* cols;
+    uint64_t* mask[S];
+    bool out_given;         // mask[s] hold the column sets to use
 };
 
 // GS of a 16-row tile of a wide group, lane (r, q) holding the q-th quarter (16 columns) of every sub-plane of row r:
 // the same search as select_quarter over 16 S keys per lane; ties go to the lowest column of the whole row (sub-plane,
-// then quarter, then column).  Records leave sub-plane by sub-plane in the layout emit_tile writes.
+// then quarter, then column).
 template <int S, typename T>
 __global__ __launch_bounds__(256) void k_gs_wide(WideGsArgs<S, T> a) {
-    constexpr int DGW = 64 * S, LRW = DGW + 1;
+    constexpr int DGW = 64 * S, LRW = tile_ld<DGW>();
     constexpr int KS = sizeof(T) == 2 ? 16 : 0;
-    __shared__ float tile[4][16 * LRW + 64];
+    __shared__ __attribute__((aligned(16))) float tile[4][16 * LRW + 64];
     const int lane = lane_id(), tg = lane >> 4, tj = lane & 15, r = lane & 15, q = lane >> 4;
     float* st = tile[threadIdx.x >> 6];
     const int nwaves = (gridDim.x * blockDim.x) >> 6, tiles = (a.n + 15) / 16;
     for (int t = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; t < tiles; t += nwaves) {
         const int r0 = t * 16;
         wave_sync();          // the previous tile's records have left the scratch
+        {
+            float y[S][4][4];
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            float y[4][4];
+            for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int reg = 0; reg < 4; ++reg) {
-                const int row = r0 + 4 * reg + tg;
-                load_cols<4, T>(a.src + (size_t)(row < a.n ? row : a.n - 1) * a.ld + 64 * s + 4 * tj, y[reg]);
-            }
+                for (int reg = 0; reg < 4; ++reg)
+                    load_cols<4, T>(a.src + (size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ld + 64 * s + 4 * tj, y[s][reg]);
             for (int j = 1; j < a.nsrc; ++j) {
+                float v[S][4][4];
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int reg = 0; reg < 4; ++reg)
+                        load_cols<4, T>(a.src + (size_t)j * a.src_gs + (size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ld + 64 * s + 4 * tj, v[s][reg]);
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                        for (int cb = 0; cb < 4; ++cb) y[s][reg][cb] += v[s][reg][cb];
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s)
 #pragma unroll
                 for (int reg = 0; reg < 4; ++reg) {
-                    const int row = r0 + 4 * reg + tg;
-                    float v[4];
-                    load_cols<4, T>(a.src + (size_t)j * a.src_gs + (size_t)(row < a.n ? row : a.n - 1) * a.ld + 64 * s + 4 * tj, v);
+                    const int rr = 4 * reg + tg, row = r0 + rr;
+                    const bool ok = row < a.n;
 #pragma unroll
-                    for (int cb = 0; cb < 4; ++cb) y[reg][cb] += v[cb];
+                    for (int cb = 0; cb < 4; ++cb) y[s][reg][cb] = stored<T>(y[s][reg][cb]);
+                    if (ok && a.y0) store_cols<4, T>(a.y0 + ((size_t)s * a.n + row) * 64 + 4 * tj, y[s][reg]);
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) y[s][reg][cb] = ok ? y[s][reg][cb] : 0.f;
+                    lds_store<4>(st + rr * LRW + 64 * s + 4 * tj, y[s][reg]);
                 }
-            }
-#pragma unroll
-            for (int reg = 0; reg < 4; ++reg) {
-                const int rr = 4 * reg + tg, row = r0 + rr;
-                const bool ok = row < a.n;
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) y[reg][cb] = stored<T>(y[reg][cb]);
-                if (ok && a.y0) store_cols<4, T>(a.y0 + ((size_t)s * a.n + row) * 64 + 4 * tj, y[reg]);
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) st[rr * LRW + 64 * s + 4 * tj + cb] = ok ? y[reg][cb] : 0.f;
-            }
         }
         wave_sync();
         const bool valid = r0 + r < a.n;
         float x[S][16];
-        uint32_t key[S][16];
-        uint32_t top = 0u;
         float ss = 0.f;
 #pragma unroll
-        for (int s = 0; s < S; ++s)
+        for (int s = 0; s < S; ++s) {
+            lds_load<16>(st + r * LRW + 64 * s + 16 * q, x[s]);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                x[s][j] = st[r * LRW + 64 * s + 16 * q + j];
-                ss += x[s][j] * x[s][j];
-                const uint32_t u = __float_as_uint(x[s][j]);
-                uint32_t kk = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-                kk = kk == 0x7FFFFFFFu ? 0x80000000u : kk;          // -0 -> +0
-                key[s][j] = kk >> KS;
-                top = max(top, key[s][j]);
-            }
+            for (int j = 0; j < 16; ++j) ss += x[s][j] * x[s][j];
+        }
         uint32_t msel[S];
         if (a.out_given) {
 #pragma unroll
-            for (int s = 0; s < S; ++s) msel[s] = (uint32_t)(a.out[s].mask[valid ? r0 + r : a.n - 1] >> (16 * q)) & 0xFFFFu;
+            for (int s = 0; s < S; ++s) msel[s] = (uint32_t)(a.mask[s][valid ? r0 + r : a.n - 1] >> (16 * q)) & 0xFFFFu;
         } else {
+            uint32_t key[S][16];
+            uint32_t top = 0u;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const uint32_t u = __float_as_uint(x[s][j] + 0.0f);          // -0 -> +0
+                    key[s][j] = (u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) >> KS;
+                    top = max(top, key[s][j]);
+                }
             top = quarter_max(top);
             auto count_ge = [&](uint32_t th) {
                 uint32_t cnt = 0u;
@@ -896,9 +1159,9 @@ __global__ __launch_bounds__(256) void k_gs_wide(WideGsArgs<S, T> a) {
             for (int s = 0; s < S; ++s) {
                 mgt[s] = meq[s] = 0u;
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    mgt[s] |= key[s][j] > lo ? 1u << j : 0u;
-                    meq[s] |= key[s][j] == lo ? 1u << j : 0u;
+                for (int j = 15; j >= 0; --j) {
+                    mgt[s] = mgt[s] + mgt[s] + (key[s][j] > lo ? 1u : 0u);
+                    meq[s] = meq[s] + meq[s] + (key[s][j] == lo ? 1u : 0u);
                 }
                 ngt += __popc(mgt[s]);
             }
@@ -924,79 +1187,52 @@ __global__ __launch_bounds__(256) void k_gs_wide(WideGsArgs<S, T> a) {
         float scale = 1.f;
         if (a.norm == GSR_NORM_RMS) scale = __builtin_amdgcn_rsqf(quarter_sum(ss) * (1.0f / (float)DGW) + a.eps);
         const int rows = min(16, a.n - r0), total = rows * a.k;
+        // first slot of this lane's quarter of every sub-plane, in column order over the whole row
+        int slot[S], at = r * a.k;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             uint32_t all[4];
             quarter_all(msel[s] | (uint32_t)__popc(msel[s]) << 16, all);
-            int slot = r * a.k;
+            slot[s] = at;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) slot += i < q ? (int)(all[i] >> 16) : 0;
-            const uint64_t mask = (uint64_t)(all[0] & 0xFFFFu) | (uint64_t)(all[1] & 0xFFFFu) << 16 |
-                                  (uint64_t)(all[2] & 0xFFFFu) << 32 | (uint64_t)(all[3] & 0xFFFFu) << 48;
-            wave_sync();   // every lane holds its values (s = 0) / the previous sub-plane's record has left the scratch
+            for (int i = 0; i < 4; ++i) {
+                slot[s] += i < q ? (int)(all[i] >> 16) : 0;
+                at += (int)(all[i] >> 16);
+            }
+            if (!a.out_given && q == 0 && r < rows)
+                a.mask[s][r0 + r] = (uint64_t)(all[0] & 0xFFFFu) | (uint64_t)(all[1] & 0xFFFFu) << 16 |
+                                    (uint64_t)(all[2] & 0xFFFFu) << 32 | (uint64_t)(all[3] & 0xFFFFu) << 48;
+        }
+        wave_sync();          // every lane holds its values: the tile can be reused
+        const int dump = 16 * LRW + lane;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            int ahead = slot[s] - dump;
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
-                const uint32_t bit = (msel[s] >> j) & 1u;
-                st[bit ? slot : 16 * LRW + lane] = x[s][j] * scale;      // dropped columns go to the dump words
-                slot += (int)bit;
-            }
-            wave_sync();
-            T* dst = a.out[s].vals + (size_t)r0 * a.k;
-            for (int i = lane; i < total; i += 64) dst[i] = from_float<T>(st[i]);
-            if (!a.out_given && q == 0 && r < rows) a.out[s].mask[r0 + r] = mask;
-        }
-    }
-}
-
-// Backward through GS and its scale for a wide group, after dH = sum over column blocks of Q W^T has been summed into
-// dh [S][n][64]: one wave per row, lane c holding column c of every sub-plane.  dZ_c = [c in I] g_c / r - Z_c (sum_t g_t
-// Z_{I_t}) / (D/C r^3) with g = dH at the recorded positions (eq. (11): only those are read); dst planes += dZ.
-template <int S, typename T>
-struct WideEpiArgs {
-    int n;
-    const float* dh;                    // [S][n][64]
-    const uint64_t* mask[S];            // column sets recorded for the block's input
-    const T* z;                         // rows of the block's input (RMS only): row stride ldz, sub-plane s at + s * z_sub
-    int64_t ldz, z_sub;
-    int norm;
-    float eps;
-    T* dst;                             // ndst groups, dst_gs apart, row stride ldd
-    int64_t ldd, dst_gs;
-    int ndst;
-};
-
-template <int S, typename T>
-__global__ __launch_bounds__(256) void k_grad_epi_wide(WideEpiArgs<S, T> a) {
-    constexpr int DGW = 64 * S;
-    const int lane = lane_id();
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    for (int row = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; row < a.n; row += nwaves) {
-        float g[S], zz[S];
-        bool kept[S];
-        float ss = 0.f, dot = 0.f;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            g[s] = a.dh[((size_t)s * a.n + row) * 64 + lane];
-            kept[s] = (a.mask[s][row] >> lane) & 1ull;
-            zz[s] = a.norm == GSR_NORM_RMS ? to_float(a.z[(size_t)row * a.ldz + (size_t)s * a.z_sub + lane]) : 0.f;
-            ss += zz[s] * zz[s];
-            dot += kept[s] ? g[s] * zz[s] : 0.f;
-        }
-        float rinv = 1.f, coef = 0.f;
-        if (a.norm == GSR_NORM_RMS) {
-            ss = sub_sum<64>(ss);
-            dot = sub_sum<64>(dot);
-            rinv = __builtin_amdgcn_rsqf(ss * (1.0f / (float)DGW) + a.eps);
-            coef = dot * (rinv * rinv * rinv) * (1.0f / (float)DGW);
-        }
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const float dz = (kept[s] ? g[s] * rinv : 0.f) - zz[s] * coef;
-            for (int j = 0; j < a.ndst; ++j) {
-                T* p = a.dst + (size_t)j * a.dst_gs + (size_t)row * a.ldd + 64 * s + lane;
-                *p = from_float<T>(to_float(*p) + dz);
+                const int bit = (int)((msel[s] >> j) & 1u);
+                st[dump + __mul24(bit, ahead)] = x[s][j] * scale;      // dropped columns go to the dump words
+                ahead += bit;
             }
         }
+        wave_sync();
+        T* dst = a.vals + (size_t)r0 * a.k;
+        for (int i = lane; i < total; i += 64) dst[i] = from_float<T>(st[i]);
+        wave_sync();
+        uint8_t* cst = reinterpret_cast<uint8_t*>(st);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            int ahead = slot[s] - 4 * dump;                            // (byte 4 dump: the lane's dump word)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int bit = (int)((msel[s] >> j) & 1u);
+                cst[4 * dump + __mul24(bit, ahead)] = (uint8_t)(64 * s + 16 * q + j);
+                ahead += bit;
+            }
+        }
+        wave_sync();
+        uint32_t* dc = reinterpret_cast<uint32_t*>(a.cols + (size_t)r0 * a.k);      // whole words, see emit_tile
+        for (int i = lane; 4 * i < total; i += 64) dc[i] = reinterpret_cast<const uint32_t*>(cst)[i];
     }
 }
 
@@ -1136,12 +1372,13 @@ struct Ctx {
                           tie_masks + seg * TIE_SUB * tie_cap, tie_cap, cfg->tie_tol};
     }
     // Record slot `slot` of layer `layer`: the values always live in the slot (they are rebuilt),
-    // the mask in the slot, or in the kept store when indices are saved.
+    // the mask in the slot, or in the kept store when indices are saved.  (Groups of S column blocks: one list of values and
+    // columns for the whole row, a mask per block.)
     Record<DG, T> rec(int slot, int layer = 0, int sub = 0) const {
         Record<DG, T> r;
         if (slot < 0) { r.vals = nullptr; r.mask = nullptr; r.cols = nullptr; return r; }
-        r.vals = (T*)(ws + lw.rec_vals[slot * S + sub]);
-        r.cols = sizeof(T) == 4 && S == 1 ? (uint8_t*)(ws + lw.rec_cols[slot]) : nullptr;
+        r.vals = (T*)(ws + lw.rec_vals[slot]);
+        r.cols = sizeof(T) == 4 || S > 1 ? (uint8_t*)(ws + lw.rec_cols[slot]) : nullptr;
         r.mask = saved ? saved + (((size_t)layer * cfg->c + slot) * S + sub) * (size_t)cfg->n : (M*)(ws + lw.rec_mask[slot * S + sub]);
         return r;
     }
@@ -1151,9 +1388,7 @@ struct Ctx {
     float* dw_partial() const { return (float*)(ws + lw.dw_partial); }
     float* hub_part() const { return (float*)(ws + lw.hub_partial); }
     float* hub_part2() const { return (float*)(ws + lw.hub_partial2); }
-    uint8_t* hub_cols() const { return (uint8_t*)(ws + lw.hub_cols); }
-    float* hub_vals() const { return (float*)(ws + lw.hub_vals); }
-    bool hub_by_value() const { return g->hub_values == 2 || (g->hub_values == 1 && 2 * cfg->k <= DG); }
+    bool hub_by_value() const { return g->hub_values == 2 || (g->hub_values == 1 && 2 * cfg->k <= DG * S); }
 };
 
 // Workgroups of 256 threads one CU keeps resident for a kernel, and the persistent grid that
@@ -1192,19 +1427,16 @@ static void launch_hub_records(const Ctx<DG, T>& x, const Record<DG, T>& in) {
     ProfScope prof(KC_HUB, x.s);
     if constexpr (sizeof(T) == 4) {
         if (x.hub_by_value()) {
-            hipLaunchKernelGGL((k_record_columns<DG>), dim3((unsigned)((x.cfg->n + 255) / 256)), dim3(256), 0, x.s, (int)x.cfg->n,
-                               x.cfg->k, (const typename MaskOf<DG>::type*)in.mask, x.hub_cols());
             hub_values_variant(x.cfg->k, [&](auto lg, auto kq) {
                 hipLaunchKernelGGL((k_hub_values<DG, decltype(lg)::value, decltype(kq)::value>),
                                    dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s, make_view(x.g, false), hc,
-                                   (const float*)in.vals, (const uint8_t*)x.hub_cols(), x.cfg->k, x.hub_part());
+                                   (const float*)in.vals, (const uint8_t*)in.cols, x.cfg->k, (int)x.cfg->n, x.hub_part(), (float*)nullptr);
             });
             return;
         }
     }
     hipLaunchKernelGGL((k_hub_records<DG, T>), dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s,
-                       make_view(x.g, false), hc, (const T*)in.vals, (const typename MaskOf<DG>::type*)in.mask, x.cfg->k,
-                       x.hub_part());
+                       make_view(x.g, false), hc, in, x.cfg->k, x.hub_part());
 }
 
 template <int DG, typename T>
@@ -1214,7 +1446,7 @@ static void launch_hub_dense(const Ctx<DG, T>& x, const T* plane, int64_t ld) {
     HubChunks hc{h.ce0, h.ce1, h.n_chunks, x.g->long_rows};
     ProfScope prof(KC_HUB, x.s);
     hipLaunchKernelGGL((k_hub_dense<DG, T>), dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s,
-                       make_view(x.g, true), hc, plane, ld, x.hub_part());
+                       make_view(x.g, true), hc, plane, ld, x.hub_part(), (float*)nullptr);
 }
 
 // Both first passes of a block's backward (records over A into hub_part, dY rows over A^T into hub_part2).
@@ -1228,25 +1460,23 @@ static bool launch_hub_both(const Ctx<DG, T>& x, const Record<DG, T>& in, const 
     const unsigned gx = hub_grid(std::max(ha.n_chunks, ht.n_chunks));
     if constexpr (sizeof(T) == 4) {
         if (x.hub_by_value()) {
-            hipLaunchKernelGGL((k_record_columns<DG>), dim3((unsigned)((x.cfg->n + 255) / 256)), dim3(256), 0, x.s, (int)x.cfg->n,
-                               x.cfg->k, (const typename MaskOf<DG>::type*)in.mask, x.hub_cols());
             // (two launches: as the two rows of one grid, as the dealing variant runs them, they took 50 us longer on the
             // Table-1-shaped graph than one after the other)
             if (ha.n_chunks > 0)
                 hub_values_variant(x.cfg->k, [&](auto lg, auto kq) {
                     hipLaunchKernelGGL((k_hub_values<DG, decltype(lg)::value, decltype(kq)::value>),
                                        dim3(hub_grid(ha.n_chunks)), dim3(256), 0, x.s, make_view(x.g, false),
-                                       ca, (const float*)in.vals, (const uint8_t*)x.hub_cols(), x.cfg->k, x.hub_part());
+                                       ca, (const float*)in.vals, (const uint8_t*)in.cols, x.cfg->k, (int)x.cfg->n, x.hub_part(),
+                                       (float*)nullptr);
                 });
             if (ht.n_chunks > 0)
                 hipLaunchKernelGGL((k_hub_dense<DG, T>), dim3(hub_grid(ht.n_chunks)), dim3(256), 0, x.s,
-                                   make_view(x.g, true), ct, dy, ldg, x.hub_part2());
+                                   make_view(x.g, true), ct, dy, ldg, x.hub_part2(), (float*)nullptr);
             return true;
         }
     }
-    hipLaunchKernelGGL((k_hub_both<DG, T>), dim3(gx, 2), dim3(256), 0, x.s, make_view(x.g, false), ca, (const T*)in.vals,
-                       (const typename MaskOf<DG>::type*)in.mask, x.cfg->k, x.hub_part(), make_view(x.g, true), ct, dy, ldg,
-                       x.hub_part2());
+    hipLaunchKernelGGL((k_hub_both<DG, T>), dim3(gx, 2), dim3(256), 0, x.s, make_view(x.g, false), ca, in, x.cfg->k, x.hub_part(),
+                       make_view(x.g, true), ct, dy, ldg, x.hub_part2());
     return true;
 }
 
@@ -1270,8 +1500,7 @@ static bool split_dw(const gsr_graph_t* g) { return (sizeof(T) == 4 || DG == 64)
 template <int DG, typename T>
 static unsigned launch_block(const Ctx<DG, T>& x, int mode, const Record<DG, T>& in, const float* w, T* plane, int64_t ld,
                              const Record<DG, T>& out, bool out_given, const T* dy, int64_t ldg, bool first_pass_done = false,
-                             TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, int ldw = DG, float* h_out = nullptr,
-                             const float* hub_part = nullptr, float* dw_partial = nullptr, int ygrid = 1) {
+                             TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, float* h_out = nullptr) {
     if (!first_pass_done) launch_hub_records<DG, T>(x, in);
     BlockArgs<DG, T> a;
     a.tie = tie;
@@ -1279,42 +1508,20 @@ static unsigned launch_block(const Ctx<DG, T>& x, int mode, const Record<DG, T>&
     a.g = make_view(x.g, false);
     a.n = (int)x.cfg->n; a.tiles = x.tiles;
     a.in = in; a.k = x.cfg->k;
-    a.hub_part = hub_part ? hub_part : x.hub_part(); a.w = w; a.ldw = ldw; a.plane = plane; a.ld = ld;
+    a.hub_part = x.hub_part(); a.w = w; a.ldw = DG; a.plane = plane; a.ld = ld;
     a.out = out; a.out_given = out_given;
-    a.norm = x.cfg->norm; a.eps = x.cfg->eps; a.dy = dy; a.ldg = ldg; a.dw_partial = dw_partial ? dw_partial : x.dw_partial();
+    a.norm = x.cfg->norm; a.eps = x.cfg->eps; a.dy = dy; a.ldg = ldg; a.dw_partial = x.dw_partial();
     if (mode != 2) tile_counters(x.g, &a.draws, &a.draws_done);
     else a.draws = a.draws_done = nullptr;
     const bool b3 = mode != 0 || !x.g->long_rows;       // (see k_block)
     const dim3 block(64 * block_waves(mode == 2, b3));
     ProfScope prof(mode == 0 ? KC_BLOCK_FWD : mode == 1 ? KC_BLOCK_INV : KC_BLOCK_BWD, x.s);
     unsigned grid = 0;
-    a.y_dw_partial = (size_t)x.g->grid * DG * DG;
-    a.y_draws = kTileCounterSet;
     auto go = [&](auto plain, auto deal, int per_cu) {
         grid = persistent_grid(x.g, per_cu);
-        // (ygrid column blocks written by one launch: the resident workgroups are shared out between them)
-        if (ygrid > 1) grid = std::max(8u, grid / (unsigned)ygrid / 8 * 8);
-        if (heavy_first(a.g.n_heavy, x.tiles, grid * (block.x / 64) / 4)) hipLaunchKernelGGL(deal, dim3(grid, (unsigned)ygrid), block, 0, x.s, a);
-        else hipLaunchKernelGGL(plain, dim3(grid, (unsigned)ygrid), block, 0, x.s, a);
+        if (heavy_first(a.g.n_heavy, x.tiles, grid * (block.x / 64) / 4)) hipLaunchKernelGGL(deal, dim3(grid), block, 0, x.s, a);
+        else hipLaunchKernelGGL(plain, dim3(grid), block, 0, x.s, a);
     };
-    if constexpr (DG == 64) {
-        if (ygrid > 1) {
-            if (mode == 0 && b3) {
-                static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, true, true>, 512);
-                go(k_block<DG, T, +1, false, false, true, true>, k_block<DG, T, +1, false, true, true, true>, per_cu);
-            } else if (mode == 0) {
-                static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, false, true>, 256);
-                go(k_block<DG, T, +1, false, false, false, true>, k_block<DG, T, +1, false, true, false, true>, per_cu);
-            } else if (mode == 1) {
-                static const int per_cu = resident_blocks((const void*)k_block<DG, T, -1, false, false, true, true>, 512);
-                go(k_block<DG, T, -1, false, false, true, true>, k_block<DG, T, -1, false, true, true, true>, per_cu);
-            } else {
-                static const int per_cu = resident_blocks((const void*)k_block<DG, T, -1, true, false, true, true>, 256);
-                go(k_block<DG, T, -1, true, false, true, true>, k_block<DG, T, -1, true, true, true, true>, per_cu);
-            }
-            return grid;
-        }
-    }
     if (mode == 0 && b3) {
         static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, true>, 512);
         go(k_block<DG, T, +1, false, false, true>, k_block<DG, T, +1, false, true, true>, per_cu);
@@ -1338,7 +1545,7 @@ static void launch_grad(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const flo
                         bool first_pass_done = false) {
     if (!first_pass_done) launch_hub_dense<DG, T>(x, dy, ldg);
     GradArgs<DG, T> a;
-    a.ldw = DG; a.dh = nullptr; a.dh_first = false;
+    a.ldw = DG;
     a.gt = make_view(x.g, true);
     a.n = (int)x.cfg->n; a.tiles = x.tiles; a.dy = dy; a.ldg = ldg; a.hub_part = first_pass_done ? x.hub_part2() : x.hub_part();
     a.w = w;
@@ -1384,168 +1591,141 @@ static bool launch_tie_fixup(const Ctx<DG, T>& x, const TieSeg<DG>& tie, const T
 // dW_i's workgroup partials from H (in x.hplane()) and dY_i; returns their number
 template <int DG, typename T>
 static unsigned launch_dw(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const TieSeg<DG>& tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f},
-                          const T* fix_plane = nullptr, int64_t fix_ld = 0, const Record<DG, T>* fix_out = nullptr,
-                          float* dw_partial = nullptr) {
+                          const T* fix_plane = nullptr, int64_t fix_ld = 0, const Record<DG, T>* fix_out = nullptr) {
     DwArgs<DG, T> a;
     a.n = (int)x.cfg->n; a.tiles = x.tiles; a.h = x.hplane(); a.dy = dy; a.ldg = ldg;
-    a.dw_partial = dw_partial ? dw_partial : x.dw_partial();
+    a.dw_partial = x.dw_partial();
+    a.S = x.S > 1 ? x.S : 0;
+    a.y_set = (size_t)x.g->grid * DG * DG;
     a.tie = fix_out ? tie : TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f};
     a.fix_plane = fix_plane; a.fix_ld = fix_ld; a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
     a.fix_out = fix_out ? *fix_out : x.rec(-1);
     ProfScope prof(KC_DW, x.s);
     static const int per_cu = resident_blocks((const void*)k_dw<DG, T>, 256);
-    const unsigned grid = persistent_grid(x.g, per_cu);
-    hipLaunchKernelGGL((k_dw<DG, T>), dim3(grid), dim3(256), 0, x.s, a);
+    unsigned grid = persistent_grid(x.g, per_cu);
+    if (a.S) grid = std::max(8u, grid / (unsigned)(a.S * a.S) / 8 * 8);       // (the resident workgroups shared out between the sets)
+    hipLaunchKernelGGL((k_dw<DG, T>), dim3(grid, a.S ? (unsigned)(a.S * a.S) : 1u), dim3(256), 0, x.s, a);
     return grid;
 }
 
-// ---- groups wider than one tile (see k_gs_wide): D/C = 64 S as S sub-planes of 64 columns -----------------------
+// ---- groups wider than one tile (see k_gather_wide): D/C = 64 S as S sub-planes of 64 columns -----------------------
 // Sub-plane s of group i of a plane set p starts 64 s elements into the group's rows (both caller layouts and the
-// step's arena keep a group's columns adjacent in a row), so the 64-column kernels work on it in place with the row
-// stride of the set.  W_i is D/C x D/C row-major; its block (mb, ob) starts at w + 64 mb D/C + 64 ob with row stride D/C.
-
-// dH_mb (+)= (A^T dY_ob) W_i[mb][ob]^T: the gradient kernel without its epilogue (always the bf16-pipe variant)
-template <typename T>
-static void launch_grad_acc(const Ctx<64, T>& x, const T* dy, int64_t ldg, const float* w, int ldw, float* dh, bool first,
-                            bool first_pass_done, int ygrid = 1) {
-    if (!first_pass_done) launch_hub_dense<64, T>(x, dy, ldg);
-    GradArgs<64, T> a;
-    a.gt = make_view(x.g, true);
-    a.n = (int)x.cfg->n; a.tiles = x.tiles; a.dy = dy; a.ldg = ldg; a.hub_part = x.hub_part();
-    a.w = w; a.ldw = ldw;
-    a.own_mask = nullptr; a.z = nullptr; a.ldz = 0; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
-    a.dst = nullptr; a.ldd = 0; a.dst_gs = 0; a.ndst = 0;
-    a.dw_partial = nullptr; a.dw_parts = 0; a.dw_out = nullptr;
-    a.dh = dh; a.dh_first = first;
-    a.y_draws = kTileCounterSet;
-    tile_counters(x.g, &a.draws, &a.draws_done);
-    ProfScope prof(KC_GRAD, x.s);
-    static const int per_cu = resident_blocks((const void*)k_grad<64, T, false, true, true>, 512);
-    unsigned grid = persistent_grid(x.g, per_cu);
-    // (ygrid blocks of dH from one launch, blockIdx.y = mb: the resident workgroups are shared out between them)
-    if (ygrid > 1) grid = std::max(8u, grid / (unsigned)ygrid / 8 * 8);
-    if (heavy_first(a.gt.n_heavy, x.tiles, grid * 2)) hipLaunchKernelGGL((k_grad<64, T, true, true, true>), dim3(grid, (unsigned)ygrid), dim3(512), 0, x.s, a);
-    else hipLaunchKernelGGL((k_grad<64, T, false, true, true>), dim3(grid, (unsigned)ygrid), dim3(512), 0, x.s, a);
+// step's arena keep a group's columns adjacent in a row).  W_i is D/C x D/C row-major.
+template <typename F>
+static void wide_blocks(int S, F&& f) {
+    if (S == 2) f(std::integral_constant<int, 2>{});
+    else if (S == 3) f(std::integral_constant<int, 3>{});
+    else f(std::integral_constant<int, 4>{});
 }
 
-// GS over the whole rows of a wide group (sum of nsrc groups first when nsrc > 1), records of slot `slot`
-template <int S, typename T>
-static void launch_gs_wide_s(const Ctx<64, T>& x, const T* src, int64_t ld, int64_t gs, int nsrc, T* y0, int slot, int layer,
-                             bool given) {
-    WideGsArgs<S, T> a;
-    a.n = (int)x.cfg->n; a.src = src; a.ld = ld; a.src_gs = gs; a.nsrc = nsrc; a.y0 = y0;
-    a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
-    for (int s = 0; s < S; ++s) a.out[s] = x.rec(slot, layer, s);
-    a.out_given = given;
-    ProfScope prof(KC_SUM, x.s);
-    hipLaunchKernelGGL((k_gs_wide<S, T>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
-}
+// GS over the whole rows of a wide group (sum of nsrc groups first when nsrc > 1), record of slot `slot`
 template <typename T>
 static void launch_gs_wide(const Ctx<64, T>& x, const T* src, int64_t ld, int64_t gs, int nsrc, T* y0, int slot, int layer,
                            bool given = false) {
-    if (x.S == 2) launch_gs_wide_s<2, T>(x, src, ld, gs, nsrc, y0, slot, layer, given);
-    else if (x.S == 3) launch_gs_wide_s<3, T>(x, src, ld, gs, nsrc, y0, slot, layer, given);
-    else launch_gs_wide_s<4, T>(x, src, ld, gs, nsrc, y0, slot, layer, given);
+    ProfScope prof(KC_SUM, x.s);
+    wide_blocks(x.S, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        WideGsArgs<S, T> a;
+        a.n = (int)x.cfg->n; a.src = src; a.ld = ld; a.src_gs = gs; a.nsrc = nsrc; a.y0 = y0;
+        a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
+        a.vals = x.rec(slot, layer).vals;
+        a.cols = x.rec(slot, layer).cols;
+        for (int s = 0; s < S; ++s) a.mask[s] = x.rec(slot, layer, s).mask;
+        a.out_given = given;
+        hipLaunchKernelGGL((k_gs_wide<S, T>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
+    });
 }
 
-template <int S, typename T>
-static void launch_epi_wide_s(const Ctx<64, T>& x, int slot, int layer, const T* z, int64_t ldz, int64_t z_sub, T* dst, int64_t ldd,
-                              int64_t dst_gs, int ndst) {
-    WideEpiArgs<S, T> a;
-    a.n = (int)x.cfg->n; a.dh = x.dh();
-    for (int s = 0; s < S; ++s) a.mask[s] = x.rec(slot, layer, s).mask;
-    a.z = z; a.ldz = ldz; a.z_sub = z_sub; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
-    a.dst = dst; a.ldd = ldd; a.dst_gs = dst_gs; a.ndst = ndst;
-    ProfScope prof(KC_GRAD, x.s);
-    hipLaunchKernelGGL((k_grad_epi_wide<S, T>), dim3((unsigned)x.g->grid * 4), dim3(256), 0, x.s, a);
-}
+// H of block `slot` + 1 into x.hplane(): the first pass over split rows, then the tiles
 template <typename T>
-static void launch_epi_wide(const Ctx<64, T>& x, int slot, int layer, const T* z, int64_t ldz, int64_t z_sub, T* dst, int64_t ldd,
-                            int64_t dst_gs, int ndst) {
-    if (x.S == 2) launch_epi_wide_s<2, T>(x, slot, layer, z, ldz, z_sub, dst, ldd, dst_gs, ndst);
-    else if (x.S == 3) launch_epi_wide_s<3, T>(x, slot, layer, z, ldz, z_sub, dst, ldd, dst_gs, ndst);
-    else launch_epi_wide_s<4, T>(x, slot, layer, z, ldz, z_sub, dst, ldd, dst_gs, ndst);
-}
-
-// First pass over the records of a wide group's S column blocks in one launch, value by value (float32 records, S = 2
-// or 3, 2 k <= D/C, a graph whose first pass runs that way): the row's k kept values are collected from the S records
-// with their columns in the whole row (k_record_columns_wide), and one pass sums them into rows of D/C sums per
-// chunk, written as S arrays of partial rows [chunks][64].  Returns false where it does not apply (then each column
-// block has a first pass of its own).
-template <typename T>
-static bool launch_hub_values_wide(const Ctx<64, T>& x, int in_slot, int layer) {
-    if constexpr (sizeof(T) != 4) {
-        return false;
-    } else {
-        const HubPlan& h = x.g->a.hub;
-        const int S = x.S, k = x.cfg->k;
-        if (!x.g->hub_values || S < 2 || S > 3 || 2 * k > 64 * S || h.n_chunks == 0) return false;
-        HubChunks hc{h.ce0, h.ce1, h.n_chunks, x.g->long_rows};
-        ProfScope prof(KC_HUB, x.s);
-        const unsigned rows_grid = (unsigned)((x.cfg->n + 255) / 256);
-        auto go = [&](auto sc) {
-            constexpr int SS = decltype(sc)::value;
-            WideRecords<SS> r;
-            for (int sub = 0; sub < SS; ++sub) {
-                const Record<64, T> rec = x.rec(in_slot, layer, sub);
-                r.vals[sub] = (const float*)rec.vals;
-                r.mask[sub] = (const uint64_t*)rec.mask;
+static void launch_gather_wide(const Ctx<64, T>& x, int slot, int layer) {
+    const HubPlan& hp = x.g->a.hub;
+    const Record<64, T> in = x.rec(slot, layer);
+    const int n = (int)x.cfg->n, k = x.cfg->k;
+    wide_blocks(x.S, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if (hp.n_chunks > 0) {
+            HubChunks hc{hp.ce0, hp.ce1, hp.n_chunks, x.g->long_rows, hp.single};
+            ProfScope prof(KC_HUB, x.s);
+            bool by_value = false;
+            if constexpr (sizeof(T) == 4 && S < 4) {
+                by_value = x.hub_by_value() && k <= 64;
+                if (by_value)
+                    hub_values_variant_wide(k, [&](auto lg, auto kq) {
+                        hipLaunchKernelGGL((k_hub_values<64 * S, decltype(lg)::value, decltype(kq)::value>), dim3(hub_grid(hp.n_chunks)),
+                                           dim3(256), 0, x.s, make_view(x.g, false), hc, (const float*)in.vals, (const uint8_t*)in.cols, k, n,
+                                           x.hub_part(), x.hplane());
+                    });
             }
-            hipLaunchKernelGGL((k_record_columns_wide<SS>), dim3(rows_grid), dim3(256), 0, x.s, (int)x.cfg->n, k, r, x.hub_vals(),
-                               x.hub_cols());
-            hub_values_variant_wide(k, [&](auto lg, auto kq) {
-                hipLaunchKernelGGL((k_hub_values<64 * SS, decltype(lg)::value, decltype(kq)::value>), dim3(hub_grid(h.n_chunks)),
-                                   dim3(256), 0, x.s, make_view(x.g, false), hc, (const float*)x.hub_vals(),
-                                   (const uint8_t*)x.hub_cols(), k, x.hub_part());
-            });
-        };
-        if (S == 2) go(std::integral_constant<int, 2>{});
-        else go(std::integral_constant<int, 3>{});
-        return true;
-    }
+            if (!by_value)
+                hipLaunchKernelGGL((k_hub_records_wide<S, T>), dim3(hub_grid(hp.n_chunks)), dim3(256), 0, x.s, make_view(x.g, false), hc,
+                                   (const T*)in.vals, (const uint8_t*)in.cols, k, n, x.hub_part(), x.hplane());
+        }
+        ProfScope prof(KC_BLOCK_FWD, x.s);
+        WideGatherArgs<S, T> a;
+        a.g = make_view(x.g, false);
+        a.n = n; a.tiles = (n + 7) / 8;
+        a.vals = in.vals; a.cols = in.cols; a.k = k;
+        a.hub_part = x.hub_part(); a.n_chunks = hp.n_chunks;
+        a.h = x.hplane();
+        tile_counters(x.g, &a.draws, &a.draws_done);
+        static const int per_cu = resident_blocks((const void*)k_gather_wide<S, T>);
+        hipLaunchKernelGGL((k_gather_wide<S, T>), dim3(persistent_grid(x.g, per_cu)), dim3(256), 0, x.s, a);
+    });
 }
 
-// plane (+/-)= f_i(Y_{i-1}) for one group: the S x S products of 64 x 64 blocks as S launches of the 64-column block
-// kernel.  mode as launch_block; dw_i (mode 2): D/C x D/C, receives dW_i.
+// Q = A^T dY_i into x.dh()
 template <typename T>
-static void wide_block(const Ctx<64, T>& x, int mode, int in_slot, int layer, const float* wi, T* plane, int64_t ld, const T* dy,
-                       int64_t ldg, float* dw_i) {
-    const int S = x.S, dgw = 64 * S;
-    const Record<64, T> none = x.rec(-1);
-    const TieSeg<64> no_tie{nullptr, nullptr, nullptr, 0, 0.f};
-    // the first pass over the records of all S column blocks at once where it runs value by value (float32, two or
-    // three blocks): the partial rows of block mb are then at hub_part + mb * chunks * 64
-    const bool one_pass = launch_hub_values_wide<T>(x, in_slot, layer);
-    const size_t part_stride = (size_t)x.g->a.hub.n_chunks * 64;
-    const size_t dw_set = (size_t)x.g->grid * 64 * 64;
-    unsigned nparts = 0;
-    // One launch per input block mb writes all S column blocks (blockIdx.y = ob: W_i's block, the plane's and dY's
-    // columns, the dW partials and the tile counters move on with it), sharing the resident waves out between them:
-    // a launch per pair (mb, ob) is one short tile per wave on a long-row graph and as long as its slowest wave.
-    // (Without the one first pass for all blocks, the pass over block mb's records comes first, inside launch_block.)
-    const bool split = mode == 2 && split_dw<64, T>(x.g);
-    for (int mb = 0; mb < S; ++mb) {
-        const float* part = one_pass ? x.hub_part() + mb * part_stride : nullptr;
-        const float* wmb = wi + (size_t)mb * 64 * dgw;
-        if (split) {
-            // the inverse of all column blocks, leaving H_mb (written once, by the workgroups of ob = 0), then dW_i's
-            // blocks (mb, ob) = H_mb^T dY_i[:, ob], a pass over H_mb each, into partial sets of their own
-            launch_block<64, T>(x, 1, x.rec(in_slot, layer, mb), wmb, plane, ld, none, false, nullptr, 0, one_pass, no_tie, dgw,
-                                x.hplane(), part, nullptr, S);
-            for (int ob = 0; ob < S; ++ob)
-                nparts = launch_dw<64, T>(x, dy + 64 * ob, ldg, no_tie, nullptr, 0, nullptr,
-                                          x.dw_partial() + (size_t)(mb * S + ob) * dw_set);
-        } else {
-            nparts = launch_block<64, T>(x, mode, x.rec(in_slot, layer, mb), wmb, plane, ld, none, false, dy, ldg, one_pass, no_tie,
-                                         dgw, nullptr, part, x.dw_partial() + (size_t)(mb * S) * dw_set, S);
-        }
+static void launch_dense_planes(const Ctx<64, T>& x, const T* dy, int64_t ldg) {
+    const HubPlan& hp = x.g->at.hub;
+    const size_t n = (size_t)x.cfg->n;
+    if (hp.n_chunks > 0) {
+        HubChunks hc{hp.ce0, hp.ce1, hp.n_chunks, x.g->long_rows, hp.single};
+        ProfScope prof(KC_HUB, x.s);
+        for (int s = 0; s < x.S; ++s)
+            hipLaunchKernelGGL((k_hub_dense<64, T>), dim3(hub_grid(hp.n_chunks)), dim3(256), 0, x.s, make_view(x.g, true), hc, dy + 64 * s, ldg,
+                               x.hub_part() + (size_t)s * hp.n_chunks * 64, x.dh() + s * n * 64);
     }
-    // dW_i: its S x S blocks from their partial sets in one launch (every launch of a kind has the same grid)
-    if (mode == 2) {
-        ProfScope prof(KC_DW_REDUCE, x.s);
-        hipLaunchKernelGGL(k_dw_reduce, dim3(64 * 64 / DW_REDUCE_ENTRIES, (unsigned)(S * S)), dim3(256), 0, x.s, (const float*)x.dw_partial(),
-                           (int)nparts, 64 * 64, dw_i, 64, dgw, dw_set, S);
-    }
+    DensePlanesArgs<T> a;
+    a.g = make_view(x.g, true);
+    a.n = (int)n; a.tiles = x.tiles; a.x = dy; a.ld = ldg; a.hub_part = x.hub_part(); a.n_chunks = hp.n_chunks; a.q = x.dh();
+    a.y_draws = kTileCounterSet;
+    tile_counters(x.g, &a.draws, &a.draws_done);
+    ProfScope prof(KC_GRAD, x.s);
+    static const int per_cu = resident_blocks((const void*)k_dense_planes<T, false>);
+    const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu) / (unsigned)x.S / 8 * 8);       // the resident workgroups shared out
+    if (heavy_first(a.g.n_heavy, x.tiles, grid)) hipLaunchKernelGGL((k_dense_planes<T, true>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
+    else hipLaunchKernelGGL((k_dense_planes<T, false>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
+}
+
+// plane (+/-)= H W_i with H in x.hplane()
+template <typename T>
+static void launch_wide_product(const Ctx<64, T>& x, int sign, const float* wi, T* plane, int64_t ld) {
+    ProfScope prof(sign > 0 ? KC_BLOCK_FWD : KC_BLOCK_INV, x.s);
+    wide_blocks(x.S, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        WideProductArgs<S, T> a;
+        a.n = (int)x.cfg->n; a.tiles = x.tiles; a.h = x.hplane(); a.w = wi; a.plane = plane; a.ld = ld;
+        const dim3 grid((unsigned)((x.tiles + 7) / 8));
+        if (sign > 0) hipLaunchKernelGGL((k_wide_product<S, T, +1>), grid, dim3(512), 0, x.s, a);
+        else hipLaunchKernelGGL((k_wide_product<S, T, -1>), grid, dim3(512), 0, x.s, a);
+    });
+}
+
+// dst += back through GS of (Q W_i^T), Q in x.dh()
+template <typename T>
+static void launch_wide_grad(const Ctx<64, T>& x, const float* wi, int slot, int layer, const T* z, int64_t ldz, int64_t z_sub, T* dst,
+                             int64_t ldd, int64_t dst_gs, int ndst) {
+    ProfScope prof(KC_GRAD, x.s);
+    wide_blocks(x.S, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        WideGradArgs<S, T> a;
+        a.n = (int)x.cfg->n; a.tiles = x.tiles; a.q = x.dh(); a.w = wi;
+        for (int s = 0; s < S; ++s) a.mask[s] = x.rec(slot, layer, s).mask;
+        a.z = z; a.ldz = ldz; a.z_sub = z_sub; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
+        a.dst = dst; a.ldd = ldd; a.dst_gs = dst_gs; a.ndst = ndst;
+        hipLaunchKernelGGL((k_wide_grad<S, T>), dim3((unsigned)((x.tiles + 7) / 8)), dim3(512), 0, x.s, a);
+    });
 }
 
 template <typename T>
@@ -1553,7 +1733,8 @@ static void wide_forward(const Ctx<64, T>& x, const float* w, const Planes<T>& p
     const int C = x.cfg->c, dgw = 64 * x.S;
     if (!slot0_ready) launch_gs_wide<T>(x, p.grp(1), p.ld, p.gs, C - 1, nullptr, 0, layer);
     for (int i = 1; i <= C; ++i) {
-        wide_block<T>(x, 0, i - 1, layer, w + (size_t)(i - 1) * dgw * dgw, p.grp(i - 1), p.ld, nullptr, 0, nullptr);
+        launch_gather_wide<T>(x, i - 1, layer);
+        launch_wide_product<T>(x, +1, w + (size_t)(i - 1) * dgw * dgw, p.grp(i - 1), p.ld);
         if (i < C) launch_gs_wide<T>(x, p.grp(i - 1), p.ld, p.gs, 1, nullptr, i, layer);
         else if (C == 2) launch_gs_wide<T>(x, p.grp(i - 1), p.ld, p.gs, 1, nullptr, 0, layer + 1);
     }
@@ -1565,7 +1746,8 @@ static void wide_inverse(const Ctx<64, T>& x, const float* w, const Planes<T>& p
     for (int i = 1; i < C; ++i) launch_gs_wide<T>(x, p.grp(i - 1), p.ld, p.gs, 1, nullptr, i, 0);
     for (int i = C; i >= 1; --i) {
         if (i == 1 && C > 2) launch_gs_wide<T>(x, p.grp(1), p.ld, p.gs, C - 1, nullptr, 0, 0);
-        wide_block<T>(x, 1, i - 1, 0, w + (size_t)(i - 1) * dgw * dgw, p.grp(i - 1), p.ld, nullptr, 0, nullptr);
+        launch_gather_wide<T>(x, i - 1, 0);
+        launch_wide_product<T>(x, -1, w + (size_t)(i - 1) * dgw * dgw, p.grp(i - 1), p.ld);
         if (i == 2 && C == 2) launch_gs_wide<T>(x, p.grp(1), p.ld, p.gs, 1, nullptr, 0, 0);
     }
 }
@@ -1589,19 +1771,24 @@ static void wide_backward(const Ctx<64, T>& x, const float* w, const Planes<T>& 
             launch_gs_wide<T>(x, y.grp(1), y.ld, y.gs, C - 1, x.y0(), 0, layer, given);
             z = x.y0(); ldz = 64; z_sub = n * 64;
         }
-        wide_block<T>(x, 2, i - 1, layer, wi, y.grp(i - 1), y.ld, dy.grp(i - 1), dy.ld, dw_out + (size_t)(i - 1) * dgw * dgw);
+        launch_gather_wide<T>(x, i - 1, layer);
+        launch_wide_product<T>(x, -1, wi, y.grp(i - 1), y.ld);
+        // dW_i = H^T dY_i: its S x S blocks from partial sets of their own, each in one launch
+        const unsigned nparts = launch_dw<64, T>(x, dy.grp(i - 1), dy.ld);
+        {
+            ProfScope prof(KC_DW_REDUCE, x.s);
+            hipLaunchKernelGGL(k_dw_reduce, dim3(64 * 64 / DW_REDUCE_ENTRIES, (unsigned)(S * S)), dim3(256), 0, x.s, (const float*)x.dw_partial(),
+                               (int)nparts, 64 * 64, dw_out + (size_t)(i - 1) * dgw * dgw, 64, dgw, (size_t)x.g->grid * 64 * 64, S);
+        }
         // the record of the rebuilt X_i, where the next block or the layer below needs it
         if (i < C) {
             if (!(in_step && layer == 0)) launch_gs_wide<T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, i, given ? layer - 1 : 0, given);
         } else if (C == 2) {
             launch_gs_wide<T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, 0, layer, given);      // X_2 = Y_0 of this layer
         }
-        // dH_mb = sum_ob (A^T dY_i[:, ob]) W_i[mb][ob]^T, then back through GS of the whole row
-        // (one launch per column block ob of dY_i for all S blocks of dH: blockIdx.y = mb)
-        for (int ob = 0; ob < S; ++ob)
-            launch_grad_acc<T>(x, dy.grp(i - 1) + 64 * ob, dy.ld, wi + 64 * ob, dgw, x.dh(), ob == 0, false, S);
-        if (i >= 2) launch_epi_wide<T>(x, i - 1, layer, z, ldz, z_sub, dy.grp(i - 2), dy.ld, dy.gs, 1);
-        else launch_epi_wide<T>(x, 0, layer, z, ldz, z_sub, dy.grp(1), dy.ld, dy.gs, C - 1);
+        launch_dense_planes<T>(x, dy.grp(i - 1), dy.ld);
+        if (i >= 2) launch_wide_grad<T>(x, wi, i - 1, layer, z, ldz, z_sub, dy.grp(i - 2), dy.ld, dy.gs, 1);
+        else launch_wide_grad<T>(x, wi, 0, layer, z, ldz, z_sub, dy.grp(1), dy.ld, dy.gs, C - 1);
     }
 }
 
@@ -1683,7 +1870,7 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
         if (split_dw<DG, T>(x.g)) {
             // X_i = Y_i - f_i(Y_{i-1}) with H kept for the weight gradient, then dW_i = H^T dY_i
             launch_block<DG, T>(x, 1, x.rec(i - 1, layer), wi, y.grp(i - 1), y.ld, out, given, nullptr, 0, true,
-                                TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, DG, x.hplane());
+                                TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, x.hplane());
             nparts = launch_dw<DG, T>(x, dy.grp(i - 1), dy.ld, out_tie, y.grp(i - 1), y.ld, out.mask ? &out : nullptr);
         } else {
             nparts = launch_block<DG, T>(x, 2, x.rec(i - 1, layer), wi, y.grp(i - 1), y.ld, out, given, dy.grp(i - 1), dy.ld, true);

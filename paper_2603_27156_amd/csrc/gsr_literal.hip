@@ -179,7 +179,7 @@ static void launch_slot_tile(const Lit& x, const SlotArgs& a, const HubPlan& h) 
     if (h.n_chunks > 0) {
         HubChunks hc{h.ce0, h.ce1, h.n_chunks, x.g->long_rows};
         hipLaunchKernelGGL((k_hub_dense<W, float>), dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s, a.g, hc,
-                           a.P, (int64_t)W, x.g->scratch);
+                           a.P, (int64_t)W, x.g->scratch, (float*)nullptr);
     }
     // as many workgroups as stay resident with this much LDS, at most the graph's persistent grid
     const int per_cu = std::min<int>(4, (int)(160 * 1024 / (4 * sizeof(SlotLds<W>))));

@@ -23,6 +23,7 @@ CsrView make_view(const gsr_graph_t* g, bool transpose) {
     v.rp = c.rp; v.ci = c.ci; v.av = c.av; v.er = c.er;
     v.hub_rows = c.hub.rows; v.hub_cptr = c.hub.cptr; v.hub_tile0 = c.hub.tile0; v.n_hub = c.hub.n_hub;
     v.hub_threshold = g->hub_threshold;
+    v.hub_chunk = g->hub_chunk;
     v.heavy = c.heavy; v.n_heavy = c.n_heavy; v.heavy_edges = kHeavyTileEdges;
     for (int x = 0; x < 9; ++x) v.heavy_ptr[x] = c.heavy_ptr[x];
     return v;
@@ -231,22 +232,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     walk.finish();
 }
 
-// float32 records: the sums of a tile in ordinary arithmetic into an LDS tile (gather_records_rows), rows stored from
-// there; 16-bit records: on the matrix cores, rows stored from the accumulators.
+// float32 records: the sums of a tile in ordinary arithmetic into an LDS tile (gather_values_rows), rows stored from
+// there; 16-bit records: on the matrix cores, rows stored from the accumulators.  *bad: the indices have been found wanting
+// by k_pack_columns / k_pack_records, nothing is written.
 template <int DG, typename T, bool DEAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_aggregate_tile(CsrView g, int n, int tiles, const T* __restrict__ vals,
-                                                        const typename MaskOf<DG>::type* __restrict__ masks, int k,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_aggregate_tile(CsrView g, int n, int tiles, Record<DG, T> in, int k,
                                                         const float* __restrict__ hub_part, float* __restrict__ h_out,
-                                                        int* draws, int* draws_done) {
-    constexpr int LR = tile_ld<DG>();
+                                                        int* draws, int* draws_done, const int* __restrict__ bad) {
+    if (*bad) return;
+    constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     struct Wave {
         TileLds t;
-        alignas(16) float st[sizeof(T) == 4 ? 16 * LR : 4];
+        alignas(16) float st[sizeof(T) == 4 ? gather_floats<DG>() : 4];
     };
+    struct None {};
     __shared__ Wave lds[4];
-    __shared__ typename std::conditional<sizeof(T) == 2, DealLut, DealLutF>::type dlut;
+    __shared__ typename std::conditional<sizeof(T) == 2, DealLut, None>::type dlut;
     if constexpr (sizeof(T) == 2) deal_lut_fill(dlut);
-    else deal_lutf_fill(dlut);
     Wave& W = lds[threadIdx.x >> 6];
     TileLds& L = W.t;
     const int lane = lane_id();
@@ -259,20 +261,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const bool has_hub = tile_begin(g, rpv, L.rp, lane);
         if (walk.dealt(g, rpv, L.rp, has_hub)) { walk.next(g); continue; }
         if constexpr (sizeof(T) == 4) {
-            tile_gather_rows<DG>(g, hub_part, has_hub, r0, L.rp, W.st, lane, [&](int e_a, int e_b) {
-                gather_records_rows<DG, 8, true>(g, vals, masks, k, __builtin_amdgcn_readfirstlane(e_a), __builtin_amdgcn_readfirstlane(e_b),
-                                                 L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf, lane, W.st, &dlut);
+            tile_gather_rows<DG, true, 20>(g, hub_part, has_hub, r0, L.rp, W.st, lane, [&](int e_a, int e_b) {
+                gather_values_rows<DG, 8, false>(g, in.vals, in.cols, k, __builtin_amdgcn_readfirstlane(e_a),
+                                                 __builtin_amdgcn_readfirstlane(e_b), lane, W.st);
             });
             wave_sync();
-            const int rows = n - r0 < 16 ? n - r0 : 16;
-            for (int r = 0; r < rows; ++r)
-                if (lane < DG) __builtin_nontemporal_store(W.st[r * LR + lane], h_out + (size_t)(r0 + r) * DG + lane);
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) {
+                const int rr = 4 * reg + (lane >> 4), row = r0 + rr;
+                float v[CPL];
+                lds_load<CPL>(W.st + rr * LR + CPL * (lane & 15), v);
+                if (row < n) store_cols<CPL, float>(h_out + (size_t)row * DG + CPL * (lane & 15), v);
+            }
         } else {
             f32x4 acc[DG / 16];
 #pragma unroll
             for (int cb = 0; cb < DG / 16; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
             tile_ranges(g, has_hub, L.rp, [&](int e_a, int e_b) {
-                gather_records_mfma<DG, T, 8>(g, vals, masks, k, __builtin_amdgcn_readfirstlane(e_a),
+                gather_records_mfma<DG, T, 8>(g, in.vals, in.mask, k, __builtin_amdgcn_readfirstlane(e_a),
                                               __builtin_amdgcn_readfirstlane(e_b), L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf,
                                               lane, acc, &dlut);
             });
@@ -350,44 +356,77 @@ __global__ __launch_bounds__(256) void k_pack_records(int64_t n, int k, int kp, 
     }
 }
 
+// float32: the values are gathered as the caller holds them, any slot order; only the columns are packed, to bytes (an
+// eighth of the traffic of a record of its own: 45 -> 20 us at 1M rows, k = 16).  kp lanes per row and the same checks.
+template <int DG>
+__global__ __launch_bounds__(256) void k_pack_columns(int64_t n, int k, int kp, const int32_t* __restrict__ i_in, uint8_t* __restrict__ c_out,
+                                                      int* __restrict__ bad) {
+    const int lane = lane_id(), t = lane % kp, sub = lane / kp, per = 64 / kp;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t r0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * per; r0 < n; r0 += nwaves * per) {
+        const int64_t row = r0 + sub;
+        const bool ok = row < n && t < k;
+        const int col = ok ? i_in[row * k + t] : 0;
+        const bool in_range = col >= 0 && col < DG;
+        const uint64_t bit = (ok && in_range) ? (uint64_t)1 << col : 0ull;
+        uint32_t lo = (uint32_t)bit, hi = (uint32_t)(bit >> 32);
+        for (int off = 1; off < kp; off <<= 1) {
+            lo |= (uint32_t)__shfl_xor((int)lo, off, 64);
+            if (DG == 64) hi |= (uint32_t)__shfl_xor((int)hi, off, 64);
+        }
+        if (ok && (!in_range || __popc(lo) + __popc(hi) != k)) *bad = 1;
+        if (ok) c_out[row * k + t] = (uint8_t)(in_range ? col : 0);
+    }
+}
+
 template <int DG, typename T>
 static gsr_status_t aggregate_impl(const gsr_graph_t* g, const void* vals, const int32_t* idx, int k, float* h_out,
                                    void* ws, int* bad, hipStream_t s) {
     using M = typename MaskOf<DG>::type;
     const int64_t n = g->n;
     char* p = (char*)ws;
-    T* v_rec = (T*)p;
+    Record<DG, T> rec;
+    T* v_rec = (T*)p;                                       // 16-bit storage; float32: the columns
     p += align_up((size_t)n * k * sizeof(T) + 16);          // the record gather loads up to 16 bytes past a record
-    M* m_rec = (M*)p;
+    rec.mask = (M*)p;
     p += align_up((size_t)n * sizeof(M));
     float* part = (float*)p;
-    // indices come from the caller: reject out-of-range or repeated columns instead of reading wild
+    // indices come from the caller: out-of-range or repeated columns are reported.  The kernels after the check are launched
+    // before its answer is known (they read nothing wild whatever the indices are and write nothing where it is bad), so the
+    // caller's thread waits once, for all of them, and the GPU not at all (54 us of gap at 1M rows).
     int kp = 1;
     while (kp < k) kp <<= 1;
     const int64_t steps = (n + 64 / kp - 1) / (64 / kp);
+    const dim3 pgrid((unsigned)std::min<int64_t>((steps + 3) / 4, 16384));
     GSR_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), s));
-    hipLaunchKernelGGL((k_pack_records<DG, T>), dim3((unsigned)std::min<int64_t>((steps + 3) / 4, 16384)), dim3(256), 0, s, n, k,
-                       kp, (const T*)vals, idx, v_rec, m_rec, bad);
-    int bad_h = 0;
-    GSR_HIP_CHECK(hipMemcpyAsync(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost, s));
-    GSR_HIP_CHECK(hipStreamSynchronize(s));
-    if (bad_h) return fail(GSR_ERR_INVALID_ARG, "idx holds a column outside [0,dg) or a repeated column");
+    if constexpr (sizeof(T) == 4) {
+        rec.vals = (T*)vals;
+        rec.cols = (uint8_t*)v_rec;
+        hipLaunchKernelGGL((k_pack_columns<DG>), pgrid, dim3(256), 0, s, n, k, kp, idx, rec.cols, bad);
+    } else {
+        rec.vals = v_rec;
+        rec.cols = nullptr;
+        hipLaunchKernelGGL((k_pack_records<DG, T>), pgrid, dim3(256), 0, s, n, k, kp, (const T*)vals, idx, v_rec, rec.mask, bad);
+    }
     CsrView v = make_view(g, false);
     if (g->a.hub.n_chunks > 0) {
         HubChunks hc{g->a.hub.ce0, g->a.hub.ce1, g->a.hub.n_chunks, g->long_rows};
-        hipLaunchKernelGGL((k_hub_records<DG, T>), dim3(hub_grid(g->a.hub.n_chunks)), dim3(256), 0, s, v, hc,
-                           (const T*)v_rec, (const M*)m_rec, k, part);
+        hipLaunchKernelGGL((k_hub_records<DG, T>), dim3(hub_grid(g->a.hub.n_chunks)), dim3(256), 0, s, v, hc, rec, k, part);
     }
     int *dn, *dx;
     tile_counters(g, &dn, &dx);
     const int tiles = (int)((n + 15) / 16);
     if (heavy_first(v.n_heavy, tiles, (unsigned)g->grid))
-        hipLaunchKernelGGL((k_aggregate_tile<DG, T, true>), dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles,
-                           (const T*)v_rec, (const M*)m_rec, k, (const float*)part, h_out, dn, dx);
+        hipLaunchKernelGGL((k_aggregate_tile<DG, T, true>), dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles, rec, k,
+                           (const float*)part, h_out, dn, dx, (const int*)bad);
     else
-        hipLaunchKernelGGL((k_aggregate_tile<DG, T, false>), dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles,
-                           (const T*)v_rec, (const M*)m_rec, k, (const float*)part, h_out, dn, dx);
+        hipLaunchKernelGGL((k_aggregate_tile<DG, T, false>), dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles, rec, k,
+                           (const float*)part, h_out, dn, dx, (const int*)bad);
     GSR_HIP_CHECK(hipGetLastError());
+    int bad_h = 0;
+    GSR_HIP_CHECK(hipMemcpyAsync(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    GSR_HIP_CHECK(hipStreamSynchronize(s));
+    if (bad_h) return fail(GSR_ERR_INVALID_ARG, "idx holds a column outside [0,dg) or a repeated column");
     return GSR_OK;
 }
 
@@ -418,9 +457,9 @@ static gsr_status_t spmm_launch(const gsr_graph_t* g, const float* x, int64_t ld
         if (h.n_chunks > 0) {
             HubChunks hc{h.ce0, h.ce1, h.n_chunks, g->long_rows};
             const dim3 hg(hub_grid(h.n_chunks));
-            if (width == 64) hipLaunchKernelGGL((k_hub_dense<64, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part);
-            else if (width == 32) hipLaunchKernelGGL((k_hub_dense<32, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part);
-            else hipLaunchKernelGGL((k_hub_dense<16, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part);
+            if (width == 64) hipLaunchKernelGGL((k_hub_dense<64, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
+            else if (width == 32) hipLaunchKernelGGL((k_hub_dense<32, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
+            else hipLaunchKernelGGL((k_hub_dense<16, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
         }
         const bool deal = heavy_first(view.n_heavy, tiles, (unsigned)g->grid);
         auto launch = [&](auto kernel) {
