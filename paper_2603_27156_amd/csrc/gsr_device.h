@@ -586,174 +586,9 @@ __device__ __forceinline__ void gather_dense_mfma(const CsrView& g, const T* __r
     }
 }
 
-// One staged edge of a record gather: where neighbour j's k values start, a_ij, and j's column mask.
-struct RecEdge {
-    uint32_t off0;   // j * k
-    float a;
-    uint32_t mlo, mhi;
-};
-
-// Dealing 16-bit record values to a lane's four columns with two byte permutes.  The window of four slots is two
-// words (slot t in bytes 2t, 2t+1); column c takes slot popcount(mask bits below c) if its bit is set, else zero.
-// For each of the 16 values of the lane's four mask bits a table holds the two v_perm_b32 selectors that build
-// (column 0 | column 1 << 16) and (column 2 | column 3 << 16) from the window (selector byte 0x0c yields zero).
-// The table sits in LDS (16 entries of 8 bytes, one ds_read_b64 per staged edge and lane).
-struct DealLut {
-    uint2 sel[16];
-};
-__device__ __forceinline__ void deal_lut_fill(DealLut& l) {
-    if (threadIdx.x < 16) {
-        const uint32_t nib = threadIdx.x;
-        uint32_t s[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const uint32_t t = (uint32_t)__popc(nib & ((1u << c) - 1u));
-            s[c] = ((nib >> c) & 1u) ? ((2u * t + 1u) << 8 | (2u * t)) : 0x0c0cu;
-        }
-        l.sel[nib] = make_uint2(s[0] | s[1] << 16, s[2] | s[3] << 16);
-    }
-    __syncthreads();
-}
-
-// acc += P * scatter(V, I) over the edges [e_a, e_b) of ordinary rows (Section 4.1, eq. (10)).
-// The record of neighbour j is its k kept values in ascending column order plus a DG-bit column
-// mask.  A lane's CPL adjacent columns occupy adjacent slots of the record, starting at
-// popcount(mask below its first column): the lane loads CPL values from there (the tail of the
-// window may belong to the next record, or to the padding that follows the last one) and deals
-// them out to the columns whose mask bit is set.  16-bit values are loaded from the even slot at
-// or below the start.  n * k must stay below 2^32.
-template <int DG, typename T, int MAXB, bool ONE_ROW = false>
-__device__ __forceinline__ void gather_records_mfma(const CsrView& g, const T* __restrict__ vals,
-                                                    const typename MaskOf<DG>::type* __restrict__ masks, int k, int e_a,
-                                                    int e_b, const int* s_rp, RecEdge* ebuf, uint8_t* rbuf, int lane,
-                                                    f32x4 (&acc)[DG / 16], const DealLut* lut = nullptr) {
-    static_assert(sizeof(T) == 2, "float32 records are summed value by value");
-    constexpr bool PERM = !ONE_ROW;                       // (callers of that case pass the table)
-    using M = typename MaskOf<DG>::type;
-    constexpr int CPL = DG / 16, NW = sizeof(T) == 4 ? CPL : CPL / 2 + 1;
-    const int i16 = lane & 15, kk = lane >> 4, bp = CPL * i16;
-    const uint32_t sh = bp & 31;
-    const bool upper = bp >= 32;
-    const uint32_t below_lo = upper ? 0xFFFFFFFFu : (1u << sh) - 1u, below_hi = upper ? (1u << sh) - 1u : 0u;
-    for (int eb = e_a; eb < e_b; eb += 64) {
-        const int e = eb + lane;
-        const bool ok = e < e_b;
-        const int j = ok ? __builtin_nontemporal_load(g.ci + e) : 0;
-        RecEdge me;
-        me.a = ok ? __builtin_nontemporal_load(g.av + e) : 0.f;
-        me.off0 = (uint32_t)j * (uint32_t)k;
-        const M m = masks[j];
-        me.mlo = (uint32_t)m;
-        if constexpr (DG == 64) me.mhi = (uint32_t)(m >> 32);
-        else me.mhi = 0u;
-        const int r = tile_row_of(s_rp, e);
-        wave_sync();          // readers of the previous chunk are done
-        ebuf[lane] = me;
-        rbuf[lane] = (uint8_t)r;
-        wave_sync();
-        const int cnt = e_b - eb < 64 ? e_b - eb : 64;
-        edge_batches<MAXB>((cnt + 3) >> 2, [&](auto gbc, int i0) {
-            constexpr int GB = decltype(gbc)::value;
-            uint32_t w[GB][NW];
-            uint32_t nib[GB];     // mask bits of this lane's CPL columns (bit 31: odd 16-bit start)
-            float p[GB];
-#pragma unroll
-            for (int u = 0; u < GB; ++u) {
-                const int ei = 4 * (i0 + u) + kk;
-                const RecEdge er = ebuf[ei];
-                const uint32_t word = upper ? er.mhi : er.mlo;
-                const uint32_t at = er.off0 + (uint32_t)__popc(er.mlo & below_lo) + (uint32_t)__popc(er.mhi & below_hi);
-                nib[u] = (word >> sh) & ((1u << CPL) - 1u);
-                if constexpr (sizeof(T) == 4) {
-                    load_words<NW>(vals + (size_t)at, w[u]);
-                } else {
-                    load_words<NW>(vals + (size_t)(at & ~1u), w[u]);
-                    nib[u] |= at << 31;
-                }
-                p[u] = (ONE_ROW || (int)rbuf[ei] == i16) ? er.a : 0.f;
-            }
-            if constexpr (PERM) {
-                // columns (0 | 1 << 16) and, with four columns per lane, (2 | 3 << 16) of every staged edge, as bf16
-                uint32_t o01[GB], o23[CPL == 4 ? GB : 1];
-#pragma unroll
-                for (int u = 0; u < GB; ++u) {
-                    const uint32_t shift = (nib[u] >> 31) * 16u;
-                    const uint32_t lo = __builtin_amdgcn_alignbit(w[u][1], w[u][0], shift);
-                    const uint2 sel = lut->sel[nib[u] & 15u];
-                    if constexpr (CPL == 4) {
-                        const uint32_t hi = __builtin_amdgcn_alignbit(w[u][2], w[u][1], shift);
-                        o01[u] = __builtin_amdgcn_perm(hi, lo, sel.x);
-                        o23[u] = __builtin_amdgcn_perm(hi, lo, sel.y);
-                    } else {
-                        o01[u] = __builtin_amdgcn_perm(0u, lo, sel.x);      // (two mask bits: the window is one word)
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < GB; u += 4) {
-                    bf16x4 ph, pm, pl;
-                    split_p4(p + u, ph, pm, pl);
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) {
-                        const uint32_t* o = cb < 2 ? o01 : o23;
-                        const bf16x4 b = (cb & 1) ? pack_upper4(o[u], o[u + 1], o[u + 2], o[u + 3])
-                                                  : pack_lower4(o[u], o[u + 1], o[u + 2], o[u + 3]);
-                        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ph, b, acc[cb], 0, 0, 0);
-                        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pm, b, acc[cb], 0, 0, 0);
-                        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl, b, acc[cb], 0, 0, 0);
-                    }
-                }
-                return;
-            }
-            uint32_t bq[sizeof(T) == 4 ? 1 : GB][CPL];   // dealt-out values (float bits) of the 16-bit variant
-#pragma unroll
-            for (int u = 0; u < GB; ++u) {
-                uint32_t q[CPL];  // the window (float bits): slot start + t
-                if constexpr (sizeof(T) == 4) {
-#pragma unroll
-                    for (int t = 0; t < CPL; ++t) q[t] = w[u][t];
-                } else {
-                    const uint32_t shift = (nib[u] >> 31) * 16u;
-#pragma unroll
-                    for (int t = 0; t < CPL / 2; ++t) {
-                        const uint32_t pair = __builtin_amdgcn_alignbit(w[u][t + 1], w[u][t], shift);
-                        q[2 * t] = pair << 16;
-                        q[2 * t + 1] = pair & 0xFFFF0000u;
-                    }
-                }
-                // a set column takes the head of the window and advances it; all-ones / all-zero
-                // words from a signed bit extract drive bitwise selects, no condition codes
-#pragma unroll
-                for (int cb = 0; cb < CPL; ++cb) {
-                    const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)nib[u], cb, 1);
-                    const uint32_t b = q[0] & m;
-#pragma unroll
-                    for (int t = 0; t + 1 < CPL - cb; ++t) q[t] = bit_select(m, q[t + 1], q[t]);
-                    if constexpr (ONE_ROW) acc[cb][0] = __builtin_fmaf(p[u], __uint_as_float(b), acc[cb][0]);
-                    else if constexpr (sizeof(T) == 4) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[u], __uint_as_float(b), acc[cb], 0, 0, 0);
-                    else bq[u][cb] = b;
-                }
-            }
-            if constexpr (sizeof(T) != 4 && !ONE_ROW) {
-#pragma unroll
-                for (int u = 0; u < GB; u += 4) {
-                    bf16x4 ph, pm, pl;
-                    split_p4(p + u, ph, pm, pl);
-#pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) {
-                        const bf16x4 b = pack_upper4(bq[u][cb], bq[u + 1][cb], bq[u + 2][cb], bq[u + 3][cb]);
-                        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ph, b, acc[cb], 0, 0, 0);
-                        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pm, b, acc[cb], 0, 0, 0);
-                        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl, b, acc[cb], 0, 0, 0);
-                    }
-                }
-            }
-        });
-    }
-}
-
-// The same sums in ordinary arithmetic with a lane per kept value, for float32 records and for groups of more than 64
-// columns (Section 4.1, eq. (10)): on this chip float32 matrix instructions do not hide under vector work, and a 16-row
-// product spends fifteen rows of every edge on zeros.  Beside its k values a record
+// ---- gathers in ordinary arithmetic -------------------------------------------------------------------------
+// acc += P * scatter(V, I) over the edges [e_a, e_b) of ordinary rows (Section 4.1, eq. (10)), a lane per kept value.  (On
+// the matrix cores a 16-row product spends fifteen rows of every edge on zeros.)  Beside its k values a record
 // holds the column of each as a byte; the value of slot t of a neighbour belongs to lane t of a group of sixteen, which
 // adds a_ij * value to that column of the destination row's sums in LDS: read, fused multiply-add, written back.  (A lane
 // that owns columns instead has to find the window of slots that may hold them from the neighbour's mask - a round trip to
@@ -1297,7 +1132,7 @@ struct Record {
     using M = typename MaskOf<DG>::type;
     T* vals;        // [n][k]
     M* mask;        // [n]
-    uint8_t* cols;  // [n][k]: column of every value (NULL: not kept)
+    uint8_t* cols;  // [n][k]: column of every value
 };
 
 // ---- the k-th largest key of a row when k is a quarter of its width -------------------------------
@@ -1696,11 +1531,10 @@ __device__ __forceinline__ bool tile_is_heavy(const CsrView& g, int rpv, const i
     return e > g.heavy_edges;
 }
 
-// Per-wave LDS of the tile operators: staged edges, the tile's row pointers, rows of the staged records.
+// Per-wave LDS of the tile operators: staged edges, the tile's row pointers.
 struct TileLds {
     EdgeRec ebuf[64];
     int rp[20];
-    uint8_t rbuf[64];
 };
 
 // The order in which a wave of these kernels visits tiles: its share of the listed heavy tiles first (DEAL, see
@@ -1787,7 +1621,6 @@ __device__ __forceinline__ HubSweep hub_sweep(const HubChunks& h) {
 struct HubLds {
     EdgeRec ebuf[64];
     int rp[20];
-    uint8_t rbuf[64];
 };
 // row pointers of the pretended tile: row 0 spans [e0, e1), rows 1..15 are empty
 __device__ __forceinline__ void hub_chunk_begin(HubLds& L, int e0, int e1, int lane) {
@@ -1812,25 +1645,6 @@ __device__ __forceinline__ float* hub_out(const HubChunks& h, float* part, float
         if (r >= 0) return rows + ((size_t)block * n + r) * cols;
     }
     return part + ((size_t)block * h.n_chunks + q) * cols;
-}
-
-// 16-bit records of at most 64 columns
-template <int DG, typename T>
-__device__ __forceinline__ void hub_records_pass(const CsrView& g, const HubChunks& h, const T* __restrict__ vals,
-                                                 const typename MaskOf<DG>::type* __restrict__ masks, int k,
-                                                 float* __restrict__ part, HubLds& L, const HubSweep w) {
-    const int lane = lane_id();
-    for (int q = w.q; q < w.end; q += w.step) {
-        const int e0 = __builtin_amdgcn_readfirstlane(h.ce0[q]), e1 = __builtin_amdgcn_readfirstlane(h.ce1[q]);
-        hub_chunk_begin(L, e0, e1, lane);
-        f32x4 acc[DG / 16];
-#pragma unroll
-        for (int cb = 0; cb < DG / 16; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        gather_records_mfma<DG, T, 16, true>(g, vals, masks, k, e0, e1, L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf, lane, acc);
-#pragma unroll
-        for (int cb = 0; cb < DG / 16; ++cb) acc[cb][0] = quarter_sum(acc[cb][0]);
-        hub_chunk_store<DG>(acc, part + (size_t)q * DG, lane);
-    }
 }
 
 // Records with the column of every value, any k and any width: a lane per value (gather_values_rows), lane group kk taking
@@ -1900,21 +1714,10 @@ __device__ __forceinline__ void hub_dense_pass(const CsrView& g, const HubChunks
     }
 }
 
-// cols != NULL: records with columns (float32), else 16-bit records with masks
-template <int DG, typename T>
-__device__ __forceinline__ void hub_any_records_pass(const CsrView& g, const HubChunks& h, const Record<DG, T>& in, int k,
-                                                     float* __restrict__ part, void* lds, const HubSweep w) {
-    if constexpr (sizeof(T) == 4)
-        hub_value_rows_pass<DG, T>(g, h, in.vals, in.cols, k, 0, part, nullptr, reinterpret_cast<HubRowsLds<DG>*>(lds)[threadIdx.x >> 6], w);
-    else
-        hub_records_pass<DG, T>(g, h, in.vals, in.mask, k, part, reinterpret_cast<HubLds*>(lds)[threadIdx.x >> 6], w);
-}
-constexpr int hub_lds_bytes(int a, int b) { return 4 * (a > b ? a : b); }
-
 template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_hub_records(CsrView g, HubChunks h, Record<DG, T> in, int k, float* __restrict__ part) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[hub_lds_bytes(sizeof(HubLds), sizeof(HubRowsLds<DG>))];
-    hub_any_records_pass<DG, T>(g, h, in, k, part, lds, hub_sweep(h));
+    __shared__ HubRowsLds<DG> lds[4];
+    hub_value_rows_pass<DG, T>(g, h, in.vals, in.cols, k, 0, part, nullptr, lds[threadIdx.x >> 6], hub_sweep(h));
 }
 
 template <int DG, typename T>
@@ -1930,9 +1733,11 @@ template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_hub_both(CsrView ga, HubChunks ha, Record<DG, T> in, int k, float* __restrict__ part_a,
                                                   CsrView gt, HubChunks ht, const T* __restrict__ x, int64_t ld,
                                                   float* __restrict__ part_t) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[hub_lds_bytes(sizeof(HubLds), sizeof(HubRowsLds<DG>))];
-    if (blockIdx.y == 0) hub_any_records_pass<DG, T>(ga, ha, in, k, part_a, lds, hub_sweep(ha));
-    else hub_dense_pass<DG, T>(gt, ht, x, ld, part_t, reinterpret_cast<HubLds*>(lds)[threadIdx.x >> 6], hub_sweep(ht));
+    union Lds { HubLds dense; HubRowsLds<DG> rows; };
+    __shared__ Lds lds[4];
+    Lds& L = lds[threadIdx.x >> 6];
+    if (blockIdx.y == 0) hub_value_rows_pass<DG, T>(ga, ha, in.vals, in.cols, k, 0, part_a, nullptr, L.rows, hub_sweep(ha));
+    else hub_dense_pass<DG, T>(gt, ht, x, ld, part_t, L.dense, hub_sweep(ht));
 }
 
 // The records of a group of S column blocks

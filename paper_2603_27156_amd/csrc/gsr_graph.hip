@@ -98,6 +98,13 @@ __global__ void k_gcn_values(int n, const int32_t* __restrict__ rp, const int32_
     }
 }
 
+// the row of every stored entry modulo 16
+__global__ void k_entry_rows(int n, const int32_t* __restrict__ rp, uint8_t* __restrict__ er) {
+    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63, nwaves = (gridDim.x * blockDim.x) >> 6;
+    for (int i = wave; i < n; i += nwaves)
+        for (int e = rp[i] + lane; e < rp[i + 1]; e += 64) er[e] = (uint8_t)(i & 15);
+}
+
 __global__ void k_fill(int64_t n, float v, float* __restrict__ out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] = v;
@@ -164,7 +171,7 @@ static int64_t row_chunk(int64_t len, int64_t chunk, bool grow) {
     return r * chunk;
 }
 
-static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, int64_t base_chunk, bool grow, Csr* out) {
+static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, int64_t base_chunk, bool grow, hipStream_t s, Csr* out) {
     std::vector<int32_t> heavy;
     for (int64_t t0 = 0; t0 < n; t0 += 16) {
         int64_t e = 0;      // stored entries of the tile's rows that are not split
@@ -180,9 +187,11 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
     GSR_TRY(upload(h.rp, &out->rp));
     GSR_TRY(upload(h.ci, &out->ci));
     GSR_TRY(upload(h.av, &out->av));
-    std::vector<uint8_t> er(h.ci.size());
-    for (int64_t i = 0; i < n; ++i) std::fill(er.begin() + h.rp[i], er.begin() + h.rp[i + 1], (uint8_t)(i & 15));
-    GSR_TRY(upload(er, &out->er));
+    GSR_HIP_CHECK(hipMalloc((void**)&out->er, std::max<size_t>(h.ci.size(), 1)));
+    if (n > 0 && !h.ci.empty()) {
+        hipLaunchKernelGGL(k_entry_rows, dim3((unsigned)std::min<int64_t>((n + 3) / 4, 4096)), dim3(256), 0, s, (int)n, out->rp, out->er);
+        GSR_HIP_CHECK(hipGetLastError());
+    }
     std::vector<int32_t> rows, cptr, crow, ce0, ce1, tile0, single;
     cptr.push_back(0);
     for (int64_t i = 0; i < n; ++i) {
@@ -275,7 +284,7 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
         w.rec_vals[s] = off;
         off += align_up(n * (size_t)cfg->k * b + 16);   // the record gather loads up to 16 bytes past a record
         w.rec_cols[s] = off;
-        if (S > 1 || b == 4) off += align_up(n * (size_t)cfg->k + 16);
+        off += align_up(n * (size_t)cfg->k + 16);
     }
     for (int s = 0; s < cfg->c * S && s < kMaxRecordSlots; ++s) {
         w.rec_mask[s] = off;
@@ -551,10 +560,10 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     g->hub_values = options().hub_values == 1 ? 2 : (options().hub_values == 0 && long_rows) ? 1 : 0;
     g->split_backward = !(long_rows || (n + 15) / 16 < (int64_t)8 * full_grid);    // (not with fewer than two tiles per resident wave)
 
-    gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, grow, &g->a);
+    gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, grow, (hipStream_t)stream, &g->a);
     if (st == GSR_OK) {
         if (symmetric) g->at = g->a;
-        else st = upload_csr(t, n, hub_threshold, hub_chunk, grow, &g->at);
+        else st = upload_csr(t, n, hub_threshold, hub_chunk, grow, (hipStream_t)stream, &g->at);
     }
     if (st == GSR_OK) {
         const size_t chunks = (size_t)std::max(std::max(g->a.hub.n_chunks, g->at.hub.n_chunks), 1);

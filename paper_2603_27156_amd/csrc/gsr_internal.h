@@ -131,7 +131,7 @@ gsr_status_t validate_config(const gsr_config_t* cfg, const gsr_graph_t* g, bool
 constexpr int kMaxRecordSlots = 32;   // groups (at most 8) x sub-planes of a group (at most 4)
 struct LayerWs {
     size_t rec_vals[kMaxRecordSlots];  // per slot: compressed values  [n][k] of T
-    size_t rec_cols[kMaxRecordSlots];  // per slot (float32, or groups of more than 64 columns): column of every value [n][k] bytes
+    size_t rec_cols[kMaxRecordSlots];  // per slot: column of every value [n][k] bytes
     size_t rec_mask[kMaxRecordSlots];  // per slot and sub-plane: column bit mask    [n] of uint32 (32 columns) / uint64 (64)
     size_t y0;           // Y_0 plane [n][dg] of T (C > 2); wide groups: [S][n][64]
     size_t h;            // [n][dg] float: H of the block being inverted, for the weight-gradient kernel; wide groups: [S][n][64], H

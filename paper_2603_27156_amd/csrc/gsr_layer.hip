@@ -23,13 +23,12 @@ namespace gsr {
 CsrView make_view(const gsr_graph_t* g, bool transpose);
 
 // per-wave LDS: a tile of 16 x tile_ld floats, 64 staged edges, 17 row pointers
-template <int DG, bool COLS = false>
+template <int DG, bool RECORDS = false>
 struct WaveLds {
-    // the tile, with what emit_tile and (COLS) gather_values_rows need behind it
-    alignas(16) float st[COLS && gather_floats<DG>() > emit_floats<DG, COLS>() ? gather_floats<DG>() : emit_floats<DG, COLS>()];
-    EdgeRec ebuf[COLS ? 1 : 64];           // 64 staged edges (RecEdge has the same size; not with gather_values_rows)
+    // the tile, with what gather_values_rows and emit_tile need behind it (RECORDS)
+    alignas(16) float st[!RECORDS ? 16 * tile_ld<DG>() : gather_floats<DG>() > emit_floats<DG, true>() ? gather_floats<DG>() : emit_floats<DG, true>()];
+    EdgeRec ebuf[RECORDS ? 1 : 64];        // 64 staged edges (not with gather_values_rows)
     int rp[20];                            // row pointers of the tile's 17 row boundaries
-    uint8_t rbuf[COLS ? 4 : 64];           // tile row of every staged edge
 };
 
 // ---- block: forward / inverse (+ weight gradient) ------------------------------------------------
@@ -70,16 +69,11 @@ template <int DG, typename T, int SIGN, bool WITH_DW, bool DEAL, bool B3 = true>
 __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgpu_waves_per_eu(WITH_DW ? 2 : 4))) void k_block(BlockArgs<DG, T> a) {
     static_assert(B3 || (SIGN > 0 && !WITH_DW), "only the forward kernel has a float32 variant");
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
-    // float32 records carry their columns (gather_values_rows, emit_tile)
-    constexpr bool COLS = sizeof(T) == 4;
-    __shared__ WaveLds<DG, COLS> lds[block_waves(WITH_DW, B3)];
+    __shared__ WaveLds<DG, true> lds[block_waves(WITH_DW, B3)];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
-    WaveLds<DG, COLS>& L = lds[wave];
+    WaveLds<DG, true>& L = lds[wave];
     float* st_h = L.st;
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
-    struct None {};
-    __shared__ typename std::conditional<sizeof(T) == 2, DealLut, None>::type dlut;
-    if constexpr (sizeof(T) == 2) deal_lut_fill(dlut);
     if constexpr (B3) load_w_lds_b3<DG>(a.w, a.ldw, false, wl);
     else load_w_lds<DG>(a.w, a.ldw, false, wl);
     f32x4 dw[WITH_DW ? DG / 16 : 1][WITH_DW ? DG / 16 : 1];
@@ -137,7 +131,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         // during the weight product.  Measured per variant (1M-node workload, float32: forward 232 us early against 241
         // late, inverse 264 against 257; the fused inverse + dW kernel gains from late rows at D/C = 32 and loses at 64,
         // the 16-bit forward kernel the other way round).
-        constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
+                constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
         float xy[4][CPL], gy[WITH_DW ? 4 : 1][CPL];
         auto own_rows = [&]() {
 #pragma unroll
@@ -158,21 +152,11 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
                 continue;
             }
         }
-        // float32: the sums in ordinary arithmetic, in the forward and in both inverse kernels alike, so that f_i is
-        // recomputed by the instructions that computed it.
-        if constexpr (COLS) {
-            tile_gather_rows<DG, true, 20>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
-                gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, __builtin_amdgcn_readfirstlane(e_a),
-                                          __builtin_amdgcn_readfirstlane(e_b), lane, st_h);
-            });
-        } else {
-            f32x4 hacc[DG / 16];
-            tile_gather<DG>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, hacc, [&](int e_a, int e_b) {
-                gather_records_mfma<DG, T, 8>(a.g, a.in.vals, a.in.mask, a.k, __builtin_amdgcn_readfirstlane(e_a),
-                                              __builtin_amdgcn_readfirstlane(e_b), L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf,
-                                              lane, hacc, &dlut);
-            });
-        }
+        // (in the forward and in both inverse kernels alike, so that f_i is recomputed by the instructions that computed it)
+        tile_gather_rows<DG, true, 20>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
+            gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, __builtin_amdgcn_readfirstlane(e_a),
+                                           __builtin_amdgcn_readfirstlane(e_b), lane, st_h);
+        });
         advance();
         rpv = tile_rp_load(a.g, t_next * 16, a.n, lane);
         if constexpr (OWN_LATE) own_rows();
@@ -219,7 +203,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         }
         if (a.out.mask) {
             wave_sync();
-            emit_tile<DG, T, COLS>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+            emit_tile<DG, T, true>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
         }
         t = t_next;
         t_end = t_end_next;
@@ -281,7 +265,7 @@ __device__ __forceinline__ void tie_fixup_rows(const TieSeg<DG>& tie, const T* _
             const bool bit = (msel >> j) & 1u;
             if (ok && bit) {
                 out.vals[slot] = from_float<T>(x[j] * scale);
-                if constexpr (sizeof(T) == 4) out.cols[slot] = (uint8_t)(q * QW + j);
+                out.cols[slot] = (uint8_t)(q * QW + j);
             }
             slot += bit ? 1 : 0;
         }
@@ -690,8 +674,7 @@ __global__ void k_zero_ints(int* p, int count) {
 template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
-    constexpr bool COLS = sizeof(T) == 4;
-    __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, COLS>()];
+    __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, true>()];
     const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
     float* st = tile[threadIdx.x >> 6];
     const int nwaves = (gridDim.x * blockDim.x) >> 6, tiles = (a.n + 15) / 16;
@@ -728,7 +711,7 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
             lds_store<CPL>(st + rr * LR + CPL * tj, y[reg]);
         }
         wave_sync();
-        emit_tile<DG, T, COLS>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+        emit_tile<DG, T, true>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
     }
 }
 
@@ -1378,7 +1361,7 @@ struct Ctx {
         Record<DG, T> r;
         if (slot < 0) { r.vals = nullptr; r.mask = nullptr; r.cols = nullptr; return r; }
         r.vals = (T*)(ws + lw.rec_vals[slot]);
-        r.cols = sizeof(T) == 4 || S > 1 ? (uint8_t*)(ws + lw.rec_cols[slot]) : nullptr;
+        r.cols = (uint8_t*)(ws + lw.rec_cols[slot]);
         r.mask = saved ? saved + (((size_t)layer * cfg->c + slot) * S + sub) * (size_t)cfg->n : (M*)(ws + lw.rec_mask[slot * S + sub]);
         return r;
     }
@@ -1480,18 +1463,14 @@ static bool launch_hub_both(const Ctx<DG, T>& x, const Record<DG, T>& in, const 
     return true;
 }
 
-// How the backward of a block takes dW_i.  float32: the inverse kernel (sixteen waves per compute unit, row-wise sums as
-// in the forward kernel, so f_i is recomputed in the arithmetic it was computed in) leaves H in memory and k_dw takes
-// H^T dY_i in a pass of its own: 476 -> 320 + 112 us per block on the 1M-node workload (-3.8 % on the step) for 512 more
-// bytes per row.  bf16 storage at D/C = 64: split as well (240 + 81 us against 340 fused at 1M nodes once the inverse
-// requested its own rows after the gather; 253 + 80 against 337 before).  bf16 storage at D/C = 32: the fused kernel
-// (inverse + dW accumulators at eight waves per compute unit), whose neighbour sums hide on the bf16 pipe: 1,243 + 228 us
-// split against 1,205 fused at 8M nodes (1,150 fused now).
+// How the backward of a block takes dW_i.  float32, and 16-bit storage at D/C = 64: the inverse kernel (sixteen waves per
+// compute unit) leaves H in memory and k_dw takes H^T dY_i in a pass of its own: 476 -> 320 + 112 us per block on the 1M-node
+// workload when it was cut in two (246 + 88 us now) for 512 more bytes per row.  16-bit storage at D/C = 32: the fused kernel
+// (inverse + dW accumulators): 1M nodes, 152 us fused against 143 + 32 us.
 // Graphs with fewer than two tiles per resident wave, or with all rows in the first pass (a launch there is one or two
 // short tiles per wave, and two more launches per block cost more than the occupancy gains: 0.56 against 0.70 ms per
 // step on the 2,000-node workload, 487 against 496 ms on the Table-1-shaped one, 8.7 against 9.0 ms on the 100k-node
-// one - which was better split, 12.0 against 12.3 ms, while a tile's split rows still cost a memory round trip each)
-// keep the fused kernel in float32 as well; it uses the same row-wise sums, so whichever way a block's backward runs
+// one) keep the fused kernel in float32 as well; it uses the same sums, so whichever way a block's backward runs
 // it rebuilds the bits the plain inverse rebuilds.
 template <int DG, typename T>
 static bool split_dw(const gsr_graph_t* g) { return (sizeof(T) == 4 || DG == 64) && g->split_backward; }

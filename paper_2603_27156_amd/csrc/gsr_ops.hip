@@ -232,9 +232,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     walk.finish();
 }
 
-// float32 records: the sums of a tile in ordinary arithmetic into an LDS tile (gather_values_rows), rows stored from
-// there; 16-bit records: on the matrix cores, rows stored from the accumulators.  *bad: the indices have been found wanting
-// by k_pack_columns / k_pack_records, nothing is written.
+// The sums of a tile into an LDS tile (gather_values_rows), rows stored from there.  *bad: the indices have been found
+// wanting by k_pack_columns, nothing is written.
 template <int DG, typename T, bool DEAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_aggregate_tile(CsrView g, int n, int tiles, Record<DG, T> in, int k,
                                                         const float* __restrict__ hub_part, float* __restrict__ h_out,
@@ -242,15 +241,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     if (*bad) return;
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     struct Wave {
-        TileLds t;
-        alignas(16) float st[sizeof(T) == 4 ? gather_floats<DG>() : 4];
+        alignas(16) float st[gather_floats<DG>()];
+        int rp[20];
     };
-    struct None {};
     __shared__ Wave lds[4];
-    __shared__ typename std::conditional<sizeof(T) == 2, DealLut, None>::type dlut;
-    if constexpr (sizeof(T) == 2) deal_lut_fill(dlut);
     Wave& W = lds[threadIdx.x >> 6];
-    TileLds& L = W.t;
     const int lane = lane_id();
     TileWalk<DEAL> walk(g, tiles, draws, draws_done);
     while (walk.more()) {
@@ -258,31 +253,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const int r0 = walk.t * 16;
         wave_sync();
         const int rpv = tile_rp_load(g, r0, n, lane);
-        const bool has_hub = tile_begin(g, rpv, L.rp, lane);
-        if (walk.dealt(g, rpv, L.rp, has_hub)) { walk.next(g); continue; }
-        if constexpr (sizeof(T) == 4) {
-            tile_gather_rows<DG, true, 20>(g, hub_part, has_hub, r0, L.rp, W.st, lane, [&](int e_a, int e_b) {
-                gather_values_rows<DG, 8, false>(g, in.vals, in.cols, k, __builtin_amdgcn_readfirstlane(e_a),
-                                                 __builtin_amdgcn_readfirstlane(e_b), lane, W.st);
-            });
-            wave_sync();
+        const bool has_hub = tile_begin(g, rpv, W.rp, lane);
+        if (walk.dealt(g, rpv, W.rp, has_hub)) { walk.next(g); continue; }
+        tile_gather_rows<DG, true, 20>(g, hub_part, has_hub, r0, W.rp, W.st, lane, [&](int e_a, int e_b) {
+            gather_values_rows<DG, 8, false>(g, in.vals, in.cols, k, __builtin_amdgcn_readfirstlane(e_a),
+                                             __builtin_amdgcn_readfirstlane(e_b), lane, W.st);
+        });
+        wave_sync();
 #pragma unroll
-            for (int reg = 0; reg < 4; ++reg) {
-                const int rr = 4 * reg + (lane >> 4), row = r0 + rr;
-                float v[CPL];
-                lds_load<CPL>(W.st + rr * LR + CPL * (lane & 15), v);
-                if (row < n) store_cols<CPL, float>(h_out + (size_t)row * DG + CPL * (lane & 15), v);
-            }
-        } else {
-            f32x4 acc[DG / 16];
-#pragma unroll
-            for (int cb = 0; cb < DG / 16; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-            tile_ranges(g, has_hub, L.rp, [&](int e_a, int e_b) {
-                gather_records_mfma<DG, T, 8>(g, in.vals, in.mask, k, __builtin_amdgcn_readfirstlane(e_a),
-                                              __builtin_amdgcn_readfirstlane(e_b), L.rp, reinterpret_cast<RecEdge*>(L.ebuf), L.rbuf,
-                                              lane, acc, &dlut);
-            });
-            store_acc_rows<DG>(acc, g, hub_part, has_hub, r0, n, L.rp, h_out, DG, lane);
+        for (int reg = 0; reg < 4; ++reg) {
+            const int rr = 4 * reg + (lane >> 4), row = r0 + rr;
+            float v[CPL];
+            lds_load<CPL>(W.st + rr * LR + CPL * (lane & 15), v);
+            if (row < n) store_cols<CPL, float>(h_out + (size_t)row * DG + CPL * (lane & 15), v);
         }
         walk.next(g);
     }
@@ -327,37 +310,11 @@ __global__ __launch_bounds__(256) void k_gs_tile(const T* __restrict__ x, int n,
     }
 }
 
-// ---- (V, I int32, any slot order) -> record (values in ascending column order + column mask) -----
-// kp lanes per row (kp: the power of two at or above k), 64 / kp rows per wave step, so that the
-// [n][k] arrays are read and written in whole rows.  The row's mask is the OR over its lanes;
-// a column outside [0, DG) or named twice sets *bad (the caller's indices are not trusted).
-template <int DG, typename T>
-__global__ __launch_bounds__(256) void k_pack_records(int64_t n, int k, int kp, const T* __restrict__ v_in,
-                                                      const int32_t* __restrict__ i_in, T* __restrict__ v_out,
-                                                      typename MaskOf<DG>::type* __restrict__ m_out, int* __restrict__ bad) {
-    using M = typename MaskOf<DG>::type;
-    const int lane = lane_id(), t = lane % kp, sub = lane / kp, per = 64 / kp;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t r0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * per; r0 < n; r0 += nwaves * per) {
-        const int64_t row = r0 + sub;
-        const bool ok = row < n && t < k;
-        const int col = ok ? i_in[row * k + t] : 0;
-        const bool in_range = col >= 0 && col < DG;
-        const M bit = (ok && in_range) ? (M)1 << col : (M)0;
-        uint32_t lo = (uint32_t)bit, hi = DG == 64 ? (uint32_t)((uint64_t)bit >> 32) : 0u;
-        for (int off = 1; off < kp; off <<= 1) {
-            lo |= (uint32_t)__shfl_xor((int)lo, off, 64);
-            if (DG == 64) hi |= (uint32_t)__shfl_xor((int)hi, off, 64);
-        }
-        const M mask = DG == 64 ? (M)(((uint64_t)hi << 32) | lo) : (M)lo;
-        if (ok && (!in_range || popc<DG>(mask) != k)) *bad = 1;
-        if (ok && in_range) v_out[row * k + popc<DG>(mask & (bit - 1))] = v_in[row * k + t];
-        if (row < n && t == 0) m_out[row] = mask;
-    }
-}
-
-// float32: the values are gathered as the caller holds them, any slot order; only the columns are packed, to bytes (an
-// eighth of the traffic of a record of its own: 45 -> 20 us at 1M rows, k = 16).  kp lanes per row and the same checks.
+// ---- I int32, any slot order -> columns as bytes -----
+// The values are gathered as the caller holds them; only the columns are packed (a record of its own, values in ascending
+// column order and a mask, took 45 us against 31 at 1M rows, k = 16).  kp lanes per row (kp: the power of two at or above
+// k), 64 / kp rows per wave step, so that the arrays are read and written in whole rows.  The row's column set is the OR
+// over its lanes; a column outside [0, DG) or named twice sets *bad (the caller's indices are not trusted).
 template <int DG>
 __global__ __launch_bounds__(256) void k_pack_columns(int64_t n, int k, int kp, const int32_t* __restrict__ i_in, uint8_t* __restrict__ c_out,
                                                       int* __restrict__ bad) {
@@ -382,14 +339,10 @@ __global__ __launch_bounds__(256) void k_pack_columns(int64_t n, int k, int kp, 
 template <int DG, typename T>
 static gsr_status_t aggregate_impl(const gsr_graph_t* g, const void* vals, const int32_t* idx, int k, float* h_out,
                                    void* ws, int* bad, hipStream_t s) {
-    using M = typename MaskOf<DG>::type;
     const int64_t n = g->n;
     char* p = (char*)ws;
-    Record<DG, T> rec;
-    T* v_rec = (T*)p;                                       // 16-bit storage; float32: the columns
-    p += align_up((size_t)n * k * sizeof(T) + 16);          // the record gather loads up to 16 bytes past a record
-    rec.mask = (M*)p;
-    p += align_up((size_t)n * sizeof(M));
+    const Record<DG, T> rec{(T*)vals, nullptr, (uint8_t*)p};
+    p += align_up((size_t)n * k);
     float* part = (float*)p;
     // indices come from the caller: out-of-range or repeated columns are reported.  The kernels after the check are launched
     // before its answer is known (they read nothing wild whatever the indices are and write nothing where it is bad), so the
@@ -399,15 +352,7 @@ static gsr_status_t aggregate_impl(const gsr_graph_t* g, const void* vals, const
     const int64_t steps = (n + 64 / kp - 1) / (64 / kp);
     const dim3 pgrid((unsigned)std::min<int64_t>((steps + 3) / 4, 16384));
     GSR_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), s));
-    if constexpr (sizeof(T) == 4) {
-        rec.vals = (T*)vals;
-        rec.cols = (uint8_t*)v_rec;
-        hipLaunchKernelGGL((k_pack_columns<DG>), pgrid, dim3(256), 0, s, n, k, kp, idx, rec.cols, bad);
-    } else {
-        rec.vals = v_rec;
-        rec.cols = nullptr;
-        hipLaunchKernelGGL((k_pack_records<DG, T>), pgrid, dim3(256), 0, s, n, k, kp, (const T*)vals, idx, v_rec, rec.mask, bad);
-    }
+    hipLaunchKernelGGL((k_pack_columns<DG>), pgrid, dim3(256), 0, s, n, k, kp, idx, rec.cols, bad);
     CsrView v = make_view(g, false);
     if (g->a.hub.n_chunks > 0) {
         HubChunks hc{g->a.hub.ce0, g->a.hub.ce1, g->a.hub.n_chunks, g->long_rows};
