@@ -1433,8 +1433,10 @@ __device__ __forceinline__ TileSweep tile_sweep(int tiles) {
 // Dynamic form of the sweep.  Tiles differ a lot in cost (a few rows have hundreds of neighbours),
 // and with a fixed assignment the kernel ends when the unluckiest wave does.  Here the tiles of an
 // XCD's eighth are dealt to nq = TILE_NQ queues (queue q owns tiles t0 + q + nq v); a wave serves
-// queue (its slot mod nq) and draws the queue's next tile from a counter, so a wave that drew
-// long rows draws fewer tiles.  The active window still moves through the rows in order.  Many
+// queue (its slot mod nq): its first tile is the one of its place among the queue's waves, every further one it draws
+// from the queue's counter, so a wave that drew long rows draws fewer tiles.  (The first tile drawn as well, every
+// launch began with a round trip to the counters; and where no XCD has more tiles than waves nothing is drawn at all
+// and no wave signs off.)  The active window still moves through the rows in order.  Many
 // queues rather than one keep the atomics on different addresses: one counter for the 512 waves
 // of an XCD serialises and costs more than the balance gains.  The next draw is requested at
 // the start of a tile and read at its end.  A launch leaves the counters as it found them (all
@@ -1451,6 +1453,9 @@ struct TileDraws {
     int end;       // one past the XCD's last tile
     int* set;      // the whole counter set
     int* done;     // waves that have signed off
+    int first;     // this wave's first tile
+    int waves;     // waves of the queue: draw v is the queue's tile waves + v
+    bool draws;    // some XCD has more tiles than waves (the same in the whole grid)
 };
 __device__ __forceinline__ TileDraws tile_draws(int tiles, int* set, int* done) {
     const int xcd = blockIdx.x & 7;
@@ -1464,21 +1469,25 @@ __device__ __forceinline__ TileDraws tile_draws(int tiles, int* set, int* done) 
     d.end = (int)((int64_t)tiles * (xcd + 1) / 8);
     d.set = set;
     d.done = done;
+    d.first = d.base + d.nq * (slot / d.nq);
+    d.waves = (waves - q + d.nq - 1) / d.nq;
+    d.draws = (tiles + 7) / 8 > waves;
     return d;
 }
 // requests a draw; the value is valid in lane 0 once the wave waits for it (tile_drawn)
 __device__ __forceinline__ int tile_request(const TileDraws& d) {
     int v = 0;
-    if (lane_id() == 0) v = atomicAdd(d.ctr, 1);
+    if (d.draws && lane_id() == 0) v = atomicAdd(d.ctr, 1);
     return v;
 }
 __device__ __forceinline__ int tile_drawn(const TileDraws& d, int requested) {
-    return d.base + d.nq * __builtin_amdgcn_readfirstlane(requested);
+    return d.draws ? d.base + d.nq * (d.waves + __builtin_amdgcn_readfirstlane(requested)) : d.end;
 }
 // Every wave of the grid calls this once, after its last tile_drawn (all its draws have returned).
 // Sign-off in two levels, an XCD's waves on the XCD's counter and the last wave of each XCD on a
 // common one, keeps the atomics on one address few.  d.done: 9 counters, 128 bytes apart.
 __device__ __forceinline__ void tile_finish(const TileDraws& d) {
+    if (!d.draws) return;
     int last = 0;
     if (lane_id() == 0) {
         // no fence: this wave's own draws have returned, and nothing but the counters is handed over
@@ -1550,12 +1559,12 @@ struct TileWalk {
         td = tile_draws(tiles, set, done);
         deal = TileDeal{0, 0, 0, false};
         if constexpr (DEAL) deal = tile_deal(g);
-        requested = tile_request(td);
+        requested = 0;
         if (DEAL && deal.on) { t = g.heavy[deal.at]; t_end = tiles; }
-        else { t = tile_drawn(td, requested); t_end = td.end; }
+        else { t = td.first; t_end = td.end; }
     }
     __device__ __forceinline__ bool more() const { return t < t_end; }
-    // at the top of a tile: ask for the next draw (while dealing, the one asked for at the start is still out)
+    // at the top of a tile: ask for the next draw (not while dealing: the sweep begins with the wave's first tile)
     __device__ __forceinline__ void ahead() { if (!DEAL || !deal.on) requested = tile_request(td); }
     // in the sweep, a heavy tile has been dealt out already
     __device__ __forceinline__ bool dealt(const CsrView& g, int rpv, const int* s_rp, bool has_hub) const {
@@ -1566,7 +1575,9 @@ struct TileWalk {
         if (DEAL && deal.on) {
             tile_deal_next(deal);
             if (deal.on) { t = g.heavy[deal.at]; return; }
+            t = td.first;
             t_end = td.end;
+            return;
         }
         t = tile_drawn(td, requested);
     }

@@ -92,9 +92,8 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
     int t = ts.first, t_end = ts.end;
     if constexpr (!WITH_DW) {
         td = tile_draws(a.tiles, a.draws, a.draws_done);
-        requested = tile_request(td);
         t_end = td.end;
-        if (!deal.on) t = tile_drawn(td, requested);
+        t = td.first;
     }
     if constexpr (DEAL) {
         if (deal.on) { t = a.g.heavy[deal.at]; t_end = a.tiles; }
@@ -111,7 +110,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
             } else if constexpr (WITH_DW) {
                 t_next = ts.first; t_end_next = ts.end;
             } else {
-                t_next = tile_drawn(td, requested); t_end_next = td.end;
+                t_next = td.first; t_end_next = td.end;
             }
         } else {
             if constexpr (WITH_DW) t_next = t + ts.step;
@@ -521,11 +520,9 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
     TileDraws td = tile_draws(a.tiles, a.draws, a.draws_done);
     TileDeal deal{0, 0, 0, false};
     if constexpr (DEAL) deal = tile_deal(a.gt);
-    int requested = tile_request(td);      // the draw that is outstanding
-    int t_end = td.end;
-    int t = 0;
+    int requested = 0;                     // the draw that is outstanding
+    int t_end = td.end, t = td.first;
     if (DEAL && deal.on) { t = a.gt.heavy[deal.at]; t_end = a.tiles; }
-    else t = tile_drawn(td, requested);
     while (t < t_end) {
         if (!DEAL || !deal.on) requested = tile_request(td);
         const int r0 = t * 16;
@@ -643,7 +640,7 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         if (DEAL && deal.on) {
             tile_deal_next(deal);
             if (deal.on) t = a.gt.heavy[deal.at];
-            else { t = tile_drawn(td, requested); t_end = td.end; }
+            else { t = td.first; t_end = td.end; }
         } else {
             t = tile_drawn(td, requested);
         }
