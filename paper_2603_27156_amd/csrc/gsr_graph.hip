@@ -550,8 +550,13 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     // With fewer than two tiles per resident wave the cut at 16 is better still (the same workload: 9.4 ms against 10.6;
     // 12 / 8: 9.6 / 9.8; chunks of 32 instead of 64: 9.7).
     const bool few_tiles = (n + 15) / 16 < (int64_t)16 * full_grid, very_few_tiles = (n + 15) / 16 < (int64_t)8 * full_grid;
+    // With at most a tile per resident wave and no row above 160 entries nothing is split: two launches per block (one in
+    // the forward sweep) cost more than the longest tile's extra rounds.  Steps of four layers, cut at 16 / not cut: 2,000
+    // nodes (rows up to 74) 401 / 285 us, 10,000 nodes 890 / 616, 20,000 (up to 131) 627 / 559; 40,000 (up to 257)
+    // 784 / 947, 60,000 (up to 371) 1,390 / 1,755.
+    const bool short_rows = (n + 15) / 16 <= (int64_t)4 * full_grid && g->max_degree <= 160;
     const int64_t hub_threshold = options().hub_threshold > 0 ? options().hub_threshold
-                                  : long_rows ? 1 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
+                                  : long_rows ? 1 : short_rows ? 160 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
     const int64_t hub_chunk = options().hub_chunk > 0 ? options().hub_chunk : (long_rows ? 512 : 64);      // (Table-1-shaped graph, rows of up to 390 entries: 289 / 274 / 263 / 263 ms per step with chunks of 128 / 256 / 512 / 1,024)
     g->hub_threshold = (int32_t)hub_threshold;
     g->hub_chunk = (int32_t)hub_chunk;
