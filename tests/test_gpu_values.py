@@ -1,0 +1,160 @@
+"""The gathers that give a lane to every kept value (records with the column of each value), at the sizes where their
+rounds, runs and passes can go wrong; the first pass that writes a row of one chunk straight to where it belongs; rows cut
+into longer partials on small graphs; tiles assigned without draws."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2603_27156_amd as gsr
+from paper_2603_27156_amd import synth
+from gpu_util import Case, assert_close
+from test_gpu_layer import run_step, ROW, PLANAR
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# lengths around the sixteen steps of a run, the 64 edges of a round and two rounds, several of them inside one 16-row tile
+LENGTHS = [0, 1, 2, 15, 16, 17, 3, 63, 64, 65, 1, 0, 127, 128, 129, 5, 31, 33, 48, 49, 4, 4, 4, 4, 200, 1, 7, 8, 9, 12, 13, 0, 61, 3, 62, 2, 66]
+
+
+@pytest.fixture
+def options():
+    changed = []
+
+    def set_option(key, value):
+        changed.append(key)
+        gsr.gsr_set_option(key, value)
+    yield set_option
+    for key in changed:
+        gsr.gsr_set_option(key, 0)
+
+
+def graph_of(lengths, n, seed):
+    """n rows of the given lengths (then of one entry), random distinct columns and values."""
+    rng = np.random.default_rng(seed)
+    lengths = list(lengths) + [1] * (n - len(lengths))
+    cols = np.concatenate([np.sort(rng.choice(n, size=l, replace=False)) for l in lengths] or [np.zeros(0)]).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    vals = rng.standard_normal(len(cols)).astype(np.float32)
+    return rowptr, cols, vals, gsr.gsr_graph_create(rowptr, cols, vals, flags=0)
+
+
+def sums_and_bound(rowptr, cols, vals, x):
+    """A x in float64 and the error a float32 sum of that many products may have: (terms + 3) roundings of 2^-24."""
+    import scipy.sparse as sp
+    a = sp.csr_matrix((vals.astype(np.float64), cols, rowptr), shape=(len(rowptr) - 1,) * 2)
+    terms = np.diff(rowptr)[:, None] + 3
+    return a @ x, terms * 2.0 ** -24 * (abs(a) @ abs(x)) + 1e-30
+
+
+@pytest.mark.parametrize("dg,k,dtype,threshold,chunk", [
+    (64, 16, "f32", 512, 0), (64, 1, "f32", 512, 0), (64, 15, "f32", 512, 0), (64, 17, "f32", 512, 0), (64, 64, "f32", 512, 0),
+    (32, 8, "f32", 512, 0), (32, 32, "f32", 512, 0), (64, 16, "bf16", 512, 0), (64, 33, "bf16", 512, 0), (32, 5, "bf16", 512, 0),
+    (64, 16, "f32", 16, 16), (64, 40, "f32", 3, 64), (32, 20, "bf16", 8, 32),
+])
+def test_value_gather_at_the_edges_of_runs_and_rounds(options, dg, k, dtype, threshold, chunk):
+    options("hub_threshold", threshold)
+    options("hub_chunk", chunk)
+    n = 421
+    rowptr, cols, vals, g = graph_of(LENGTHS, n, 3)
+    rng = np.random.default_rng(5)
+    idx = np.stack([rng.permutation(dg)[:k] for _ in range(n)]).astype(np.int32)       # any slot order
+    v = torch.from_numpy(rng.standard_normal((n, k)).astype(np.float32)).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    h = gsr.gsr_spmm_compressed(g, v, torch.from_numpy(idx).cuda(), dg).cpu().numpy()
+    dense = np.zeros((n, dg))
+    np.put_along_axis(dense, idx.astype(np.int64), v.float().cpu().numpy().astype(np.float64), 1)
+    ref, bound = sums_and_bound(rowptr, cols, vals, dense)
+    assert (np.abs(h - ref) <= bound).all(), float((np.abs(h - ref) / bound).max())
+
+
+@pytest.mark.parametrize("wrong", ["negative", "past", "repeated"])
+def test_refused_indices_write_nothing_and_leave_the_graph_usable(wrong):
+    n, k, dg = 421, 16, 64
+    rowptr, cols, vals, g = graph_of(LENGTHS, n, 4)
+    idx = torch.arange(k, dtype=torch.int32).repeat(n, 1)
+    good = idx.clone().cuda()
+    idx[300, 3] = {"negative": -1, "past": dg, "repeated": 5}[wrong]
+    idx = idx.cuda()
+    v = torch.randn(n, k, device="cuda")
+    h = torch.full((n, dg), 7.0, device="cuda")
+    lib = gsr.lib()
+    nbytes = lib.gsr_spmm_compressed_workspace(g.ptr, ctypes.c_int32(k), ctypes.c_int32(dg))
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+
+    def call(i):
+        return lib.gsr_spmm_compressed(g.ptr, ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(i.data_ptr()), ctypes.c_int32(k),
+                                       ctypes.c_int32(dg), ctypes.c_int32(0), ctypes.c_void_p(h.data_ptr()),
+                                       ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(nbytes), gsr._stream())
+    assert call(idx) == gsr.GSR_ERR_INVALID_ARG
+    assert bool((h == 7.0).all())
+    assert call(good) == gsr.GSR_OK
+    dense = np.zeros((n, dg))
+    dense[:, :k] = v.cpu().numpy()
+    ref, bound = sums_and_bound(rowptr, cols, vals, dense)
+    assert (np.abs(h.cpu().numpy() - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("n,d,c,k,threshold,chunk,layout", [
+    (1003, 256, 2, 40, 8, 16, ROW),          # rows of one chunk, of several, and gathered ones in the same eight rows
+    (777, 384, 2, 16, 1, 512, PLANAR),       # every row of two entries or more is one chunk
+    (500, 512, 2, 70, 4, 4, ROW),            # nothing fits one chunk; five passes over the kept values
+    (9, 384, 3, 3, 2, 8, PLANAR),            # a half and a bit of a 16-row tile
+])
+def test_wide_rows_of_one_chunk_and_of_several(options, n, d, c, k, threshold, chunk, layout):
+    options("hub_threshold", threshold)
+    options("hub_chunk", chunk)
+    cs = Case(synth.scaled(synth.workload(2), n, l=1, d=d, c=c, k=k), 0, layout)
+    W = cs.inp.weights[0]
+    Wd = torch.from_numpy(W).to(cs.dev)
+    X = cs.x0_on_grid()
+    Y_ref = oracle.layer_forward(cs.og, cs.ocfg, W, X)
+    y = cs.to_dev(X)
+    gsr.gsr_layer_forward(cs.gg, cs.gcfg, Wd, y)
+    assert_close("Y", cs.to_host(y), Y_ref)
+    dY = (np.random.default_rng(17).standard_normal((n, d)) * 1e-3).astype(np.float32).astype(np.float64)
+    Xb_ref, dX_ref, dW_ref = oracle.layer_backward(cs.og, cs.ocfg, W, Y_ref, dY)
+    yb, dyb = cs.to_dev(Y_ref), cs.to_dev(dY)
+    dW = torch.empty((c, d // c, d // c), dtype=torch.float32, device=cs.dev)
+    gsr.gsr_layer_backward(cs.gg, cs.gcfg, Wd, yb, dyb, dW)
+    assert_close("X rebuilt", cs.to_host(yb), Xb_ref)
+    assert_close("dX", cs.to_host(dyb), dX_ref)
+    assert_close("dW", dW.cpu().numpy(), dW_ref)
+
+
+@pytest.mark.parametrize("longest", [160, 161])
+def test_short_rows_are_not_split_on_a_small_graph(longest):
+    rowptr, cols, vals, g = graph_of([longest] + LENGTHS[:24], 500, 8)
+    assert gsr.gsr_graph_info(g)["n_hub_rows"] == (0 if longest <= 160 else sum(l > 16 for l in [longest] + LENGTHS[:24]))
+    x = torch.randn(500, 64, device="cuda")
+    y = gsr.gsr_spmm(g, x).cpu().numpy()
+    ref, bound = sums_and_bound(rowptr, cols, vals, x.cpu().numpy().astype(np.float64))
+    assert (np.abs(y - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("sinks,width", [(1_024, 64), (1_025, 64), (5_000, 64), (5_000, 16), (2_500, 32)])
+def test_nets_of_thousands_of_sinks_on_a_small_graph(sinks, width):
+    n = 6_001
+    lengths = [sinks] * 8 + [3] * 100            # eight nets side by side in one tile
+    rowptr, cols, vals, g = graph_of(lengths, n, 6)
+    x = torch.randn(n, width, device="cuda")
+    y = gsr.gsr_spmm(g, x).cpu().numpy()
+    ref, bound = sums_and_bound(rowptr, cols, vals, x.cpu().numpy().astype(np.float64))
+    assert (np.abs(y - ref) <= bound).all(), float((np.abs(y - ref) / bound).max())
+
+
+@pytest.mark.parametrize("c,dg,k,dtype,save", [(2, 64, 16, "f32", 2), (4, 32, 8, "f32", 1), (3, 64, 9, "f32", 0), (3, 64, 16, "bf16", 1),
+                                               (4, 32, 8, "bf16", 1)])
+def test_drawn_and_given_tiles_give_the_same_bits(options, c, dg, k, dtype, save):
+    """With a grid of eight workgroups the same graph has many tiles per wave (tiles are drawn, a block's backward is cut in
+    two kernels); with the default one every tile has a wave of its own."""
+    options("hub_threshold", 64)       # (the defaults depend on the grid)
+    options("hub_chunk", 64)
+    w = synth.scaled(synth.workload(2), 3001, l=3, d=c * dg, c=c, k=k, dtype=dtype)
+    one = run_step(Case(w, 0, PLANAR), raw=True, save_indices=save)
+    options("max_workgroups", 8)
+    two = run_step(Case(w, 0, PLANAR), raw=True, save_indices=save)
+    for key in ("yhat", "XL", "X0rec", "dX0"):
+        assert torch.equal(one[key], two[key]), key
+    assert_close("dW", two["dW"].float().cpu().numpy(), one["dW"].double().cpu().numpy())
