@@ -1768,7 +1768,10 @@ __global__ __launch_bounds__(256) void k_hub_records_wide(CsrView g, HubChunks h
 // keep rows of their own, so two such chains are in flight.  At the end of a chunk the rows of the places are added in
 // place order and cleared.  Scattering into zeroed rows, reading them back sixteen bytes wide into running sums and
 // clearing them again was 3 % slower; LDS float atomics were four times slower (one such instruction takes some 140
-// cycles).  The order of the additions is fixed by the edge list and the lane layout.
+// cycles).  The loads of a whole round of 64 edges are in flight together where k <= 16, and the next round's edges before
+// them (50k nodes of mean degree 236, 192 columns: k = 16 170 -> 162 us per launch, k = 51 226 -> 210); what is left is the
+// LDS pipe, where the sums of unrelated columns collide on banks.  The order of the additions is fixed by the edge list and
+// the lane layout.
 template <int DG, int LG>
 struct HubValLds {
     uint2 ebuf[64];                   // (j * k, a_ij) of the staged edges
@@ -1782,7 +1785,7 @@ __device__ __forceinline__ void hub_values_pass(const CsrView& g, const HubChunk
                                                 float* __restrict__ rows, HubValLds<DG, LG>& L, const HubSweep w) {
     constexpr int LPE = 1 << LG, NE = 64 >> LG;          // lanes per edge, edges per instruction
     constexpr int MAXS = 64 / NE;                        // instructions per round of 64 staged edges
-    constexpr int GB = KQ == 1 ? (MAXS < 8 ? MAXS : 8) : KQ == 2 ? 4 : 2;
+    constexpr int GB = KQ == 1 ? MAXS : MAXS / KQ;       // instructions whose loads are in flight together
     constexpr int TOT = NE * DG;
     static_assert(MAXS % GB == 0 && GB % 2 == 0, "a round is a whole number of batches, a batch of pairs");
     const int lane = lane_id();
@@ -1792,41 +1795,51 @@ __device__ __forceinline__ void hub_values_pass(const CsrView& g, const HubChunk
     for (int i = lane; i < 2 * TOT; i += 64) base[i] = 0.f;
     for (int q = w.q; q < w.end; q += w.step) {
         const int e0 = __builtin_amdgcn_readfirstlane(h.ce0[q]), e1 = __builtin_amdgcn_readfirstlane(h.ce1[q]);
+        // places past the last edge: the last edge once more with a_ij = 0
+        // (with sixteen lanes per edge a place is a row of sixteen lanes, and an instruction could take its edge
+        // from a lane of the row by a DPP row broadcast instead of from LDS: measured 2.5 % slower)
+        uint32_t j_next = 0;
+        float a_next = 0.f;
+        auto request = [&](int eb) {
+            const int e = eb + lane, ec = e < e1 ? e : e1 - 1;
+            j_next = (uint32_t)__builtin_nontemporal_load(g.ci + ec);
+            const float av = __builtin_nontemporal_load(g.av + ec);
+            a_next = e < e1 ? av : 0.f;
+        };
+        request(e0);
         for (int eb = e0; eb < e1; eb += 64) {
-            // places past the last edge: the last edge once more with a_ij = 0
-            // (with sixteen lanes per edge a place is a row of sixteen lanes, and an instruction could take its edge
-            // from a lane of the row by a DPP row broadcast instead of from LDS: measured 2.5 % slower)
-            const int e = eb + lane;
-            const bool ok = e < e1;
-            const int ec = ok ? e : e1 - 1;
-            const int j = __builtin_nontemporal_load(g.ci + ec);
-            const float a = ok ? __builtin_nontemporal_load(g.av + ec) : 0.f;
             wave_sync();          // readers of the previous round are done
-            L.ebuf[lane] = make_uint2((uint32_t)j * (uint32_t)k, __float_as_uint(a));
+            L.ebuf[lane] = make_uint2(j_next * (uint32_t)k, __float_as_uint(a_next));
             wave_sync();
             const int cnt = e1 - eb < 64 ? e1 - eb : 64;
-            const int steps = ((cnt + NE - 1) / NE + GB - 1) / GB * GB;
-            for (int s0 = 0; s0 < steps; s0 += GB) {
-                float v[GB][KQ];
-                uint32_t c[GB][KQ];
+            const int need = (cnt + NE - 1) / NE;
+            if (eb + 64 < e1) request(eb + 64);        // the next round's edges arrive while this one is added
+            // NB instructions from s0 on: all loads first
+            auto batch = [&](auto nbc, int s0) {
+                constexpr int NB = decltype(nbc)::value;
+                asm volatile("; %0 steps" ::"n"(NB));        // (keeps the variants apart, see gather_values_rows)
+                float v[NB][KQ], a[NB];
+                uint32_t c[NB][KQ];
 #pragma unroll
-                for (int u = 0; u < GB; ++u) {
+                for (int u = 0; u < NB; ++u) {
                     const uint2 er = L.ebuf[(s0 + u) * NE + place];
+                    a[u] = __uint_as_float(er.y);
 #pragma unroll
                     for (int w = 0; w < KQ; ++w) {
                         // (a lane past the record's last slot takes slot 0 again: with one value per lane it writes
                         // what slot 0's lane writes)
                         const int tt = t + w * LPE;
                         const uint32_t at = er.x + (uint32_t)(tt < k ? tt : 0);
-                        v[u][w] = vals[at] * __uint_as_float(er.y);
+                        v[u][w] = vals[at];
                         c[u][w] = cols[at];
                     }
                 }
                 // sum += value, read and written back: the lanes of an instruction hold different places or different
                 // columns of one record, so no two of them meet; even and odd instructions keep rows of their own so
                 // that two read - add - write chains are in flight
+                wave_sync();
 #pragma unroll
-                for (int u = 0; u < GB; u += 2) {
+                for (int u = 0; u < NB; u += 2) {
 #pragma unroll
                     for (int w = 0; w < KQ; ++w) {
                         const bool has = KQ == 1 || t + w * LPE < k;      // (else slot 0 once more: not added again)
@@ -1835,11 +1848,19 @@ __device__ __forceinline__ void hub_values_pass(const CsrView& g, const HubChunk
                         const float o0 = base[i0];
                         const float o1 = base[i1];
                         wave_sync();
-                        base[i0] = o0 + (has ? v[u][w] : 0.f);
-                        base[i1] = o1 + (has ? v[u + 1][w] : 0.f);
+                        base[i0] = o0 + (has ? v[u][w] * a[u] : 0.f);
+                        base[i1] = o1 + (has ? v[u + 1][w] * a[u + 1] : 0.f);
                         wave_sync();
                     }
                 }
+            };
+            if constexpr (GB >= 8) {
+                for (int s0 = 0; s0 < need; s0 += GB) {
+                    if (need - s0 > GB / 2) batch(std::integral_constant<int, GB>{}, s0);
+                    else batch(std::integral_constant<int, GB / 2>{}, s0);
+                }
+            } else {
+                for (int s0 = 0; s0 < need; s0 += GB) batch(std::integral_constant<int, GB>{}, s0);
             }
         }
         // the sums of the places are added in place order, even rows before odd rows, and the rows cleared
