@@ -75,9 +75,8 @@ typedef struct gsr_graph gsr_graph_t; /* opaque */
  *   N < 2^31 nodes; fewer than 2^31 stored entries after symmetrisation and self-loops (device row pointers are
  *   32-bit; the input row pointers may be 64-bit);  N * k < 2^32 (32-bit offsets into the compressed values);
  *   2 <= C <= 8;  D/C in {32, 64, 128, 192, 256};  gsr_step: D <= 512 (the scalar head).
- *   D/C above 64 (the paper's own models: hidden 256 or 384 in two groups, Section 5) runs as D/C / 64 column blocks of
- *   64 through the same kernels, (D/C / 64)^2 launches per block, with GS over the whole row; it takes
- *   save_indices 0 or 1. */
+ *   D/C above 64 (the paper's own models: hidden 256 or 384 in two groups, Section 5) runs as separate passes
+ *   (aggregation, weight product, GS over the whole row) over planes of 64 columns; it takes save_indices 0 or 1. */
 typedef struct gsr_config {
     int64_t n;      /* nodes N */
     int32_t d;      /* feature width D */
@@ -121,13 +120,12 @@ const char* gsr_version(void);
  *                     four / two 16-row tiles per resident wave; 160 on graphs with at most one and no row above 160
  *                     entries (nothing is cut); 1 on graphs whose mean row has 64 stored entries or
  *                     more (every row of two entries or more then goes through the first pass)
- *   "hub_chunk"       neighbours per first-pass partial sum; 0, the default: 64, or 512 on graphs of long rows
- *   "hub_values"      how the first pass sums float32 records (layer and step calls): 1 = a lane per record value,
- *                     through a byte per value naming its column that a small kernel writes from the masks first;
- *                     2 = a lane per group of columns, as the tile kernels do; 0, the default: 1 on graphs whose mean
- *                     row has 64 stored entries or more, while 2 k <= D/C (groups of 128 or 192 columns: one such
- *                     pass for all their column blocks; of 256: a pass per block of 64 while 2 k <= 64).  Read when
- *                     a graph is created
+ *   "hub_chunk"       neighbours per first-pass partial sum; 0, the default: 64 (more for rows above 1,024 entries on
+ *                     graphs with fewer than four 16-row tiles per resident wave), or 512 on graphs of long rows
+ *   "hub_values"      how the first pass sums float32 records (layer and step calls): 1 = as many lanes per edge
+ *                     as a record has values (up to 16), two chains of sums each; 2 = as the tile kernels do, four
+ *                     edges at a time; 0, the default: 1 on graphs whose mean row has 64 stored entries or more, while
+ *                     2 k <= D/C (and k <= 64, D/C < 256 where D/C is above 64).  Read when a graph is created
  *   "max_workgroups"  workgroups of the persistent kernels, multiple of 8 (0: as many as stay resident, at most 4 per CU)
  *   "profile"         bit mask of kernel classes to time (see gsr_profile_read); read at once */
 gsr_status_t gsr_set_option(const char* key, int64_t value);

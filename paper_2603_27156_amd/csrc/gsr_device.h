@@ -58,9 +58,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// (a & m) | (b & ~m)
-__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
-
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 // bits of a wave-wide ballot that belong to this lane's row
@@ -469,9 +466,10 @@ struct EdgeRec {
 
 // Row pointer of row r0 + lane (clamped at n) for the 17 row boundaries of a tile, in lanes 0..16.
 // Split from tile_begin so that a kernel can request its other per-tile data before it waits.
-__device__ __forceinline__ int tile_rp_load(const CsrView& g, int r0, int n, int lane) {
+__device__ __forceinline__ int tile_rp_load(const CsrView& g, uint32_t r0, int n, int lane) {
     int rpv = 0;
-    if (lane < 17) rpv = g.rp[r0 + lane < n ? r0 + lane : n];
+    const uint32_t r = r0 + (uint32_t)lane;   // unsigned: a tile past the last may lie beyond 2^31
+    if (lane < 17) rpv = g.rp[r < (uint32_t)n ? r : (uint32_t)n];
     return rpv;
 }
 

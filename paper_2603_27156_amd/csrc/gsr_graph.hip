@@ -136,11 +136,9 @@ static void free_csr(Csr& c) {
     if (c.rp) (void)hipFree(c.rp);
     if (c.ci) (void)hipFree(c.ci);
     if (c.av) (void)hipFree(c.av);
-    if (c.er) (void)hipFree(c.er);
     if (c.hub.rows) (void)hipFree(c.hub.rows);
     if (c.hub.cptr) (void)hipFree(c.hub.cptr);
     if (c.hub.tile0) (void)hipFree(c.hub.tile0);
-    if (c.hub.crow) (void)hipFree(c.hub.crow);
     if (c.hub.ce0) (void)hipFree(c.hub.ce0);
     if (c.hub.ce1) (void)hipFree(c.hub.ce1);
     if (c.hub.single) (void)hipFree(c.hub.single);
@@ -186,9 +184,11 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
     GSR_TRY(upload(heavy, &out->heavy));
     GSR_TRY(upload(h.rp, &out->rp));
     GSR_TRY(upload(h.ci, &out->ci));
-    GSR_TRY(upload(h.av, &out->av));
-    GSR_HIP_CHECK(hipMalloc((void**)&out->er, std::max<size_t>(h.ci.size(), 1)));
-    if (n > 0 && !h.ci.empty()) {
+    const size_t nnz = h.ci.size();
+    GSR_HIP_CHECK(hipMalloc((void**)&out->av, std::max<size_t>(nnz, 1) * (sizeof(float) + 1)));
+    out->er = (uint8_t*)(out->av + std::max<size_t>(nnz, 1));
+    if (nnz > 0) {
+        GSR_HIP_CHECK(hipMemcpy(out->av, h.av.data(), nnz * sizeof(float), hipMemcpyHostToDevice));
         hipLaunchKernelGGL(k_entry_rows, dim3((unsigned)std::min<int64_t>((n + 3) / 4, 4096)), dim3(256), 0, s, (int)n, out->rp, out->er);
         GSR_HIP_CHECK(hipGetLastError());
     }
@@ -214,7 +214,6 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
     GSR_TRY(upload(tile0, &out->hub.tile0));
     GSR_TRY(upload(rows, &out->hub.rows));
     GSR_TRY(upload(cptr, &out->hub.cptr));
-    GSR_TRY(upload(crow, &out->hub.crow));
     GSR_TRY(upload(ce0, &out->hub.ce0));
     GSR_TRY(upload(ce1, &out->hub.ce1));
     GSR_TRY(upload(single, &out->hub.single));

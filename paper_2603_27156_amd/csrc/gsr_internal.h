@@ -73,7 +73,6 @@ struct HubPlan {
     int32_t* rows = nullptr;  // device [n_hub]    ascending row ids
     int32_t* cptr = nullptr;  // device [n_hub+1]  first chunk of each hub row
     int32_t* tile0 = nullptr; // device [tiles+1]  hub rows before row 16 t (the place in `rows` of tile t's first hub row)
-    int32_t* crow = nullptr;  // device [n_chunks] row of the chunk
     int32_t* ce0 = nullptr;   // device [n_chunks] first edge
     int32_t* ce1 = nullptr;   // device [n_chunks] one past the last edge
     int32_t* single = nullptr; // device [n_chunks] the row if the chunk is all of it, else -1
@@ -89,7 +88,7 @@ struct Csr {
     int32_t* rp = nullptr;  // device [n+1]
     int32_t* ci = nullptr;  // device [nnz]
     float* av = nullptr;    // device [nnz]
-    uint8_t* er = nullptr;  // device [nnz]  row of the entry modulo 16
+    uint8_t* er = nullptr;  // device [nnz]  row of the entry modulo 16 (behind av, in its allocation)
     HubPlan hub;
     int32_t* heavy = nullptr;  // device [n_heavy]: the heavy tiles, ascending
     int32_t n_heavy = 0;
@@ -106,9 +105,7 @@ struct gsr_graph {
     bool has_transpose = false;
     bool split_backward = true;   // float32: the backward of a block as inverse kernel + k_dw (large graphs), else fused
     bool long_rows = false;  // the mean row has 64 stored entries or more: nearly every row goes through the first pass
-    int hub_values = 0;      // the first pass over float32 records runs value by value (k_hub_values): 0 never, 1 while
-                             // 2 k <= D/C (beyond that the dealing of the tile kernels is faster: 650 against 490 ms per step
-                             // at k = D/C = 64 on the Table-1-shaped graph, 464 against 473 at k = 32), 2 always
+    int hub_values = 0;      // the first pass over float32 records runs as k_hub_values: 0 never, 1 while 2 k <= D/C, 2 always
     int32_t hub_threshold = 512;
     int32_t hub_chunk = 64;
     int device = 0;

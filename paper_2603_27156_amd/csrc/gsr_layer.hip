@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
             else t_next = tile_drawn(td, requested);
         }
     };
-    int rpv = tile_rp_load(a.g, t * 16, a.n, lane);
+    int rpv = tile_rp_load(a.g, (uint32_t)t * 16u, a.n, lane);
 
     while (t < t_end) {
         if constexpr (!WITH_DW) {
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
             if (!deal.on && tile_is_heavy(a.g, rpv, L.rp, has_hub)) {      // dealt out before the sweep
                 advance();
                 t = t_next;
-                rpv = tile_rp_load(a.g, t * 16, a.n, lane);
+                rpv = tile_rp_load(a.g, (uint32_t)t * 16u, a.n, lane);
                 continue;
             }
         }
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
                                            __builtin_amdgcn_readfirstlane(e_b), lane, st_h);
         });
         advance();
-        rpv = tile_rp_load(a.g, t_next * 16, a.n, lane);
+        rpv = tile_rp_load(a.g, (uint32_t)t_next * 16u, a.n, lane);
         if constexpr (OWN_LATE) own_rows();
         if constexpr (WITH_DW) {
 #pragma unroll
