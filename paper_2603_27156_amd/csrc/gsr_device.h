@@ -530,7 +530,8 @@ __device__ __forceinline__ void gather_dense_mfma(const CsrView& g, const T* __r
         const int e = eb + lane;
         const bool ok = e < e_b;
         EdgeRec me;
-        me.j = ok ? __builtin_nontemporal_load(g.ci + e) : 0;
+        if constexpr (ONE_ROW) me.j = __builtin_nontemporal_load(g.ci + (ok ? e : e_b - 1));   // a place past the end: 0 times a row of its own
+        else me.j = ok ? __builtin_nontemporal_load(g.ci + e) : 0;
         me.a = ok ? __builtin_nontemporal_load(g.av + e) : 0.f;
         me.r = tile_row_of(s_rp, e);
         me.pad = 0;
@@ -1745,8 +1746,11 @@ __global__ __launch_bounds__(256) void k_hub_both(CsrView ga, HubChunks ha, Reco
     union Lds { HubLds dense; HubRowsLds<DG> rows; };
     __shared__ Lds lds[4];
     Lds& L = lds[threadIdx.x >> 6];
-    if (blockIdx.y == 0) hub_value_rows_pass<DG, T>(ga, ha, in.vals, in.cols, k, 0, part_a, nullptr, L.rows, hub_sweep(ha));
-    else hub_dense_pass<DG, T>(gt, ht, x, ld, part_t, L.dense, hub_sweep(ht));
+    const bool rec = blockIdx.y == 0;
+    if (rec && k < DG) hub_value_rows_pass<DG, T>(ga, ha, in.vals, in.cols, k, 0, part_a, nullptr, L.rows, hub_sweep(ha));
+    else                                              // (k = D/C: a record is its row)
+        hub_dense_pass<DG, T>(rec ? ga : gt, rec ? ha : ht, rec ? in.vals : x, rec ? DG : ld, rec ? part_a : part_t, L.dense,
+                              hub_sweep(rec ? ha : ht));
 }
 
 // The records of a group of S column blocks

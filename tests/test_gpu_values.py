@@ -158,3 +158,18 @@ def test_drawn_and_given_tiles_give_the_same_bits(options, c, dg, k, dtype, save
     for key in ("yhat", "XL", "X0rec", "dX0"):
         assert torch.equal(one[key], two[key]), key
     assert_close("dW", two["dW"].float().cpu().numpy(), one["dW"].double().cpu().numpy())
+
+
+@pytest.mark.parametrize("dg,c,chunk", [(64, 2, 4), (64, 3, 100), (32, 4, 4), (32, 2, 100)])
+def test_first_pass_where_every_column_is_kept(options, dg, c, chunk):
+    """k = D/C: the first pass takes the records as the rows they are (rows cut at 6 entries, chunks shorter and longer than a
+    round of 64 edges)."""
+    options("hub_threshold", 6)
+    options("hub_chunk", chunk)
+    cs = Case(synth.scaled(synth.workload(2), 700, levels=6, d=dg * c, c=c, k=dg, l=2, hubs=2), 11, PLANAR)
+    assert gsr.gsr_graph_info(cs.gg)["n_hub_rows"] > 0
+    ref = oracle.step(cs.og, cs.ocfg, cs.w.l, cs.x0_on_grid(), cs.inp.weights, cs.inp.w_out, cs.inp.b_out, cs.inp.target)
+    out = run_step(cs)
+    assert np.isclose(out["loss"], ref["loss"], rtol=1e-4)
+    for key in ("yhat", "XL", "X0rec", "dW", "dwout", "dX0"):
+        assert_close(key, out[key], ref[key])
