@@ -153,8 +153,14 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         }
         // (in the forward and in both inverse kernels alike, so that f_i is recomputed by the instructions that computed it)
         tile_gather_rows<DG, true, 20>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
-            gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, __builtin_amdgcn_readfirstlane(e_a),
-                                           __builtin_amdgcn_readfirstlane(e_b), lane, st_h);
+            const int ea = __builtin_amdgcn_readfirstlane(e_a), eb = __builtin_amdgcn_readfirstlane(e_b);
+            if constexpr (sizeof(T) == 4) {
+                if (a.k == DG) {      // every column kept, in order: dense rows (1M nodes, k = 64: 277 against 487 us)
+                    gather_dense_rows<DG, 8>(a.g, a.in.vals, DG, ea, eb, lane, st_h);
+                    return;
+                }
+            }
+            gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, ea, eb, lane, st_h);
         });
         advance();
         rpv = tile_rp_load(a.g, (uint32_t)t_next * 16u, a.n, lane);
