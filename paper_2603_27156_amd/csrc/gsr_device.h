@@ -641,13 +641,25 @@ struct RunEdges {
     float a;         // a_ij (of the last edge in the places past it)
     int steps;       // edges per run, at most 16 (wave-uniform)
 };
+// Edges per run of a round over the edges [eb, e_b): at least one step's worth.
+template <int ROUND>
+__host__ __device__ constexpr int run_steps(int eb, int e_b) {
+    const int cnt = e_b - eb < 1 ? 1 : e_b - eb < 64 ? e_b - eb : 64;
+    return (((cnt + 3) >> 2) + ROUND - 1) / ROUND * ROUND;
+}
+// The entry a lane loads in that round: its edge, or the last one in the places past it.  The first round is asked for before
+// anyone knows that there is one, so the range may be empty (a tile without entries), also at the front of the arrays: the entry
+// is then one nobody uses, and one that exists (the arrays have room for an entry on a graph without any).
+__host__ __device__ constexpr int run_entry(int eb, int e_b, int steps, int lane) {
+    const int slot = lane & 15, last = e_b > 0 ? e_b - 1 : 0;
+    const int e = eb + (lane >> 4) * steps + (slot < steps ? slot : steps - 1);
+    return e < last ? e : last;
+}
 template <int ROUND>
 __device__ __forceinline__ RunEdges run_edges(const CsrView& g, int eb, int e_b, int lane) {
     RunEdges d;
-    const int cnt = e_b - eb < 64 ? e_b - eb : 64, slot = lane & 15;
-    d.steps = (((cnt + 3) >> 2) + ROUND - 1) / ROUND * ROUND;
-    const int e = eb + (lane >> 4) * d.steps + (slot < d.steps ? slot : d.steps - 1);
-    const int ec = e < e_b ? e : e_b - 1;
+    d.steps = run_steps<ROUND>(eb, e_b);
+    const int ec = run_entry(eb, e_b, d.steps, lane);
     d.j = __builtin_nontemporal_load(g.ci + ec);
     d.a = __builtin_nontemporal_load(g.av + ec);
     d.r = __builtin_nontemporal_load(g.er + ec);

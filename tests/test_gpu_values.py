@@ -9,7 +9,7 @@ import pytest
 import oracle
 import paper_2603_27156_amd as gsr
 from paper_2603_27156_amd import synth
-from gpu_util import Case, assert_close
+from gpu_util import Case, assert_close, rel_norm, BF16_REL
 from test_gpu_layer import run_step, ROW, PLANAR
 
 pytestmark = pytest.mark.gpu
@@ -173,3 +173,61 @@ def test_first_pass_where_every_column_is_kept(options, dg, c, chunk):
     assert np.isclose(out["loss"], ref["loss"], rtol=1e-4)
     for key in ("yhat", "XL", "X0rec", "dW", "dwout", "dX0"):
         assert_close(key, out[key], ref[key])
+
+
+def graph_with_empty_tiles(kind, n, seed):
+    """Rows of one to nine entries, none in the named places (tiles are sixteen rows)."""
+    rng = np.random.default_rng(seed)
+    lengths = rng.integers(1, 10, size=n)
+    if kind == "front":
+        lengths[:37] = 0
+    elif kind == "middle and end":
+        lengths[48:96] = 0
+        lengths[n - 33:] = 0
+    else:
+        lengths[:] = 0
+    cols = [np.sort(rng.choice(n, size=l, replace=False)) for l in lengths]
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    cols = np.concatenate([np.zeros(0)] + cols).astype(np.int32)
+    return rowptr, cols, rng.standard_normal(len(cols)).astype(np.float32) * 0.3
+
+
+@pytest.mark.parametrize("kind", ["front", "middle and end", "everywhere"])
+@pytest.mark.parametrize("dg,dtype", [(32, "f32"), (64, "f32"), (128, "f32"), (32, "bf16"), (64, "bf16")])
+def test_tiles_without_entries(kind, dg, dtype):
+    """No neighbours, no self-loops: a gather with nothing to gather, also at the very front of the arrays."""
+    n, c = 203, 3
+    rowptr, cols, vals = graph_with_empty_tiles(kind, n, 7)
+    cs = Case(synth.scaled(synth.workload(2), n, l=1, d=c * dg, c=c, k=dg // 4, dtype=dtype), 0, ROW)
+    cs.og = oracle.graph_from_csr(rowptr, cols, vals)
+    cs.gg = gsr.gsr_graph_create(rowptr, cols, vals=vals, flags=0)
+    if dg <= 64:
+        k = 9
+        idx = np.stack([np.random.default_rng(r).permutation(dg)[:k] for r in range(n)]).astype(np.int32)
+        v = torch.randn(n, k, device="cuda").to(cs.tdtype)
+        h = gsr.gsr_spmm_compressed(cs.gg, v, torch.from_numpy(idx).cuda(), dg).cpu().numpy()
+        dense = np.zeros((n, dg))
+        np.put_along_axis(dense, idx.astype(np.int64), v.float().cpu().numpy().astype(np.float64), 1)
+        ref, bound = sums_and_bound(rowptr, cols, vals, dense)
+        assert (np.abs(h - ref) <= bound).all()
+    X = cs.x0_on_grid()
+    dY = synth.to_bf16_grid((np.random.default_rng(17).standard_normal((n, c * dg))).astype(np.float32)).astype(np.float64)
+    W = cs.inp.weights[0]
+    Wd = torch.from_numpy(W).to(cs.dev)
+    Y_ref = oracle.layer_forward(cs.og, cs.ocfg, W, X)
+    y = cs.to_dev(X)
+    gsr.gsr_layer_forward(cs.gg, cs.gcfg, Wd, y)
+    x = cs.to_dev(Y_ref)
+    gsr.gsr_layer_inverse(cs.gg, cs.gcfg, Wd, x)
+    ref = oracle.layer_backward(cs.og, cs.ocfg, W, Y_ref, dY)
+    yb, dyb = cs.to_dev(Y_ref), cs.to_dev(dY)
+    dW = torch.full((c, dg, dg), 7.0, dtype=torch.float32, device=cs.dev)
+    gsr.gsr_layer_backward(cs.gg, cs.gcfg, Wd, yb, dyb, dW)
+    got = (cs.to_host(y), cs.to_host(x), cs.to_host(yb), cs.to_host(dyb), dW.cpu().numpy())
+    for name, a, b in zip(("Y", "X", "X rebuilt", "dX", "dW"), got, (Y_ref, oracle.layer_inverse(cs.og, cs.ocfg, W, Y_ref), *ref)):
+        if dtype == "f32":
+            assert_close(name, a, b)
+        else:
+            assert rel_norm(a, b) < BF16_REL, name
+    if kind == "everywhere":         # f_i is zero: the planes pass through, no gradient reaches W
+        assert np.array_equal(got[0], X) and np.array_equal(got[3], dY) and not got[4].any()
