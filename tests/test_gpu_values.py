@@ -101,6 +101,8 @@ def test_refused_indices_write_nothing_and_leave_the_graph_usable(wrong):
     (777, 384, 2, 16, 1, 512, PLANAR),       # every row of two entries or more is one chunk
     (500, 512, 2, 70, 4, 4, ROW),            # nothing fits one chunk; five passes over the kept values
     (9, 384, 3, 3, 2, 8, PLANAR),            # a half and a bit of a 16-row tile
+    (601, 256, 2, 16, 4, 2 ** 31, ROW),      # "never cut", beyond what 32 bits hold
+    (601, 256, 2, 16, 4, 2 ** 32 + 3, ROW),
 ])
 def test_wide_rows_of_one_chunk_and_of_several(options, n, d, c, k, threshold, chunk, layout):
     options("hub_threshold", threshold)
