@@ -554,7 +554,7 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     // nodes (rows up to 74) 401 / 285 us, 10,000 nodes 890 / 616, 20,000 (up to 131) 627 / 559; 40,000 (up to 257)
     // 784 / 947, 60,000 (up to 371) 1,390 / 1,755.
     const bool short_rows = (n + 15) / 16 <= (int64_t)4 * full_grid && g->max_degree <= 160;
-    const int64_t hub_threshold = options().hub_threshold > 0 ? options().hub_threshold
+    const int64_t hub_threshold = options().hub_threshold > 0 ? std::min<int64_t>(options().hub_threshold, INT32_MAX)
                                   : long_rows ? 1 : short_rows ? 160 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
     // (the kernels hold both as 32 bits, and a row has fewer than 2^31 entries: more than that means "never cut")
     const int64_t hub_chunk = options().hub_chunk > 0 ? std::min<int64_t>(options().hub_chunk, INT32_MAX) : (long_rows ? 512 : 64);      // (Table-1-shaped graph, rows of up to 390 entries: 289 / 274 / 263 / 263 ms per step with chunks of 128 / 256 / 512 / 1,024)

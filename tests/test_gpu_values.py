@@ -125,6 +125,21 @@ def test_wide_rows_of_one_chunk_and_of_several(options, n, d, c, k, threshold, c
     assert_close("dW", dW.cpu().numpy(), dW_ref)
 
 
+@pytest.mark.parametrize("dg", [32, 64, 128])
+@pytest.mark.parametrize("threshold", [2 ** 31, 2 ** 32, 2 ** 32 + 3])
+def test_rows_are_never_split_with_a_threshold_beyond_32_bits(options, dg, threshold):
+    options("hub_threshold", threshold)
+    n, c = 601, 2
+    cs = Case(synth.scaled(synth.workload(2), n, l=1, d=c * dg, c=c, k=dg // 4), 0, ROW)
+    assert gsr.gsr_graph_info(cs.gg)["n_hub_rows"] == 0
+    X = cs.x0_on_grid()
+    y = cs.to_dev(X)
+    gsr.gsr_layer_forward(cs.gg, cs.gcfg, torch.from_numpy(cs.inp.weights[0]).to(cs.dev), y)
+    assert_close("Y", cs.to_host(y), oracle.layer_forward(cs.og, cs.ocfg, cs.inp.weights[0], X))
+    x = torch.randn(n, 64, device="cuda")
+    assert_close("A x", gsr.gsr_spmm(cs.gg, x).cpu().numpy(), oracle.spmm(cs.og, x.cpu().numpy()))
+
+
 @pytest.mark.parametrize("longest", [160, 161])
 def test_short_rows_are_not_split_on_a_small_graph(longest):
     rowptr, cols, vals, g = graph_of([longest] + LENGTHS[:24], 500, 8)
