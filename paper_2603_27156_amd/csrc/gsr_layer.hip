@@ -189,7 +189,6 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
             if constexpr (WITH_DW) mfma_outer_b3<DG>(st_h, gy, dw);
         } else {
             mfma_tile<DG>(st_h, wl, acc);
-            if constexpr (WITH_DW) mfma_outer<DG>(st_h, gy, dw);
         }
         wave_sync();                                       // H has been read: the tile is free
         // residual: four rows per instruction, CPL adjacent elements per lane
@@ -342,7 +341,7 @@ struct DwArgs {
     int n, tiles;
     const float* h;         // [n][DG]
     // groups of S column blocks: blockIdx.y = mb S + ob takes H_mb (planes of [n][64]) and dY's columns 64 ob on, into a set
-    // of partials of its own, y_set floats on (S = 0: one set)
+    // of partials of its own, y_set floats on
     int S;
     size_t y_set;
     const T* dy;            // row stride ldg
@@ -358,9 +357,13 @@ struct DwArgs {
     Record<DG, T> fix_out;
 };
 
-template <int DG, typename T>
+// WIDE: groups of S column blocks.  Their workgroups are shared out between S^2 sets, so a wave sums that many times more
+// tiles than one of a plain group does (or of the kernels that took these products before, a set per input block): sums as
+// mfma_outer takes them keep dW at least as close to 64 bits as it was (1.4e-7 against 2.4e-7 on 50k rows, groups of 192;
+// 2.8e-7 against 6.1e-7 on 200k rows, groups of 128) at 1.4 % and -0.8 % of the time of those layers' backward.
+template <int DG, typename T, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_dw(DwArgs<DG, T> a) {
-    if (a.S) {
+    if constexpr (WIDE) {
         a.h += (size_t)(blockIdx.y / a.S) * a.n * DG;
         a.dy += 64 * (blockIdx.y % a.S);
         a.dw_partial += (size_t)blockIdx.y * a.y_set;
@@ -409,7 +412,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         t += ts.step;
         if (t < ts.end) request(t);
         wave_sync();
-        mfma_outer_b3<DG>(st, g, dw);
+        if constexpr (WIDE) mfma_outer<DG>(st, g, dw);
+        else mfma_outer_b3<DG>(st, g, dw);
     }
     // workgroup partial of dW_i: the four waves add their accumulators in wave order
     __shared__ float red[DG * DG];
@@ -1584,16 +1588,23 @@ static unsigned launch_dw(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const T
     DwArgs<DG, T> a;
     a.n = (int)x.cfg->n; a.tiles = x.tiles; a.h = x.hplane(); a.dy = dy; a.ldg = ldg;
     a.dw_partial = x.dw_partial();
-    a.S = x.S > 1 ? x.S : 0;
+    a.S = x.S;
     a.y_set = (size_t)x.g->grid * DG * DG;
     a.tie = fix_out ? tie : TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f};
     a.fix_plane = fix_plane; a.fix_ld = fix_ld; a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
     a.fix_out = fix_out ? *fix_out : x.rec(-1);
     ProfScope prof(KC_DW, x.s);
-    static const int per_cu = resident_blocks((const void*)k_dw<DG, T>, 256);
-    unsigned grid = persistent_grid(x.g, per_cu);
-    if (a.S) grid = std::max(8u, grid / (unsigned)(a.S * a.S) / 8 * 8);       // (the resident workgroups shared out between the sets)
-    hipLaunchKernelGGL((k_dw<DG, T>), dim3(grid, a.S ? (unsigned)(a.S * a.S) : 1u), dim3(256), 0, x.s, a);
+    if constexpr (DG == 64) {
+        if (x.S > 1) {       // the resident workgroups shared out between the sets
+            static const int per_cu = resident_blocks((const void*)k_dw<DG, T, true>, 256);
+            const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu) / (unsigned)(x.S * x.S) / 8 * 8);
+            hipLaunchKernelGGL((k_dw<DG, T, true>), dim3(grid, (unsigned)(x.S * x.S)), dim3(256), 0, x.s, a);
+            return grid;
+        }
+    }
+    static const int per_cu = resident_blocks((const void*)k_dw<DG, T, false>, 256);
+    const unsigned grid = persistent_grid(x.g, per_cu);
+    hipLaunchKernelGGL((k_dw<DG, T, false>), dim3(grid), dim3(256), 0, x.s, a);
     return grid;
 }
 

@@ -225,3 +225,23 @@ def test_wide_step_replays_from_a_graph(long_rows):
         torch.cuda.synchronize()
         for k in want:
             assert torch.equal(eager[k], want[k]), (rep, k)
+
+
+@pytest.mark.parametrize("d,n", [(256, 400_000), (384, 150_000)])
+def test_weight_gradient_of_a_wide_group_keeps_float32_accuracy(d, n):
+    """A = I and every column kept: H of the second block is Y_1 itself, and dW_2 = Y_1^T dY_2 shows the error of the product
+    alone.  An entry passes R = (four steps of a tile) + (tiles a wave sums) + (four waves) + (sums over partials) roundings of
+    its value so far, each off by 2^-24 / sqrt(3) of it at most in the mean square, independent of each other."""
+    S, k = d // 128, d // 2
+    g = gsr.gsr_graph_create(np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32), flags=0)
+    cfg = gsr.Config(n=n, d=d, c=2, k=k, layout=PLANAR)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    y, dy = (torch.randn(2, n, k, generator=gen, device="cuda") for _ in range(2))
+    ref = y[0].double().T @ dy[1].double()
+    dw = torch.empty(2, k, k, device="cuda")
+    gsr.gsr_layer_backward(g, cfg, torch.zeros(2, k, k, device="cuda"), y, dy, dw)
+    err = float((dw[1].double() - ref).norm() / ref.norm())
+    workgroups = 2 * 256 // S ** 2 // 8 * 8                  # at least two per compute unit, shared out between S^2 sets
+    roundings = 4 + n / 16 / (4 * workgroups) + 4 + (workgroups / 16 + 16)
+    print(f"[dw] D/C={k} n={n} error {err:.2e} bound {2.0 ** -24 * (roundings / 3) ** 0.5:.2e}", flush=True)
+    assert err <= 2.0 ** -24 * (roundings / 3) ** 0.5
