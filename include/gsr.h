@@ -124,8 +124,10 @@ const char* gsr_version(void);
  *                     graphs with fewer than four 16-row tiles per resident wave), or 512 on graphs of long rows
  *   "hub_values"      how the first pass sums float32 records (layer and step calls): 1 = as many lanes per edge
  *                     as a record has values (up to 16), two chains of sums each; 2 = as the tile kernels do, four
- *                     edges at a time; 0, the default: 1 on graphs whose mean row has 64 stored entries or more, while
- *                     2 k <= D/C (and k <= 64, D/C < 256 where D/C is above 64).  Read when a graph is created
+ *                     edges at a time; 0, the default: 1 on graphs whose mean row has 64 stored entries or more (and
+ *                     k <= 64, D/C < 256 where D/C is above 64).  With 0 and 2, and with 16-bit storage whatever the
+ *                     option, records of more than half of the columns are held as rows and summed as rows.  Read
+ *                     when a graph is created
  *   "max_workgroups"  workgroups of the persistent kernels, multiple of 8 (0: as many as stay resident, at most 4 per CU)
  *   "profile"         bit mask of kernel classes to time (see gsr_profile_read); read at once */
 gsr_status_t gsr_set_option(const char* key, int64_t value);

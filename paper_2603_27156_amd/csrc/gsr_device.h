@@ -368,6 +368,13 @@ __device__ __forceinline__ void load_words(const void* p, uint32_t (&w)[NW]) {
     }
 }
 
+// column cb of a lane's adjacent columns as they were loaded
+template <typename T, int NW>
+__device__ __forceinline__ float word_col(const uint32_t (&w)[NW], int cb) {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(w[cb]);
+    else return __uint_as_float((cb & 1) ? (w[cb >> 1] & 0xFFFF0000u) : (w[cb >> 1] << 16));
+}
+
 // ---- tile register layout ---------------------------------------------------------------------------
 // What the MFMA leaves in a wave's accumulators for a 16 x DG tile when the A operand takes tile
 // row 4 (i % 4) + i / 4 as its row i and the B operand takes column CPL j + cb as column j of
@@ -390,14 +397,11 @@ __device__ __forceinline__ void load_cols(const T* p, float (&v)[CPL]) {       /
         w[0] = t[0]; w[1] = t[1]; w[2] = t[2]; w[3] = t[3];
     }
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        if constexpr (sizeof(T) == 4) v[c] = __uint_as_float(w[c]);
-        else v[c] = __uint_as_float((c & 1) ? (w[c >> 1] & 0xFFFF0000u) : (w[c >> 1] << 16));
-    }
+    for (int c = 0; c < CPL; ++c) v[c] = word_col<T>(w, c);
 }
 // v must hold values representable in T (as stored<T>() returns them)
-template <int CPL, typename T>
-__device__ __forceinline__ void store_cols(T* p, const float (&v)[CPL]) {      // non-temporal
+template <int CPL, typename T, bool CACHED = false>
+__device__ __forceinline__ void store_cols(T* p, const float (&v)[CPL]) {      // non-temporal, or CACHED
     constexpr int NW = CPL * (int)sizeof(T) / 4;
     uint32_t w[NW];
 #pragma unroll
@@ -405,14 +409,18 @@ __device__ __forceinline__ void store_cols(T* p, const float (&v)[CPL]) {      /
         if constexpr (sizeof(T) == 4) w[i] = __float_as_uint(v[i]);
         else w[i] = (__float_as_uint(v[2 * i]) >> 16) | (__float_as_uint(v[2 * i + 1]) & 0xFFFF0000u);
     }
+    auto put = [](auto v, auto* q) {
+        if constexpr (CACHED) *q = v;
+        else __builtin_nontemporal_store(v, q);
+    };
     if constexpr (NW == 1) {
-        __builtin_nontemporal_store(w[0], reinterpret_cast<uint32_t*>(p));
+        put(w[0], reinterpret_cast<uint32_t*>(p));
     } else if constexpr (NW == 2) {
         u32x2a t; t[0] = w[0]; t[1] = w[1];
-        __builtin_nontemporal_store(t, reinterpret_cast<u32x2a*>(p));
+        put(t, reinterpret_cast<u32x2a*>(p));
     } else {
         u32x4a t; t[0] = w[0]; t[1] = w[1]; t[2] = w[2]; t[3] = w[3];
-        __builtin_nontemporal_store(t, reinterpret_cast<u32x4a*>(p));
+        put(t, reinterpret_cast<u32x4a*>(p));
     }
 }
 // sum over the 16 lanes of this lane's group, the same value in all of them
@@ -553,12 +561,7 @@ __device__ __forceinline__ void gather_dense_mfma(const CsrView& g, const T* __r
 #pragma unroll
                 for (int u = 0; u < GB; ++u)
 #pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) {
-                        uint32_t bits;
-                        if constexpr (sizeof(T) == 4) bits = w[u][cb];
-                        else bits = (cb & 1) ? (w[u][cb >> 1] & 0xFFFF0000u) : (w[u][cb >> 1] << 16);
-                        acc[cb][0] = __builtin_fmaf(p[u], __uint_as_float(bits), acc[cb][0]);
-                    }
+                    for (int cb = 0; cb < CPL; ++cb) acc[cb][0] = __builtin_fmaf(p[u], word_col<T>(w[u], cb), acc[cb][0]);
             } else if constexpr (sizeof(T) == 4) {
 #pragma unroll
                 for (int u = 0; u < GB; ++u)
@@ -730,17 +733,17 @@ __device__ __forceinline__ void gather_values_rows(const CsrView& g, const T* __
     }
 }
 
-// The same for a dense float32 plane X (row stride ld): st += P * X over the edges [e_a, e_b) of ordinary rows, lane j of
+// The same for a dense plane X (row stride ld): st += P * X over the edges [e_a, e_b) of ordinary rows, lane j of
 // a group keeping a running sum of its CPL columns for the run's present row in registers and adding it to the row of the
 // tile when the row changes and at the end of the round.  Two groups never add to one row in the same instruction: inside
 // a round only the last run that holds a row sees it end; the sums left at the end of the round are added group by group.
 // Lane s of a group holds edge s of the run (row_lane hands it to the others).
-template <int DG, int S0, int... U>
-__device__ __forceinline__ void dense_run(const float* __restrict__ xl, uint32_t ldu, uint32_t j, uint32_t a, uint32_t r, float* mine,
+template <int DG, int S0, typename T, int... U>
+__device__ __forceinline__ void dense_run(const T* __restrict__ xl, uint32_t ldu, uint32_t j, uint32_t a, uint32_t r, float* mine,
                                           uint32_t& cur, float (&run)[DG / 16], std::integer_sequence<int, U...>) {
-    constexpr int CPL = DG / 16, LR = tile_ld<DG>();
-    uint32_t w[sizeof...(U)][CPL];
-    (load_words<CPL>(xl + (size_t)row_lane<S0 + U>(j) * ldu, w[U]), ...);
+    constexpr int CPL = DG / 16, LR = tile_ld<DG>(), NW = CPL * (int)sizeof(T) / 4;
+    uint32_t w[sizeof...(U)][NW];
+    (load_words<NW>(xl + (size_t)row_lane<S0 + U>(j) * ldu, w[U]), ...);
     (([&] {
          const uint32_t row = row_lane<S0 + U>(r);
          if (row != cur) {
@@ -756,18 +759,18 @@ __device__ __forceinline__ void dense_run(const float* __restrict__ xl, uint32_t
          }
          const float p = __uint_as_float(row_lane<S0 + U>(a));
 #pragma unroll
-         for (int cb = 0; cb < CPL; ++cb) run[cb] = __builtin_fmaf(p, __uint_as_float(w[U][cb]), run[cb]);
+         for (int cb = 0; cb < CPL; ++cb) run[cb] = __builtin_fmaf(p, word_col<T>(w[U], cb), run[cb]);
      }()),
      ...);
 }
 
-template <int DG, int GB>
-__device__ __forceinline__ void gather_dense_rows(const CsrView& g, const float* __restrict__ x, int64_t ld, int e_a, int e_b,
+template <int DG, int GB, typename T>
+__device__ __forceinline__ void gather_dense_rows(const CsrView& g, const T* __restrict__ x, int64_t ld, int e_a, int e_b,
                                                   int lane, float* st) {
     constexpr int CPL = DG / 16, LR = tile_ld<DG>();
     static_assert(GB == 8, "a run is one or two batches");
     const int i16 = lane & 15, kk = lane >> 4;
-    const float* xl = x + CPL * i16;
+    const T* xl = x + CPL * i16;
     const uint32_t ldu = (uint32_t)ld;
     float* mine = st + CPL * i16;
     for (int eb = e_a; eb < e_b; eb += 64) {
@@ -1144,11 +1147,12 @@ __device__ __forceinline__ void mfma_outer(const float* st_h, const float (&gy)[
 
 // ---- GS of a 16-row tile --------------------------------------------------------------------------
 // Compressed record of a row ("CBSR" of Section 4.3): the k kept values in ascending column
-// order (already RMS-scaled) and the row's column bit mask.
+// order (already RMS-scaled) and the row's column bit mask.  Where more than half of the columns are kept a record is held as
+// the row itself, zeros in the dropped columns (cols == NULL; see records_as_rows).
 template <int DG, typename T>
 struct Record {
     using M = typename MaskOf<DG>::type;
-    T* vals;        // [n][k]
+    T* vals;        // [n][k], or [n][DG] as rows
     M* mask;        // [n]
     uint8_t* cols;  // [n][k]: column of every value
 };
@@ -1350,12 +1354,14 @@ __device__ __forceinline__ float record_scale(const float (&x)[DG / 4], int norm
 // application selected (Section 4.2 keeps the indices of the forward pass) and only the values
 // are taken, from the present rows.  st is overwritten.  With idx_out (and ist, 16 * DG words of
 // LDS scratch) the kept column numbers are written as well, [n][k] in ascending order, and
-// out.mask may be NULL.  With COLS the kept columns are written as bytes too, [n][k] like the values.
-// Floats of LDS emit_tile works with: the tile, 64 dump words, and with COLS a byte for every one of those.
-template <int DG, bool COLS>
-constexpr int emit_floats() { return (16 * tile_ld<DG>() + 64) + (COLS ? (16 * tile_ld<DG>() + 64) / 4 : 0); }
+// out.mask may be NULL.  FORM says what leaves: the values, the values and their columns as bytes ([n][k] like the values),
+// or the row with zeros in the dropped columns.
+// Floats of LDS emit_tile works with: the tile, 64 dump words, and with columns a byte for every one of those.
+enum RecordForm { REC_VALUES, REC_COLUMNS, REC_ROWS };
+template <int DG, RecordForm FORM>
+constexpr int emit_floats() { return (16 * tile_ld<DG>() + 64) + (FORM == REC_COLUMNS ? (16 * tile_ld<DG>() + 64) / 4 : 0); }
 
-template <int DG, typename T, bool COLS = false>
+template <int DG, typename T, RecordForm FORM = REC_VALUES>
 __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int norm, float eps, const Record<DG, T>& out,
                                           bool given, int lane, int32_t* idx_out = nullptr, int* ist = nullptr,
                                           TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}) {
@@ -1401,31 +1407,49 @@ __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int n
         }
     }
     const float scale = record_scale<DG>(x, norm, eps);
+    const int rows = min(16, n - r0);
+    if (!given && out.mask && q == 0 && r < rows) out.mask[r0 + r] = mask;
+    if constexpr (FORM == REC_ROWS) {
+        constexpr int CPL = DG / 16;
+#pragma unroll
+        for (int j = 0; j < QW; ++j) x[j] = (msel >> j) & 1u ? x[j] * scale : 0.f;
+        lds_store<QW>(st + r * LR + q * QW, x);       // (the lane's own quarter)
+        wave_sync();
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) {           // four rows per store instruction
+            const int rr = 4 * reg + q;
+            float v[CPL];
+            lds_load<CPL>(st + rr * LR + CPL * r, v);
+#pragma unroll
+            for (int cb = 0; cb < CPL; ++cb) v[cb] = stored<T>(v[cb]);
+            if (rr < rows) store_cols<CPL, T, true>(out.vals + (size_t)(r0 + rr) * DG + CPL * r, v);
+        }
+        return;
+    }
     wave_sync();   // every lane holds its quarter: the tile can be reused for the compacted values
     // a kept value goes to its slot, a dropped one to the lane's dump word: word number = dump + bit * (slot - dump)
     const int dump = 16 * LR + lane;
-    uint8_t* cst = reinterpret_cast<uint8_t*>(st + 16 * LR + 64);      // (COLS: the column beside every word)
+    uint8_t* cst = reinterpret_cast<uint8_t*>(st + 16 * LR + 64);      // (REC_COLUMNS: the column beside every word)
     int ahead = slot - dump;
 #pragma unroll
     for (int j = 0; j < QW; ++j) {
         const int bit = (int)((msel >> j) & 1u);
         const int at = dump + __mul24(bit, ahead);
         st[at] = x[j] * scale;
-        if constexpr (COLS) cst[at] = (uint8_t)(q * QW + j);
+        if constexpr (FORM == REC_COLUMNS) cst[at] = (uint8_t)(q * QW + j);
         if (idx_out && bit) ist[dump + ahead] = q * QW + j;
         ahead += bit;
     }
     wave_sync();
-    const int rows = min(16, n - r0), total = rows * k;
+    const int total = rows * k;
     T* dst = out.vals + (size_t)r0 * k;
     for (int i = lane; i < total; i += 64) dst[i] = from_float<T>(st[i]);
-    if constexpr (COLS) {        // whole words: the array is padded, and 16 k bytes per tile keep r0 * k a multiple of four
+    if constexpr (FORM == REC_COLUMNS) {        // whole words: the array is padded, and 16 k bytes per tile keep r0 * k a multiple of four
         uint32_t* dc = reinterpret_cast<uint32_t*>(out.cols + (size_t)r0 * k);
         for (int i = lane; 4 * i < total; i += 64) dc[i] = reinterpret_cast<const uint32_t*>(cst)[i];
     }
     if (idx_out)
         for (int i = lane; i < total; i += 64) idx_out[(size_t)r0 * k + i] = ist[i];
-    if (!given && out.mask && q == 0 && r < rows) out.mask[r0 + r] = mask;
 }
 
 // ---- persistent row-tile schedule ---------------------------------------------------------------
@@ -1766,8 +1790,8 @@ __global__ __launch_bounds__(256) void k_hub_both(CsrView ga, HubChunks ha, Reco
     __shared__ Lds lds[4];
     Lds& L = lds[threadIdx.x >> 6];
     const bool rec = blockIdx.y == 0;
-    if (rec && k < DG) hub_value_rows_pass<DG, T>(ga, ha, in.vals, in.cols, k, 0, part_a, nullptr, L.rows, hub_sweep(ha));
-    else                                              // (k = D/C: a record is its row)
+    if (rec && in.cols) hub_value_rows_pass<DG, T>(ga, ha, in.vals, in.cols, k, 0, part_a, nullptr, L.rows, hub_sweep(ha));
+    else                                              // (or records held as rows)
         hub_dense_pass<DG, T>(rec ? ga : gt, rec ? ha : ht, rec ? in.vals : x, rec ? DG : ld, rec ? part_a : part_t, L.dense,
                               hub_sweep(rec ? ha : ht));
 }

@@ -271,19 +271,33 @@ void tile_counters(const gsr_graph_t* g, int** set, int** done) {
     *done = g->draws + kTileCounters;
 }
 
+// A gather of values walks a round's edges ceil(k / 16) times and a gather of rows once, whatever k; a record of k float32
+// values and their columns is 5 k bytes, the row 4 D/C.  Forward layer of two groups, values / rows, us, 1M nodes, D/C = 64:
+// float32 k = 33 891 / 695, 48 975 / 723, 64 (values already read as rows by the tiles) 709 / 640; 16-bit 777 / 623,
+// 841 / 663, 895 / 468; D/C = 32, k = 17: 543 / 438 and 511 / 432; 50k nodes of mean degree 236, D/C = 64, k = 33: 834 / 392
+// and 786 / 313.  At k = D/C / 2 the values take 738 and 677 us on the 1M-node graph, which rows would take as well; further
+// down they win.
+bool records_as_rows(const gsr_config_t* cfg, const gsr_graph_t* g) {
+    const int dg = cfg->d / cfg->c;
+    if (cfg->dtype == GSR_F32 && g->hub_values == 2) return false;       // the value-by-value first pass was asked for
+    if (dg > 64) return false;
+    return 2 * cfg->k > dg;
+}
+
 LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
     LayerWs w;
     memset(&w, 0, sizeof(w));
     size_t n = (size_t)cfg->n, dg = (size_t)(cfg->d / cfg->c), b = dtype_size(cfg->dtype);
     const int S = sub_planes(cfg);
     const size_t dgs = dg / S;                       // columns of a tile: 32 or 64
+    const bool rows = records_as_rows(cfg, g);
     size_t off = 0;
     // (groups of S column blocks: one list of values and columns per group, a mask per block)
     for (int s = 0; s < cfg->c; ++s) {
         w.rec_vals[s] = off;
-        off += align_up(n * (size_t)cfg->k * b + 16);   // the record gather loads up to 16 bytes past a record
+        off += align_up(n * (rows ? dg : (size_t)cfg->k) * b);
         w.rec_cols[s] = off;
-        off += align_up(n * (size_t)cfg->k + 16);
+        if (!rows) off += align_up(n * (size_t)cfg->k + 4);          // (written in whole words)
     }
     for (int s = 0; s < cfg->c * S && s < kMaxRecordSlots; ++s) {
         w.rec_mask[s] = off;

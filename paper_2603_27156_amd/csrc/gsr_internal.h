@@ -105,7 +105,7 @@ struct gsr_graph {
     bool has_transpose = false;
     bool split_backward = true;   // float32: the backward of a block as inverse kernel + k_dw (large graphs), else fused
     bool long_rows = false;  // the mean row has 64 stored entries or more: nearly every row goes through the first pass
-    int hub_values = 0;      // the first pass over float32 records runs as k_hub_values: 0 never, 1 while 2 k <= D/C, 2 always
+    int hub_values = 0;      // the first pass over float32 records runs as k_hub_values: 0 never, 1 unless they are held as rows, 2 always
     int32_t hub_threshold = 512;
     int32_t hub_chunk = 64;
     int device = 0;
@@ -127,8 +127,8 @@ gsr_status_t validate_config(const gsr_config_t* cfg, const gsr_graph_t* g, bool
 // Workspace carving shared by gsr_workspace_size and the layer / step calls.
 constexpr int kMaxRecordSlots = 32;   // groups (at most 8) x sub-planes of a group (at most 4)
 struct LayerWs {
-    size_t rec_vals[kMaxRecordSlots];  // per slot: compressed values  [n][k] of T
-    size_t rec_cols[kMaxRecordSlots];  // per slot: column of every value [n][k] bytes
+    size_t rec_vals[kMaxRecordSlots];  // per slot: compressed values [n][k] of T, or rows [n][dg]
+    size_t rec_cols[kMaxRecordSlots];  // per slot: column of every value [n][k] bytes (not with rows)
     size_t rec_mask[kMaxRecordSlots];  // per slot and sub-plane: column bit mask    [n] of uint32 (32 columns) / uint64 (64)
     size_t y0;           // Y_0 plane [n][dg] of T (C > 2); wide groups: [S][n][64]
     size_t h;            // [n][dg] float: H of the block being inverted, for the weight-gradient kernel; wide groups: [S][n][64], H
@@ -152,6 +152,8 @@ struct StepWs {
     size_t total;
 };
 LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g);
+// Whether the layer and step calls hold the records of (cfg, g) as rows, zeros in the dropped columns.
+bool records_as_rows(const gsr_config_t* cfg, const gsr_graph_t* g);
 int64_t tie_capacity(const gsr_config_t* cfg);
 constexpr int kTieSub = 16, kTieCounterStride = 32;     // (device code: TIE_SUB, TIE_COUNTER_STRIDE)
 

@@ -26,7 +26,7 @@ CsrView make_view(const gsr_graph_t* g, bool transpose);
 template <int DG, bool RECORDS = false>
 struct WaveLds {
     // the tile, with what gather_values_rows and emit_tile need behind it (RECORDS)
-    alignas(16) float st[!RECORDS ? 16 * tile_ld<DG>() : gather_floats<DG>() > emit_floats<DG, true>() ? gather_floats<DG>() : emit_floats<DG, true>()];
+    alignas(16) float st[!RECORDS ? 16 * tile_ld<DG>() : gather_floats<DG>() > emit_floats<DG, REC_COLUMNS>() ? gather_floats<DG>() : emit_floats<DG, REC_COLUMNS>()];
     EdgeRec ebuf[RECORDS ? 1 : 64];        // 64 staged edges (not with gather_values_rows)
     int rp[20];                            // row pointers of the tile's 17 row boundaries
 };
@@ -65,7 +65,7 @@ struct BlockArgs {
 // always use the split form: the plain and the fused inverse must rebuild the same bits.
 constexpr int block_waves(bool with_dw, bool b3) { return (!with_dw && b3) ? 8 : 4; }
 
-template <int DG, typename T, int SIGN, bool WITH_DW, bool DEAL, bool B3 = true>
+template <int DG, typename T, int SIGN, bool WITH_DW, bool DEAL, bool B3, RecordForm FORM>
 __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgpu_waves_per_eu(WITH_DW ? 2 : 4))) void k_block(BlockArgs<DG, T> a) {
     static_assert(B3 || (SIGN > 0 && !WITH_DW), "only the forward kernel has a float32 variant");
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
@@ -154,13 +154,8 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         // (in the forward and in both inverse kernels alike, so that f_i is recomputed by the instructions that computed it)
         tile_gather_rows<DG, true, 20>(a.g, a.hub_part, has_hub, r0, L.rp, st_h, lane, [&](int e_a, int e_b) {
             const int ea = __builtin_amdgcn_readfirstlane(e_a), eb = __builtin_amdgcn_readfirstlane(e_b);
-            if constexpr (sizeof(T) == 4) {
-                if (a.k == DG) {      // every column kept, in order: dense rows (1M nodes, k = 64: 277 against 487 us)
-                    gather_dense_rows<DG, 8>(a.g, a.in.vals, DG, ea, eb, lane, st_h);
-                    return;
-                }
-            }
-            gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, ea, eb, lane, st_h);
+            if constexpr (FORM == REC_ROWS) gather_dense_rows<DG, 8>(a.g, a.in.vals, DG, ea, eb, lane, st_h);
+            else gather_values_rows<DG, 4, !B3>(a.g, a.in.vals, a.in.cols, a.k, ea, eb, lane, st_h);
         });
         advance();
         rpv = tile_rp_load(a.g, (uint32_t)t_next * 16u, a.n, lane);
@@ -207,7 +202,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         }
         if (a.out.mask) {
             wave_sync();
-            emit_tile<DG, T, true>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+            emit_tile<DG, T, FORM>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
         }
         t = t_next;
         t_end = t_end_next;
@@ -260,6 +255,7 @@ __device__ __forceinline__ void tie_fixup_rows(const TieSeg<DG>& tie, const T* _
         const uint32_t msel = (uint32_t)(m >> (QW * q)) & ((1u << QW) - 1u);
         uint32_t all[4];
         quarter_all((uint32_t)__popc(msel), all);
+        const bool as_row = !out.cols;
         size_t slot = row * k;
 #pragma unroll
         for (int i = 0; i < 3; ++i) slot += i < q ? all[i] : 0u;
@@ -267,7 +263,9 @@ __device__ __forceinline__ void tie_fixup_rows(const TieSeg<DG>& tie, const T* _
 #pragma unroll
         for (int j = 0; j < QW; ++j) {
             const bool bit = (msel >> j) & 1u;
-            if (ok && bit) {
+            if (as_row) {
+                if (ok) out.vals[row * DG + q * QW + j] = from_float<T>(bit ? x[j] * scale : 0.f);
+            } else if (ok && bit) {
                 out.vals[slot] = from_float<T>(x[j] * scale);
                 out.cols[slot] = (uint8_t)(q * QW + j);
             }
@@ -678,10 +676,10 @@ __global__ void k_zero_ints(int* p, int count) {
     if (i < count) p[i] = 0;
 }
 
-template <int DG, typename T>
+template <int DG, typename T, RecordForm FORM>
 __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
-    __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, true>()];
+    __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, REC_COLUMNS>()];
     const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
     float* st = tile[threadIdx.x >> 6];
     const int nwaves = (gridDim.x * blockDim.x) >> 6, tiles = (a.n + 15) / 16;
@@ -718,7 +716,7 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
             lds_store<CPL>(st + rr * LR + CPL * tj, y[reg]);
         }
         wave_sync();
-        emit_tile<DG, T, true>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+        emit_tile<DG, T, FORM>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
     }
 }
 
@@ -1349,6 +1347,7 @@ struct Ctx {
     LayerWs lw;
     int tiles;
     int S;          // sub-planes of a group: 1, or D/C / 64 for groups wider than a tile (then DG = 64)
+    bool rows;      // records are held as rows (records_as_rows)
     M* saved;       // [L+1][C][S][n] column masks kept from the forward sweep, or NULL
     // rows kept because they selected at a near-tie (cfg->save_indices == 2), per segment (layer, slot), or NULL
     int* tie_counts;
@@ -1368,7 +1367,7 @@ struct Ctx {
         Record<DG, T> r;
         if (slot < 0) { r.vals = nullptr; r.mask = nullptr; r.cols = nullptr; return r; }
         r.vals = (T*)(ws + lw.rec_vals[slot]);
-        r.cols = (uint8_t*)(ws + lw.rec_cols[slot]);
+        r.cols = rows ? nullptr : (uint8_t*)(ws + lw.rec_cols[slot]);
         r.mask = saved ? saved + (((size_t)layer * cfg->c + slot) * S + sub) * (size_t)cfg->n : (M*)(ws + lw.rec_mask[slot * S + sub]);
         return r;
     }
@@ -1378,7 +1377,7 @@ struct Ctx {
     float* dw_partial() const { return (float*)(ws + lw.dw_partial); }
     float* hub_part() const { return (float*)(ws + lw.hub_partial); }
     float* hub_part2() const { return (float*)(ws + lw.hub_partial2); }
-    bool hub_by_value() const { return g->hub_values == 2 || (g->hub_values == 1 && 2 * cfg->k <= DG * S); }
+    bool hub_by_value() const { return !rows && g->hub_values != 0; }
 };
 
 // Workgroups of 256 threads one CU keeps resident for a kernel, and the persistent grid that
@@ -1406,7 +1405,8 @@ static void launch_sum(const Ctx<DG, T>& x, const T* src, int64_t ld, int64_t gs
     a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
     a.out = out; a.out_given = out_given;
     ProfScope prof(KC_SUM, x.s);
-    hipLaunchKernelGGL((k_sum<DG, T>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
+    if (x.rows) hipLaunchKernelGGL((k_sum<DG, T, REC_ROWS>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
+    else hipLaunchKernelGGL((k_sum<DG, T, REC_COLUMNS>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
 }
 
 template <int DG, typename T>
@@ -1415,6 +1415,11 @@ static void launch_hub_records(const Ctx<DG, T>& x, const Record<DG, T>& in) {
     if (h.n_chunks == 0) return;
     HubChunks hc{h.ce0, h.ce1, h.n_chunks, x.g->long_rows};
     ProfScope prof(KC_HUB, x.s);
+    if (!in.cols) {
+        hipLaunchKernelGGL((k_hub_dense<DG, T>), dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s, make_view(x.g, false), hc,
+                           (const T*)in.vals, (int64_t)DG, x.hub_part(), (float*)nullptr);
+        return;
+    }
     if constexpr (sizeof(T) == 4) {
         if (x.hub_by_value()) {
             hub_values_variant(x.cfg->k, [&](auto lg, auto kq) {
@@ -1424,13 +1429,6 @@ static void launch_hub_records(const Ctx<DG, T>& x, const Record<DG, T>& in) {
             });
             return;
         }
-    }
-    if (x.cfg->k == DG) {
-        // Every column is kept, in ascending order: a record is its row, and a pass over rows adds it without going through LDS
-        // value by value (Table-1-shaped graph, six groups of 64, k = 64: 346 ms per step against 668).
-        hipLaunchKernelGGL((k_hub_dense<DG, T>), dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s, make_view(x.g, false), hc,
-                           (const T*)in.vals, (int64_t)DG, x.hub_part(), (float*)nullptr);
-        return;
     }
     hipLaunchKernelGGL((k_hub_records<DG, T>), dim3(hub_grid(h.n_chunks)), dim3(256), 0, x.s,
                        make_view(x.g, false), hc, in, x.cfg->k, x.hub_part());
@@ -1515,19 +1513,24 @@ static unsigned launch_block(const Ctx<DG, T>& x, int mode, const Record<DG, T>&
         if (heavy_first(a.g.n_heavy, x.tiles, grid * (block.x / 64) / 4)) hipLaunchKernelGGL(deal, dim3(grid), block, 0, x.s, a);
         else hipLaunchKernelGGL(plain, dim3(grid), block, 0, x.s, a);
     };
-    if (mode == 0 && b3) {
-        static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, true>, 512);
-        go(k_block<DG, T, +1, false, false, true>, k_block<DG, T, +1, false, true, true>, per_cu);
-    } else if (mode == 0) {
-        static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, false>, 256);
-        go(k_block<DG, T, +1, false, false, false>, k_block<DG, T, +1, false, true, false>, per_cu);
-    } else if (mode == 1) {
-        static const int per_cu = resident_blocks((const void*)k_block<DG, T, -1, false, false, true>, 512);
-        go(k_block<DG, T, -1, false, false, true>, k_block<DG, T, -1, false, true, true>, per_cu);
-    } else {
-        static const int per_cu = resident_blocks((const void*)k_block<DG, T, -1, true, false, true>, 256);
-        go(k_block<DG, T, -1, true, false, true>, k_block<DG, T, -1, true, true, true>, per_cu);
-    }
+    auto launch = [&](auto form) {
+        constexpr RecordForm F = decltype(form)::value;
+        if (mode == 0 && b3) {
+            static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, true, F>, 512);
+            go(k_block<DG, T, +1, false, false, true, F>, k_block<DG, T, +1, false, true, true, F>, per_cu);
+        } else if (mode == 0) {
+            static const int per_cu = resident_blocks((const void*)k_block<DG, T, +1, false, false, false, F>, 256);
+            go(k_block<DG, T, +1, false, false, false, F>, k_block<DG, T, +1, false, true, false, F>, per_cu);
+        } else if (mode == 1) {
+            static const int per_cu = resident_blocks((const void*)k_block<DG, T, -1, false, false, true, F>, 512);
+            go(k_block<DG, T, -1, false, false, true, F>, k_block<DG, T, -1, false, true, true, F>, per_cu);
+        } else {
+            static const int per_cu = resident_blocks((const void*)k_block<DG, T, -1, true, false, true, F>, 256);
+            go(k_block<DG, T, -1, true, false, true, F>, k_block<DG, T, -1, true, true, true, F>, per_cu);
+        }
+    };
+    if (x.rows) launch(std::integral_constant<RecordForm, REC_ROWS>{});
+    else launch(std::integral_constant<RecordForm, REC_COLUMNS>{});
     return grid;
 }
 
@@ -1902,6 +1905,7 @@ static Ctx<DG, T> make_ctx(const gsr_graph_t* g, const gsr_config_t* cfg, void* 
     x.g = g; x.cfg = cfg; x.s = s; x.ws = (char*)ws; x.lw = carve_layer(cfg, g);
     x.tiles = (int)((cfg->n + 15) / 16);
     x.S = sub_planes(cfg);
+    x.rows = records_as_rows(cfg, g);
     x.saved = nullptr;
     x.tie_counts = nullptr; x.tie_rows = nullptr; x.tie_masks = nullptr; x.tie_cap = 0;
     return x;

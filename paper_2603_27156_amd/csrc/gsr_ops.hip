@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256) void k_gs_tile(const T* __restrict__ x, int n,
                                                  T* __restrict__ vals, int32_t* __restrict__ idx) {
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     struct Wave {
-        alignas(16) float st[emit_floats<DG, false>()];
+        alignas(16) float st[emit_floats<DG, REC_VALUES>()];
         int ist[16 * DG];
     };
     __shared__ Wave lds[4];

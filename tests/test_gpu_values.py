@@ -248,3 +248,33 @@ def test_tiles_without_entries(kind, dg, dtype):
             assert rel_norm(a, b) < BF16_REL, name
     if kind == "everywhere":         # f_i is zero: the planes pass through, no gradient reaches W
         assert np.array_equal(got[0], X) and np.array_equal(got[3], dY) and not got[4].any()
+
+
+@pytest.mark.parametrize("dg,c,k,dtype,save,threshold,chunk", [
+    (64, 2, 33, "f32", 2, 6, 4), (64, 3, 63, "f32", 1, 512, 0), (64, 4, 40, "f32", 0, 6, 100), (64, 2, 64, "f32", 2, 512, 0),
+    (32, 2, 17, "f32", 0, 6, 4), (32, 4, 31, "f32", 2, 512, 0), (32, 2, 32, "f32", 1, 6, 100),
+    (64, 2, 33, "bf16", 1, 6, 4), (64, 3, 64, "bf16", 1, 512, 0), (32, 4, 17, "bf16", 1, 512, 0), (32, 2, 31, "bf16", 2, 6, 100),
+])
+@pytest.mark.parametrize("workgroups", [0, 8])
+def test_records_held_as_rows(options, dg, c, k, dtype, save, threshold, chunk, workgroups):
+    """More than half of the columns kept: every form of the step, at the smallest such k, the largest and between."""
+    options("hub_threshold", threshold)
+    options("hub_chunk", chunk)
+    options("max_workgroups", workgroups)         # (8: a block's backward is cut in two kernels, tiles are drawn)
+    tol = 2.0 ** -4
+    cs = Case(synth.scaled(synth.workload(2), 1501, levels=6, d=dg * c, c=c, k=k, l=2, hubs=2, dtype=dtype), 11, PLANAR)
+    ref = oracle.step(cs.og, cs.ocfg, cs.w.l, cs.x0_on_grid(), cs.inp.weights, cs.inp.w_out, cs.inp.b_out, cs.inp.target,
+                      variant={0: 0, 1: 2, 2: 3}[save], tie_tol=tol)
+    out = run_step(cs, save_indices=save, tie_tol=tol, tie_capacity=16 * cs.w.n)
+    assert np.isclose(out["loss"], ref["loss"], rtol=1e-4 if dtype == "f32" else BF16_REL)
+    for key in ("yhat", "XL", "dW", "dwout", "dX0") + (("X0rec",) if dtype == "f32" else ()):
+        if dtype == "f32":
+            assert_close(key, out[key], ref[key])
+        else:
+            assert rel_norm(out[key], ref[key]) < BF16_REL, key
+    x = cs.to_dev(cs.x0_on_grid())                # the layer calls, and what they rebuild
+    W = torch.from_numpy(cs.inp.weights[0]).to(cs.dev)
+    gsr.gsr_layer_forward(cs.gg, cs.gcfg, W, x)
+    gsr.gsr_layer_inverse(cs.gg, cs.gcfg, W, x)
+    if dtype == "f32":
+        assert_close("inverse(forward(X)) vs X", cs.to_host(x), cs.x0_on_grid(), rtol=1e-4, atol=1e-4)
