@@ -356,9 +356,12 @@ struct DwArgs {
 };
 
 // WIDE: groups of S column blocks.  Their workgroups are shared out between S^2 sets, so a wave sums that many times more
-// tiles than one of a plain group does (or of the kernels that took these products before, a set per input block): sums as
-// mfma_outer takes them keep dW at least as close to 64 bits as it was (1.4e-7 against 2.4e-7 on 50k rows, groups of 192;
-// 2.8e-7 against 6.1e-7 on 200k rows, groups of 128) at 1.4 % and -0.8 % of the time of those layers' backward.
+// tiles than one of a plain group does (or of the kernels that took these products before, a set per input block).  With
+// float32 rows, sums as mfma_outer takes them keep dW at least as close to 64 bits as it was (1.4e-7 against 2.4e-7 on 50k
+// rows, groups of 192; 2.8e-7 against 6.1e-7 on 200k rows, groups of 128) at 1 % of the time of those layers' backward.  With
+// 16-bit rows of dY half of the split products are zero and the sums hold (A = I, 150k - 400k rows, groups of 128 / 192 / 256:
+// 1.7e-7 / 1.6e-7 / 1.8e-7 against 1.7e-7 / 1.6e-7 / 1.6e-7; 256 with twice the workgroups 1.5e-7), and float32 products
+// would cost 4 %.
 template <int DG, typename T, bool WIDE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_dw(DwArgs<DG, T> a) {
     if constexpr (WIDE) {
@@ -410,7 +413,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         t += ts.step;
         if (t < ts.end) request(t);
         wave_sync();
-        if constexpr (WIDE) mfma_outer<DG>(st, g, dw);
+        if constexpr (WIDE && sizeof(T) == 4) mfma_outer<DG>(st, g, dw);
         else mfma_outer_b3<DG>(st, g, dw);
     }
     // workgroup partial of dW_i: the four waves add their accumulators in wave order
@@ -1598,9 +1601,10 @@ static unsigned launch_dw(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const T
     a.fix_out = fix_out ? *fix_out : x.rec(-1);
     ProfScope prof(KC_DW, x.s);
     if constexpr (DG == 64) {
-        if (x.S > 1) {       // the resident workgroups shared out between the sets
+        if (x.S > 1) {       // the resident workgroups shared out between the sets (16-bit groups of 256: two rounds of them)
             static const int per_cu = resident_blocks((const void*)k_dw<DG, T, true>, 256);
-            const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu) / (unsigned)(x.S * x.S) / 8 * 8);
+            const unsigned rounds = sizeof(T) == 2 && x.S == 4 ? 2 : 1;
+            const unsigned grid = std::max(8u, rounds * persistent_grid(x.g, per_cu) / (unsigned)(x.S * x.S) / 8 * 8);
             hipLaunchKernelGGL((k_dw<DG, T, true>), dim3(grid, (unsigned)(x.S * x.S)), dim3(256), 0, x.s, a);
             return grid;
         }
