@@ -276,11 +276,15 @@ void tile_counters(const gsr_graph_t* g, int** set, int** done) {
 // float32 k = 33 891 / 695, 48 975 / 723, 64 (values already read as rows by the tiles) 709 / 640; 16-bit 777 / 623,
 // 841 / 663, 895 / 468; D/C = 32, k = 17: 543 / 438 and 511 / 432; 50k nodes of mean degree 236, D/C = 64, k = 33: 834 / 392
 // and 786 / 313.  At k = D/C / 2 the values take 738 and 677 us on the 1M-node graph, which rows would take as well; further
-// down they win.
+// down they win.  Wider groups on 200k nodes, float32: D/C = 128, k = 80 638 / 574, 128 757 / 522; 192, k = 128 1,041 / 951.
+// On a graph of long rows their rows are a first pass per block of 64 columns and the values one whose round of sixteen lanes
+// turns k / 16 times; up to k = 64 that is k_hub_values in float32, beyond it the slower k_hub_records_wide: 50k nodes of mean
+// degree 236, D/C = 192, k = 64 912 / -, 72 1,419 / 1,212, 96 1,620 / 1,218; 128, k = 80 1,273 / 811; 256 (no k_hub_values),
+// k = 80 1,500 / 1,701, 96 1,765 / 1,701, 16-bit, k = 80 1,422 / 1,396.
 bool records_as_rows(const gsr_config_t* cfg, const gsr_graph_t* g) {
     const int dg = cfg->d / cfg->c;
     if (cfg->dtype == GSR_F32 && g->hub_values == 2) return false;       // the value-by-value first pass was asked for
-    if (dg > 64) return false;
+    if (dg > 64 && g->long_rows) return cfg->k > (cfg->dtype == GSR_F32 && dg == 256 ? 80 : 64);
     return 2 * cfg->k > dg;
 }
 

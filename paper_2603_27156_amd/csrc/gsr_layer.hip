@@ -799,7 +799,7 @@ __global__ __launch_bounds__(256) void k_gather_wide(WideGatherArgs<S, T> a) {
     walk.finish();
 }
 
-// Q = A^T dY, blockIdx.y a block of 64 columns: planes q [S][n][64]
+// Q = A X of dense rows (dY over A^T, or records held as rows over A), blockIdx.y a block of 64 columns: planes q [S][n][64]
 template <typename T>
 struct DensePlanesArgs {
     CsrView g;
@@ -1039,8 +1039,8 @@ struct WideGsArgs {
     T* y0;                  // [S][n][64]: the sum, sub-plane by sub-plane (NULL: not kept)
     int k, norm;
     float eps;
-    T* vals;                // the record: [n][k] values of the whole row in column order and their columns
-    uint8_t* cols;
+    T* vals;                // the record: [n][k] values of the whole row in column order and their columns,
+    uint8_t* cols;          // or (cols == NULL) rows [n][64 S] with zeros in the dropped columns
     uint64_t* mask[S];
     bool out_given;         // mask[s] hold the column sets to use
 };
@@ -1193,6 +1193,27 @@ __global__ __launch_bounds__(256) void k_gs_wide(WideGsArgs<S, T> a) {
             if (!a.out_given && q == 0 && r < rows)
                 a.mask[s][r0 + r] = (uint64_t)(all[0] & 0xFFFFu) | (uint64_t)(all[1] & 0xFFFFu) << 16 |
                                     (uint64_t)(all[2] & 0xFFFFu) << 32 | (uint64_t)(all[3] & 0xFFFFu) << 48;
+        }
+        if (!a.cols) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) x[s][j] = (msel[s] >> j) & 1u ? x[s][j] * scale : 0.f;
+                lds_store<16>(st + r * LRW + 64 * s + 16 * q, x[s]);      // (the lane's own columns)
+            }
+            wave_sync();
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const int rr = 4 * reg + tg;
+                    float v[4];
+                    lds_load<4>(st + rr * LRW + 64 * s + 4 * tj, v);
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) v[cb] = stored<T>(v[cb]);
+                    if (rr < rows) store_cols<4, T, true>(a.vals + (size_t)(r0 + rr) * DGW + 64 * s + 4 * tj, v);
+                }
+            continue;
         }
         wave_sync();          // every lane holds its values: the tile can be reused
         const int dump = 16 * LRW + lane;
@@ -1643,12 +1664,40 @@ static void launch_gs_wide(const Ctx<64, T>& x, const T* src, int64_t ld, int64_
     });
 }
 
+// A X (or A^T X) of dense rows X of 64 S columns into planes [S][n][64]
+template <typename T>
+static void launch_dense_planes(const Ctx<64, T>& x, bool transpose, const T* src, int64_t ld, float* planes, KernelClass kc) {
+    const HubPlan& hp = transpose ? x.g->at.hub : x.g->a.hub;
+    const size_t n = (size_t)x.cfg->n;
+    if (hp.n_chunks > 0) {
+        HubChunks hc{hp.ce0, hp.ce1, hp.n_chunks, x.g->long_rows, hp.single};
+        ProfScope prof(KC_HUB, x.s);
+        for (int s = 0; s < x.S; ++s)
+            hipLaunchKernelGGL((k_hub_dense<64, T>), dim3(hub_grid(hp.n_chunks)), dim3(256), 0, x.s, make_view(x.g, transpose), hc, src + 64 * s, ld,
+                               x.hub_part() + (size_t)s * hp.n_chunks * 64, planes + s * n * 64);
+    }
+    DensePlanesArgs<T> a;
+    a.g = make_view(x.g, transpose);
+    a.n = (int)n; a.tiles = x.tiles; a.x = src; a.ld = ld; a.hub_part = x.hub_part(); a.n_chunks = hp.n_chunks; a.q = planes;
+    a.y_draws = kTileCounterSet;
+    tile_counters(x.g, &a.draws, &a.draws_done);
+    ProfScope prof(kc, x.s);
+    static const int per_cu = resident_blocks((const void*)k_dense_planes<T, false>);
+    const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu) / (unsigned)x.S / 8 * 8);       // the resident workgroups shared out
+    if (heavy_first(a.g.n_heavy, x.tiles, grid)) hipLaunchKernelGGL((k_dense_planes<T, true>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
+    else hipLaunchKernelGGL((k_dense_planes<T, false>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
+}
+
 // H of block `slot` + 1 into x.hplane(): the first pass over split rows, then the tiles
 template <typename T>
 static void launch_gather_wide(const Ctx<64, T>& x, int slot, int layer) {
     const HubPlan& hp = x.g->a.hub;
     const Record<64, T> in = x.rec(slot, layer);
     const int n = (int)x.cfg->n, k = x.cfg->k;
+    if (!in.cols) {
+        launch_dense_planes<T>(x, false, in.vals, 64 * x.S, x.hplane(), KC_BLOCK_FWD);
+        return;
+    }
     wide_blocks(x.S, [&](auto sc) {
         constexpr int S = decltype(sc)::value;
         if (hp.n_chunks > 0) {
@@ -1679,30 +1728,6 @@ static void launch_gather_wide(const Ctx<64, T>& x, int slot, int layer) {
         static const int per_cu = resident_blocks((const void*)k_gather_wide<S, T>);
         hipLaunchKernelGGL((k_gather_wide<S, T>), dim3(persistent_grid(x.g, per_cu)), dim3(256), 0, x.s, a);
     });
-}
-
-// Q = A^T dY_i into x.dh()
-template <typename T>
-static void launch_dense_planes(const Ctx<64, T>& x, const T* dy, int64_t ldg) {
-    const HubPlan& hp = x.g->at.hub;
-    const size_t n = (size_t)x.cfg->n;
-    if (hp.n_chunks > 0) {
-        HubChunks hc{hp.ce0, hp.ce1, hp.n_chunks, x.g->long_rows, hp.single};
-        ProfScope prof(KC_HUB, x.s);
-        for (int s = 0; s < x.S; ++s)
-            hipLaunchKernelGGL((k_hub_dense<64, T>), dim3(hub_grid(hp.n_chunks)), dim3(256), 0, x.s, make_view(x.g, true), hc, dy + 64 * s, ldg,
-                               x.hub_part() + (size_t)s * hp.n_chunks * 64, x.dh() + s * n * 64);
-    }
-    DensePlanesArgs<T> a;
-    a.g = make_view(x.g, true);
-    a.n = (int)n; a.tiles = x.tiles; a.x = dy; a.ld = ldg; a.hub_part = x.hub_part(); a.n_chunks = hp.n_chunks; a.q = x.dh();
-    a.y_draws = kTileCounterSet;
-    tile_counters(x.g, &a.draws, &a.draws_done);
-    ProfScope prof(KC_GRAD, x.s);
-    static const int per_cu = resident_blocks((const void*)k_dense_planes<T, false>);
-    const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu) / (unsigned)x.S / 8 * 8);       // the resident workgroups shared out
-    if (heavy_first(a.g.n_heavy, x.tiles, grid)) hipLaunchKernelGGL((k_dense_planes<T, true>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
-    else hipLaunchKernelGGL((k_dense_planes<T, false>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
 }
 
 // plane (+/-)= H W_i with H in x.hplane()
@@ -1793,7 +1818,7 @@ static void wide_backward(const Ctx<64, T>& x, const float* w, const Planes<T>& 
         } else if (C == 2) {
             launch_gs_wide<T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, 0, layer, given);      // X_2 = Y_0 of this layer
         }
-        launch_dense_planes<T>(x, dy.grp(i - 1), dy.ld);
+        launch_dense_planes<T>(x, true, dy.grp(i - 1), dy.ld, x.dh(), KC_GRAD);       // Q = A^T dY_i
         if (i >= 2) launch_wide_grad<T>(x, wi, i - 1, layer, z, ldz, z_sub, dy.grp(i - 2), dy.ld, dy.gs, 1);
         else launch_wide_grad<T>(x, wi, 0, layer, z, ldz, z_sub, dy.grp(1), dy.ld, dy.gs, C - 1);
     }

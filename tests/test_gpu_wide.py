@@ -162,6 +162,38 @@ def test_wide_groups_with_bf16_storage():
     audit_layer_backward(cs, W, Y, dY, "wide bf16 bwd", bar=functools.partial(bf16_bar, steps=2.0), dw_rtol=2e-2, max_flips=0.2)
 
 
+@pytest.mark.parametrize("base,d,k,save,threshold,chunk", [
+    (2, 256, 65, 1, 512, 0), (2, 256, 128, 0, 6, 4), (2, 384, 97, 0, 1, 512), (2, 512, 129, 1, 4, 4), (2, 512, 256, 0, 512, 0),
+    (5, 256, 65, 0, 0, 0), (5, 384, 65, 1, 0, 0), (5, 512, 80, 0, 0, 0), (5, 512, 81, 0, 0, 0),      # long rows: rows above 64, or 80
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_wide_records_held_as_rows(base, d, k, save, threshold, chunk, dtype):
+    """More columns kept than the value gather serves well, at the smallest such k and the largest."""
+    from gpu_util import bf16_bar
+    gsr.gsr_set_option("hub_threshold", threshold)
+    gsr.gsr_set_option("hub_chunk", chunk)
+    try:
+        cs = Case(synth.scaled(synth.workload(base), 901, levels=6, d=d, c=2, k=k, l=2, norm="rms", dtype=dtype), 4, ROW)
+    finally:
+        gsr.gsr_set_option("hub_threshold", 0)
+        gsr.gsr_set_option("hub_chunk", 0)
+    w = cs.w
+    if dtype == "bf16":          # the first group's rows follow from identical inputs (see test_wide_groups_with_bf16_storage)
+        X = cs.x0_on_grid()
+        y = cs.to_dev(X)
+        gsr.gsr_layer_forward(cs.gg, cs.gcfg, torch.from_numpy(cs.inp.weights[0]).to(cs.dev), y)
+        Y, Y_ref = cs.to_host(y), oracle.layer_forward(cs.og, cs.ocfg, cs.inp.weights[0], X)
+        # (the library rounds a row after each of the D/C / 64 blocks of its sum, the oracle once: each rounding moves it by at
+        # most half a step of a partial sum, which may be as large as the row's largest entry)
+        assert not bf16_bar(Y[:, :w.dg], Y_ref[:, :w.dg], steps=w.dg / 64).any() and rel_norm(Y, Y_ref) <= 2 * BF16_REL
+        return
+    ref = oracle.step(cs.og, cs.ocfg, w.l, cs.x0_on_grid(), cs.inp.weights, cs.inp.w_out, cs.inp.b_out, cs.inp.target, variant=2 * save)
+    out = run_step(cs, save_indices=save)
+    assert np.isclose(out["loss"], ref["loss"], rtol=1e-4)
+    for key in ("yhat", "XL", "X0rec", "dW", "dwout", "dX0"):
+        assert_close(key, out[key], ref[key])
+
+
 def test_wide_groups_refuse_the_near_tie_list():
     cs = wide_case(500, 256, 2, 16, 2)
     with pytest.raises(gsr.GsrError) as e:
