@@ -232,9 +232,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     walk.finish();
 }
 
-// The sums of a tile into an LDS tile (gather_values_rows), rows stored from there.  *bad: the indices have been found
-// wanting by k_pack_columns, nothing is written.
-template <int DG, typename T, bool DEAL>
+// The sums of a tile into an LDS tile (gather_values_rows, or gather_dense_rows where the values were laid out as rows), rows
+// stored from there.  *bad: the indices have been found wanting by the kernel before, nothing is written.
+template <int DG, typename T, RecordForm FORM, bool DEAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_aggregate_tile(CsrView g, int n, int tiles, Record<DG, T> in, int k,
                                                         const float* __restrict__ hub_part, float* __restrict__ h_out,
                                                         int* draws, int* draws_done, const int* __restrict__ bad) {
@@ -256,8 +256,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const bool has_hub = tile_begin(g, rpv, W.rp, lane);
         if (walk.dealt(g, rpv, W.rp, has_hub)) { walk.next(g); continue; }
         tile_gather_rows<DG, true, 20>(g, hub_part, has_hub, r0, W.rp, W.st, lane, [&](int e_a, int e_b) {
-            gather_values_rows<DG, 8, false>(g, in.vals, in.cols, k, __builtin_amdgcn_readfirstlane(e_a),
-                                             __builtin_amdgcn_readfirstlane(e_b), lane, W.st);
+            const int ea = __builtin_amdgcn_readfirstlane(e_a), eb = __builtin_amdgcn_readfirstlane(e_b);
+            if constexpr (FORM == REC_ROWS) gather_dense_rows<DG, 8>(g, in.vals, DG, ea, eb, lane, W.st);
+            else gather_values_rows<DG, 8, false>(g, in.vals, in.cols, k, ea, eb, lane, W.st);
         });
         wave_sync();
 #pragma unroll
@@ -336,37 +337,113 @@ __global__ __launch_bounds__(256) void k_pack_columns(int64_t n, int k, int kp, 
     }
 }
 
+// ---- (V, I int32, any slot order) -> rows with zeros in the columns not named -----
+// A 16-row tile per wave: its k-wide arrays are one contiguous piece each, their values go to their columns of an LDS tile, and
+// the tile leaves in whole rows.  A byte beside every place marks it as named; a row with fewer than k marks had a column outside
+// [0, DG) or named one twice: *bad as in k_pack_columns.  (As bits, by atomic or on a word per 32
+// columns: 453 us against 366 for GS-shaped input of 1M rows, k = dg = 64.)
+template <int DG, typename T>
+__global__ __launch_bounds__(256) void k_pack_rows(int n, int k, const T* __restrict__ v_in, const int32_t* __restrict__ i_in, T* __restrict__ out,
+                                                   int* __restrict__ bad) {
+    constexpr int LR = tile_ld<DG>(), CPL = DG / 16, NB = 4;
+    using Marks = typename std::conditional<CPL == 4, uint32_t, uint16_t>::type;       // of a lane's adjacent columns
+    struct Wave {
+        alignas(16) float st[16 * LR];
+        alignas(16) uint8_t named[16 * DG];
+    };
+    __shared__ Wave lds[4];
+    Wave& L = lds[threadIdx.x >> 6];
+    const int lane = lane_id(), nwaves = (gridDim.x * blockDim.x) >> 6, tiles = (n + 15) / 16;
+    bool wrong = false;
+    for (int t = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; t < tiles; t += nwaves) {
+        const int r0 = t * 16, rows = n - r0 < 16 ? n - r0 : 16, total = rows * k;
+        const T* v0 = v_in + (size_t)r0 * k;
+        const int32_t* i0 = i_in + (size_t)r0 * k;
+        wave_sync();          // the tile before has left
+        for (int i = 4 * lane; i < 16 * LR; i += 256) *reinterpret_cast<f32v4*>(L.st + i) = f32v4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 16 * lane; i < 16 * DG; i += 1024) *reinterpret_cast<f32v4*>(L.named + i) = f32v4{0.f, 0.f, 0.f, 0.f};
+        wave_sync();
+        for (int b = lane; b < total; b += 64 * NB) {
+            T v[NB];
+            int col[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int i = b + 64 * u < total ? b + 64 * u : b;
+                v[u] = v0[i];
+                col[u] = i0[i];
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int i = b + 64 * u;
+                if (i >= total || col[u] < 0 || col[u] >= DG) continue;
+                const int row = (int)((uint32_t)i / (uint32_t)k);
+                L.named[row * DG + col[u]] = 1;
+                L.st[row * LR + col[u]] = to_float(v[u]);
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) {
+            const int rr = 4 * reg + (lane >> 4);
+            float v[CPL];
+            lds_load<CPL>(L.st + rr * LR + CPL * (lane & 15), v);
+            if (rr < rows) store_cols<CPL, T, true>(out + (size_t)(r0 + rr) * DG + CPL * (lane & 15), v);
+            const float marks = group16_sum((float)__popc((uint32_t)*reinterpret_cast<const Marks*>(L.named + rr * DG + CPL * (lane & 15))));
+            wrong = wrong || (rr < rows && (int)marks != k);
+        }
+    }
+    if (wrong) *bad = 1;
+}
+
+// Whether gsr_spmm_compressed lays the values out as rows first.  The values go sixteen at a time, ceil(k / 16) walks over the
+// edges, the rows at once, for a longer pass over the arrays before.  The call, values / rows, us: 1M rows, dg = 64, float32
+// k = 33 447 / 326, 64 555 / 366, 16-bit k = 24 275 / 240, 64 501 / 288; dg = 32, k = 17 248 / 207, 16-bit 245 / 181; long rows
+// (50k of mean length 236), dg = 64, k = 24 303 / 217, 16-bit 298 / 177.  float32 up to half of the columns on other graphs: one
+// or two walks over short lists (k = 24 285 us) are no slower than the 256-byte rows (326 at k = 33).
+static bool compressed_as_rows(const gsr_graph_t* g, int k, int dg, int32_t dtype) {
+    return k > 16 && (2 * k > dg || g->long_rows || dtype == GSR_BF16);
+}
+
 template <int DG, typename T>
 static gsr_status_t aggregate_impl(const gsr_graph_t* g, const void* vals, const int32_t* idx, int k, float* h_out,
                                    void* ws, int* bad, hipStream_t s) {
     const int64_t n = g->n;
     char* p = (char*)ws;
-    const Record<DG, T> rec{(T*)vals, nullptr, (uint8_t*)p};
-    p += align_up((size_t)n * k);
+    const bool as_rows = compressed_as_rows(g, k, DG, sizeof(T) == 2 ? GSR_BF16 : GSR_F32);
+    const Record<DG, T> rec{as_rows ? (T*)p : (T*)vals, nullptr, as_rows ? nullptr : (uint8_t*)p};
+    p += align_up(as_rows ? (size_t)n * DG * sizeof(T) : (size_t)n * k);
     float* part = (float*)p;
     // indices come from the caller: out-of-range or repeated columns are reported.  The kernels after the check are launched
     // before its answer is known (they read nothing wild whatever the indices are and write nothing where it is bad), so the
     // caller's thread waits once, for all of them, and the GPU not at all (54 us of gap at 1M rows).
-    int kp = 1;
-    while (kp < k) kp <<= 1;
-    const int64_t steps = (n + 64 / kp - 1) / (64 / kp);
-    const dim3 pgrid((unsigned)std::min<int64_t>((steps + 3) / 4, 16384));
     GSR_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), s));
-    hipLaunchKernelGGL((k_pack_columns<DG>), pgrid, dim3(256), 0, s, n, k, kp, idx, rec.cols, bad);
+    const int tiles = (int)((n + 15) / 16);
+    if (as_rows) {
+        hipLaunchKernelGGL((k_pack_rows<DG, T>), dim3((unsigned)std::min((tiles + 3) / 4, 8192)), dim3(256), 0, s, (int)n, k, (const T*)vals, idx,
+                           rec.vals, bad);
+    } else {
+        int kp = 1;
+        while (kp < k) kp <<= 1;
+        const int64_t steps = (n + 64 / kp - 1) / (64 / kp);
+        hipLaunchKernelGGL((k_pack_columns<DG>), dim3((unsigned)std::min<int64_t>((steps + 3) / 4, 16384)), dim3(256), 0, s, n, k, kp, idx,
+                           rec.cols, bad);
+    }
     CsrView v = make_view(g, false);
     if (g->a.hub.n_chunks > 0) {
         HubChunks hc{g->a.hub.ce0, g->a.hub.ce1, g->a.hub.n_chunks, g->long_rows};
-        hipLaunchKernelGGL((k_hub_records<DG, T>), dim3(hub_grid(g->a.hub.n_chunks)), dim3(256), 0, s, v, hc, rec, k, part);
+        const dim3 hg(hub_grid(g->a.hub.n_chunks));
+        if (as_rows) hipLaunchKernelGGL((k_hub_dense<DG, T>), hg, dim3(256), 0, s, v, hc, (const T*)rec.vals, (int64_t)DG, part, (float*)nullptr);
+        else hipLaunchKernelGGL((k_hub_records<DG, T>), hg, dim3(256), 0, s, v, hc, rec, k, part);
     }
     int *dn, *dx;
     tile_counters(g, &dn, &dx);
-    const int tiles = (int)((n + 15) / 16);
-    if (heavy_first(v.n_heavy, tiles, (unsigned)g->grid))
-        hipLaunchKernelGGL((k_aggregate_tile<DG, T, true>), dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles, rec, k,
-                           (const float*)part, h_out, dn, dx, (const int*)bad);
-    else
-        hipLaunchKernelGGL((k_aggregate_tile<DG, T, false>), dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles, rec, k,
-                           (const float*)part, h_out, dn, dx, (const int*)bad);
+    const bool deal = heavy_first(v.n_heavy, tiles, (unsigned)g->grid);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles, rec, k, (const float*)part, h_out, dn, dx,
+                           (const int*)bad);
+    };
+    if (as_rows) deal ? launch(k_aggregate_tile<DG, T, REC_ROWS, true>) : launch(k_aggregate_tile<DG, T, REC_ROWS, false>);
+    else deal ? launch(k_aggregate_tile<DG, T, REC_COLUMNS, true>) : launch(k_aggregate_tile<DG, T, REC_COLUMNS, false>);
     GSR_HIP_CHECK(hipGetLastError());
     int bad_h = 0;
     GSR_HIP_CHECK(hipMemcpyAsync(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -547,8 +624,11 @@ gsr_status_t gsr_spmm_noalloc(const gsr_graph_t* g, const float* x, int64_t ldx,
 
 size_t gsr_spmm_compressed_workspace(const gsr_graph_t* g, int32_t k, int32_t dg) {
     if (!g || k < 1 || dg < 1) return 0;
-    return align_up((size_t)g->n * k * 4 + 16) + align_up((size_t)g->n * 8) +
-           align_up((size_t)std::max(g->a.hub.n_chunks, 1) * dg * sizeof(float)) + 256;
+    // the columns as bytes, or the values as rows of either type; then the first-pass sums and the answer of the check
+    size_t lists = (size_t)g->n * k * 4 + (size_t)g->n * 8;
+    if (compressed_as_rows(g, k, dg, GSR_BF16)) lists = std::max(lists, (size_t)g->n * dg * 2);
+    if (compressed_as_rows(g, k, dg, GSR_F32)) lists = std::max(lists, (size_t)g->n * dg * 4);
+    return align_up(lists + 256) + align_up((size_t)std::max(g->a.hub.n_chunks, 1) * dg * sizeof(float)) + 256;
 }
 
 gsr_status_t gsr_spmm_compressed(const gsr_graph_t* g, const void* vals, const int32_t* idx, int32_t k, int32_t dg,

@@ -53,6 +53,8 @@ def sums_and_bound(rowptr, cols, vals, x):
     (64, 16, "f32", 512, 0), (64, 1, "f32", 512, 0), (64, 15, "f32", 512, 0), (64, 17, "f32", 512, 0), (64, 64, "f32", 512, 0),
     (32, 8, "f32", 512, 0), (32, 32, "f32", 512, 0), (64, 16, "bf16", 512, 0), (64, 33, "bf16", 512, 0), (32, 5, "bf16", 512, 0),
     (64, 16, "f32", 16, 16), (64, 40, "f32", 3, 64), (32, 20, "bf16", 8, 32),
+    # (laid out as rows first: k above 16 in 16-bit storage, above dg / 2 in float32)
+    (64, 17, "bf16", 512, 0), (64, 64, "bf16", 6, 4), (64, 33, "f32", 512, 0), (32, 17, "f32", 16, 16), (32, 31, "bf16", 512, 0),
 ])
 def test_value_gather_at_the_edges_of_runs_and_rounds(options, dg, k, dtype, threshold, chunk):
     options("hub_threshold", threshold)
@@ -69,15 +71,16 @@ def test_value_gather_at_the_edges_of_runs_and_rounds(options, dg, k, dtype, thr
     assert (np.abs(h - ref) <= bound).all(), float((np.abs(h - ref) / bound).max())
 
 
+@pytest.mark.parametrize("k,dtype", [(16, "f32"), (40, "f32"), (64, "f32"), (24, "bf16")])
 @pytest.mark.parametrize("wrong", ["negative", "past", "repeated"])
-def test_refused_indices_write_nothing_and_leave_the_graph_usable(wrong):
-    n, k, dg = 421, 16, 64
+def test_refused_indices_write_nothing_and_leave_the_graph_usable(wrong, k, dtype):
+    n, dg = 421, 64
     rowptr, cols, vals, g = graph_of(LENGTHS, n, 4)
     idx = torch.arange(k, dtype=torch.int32).repeat(n, 1)
     good = idx.clone().cuda()
     idx[300, 3] = {"negative": -1, "past": dg, "repeated": 5}[wrong]
     idx = idx.cuda()
-    v = torch.randn(n, k, device="cuda")
+    v = torch.randn(n, k, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
     h = torch.full((n, dg), 7.0, device="cuda")
     lib = gsr.lib()
     nbytes = lib.gsr_spmm_compressed_workspace(g.ptr, ctypes.c_int32(k), ctypes.c_int32(dg))
@@ -85,13 +88,13 @@ def test_refused_indices_write_nothing_and_leave_the_graph_usable(wrong):
 
     def call(i):
         return lib.gsr_spmm_compressed(g.ptr, ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(i.data_ptr()), ctypes.c_int32(k),
-                                       ctypes.c_int32(dg), ctypes.c_int32(0), ctypes.c_void_p(h.data_ptr()),
+                                       ctypes.c_int32(dg), ctypes.c_int32(0 if dtype == "f32" else 1), ctypes.c_void_p(h.data_ptr()),
                                        ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(nbytes), gsr._stream())
     assert call(idx) == gsr.GSR_ERR_INVALID_ARG
     assert bool((h == 7.0).all())
     assert call(good) == gsr.GSR_OK
     dense = np.zeros((n, dg))
-    dense[:, :k] = v.cpu().numpy()
+    dense[:, :k] = v.float().cpu().numpy()
     ref, bound = sums_and_bound(rowptr, cols, vals, dense)
     assert (np.abs(h.cpu().numpy() - ref) <= bound).all()
 
