@@ -130,7 +130,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         // during the weight product.  Measured per variant (1M-node workload, float32: forward 232 us early against 241
         // late, inverse 264 against 257; the fused inverse + dW kernel gains from late rows at D/C = 32 and loses at 64,
         // the 16-bit forward kernel the other way round).
-                constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
+        constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
         float xy[4][CPL], gy[WITH_DW ? 4 : 1][CPL];
         auto own_rows = [&]() {
 #pragma unroll
@@ -539,14 +539,16 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         const int r0 = t * 16;
         wave_sync();
         const int rpv = tile_rp_load(a.gt, r0, a.n, lane);
-        // what the epilogue needs of the tile's own rows is requested first
+        // what the epilogue needs of the tile's own rows is requested first (but for the masks in the one variant that would
+        // spill a register)
+        constexpr bool OWN_LATE = DEAL && !B3 && sizeof(T) == 2 && DG == 64;
         typename MaskOf<DG>::type own[4];
         float z[4][CPL];
 #pragma unroll
         for (int reg = 0; reg < 4; ++reg) {
             const int row = r0 + 4 * reg + tg;
             const size_t rowc = (size_t)(row < a.n ? row : a.n - 1);
-            own[reg] = a.own_mask[rowc];
+            if constexpr (!OWN_LATE) own[reg] = a.own_mask[rowc];
             if (a.norm == GSR_NORM_RMS) load_cols<CPL, T>(a.z + rowc * a.ldz + CPL * tj, z[reg]);
         }
         const bool has_hub = tile_begin(a.gt, rpv, L.rp, lane);
@@ -580,6 +582,7 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         for (int reg = 0; reg < 4; ++reg) {
             const int row = r0 + 4 * reg + tg;
             const bool ok = row < a.n;
+            if constexpr (OWN_LATE) own[reg] = a.own_mask[ok ? row : a.n - 1];
             const uint32_t bits = ok ? (uint32_t)(own[reg] >> (CPL * tj)) & ((1u << CPL) - 1u) : 0u;
             if (a.norm == GSR_NORM_RMS) {
                 // V = Z[I] * rinv, rinv = (mean Z^2 + eps)^-1/2:
@@ -605,8 +608,9 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         {
             // JC planes at a time: all their rows are requested before the first is written back (block 1 updates C - 1
             // planes; one plane after the other took 3.2 ms against 1.2 ms for a one-plane launch at 8M rows, C = 8, 16-bit
-            // rows of 32 columns).  float32 at 64 columns: two planes spill registers, 285 us per launch against 273
-                        constexpr int JC = CPL <= 2 ? 4 : sizeof(T) == 4 ? 1 : 2;
+            // rows of 32 columns).  float32 at 64 columns: two planes spill registers, 285 us per launch against 273; at 32
+            // columns four do.
+            constexpr int JC = sizeof(T) == 4 ? (CPL <= 2 ? 2 : 1) : CPL <= 2 ? 4 : 2;
             if (a.ndst == 1) {          // the common case on its own, so that it requests nothing twice
                 float g[4][CPL];
 #pragma unroll
