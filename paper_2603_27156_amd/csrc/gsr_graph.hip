@@ -567,11 +567,14 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     // With fewer than two tiles per resident wave the cut at 16 is better still (the same workload: 9.4 ms against 10.6;
     // 12 / 8: 9.6 / 9.8; chunks of 32 instead of 64: 9.7).
     const bool few_tiles = (n + 15) / 16 < (int64_t)16 * full_grid, very_few_tiles = (n + 15) / 16 < (int64_t)8 * full_grid;
-    // With at most a tile per resident wave and no row above 160 entries nothing is split: two launches per block (one in
+    // With at most a tile per resident wave and no row above 160 entries (of A^T neither) nothing is split: two launches per block (one in
     // the forward sweep) cost more than the longest tile's extra rounds.  Steps of four layers, cut at 16 / not cut: 2,000
     // nodes (rows up to 74) 401 / 285 us, 10,000 nodes 890 / 616, 20,000 (up to 131) 627 / 559; 40,000 (up to 257)
     // 784 / 947, 60,000 (up to 371) 1,390 / 1,755.
-    const bool short_rows = (n + 15) / 16 <= (int64_t)4 * full_grid && g->max_degree <= 160;
+    int64_t longest = g->max_degree;
+    if (!symmetric)
+        for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, t.rp[i + 1] - t.rp[i]);
+    const bool short_rows = (n + 15) / 16 <= (int64_t)4 * full_grid && longest <= 160;
     const int64_t hub_threshold = options().hub_threshold > 0 ? std::min<int64_t>(options().hub_threshold, INT32_MAX)
                                   : long_rows ? 1 : short_rows ? 160 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
     // (the kernels hold both as 32 bits, and a row has fewer than 2^31 entries: more than that means "never cut")

@@ -153,6 +153,27 @@ def test_short_rows_are_not_split_on_a_small_graph(longest):
     assert (np.abs(y - ref) <= bound).all()
 
 
+@pytest.mark.parametrize("sinks", [160, 161])
+def test_short_rows_of_the_transpose_count_as_well(sinks):
+    """A directed graph: rows of A are short, a net of A^T (a column of A) has `sinks` entries."""
+    n = 500
+    rng = np.random.default_rng(9)
+    rows = [np.sort(rng.choice(np.arange(1, n), size=20, replace=False)) for _ in range(n)]
+    for r in range(sinks):
+        rows[r] = np.concatenate([[0], rows[r][1:]])
+    rowptr, cols = np.arange(n + 1, dtype=np.int32) * 20, np.concatenate(rows).astype(np.int32)
+    vals = rng.standard_normal(len(cols)).astype(np.float32)
+    g = gsr.gsr_graph_create(rowptr, cols, vals, flags=0)
+    assert gsr.gsr_graph_info(g)["n_hub_rows"] == (0 if sinks <= 160 else n)       # not cut, or cut at 16 entries
+    x = torch.randn(n, 64, device="cuda")
+    for transpose in (0, 1):
+        import scipy.sparse as sp
+        a = sp.csr_matrix((vals, cols, rowptr), shape=(n, n))
+        a = (a.T if transpose else a).tocsr()
+        ref, bound = sums_and_bound(a.indptr, a.indices, a.data, x.cpu().numpy().astype(np.float64))
+        assert (np.abs(gsr.gsr_spmm(g, x, transpose=bool(transpose)).cpu().numpy() - ref) <= bound).all()
+
+
 @pytest.mark.parametrize("sinks,width", [(1_024, 64), (1_025, 64), (5_000, 64), (5_000, 16), (2_500, 32)])
 def test_nets_of_thousands_of_sinks_on_a_small_graph(sinks, width):
     n = 6_001
