@@ -195,7 +195,7 @@ gsr_status_t gsr_spmm(const gsr_graph_t* g, const float* x, int64_t ldx, int32_t
  * results; the scratch gsr_spmm keeps in the graph (the tile counters of its sweep and the first-pass sums of split
  * rows) lives in a fixed device array of the library instead, 4.1 MiB per GPU, held until the process ends.  The call
  * allocates and frees nothing and only launches kernels.  Limits: at most 16,384 first-pass chunks (rows above
- * "hub_threshold" stored entries, cut every "hub_chunk"), else GSR_ERR_UNSUPPORTED; the graph's device must be the
+ * "hub_threshold" stored entries, cut every "hub_chunk" or, where that is left to the library, by its rule), else GSR_ERR_UNSUPPORTED; the graph's device must be the
  * current one.  All calls on one GPU share the array: two that overlap (different streams or threads) race. */
 gsr_status_t gsr_spmm_noalloc(const gsr_graph_t* g, const float* x, int64_t ldx, int32_t width, float* y,
                               int64_t ldy, int32_t transpose, void* stream);
@@ -213,7 +213,10 @@ gsr_status_t gsr_spmm_compressed(const gsr_graph_t* g, const void* vals, const i
 
 /* ---- layers and the step ----
  *
- * Bytes of device workspace the layer / step calls need for (cfg, g).  gsr_step's figure
+ * Bytes of device workspace the layer / step calls need for (cfg, g).  The layer's figure holds, among others, a record
+ * per group: N k values of cfg->dtype and N k bytes naming their columns, or (records held as rows) N D/C values, and the
+ * column masks; the partial rows of split rows; and with D/C above 64 always two float32 planes of N D/C (the neighbour
+ * sums H and A^T dY), up to 64 one, on graphs large enough that a block's backward runs in two kernels.  gsr_step's figure
  * includes its activation and gradient arena and does not grow with cfg->l (the reversible
  * scheme's memory is independent of depth, Sections 1 and 2) unless cfg->save_indices is set. */
 gsr_status_t gsr_workspace_size(const gsr_config_t* cfg, const gsr_graph_t* g, size_t* layer_bytes,

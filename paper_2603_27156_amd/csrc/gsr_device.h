@@ -436,8 +436,8 @@ __device__ __forceinline__ float group16_sum(float v) {
 // With 16-bit stored values the product P * X runs on v_mfma_f32_16x16x16_bf16: sixteen edges per
 // instruction instead of four.  The K index is permuted so that nothing has to move between
 // lanes: K slot 4 kk + u of lane group kk is edge kk of staged group u (u = 0..3), which is what
-// the lane already holds after four loads.  X is exact in bf16; a_ij is split into two bf16 terms
-// (a = hi + lo + O(2^-17 a)), one MFMA each, float32 accumulation.
+// the lane already holds after four loads.  X is exact in bf16; a_ij is split into three bf16 terms
+// (a = hi + mid + lo exactly), one MFMA each, float32 accumulation.
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 
 // upper halves of four float32 words as four bf16
@@ -488,9 +488,6 @@ __device__ __forceinline__ bool tile_begin(const CsrView& g, int rpv, int* s_rp,
     wave_sync();
     const bool hub = lane < 16 && (s_rp[lane + 1] - rpv) > g.hub_threshold;
     return ballot(hub) != 0ull;
-}
-__device__ __forceinline__ bool tile_begin(const CsrView& g, int r0, int n, int* s_rp, int lane) {
-    return tile_begin(g, tile_rp_load(g, r0, n, lane), s_rp, lane);
 }
 
 // tile row of edge e: the last row boundary at or below e
@@ -929,7 +926,7 @@ __device__ __forceinline__ void tile_gather(const CsrView& g, const float* __res
 // A wave multiplies its 16 x DG tile (staged in LDS, row stride tile_ld) by a DG x DG matrix with
 // v_mfma_f32_16x16x4_f32:
 //   A[i][kk]: lane = kk*16 + i;  B[kk][j]: lane = kk*16 + j;  D[4*(lane/16)+r][lane%16] in reg r.
-// The DG x DG weight matrix (row stride ldw in memory: DG, or more when it is a block of a wider matrix) sits in LDS (odd row stride DG + 1, which spreads the four k-rows of a
+// The DG x DG weight matrix sits in LDS (odd row stride DG + 1, which spreads the four k-rows of a
 // B operand over different banks), loaded once per workgroup; transposed = true stores W^T.
 template <int DG>
 struct WLds {
@@ -938,7 +935,7 @@ struct WLds {
 };
 
 template <int DG>
-__device__ __forceinline__ void load_w_lds(const float* __restrict__ w, int ldw, bool transposed, WLds<DG>& l) {
+__device__ __forceinline__ void load_w_lds(const float* __restrict__ w, bool transposed, WLds<DG>& l) {
     // eight loads of a thread in flight at a time: on a graph where a launch is one short tile per wave this
     // prologue is a good part of the launch, and one load after the other is a round trip to memory each
     // (the transposed form, whose loads touch a cache line per lane, was a tenth slower that way and keeps the plain loop)
@@ -947,15 +944,14 @@ __device__ __forceinline__ void load_w_lds(const float* __restrict__ w, int ldw,
     if (transposed) {
         for (int i = threadIdx.x; i < DG * DG; i += nt) {
             const int r = i / DG, cc = i % DG;
-            l.w[r * WLds<DG>::WP + cc] = w[cc * ldw + r];
+            l.w[r * WLds<DG>::WP + cc] = w[cc * DG + r];
         }
     } else {
         for (int i0 = threadIdx.x; i0 < DG * DG; i0 += NL * nt) {
             float v[NL];
 #pragma unroll
             for (int u = 0; u < NL; ++u) {
-                const int i = i0 + u * nt < DG * DG ? i0 + u * nt : 0;
-                v[u] = w[(i / DG) * ldw + i % DG];
+                v[u] = w[i0 + u * nt < DG * DG ? i0 + u * nt : 0];
             }
 #pragma unroll
             for (int u = 0; u < NL; ++u) {
@@ -990,9 +986,12 @@ __device__ __forceinline__ void mfma_tile(const float* st, const WLds<DG>& wl, f
 // ---- the same products on the bf16 matrix pipe, exact to float32 rounding --------------------------------
 // A float32 value is the exact sum of three bf16 terms (8 + 8 + 8 significant bits: hi = the value truncated to bf16,
 // mid = the remainder truncated, lo = what is left).  A product a b is then the sum of nine exact bf16 products, of
-// which the six with the largest weights (hi hi, hi mid, mid hi, hi lo, mid mid, lo hi) carry it to 2^-24 relative:
-// what a float32 multiply would round away.  v_mfma_f32_16x16x16_bf16 forms such products exactly and adds them in
-// float32, takes 16 K-slots per instruction and, unlike the float32 matrix instructions of this chip, runs beside
+// which the six with the largest weights (hi hi, hi mid, mid hi, hi lo, mid mid, lo hi) are taken.  What the other three
+// would add is 2^-24.5 of the product on average and 2^-21.1 at most (normally distributed factors; a float32 multiply:
+// 2^-25.5 and 2^-24); over a row of H W_i the sum's own rounding covers it: Y's error against 64 bits is the float32
+// instructions' or a little less (50k nodes of mean degree 236, groups of 192: 5.5e-8 against 5.6e-8; ten more draws of
+// such graphs and widths: 1 - 5 % less each).  (A long sum over rows, dW, is another matter: see mfma_outer.)
+// v_mfma_f32_16x16x16_bf16 takes 16 K-slots per instruction and, unlike the float32 matrix instructions of this chip, runs beside
 // the vector pipe, so the six products of a 16-deep step cost less than the one float32 instruction sequence they
 // replace and hide under the vector work of the other waves.
 // W is kept in LDS already split and laid out as B operands: entry [term][s][cb][lane] holds, for lane (kk = lane / 16,
@@ -1626,13 +1625,12 @@ struct TileWalk {
     __device__ __forceinline__ void finish() { tile_finish(td); }
 };
 
-// ---- first pass over the chunks of very long rows ------------------------------------------------
-// One wave per chunk, through the staging and the wide loads of the tile gathers: the chunk is
-// treated as a tile whose row 0 owns every edge, so all of a chunk's neighbours are in flight at
-// once (a chain of one row pointer, the edges, the masks and the values instead of one such chain
-// per edge).  The sums form in ordinary arithmetic (ONE_ROW of the gathers): lane (kk, j) adds the
-// edges kk, kk + 4, .. for its columns, the four lane groups are added at the end.
-// part[chunk][DG] receives the un-scaled partial row.
+// ---- first pass over the chunks of split rows ------------------------------------------------
+// One wave per chunk, ordinary arithmetic.  Dense rows (hub_dense_pass: dY, the operand of gsr_spmm, records held as rows) go
+// through the staging and the wide loads of the tile gathers, the chunk treated as a tile whose row 0 owns every edge
+// (ONE_ROW): lane (kk, j) adds the edges kk, kk + 4, .. for its columns, and the four lane groups are added at the end.
+// Records of values go a lane per value into rows of sums in LDS, four edges at a time (hub_value_rows_pass), or as many as
+// their values leave lanes for (hub_values_pass).  part[chunk][DG] receives the un-scaled partial row.
 struct HubChunks {
     const int32_t* ce0;
     const int32_t* ce1;

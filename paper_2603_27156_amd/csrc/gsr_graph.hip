@@ -534,12 +534,11 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     g->symmetric = symmetric;
     g->has_transpose = true;
     // Rows above the threshold are cut into chunks that a first pass sums, one wave per chunk.  Sparse graphs with a few
-    // very long rows: 512 / 64.  Graphs whose mean row is long (the 49,600-node, 11.7M-entry workload shaped like the
-    // paper's Table 1: 871 ms per step with 512 / 64, 661 with 64 / 64, 566 with 64 / 256) are better served when nearly
-    // every row goes through the first pass, whose lanes add a row's entries in ordinary arithmetic instead of spending
-    // a 16-row matrix product on them.  Every row of two entries or more, in fact: a launch of a tile kernel is one
-    // tile per wave there, and it ended with the few tiles that still had short rows to gather themselves (that stage
-    // 6 us at the median, 26 us at most; 503 ms per step with the cut at 64, 460 at 32, 445 at 8, 443 at 1).
+    // very long rows: 512 / 64.  On graphs whose mean row is long (50k nodes, 11.7M entries, shaped like the paper's Table 1)
+    // nearly every row goes through the first pass: a launch of a tile kernel is one tile per wave there, and it ends with the
+    // tiles that have rows to gather themselves.  Steps of four layers, cut at 1 / 8 / 64 / 512 entries: two groups of 192,
+    // k = 16 8,971 / 9,011 / 9,241 / 10,234 us, six of 64 13,143 / 13,174 / 13,655 / 16,356, k = 32 15,289 / 14,952 / 16,005 /
+    // 22,206.
     const bool long_rows = g->nnz >= 64 * n;
     g->long_rows = long_rows;
 
@@ -552,25 +551,24 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     int grid = options().max_workgroups > 0 ? (int)options().max_workgroups : g->num_cus * 4;
     g->grid = std::max(8, grid / 8 * 8);
     const int full_grid = g->grid;
-    // A graph of a few hundred tiles is served best by a workgroup per two tiles (every workgroup of a layer kernel
-    // first loads and splits W_i): on the 2,000-node workload, 125 tiles, the step takes 0.35 ms with 64 workgroups
-    // per launch against 0.47 with 512, 0.37 with 256, 0.40 with 16.
+    // A graph of a few hundred tiles is served by a workgroup per two tiles (every workgroup of a layer kernel first loads and
+    // splits W_i): a step of four layers on 2,000 nodes, 125 tiles, with 16 / 32 / 64 / 128 / 256 / 512 workgroups per launch
+    // 456 / 295 / 284 / 281 / 282 / 286 us.
     if (options().max_workgroups <= 0) {
         const int64_t by_tiles = std::max<int64_t>(64, ((n + 15) / 16 / 2 + 7) / 8 * 8);
         if (by_tiles < g->grid) g->grid = (int)by_tiles;
     }
     // Small graphs (fewer than four tiles per resident wave: a launch is as long as its longest tile, and the heavy
-    // tiles are not dealt out first) are cut at 64 as well, with chunks of 64: on the 100k-node workload (6,250 tiles
-    // for 4,096 waves, rows of up to 575 entries) the step takes 11.5 ms against 16.0 with the cut at 512, while the
-    // 1M-node workload (15 tiles per wave) is best left at 512 (79.0 ms per 16 layers against 79.7 / 82.4 / 82.7 at
-    // 256 / 128 / 64).
-    // With fewer than two tiles per resident wave the cut at 16 is better still (the same workload: 9.4 ms against 10.6;
-    // 12 / 8: 9.6 / 9.8; chunks of 32 instead of 64: 9.7).
+    // tiles are not dealt out first) are cut at 64, with chunks of 64, with fewer than two tiles per resident wave at 16; larger
+    // ones are best left at 512.  Steps of four layers of two groups of 64, cut at 16 / 64 / 512, us: 60k nodes 877 / 939 /
+    // 1,096, 100k 1,211 / 1,347 / 1,667, 130k (two tiles per wave) 1,478 / 1,516 / 1,986, 200k 1,990 / 2,132 / 2,499, 260k
+    // 2,418 / 2,555 / 2,773, 400k 3,319 / 3,430 / 3,283, 1M 7,590 / 7,563 / 7,256 (so the cut at 16 would serve up to four
+    // tiles per wave by now).
     const bool few_tiles = (n + 15) / 16 < (int64_t)16 * full_grid, very_few_tiles = (n + 15) / 16 < (int64_t)8 * full_grid;
-    // With at most a tile per resident wave and no row above 160 entries (of A^T neither) nothing is split: two launches per block (one in
-    // the forward sweep) cost more than the longest tile's extra rounds.  Steps of four layers, cut at 16 / not cut: 2,000
-    // nodes (rows up to 74) 401 / 285 us, 10,000 nodes 890 / 616, 20,000 (up to 131) 627 / 559; 40,000 (up to 257)
-    // 784 / 947, 60,000 (up to 371) 1,390 / 1,755.
+    // With at most a tile per resident wave and no row above 160 entries (of A^T neither) nothing is split: two launches per
+    // block (one in the forward sweep) cost more than the longest tile's extra rounds.  The same steps, cut at 16 / not cut:
+    // 2,000 nodes (rows up to 74) 487 / 374 us, 10,000 554 / 415, 20,000 (up to 131) 628 / 560; 40,000 (up to 257) 786 / 856,
+    // 60,000 (up to 371) 877 / 1,096.
     int64_t longest = g->max_degree;
     if (!symmetric)
         for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, t.rp[i + 1] - t.rp[i]);
@@ -578,13 +576,16 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     const int64_t hub_threshold = options().hub_threshold > 0 ? std::min<int64_t>(options().hub_threshold, INT32_MAX)
                                   : long_rows ? 1 : short_rows ? 160 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
     // (the kernels hold both as 32 bits, and a row has fewer than 2^31 entries: more than that means "never cut")
-    const int64_t hub_chunk = options().hub_chunk > 0 ? std::min<int64_t>(options().hub_chunk, INT32_MAX) : (long_rows ? 512 : 64);      // (Table-1-shaped graph, rows of up to 390 entries: 289 / 274 / 263 / 263 ms per step with chunks of 128 / 256 / 512 / 1,024)
+    const int64_t hub_chunk = options().hub_chunk > 0 ? std::min<int64_t>(options().hub_chunk, INT32_MAX) : (long_rows ? 512 : 64);      // (long rows, up to 390 entries, the steps above with chunks of 64 / 128 / 256 / 512 / 1,024: two groups of 192 11,358 / 10,332 / 9,787 / 8,971 / 8,965 us)
     g->hub_threshold = (int32_t)hub_threshold;
     g->hub_chunk = (int32_t)hub_chunk;
     // (with more tiles per wave the tile with the long nets starts early and is hidden: there the first pass is better short)
     const bool grow = few_tiles && !long_rows && options().hub_chunk == 0;
     g->hub_values = options().hub_values == 1 ? 2 : (options().hub_values == 0 && long_rows) ? 1 : 0;
-    g->split_backward = !(long_rows || (n + 15) / 16 < (int64_t)8 * full_grid);    // (not with fewer than two tiles per resident wave)
+    // (not with fewer than two tiles per resident wave: the same steps, fused / split, 2,000 nodes 374 / 407 us, 100k 1,213 /
+    // 1,304, 130k 1,482 / 1,611.  On long rows either way takes the same time, backward layer of two groups of 64 754 / 755 us,
+    // and the fused one less memory)
+    g->split_backward = !(long_rows || (n + 15) / 16 < (int64_t)8 * full_grid);
 
     gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, grow, (hipStream_t)stream, &g->a);
     if (st == GSR_OK) {

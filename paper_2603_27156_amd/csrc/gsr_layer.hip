@@ -39,8 +39,7 @@ struct BlockArgs {
     Record<DG, T> in;       // record of Y_{i-1}
     int k;
     const float* hub_part;  // first-pass partial rows of split rows
-    const float* w;         // W_i [DG][DG], row stride ldw (DG, or D/C when the block is a part of a wider matrix)
-    int ldw;
+    const float* w;         // W_i [DG][DG]
     T* plane;               // X_i on entry / Y_i on return (or the reverse), row stride ld
     int64_t ld;
     Record<DG, T> out;      // record of the row written (out.mask == NULL: none)
@@ -74,8 +73,8 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
     WaveLds<DG, true>& L = lds[wave];
     float* st_h = L.st;
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
-    if constexpr (B3) load_w_lds_b3<DG>(a.w, a.ldw, false, wl);
-    else load_w_lds<DG>(a.w, a.ldw, false, wl);
+    if constexpr (B3) load_w_lds_b3<DG>(a.w, DG, false, wl);
+    else load_w_lds<DG>(a.w, false, wl);
     f32x4 dw[WITH_DW ? DG / 16 : 1][WITH_DW ? DG / 16 : 1];
     if constexpr (WITH_DW) {
 #pragma unroll
@@ -456,8 +455,7 @@ struct GradArgs {
     const T* dy;            // dY_i (complete), row stride ldg
     int64_t ldg;
     const float* hub_part;
-    const float* w;         // W_i, row stride ldw
-    int ldw;
+    const float* w;         // W_i [DG][DG]
     const M* own_mask;      // columns recorded for Y_{i-1}
     const T* z;             // Y_{i-1} rows (RMS only), row stride ldz
     int64_t ldz;
@@ -526,8 +524,8 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
     static_assert(GRAD_WAVES >= 4 && sizeof(lds) >= 256 * sizeof(float), "dw_reduce_slices works with the first 256 threads");
     if (a.dw_out) dw_reduce_slices<DG * DG>(a.dw_partial, a.dw_parts, a.dw_out, reinterpret_cast<float*>(lds));
-    if constexpr (B3) load_w_lds_b3<DG>(a.w, a.ldw, true, wl);
-    else load_w_lds<DG>(a.w, a.ldw, true, wl);
+    if constexpr (B3) load_w_lds_b3<DG>(a.w, DG, true, wl);
+    else load_w_lds<DG>(a.w, true, wl);
     TileDraws td = tile_draws(a.tiles, a.draws, a.draws_done);
     TileDeal deal{0, 0, 0, false};
     if constexpr (DEAL) deal = tile_deal(a.gt);
@@ -1507,10 +1505,9 @@ static bool launch_hub_both(const Ctx<DG, T>& x, const Record<DG, T>& in, const 
 // compute unit) leaves H in memory and k_dw takes H^T dY_i in a pass of its own: 476 -> 320 + 112 us per block on the 1M-node
 // workload when it was cut in two (246 + 88 us now) for 512 more bytes per row.  16-bit storage at D/C = 32: the fused kernel
 // (inverse + dW accumulators): 1M nodes, 152 us fused against 143 + 32 us.
-// Graphs with fewer than two tiles per resident wave, or with all rows in the first pass (a launch there is one or two
-// short tiles per wave, and two more launches per block cost more than the occupancy gains: 0.56 against 0.70 ms per
-// step on the 2,000-node workload, 487 against 496 ms on the Table-1-shaped one, 8.7 against 9.0 ms on the 100k-node
-// one) keep the fused kernel in float32 as well; it uses the same sums, so whichever way a block's backward runs
+// Graphs with fewer than two tiles per resident wave (a launch there is one or two short tiles per wave, and two more launches
+// per block cost more than the occupancy gains), or with all rows in the first pass, keep the fused kernel in float32 as well
+// (figures where the rule is made, with the graph); it uses the same sums, so whichever way a block's backward runs
 // it rebuilds the bits the plain inverse rebuilds.
 template <int DG, typename T>
 static bool split_dw(const gsr_graph_t* g) { return (sizeof(T) == 4 || DG == 64) && g->split_backward; }
@@ -1527,7 +1524,7 @@ static unsigned launch_block(const Ctx<DG, T>& x, int mode, const Record<DG, T>&
     a.g = make_view(x.g, false);
     a.n = (int)x.cfg->n; a.tiles = x.tiles;
     a.in = in; a.k = x.cfg->k;
-    a.hub_part = x.hub_part(); a.w = w; a.ldw = DG; a.plane = plane; a.ld = ld;
+    a.hub_part = x.hub_part(); a.w = w; a.plane = plane; a.ld = ld;
     a.out = out; a.out_given = out_given;
     a.norm = x.cfg->norm; a.eps = x.cfg->eps; a.dy = dy; a.ldg = ldg; a.dw_partial = x.dw_partial();
     if (mode != 2) tile_counters(x.g, &a.draws, &a.draws_done);
@@ -1569,7 +1566,6 @@ static void launch_grad(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const flo
                         bool first_pass_done = false) {
     if (!first_pass_done) launch_hub_dense<DG, T>(x, dy, ldg);
     GradArgs<DG, T> a;
-    a.ldw = DG;
     a.gt = make_view(x.g, true);
     a.n = (int)x.cfg->n; a.tiles = x.tiles; a.dy = dy; a.ldg = ldg; a.hub_part = first_pass_done ? x.hub_part2() : x.hub_part();
     a.w = w;
