@@ -59,7 +59,7 @@ def kernel_class(name: str):
 
 
 def short(name: str) -> str:
-    name = re.sub(r"^void ", "", name)
+    name = re.sub(r"^void ", "", name).replace("(gsr::RecordForm)", "")
     return re.sub(r"\(.*", "", name).replace("gsr::", "")
 
 

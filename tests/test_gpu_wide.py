@@ -1,6 +1,6 @@
 """Groups wider than one 64-column tile: D/C = 128, 192, 256, the widths of the paper's own models (Section 5: hidden
-256 or 384 in two groups; Algorithm 1 splits into two).  They run as D/C / 64 column blocks through the 64-column
-kernels with GS over the whole row, and are compared with the oracle like every other width."""
+256 or 384 in two groups; Algorithm 1 splits into two).  They run as passes over planes of 64 columns with GS over the
+whole row, and are compared with the oracle like every other width."""
 import numpy as np
 import pytest
 
