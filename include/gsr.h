@@ -171,6 +171,7 @@ gsr_status_t gsr_graph_info(const gsr_graph_t* g, int64_t* n, int64_t* nnz, int6
  * Any output pointer may be NULL. */
 gsr_status_t gsr_graph_export(const gsr_graph_t* g, int64_t* rowptr, int32_t* colidx, float* vals);
 
+/* May be called while another stream's work is being captured into a HIP graph (the captured work must not use `g`). */
 gsr_status_t gsr_graph_destroy(gsr_graph_t* g);
 
 /* ---- operators exposed as the paper defines them ----

@@ -647,11 +647,16 @@ gsr_status_t gsr_graph_export(const gsr_graph_t* g, int64_t* rowptr, int32_t* co
 
 gsr_status_t gsr_graph_destroy(gsr_graph_t* g) {
     if (!g) return GSR_OK;
+    // A handle may go whenever a garbage collector finds it, also while a stream is being captured: freeing memory is nothing
+    // the capture records, but outside the relaxed mode it would end it with an error.
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     if (!g->symmetric) free_csr(g->at);
     free_csr(g->a);
     if (g->scratch) (void)hipFree(g->scratch);
     if (g->draws) (void)hipFree(g->draws);
     if (g->dinv) (void)hipFree(g->dinv);
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
     delete g;
     return GSR_OK;
 }

@@ -440,6 +440,31 @@ def test_layer_with_an_odd_number_of_launches_replays_from_a_graph():
         assert torch.equal(y, want), rep
 
 
+def test_a_graph_destroyed_during_a_capture_leaves_the_capture_whole():
+    """As a garbage collection in the middle of a capture does with a handle that nobody holds any more."""
+    c = Case(workloads()["cfg1s"], 0, PLANAR)
+    other = gsr.gsr_graph_create(c.inp.rowptr, c.inp.colidx)
+    W = torch.from_numpy(c.inp.weights[0]).to(c.dev)
+    ws = torch.empty(gsr.gsr_workspace_size(c.gg, c.gcfg)[0], dtype=torch.uint8, device=c.dev)
+    x0 = c.to_dev(c.x0_on_grid())
+    want, x = x0.clone(), x0.clone()
+    gsr.gsr_layer_forward(c.gg, c.gcfg, W, want, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gsr.gsr_layer_forward(c.gg, c.gcfg, W, x, ws)
+        other.destroy()
+    for _ in range(3):
+        x.copy_(x0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x, want)
+        y = x0.clone()
+        gsr.gsr_layer_forward(c.gg, c.gcfg, W, y, ws)          # eager work between the replays
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
+
+
 @pytest.mark.parametrize("workgroups,heavy_share", [(8, 0.3), (8, 1.0), (0, 1.0), (16, 0.05)])
 def test_heavy_tiles_dealt_before_the_sweep(workgroups, heavy_share):
     """Graphs on which the layer kernels deal the long tiles (more than 512 stored entries) to their waves before
