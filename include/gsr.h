@@ -117,8 +117,8 @@ const char* gsr_version(void);
 /* Process-wide tunables, read by the next gsr_graph_create:
  *   "hub_threshold"   rows with more stored entries than this are reduced in two passes (Section 2 notes nets
  *                     with more than 8,000 neighbours); 0, the default: 512; 64 or 16 on graphs with fewer than
- *                     four / two 16-row tiles per resident wave; 160 on graphs with at most one and no row of A or A^T
- *                     above 160 entries (nothing is cut); 1 on graphs whose mean row has 64 stored entries or
+ *                     four / two 16-row tiles per resident wave; 160 with at most one and no row above 160
+ *                     entries, A and A^T each by its own rows (nothing is cut); 1 on graphs whose mean row has 64 stored entries or
  *                     more (every row of two entries or more then goes through the first pass)
  *   "hub_chunk"       neighbours per first-pass partial sum; 0, the default: 64 (more for rows above 1,024 entries on
  *                     graphs with fewer than four 16-row tiles per resident wave), or 512 on graphs of long rows

@@ -179,6 +179,7 @@ static gsr_status_t upload_csr(const HostCsr& h, int64_t n, int64_t threshold, i
         }
         if (e > kHeavyTileEdges) heavy.push_back((int32_t)(t0 / 16));
     }
+    out->hub_threshold = (int32_t)threshold;
     out->n_heavy = (int32_t)heavy.size();
     split_heavy(heavy, (int)((n + 15) / 16), out);
     GSR_TRY(upload(heavy, &out->heavy));
@@ -565,19 +566,31 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     // 2,418 / 2,555 / 2,773, 400k 3,319 / 3,430 / 3,283, 1M 7,590 / 7,563 / 7,256 (so the cut at 16 would serve up to four
     // tiles per wave by now).
     const bool few_tiles = (n + 15) / 16 < (int64_t)16 * full_grid, very_few_tiles = (n + 15) / 16 < (int64_t)8 * full_grid;
-    // With at most a tile per resident wave and no row above 160 entries (of A^T neither) nothing is split: two launches per
+    // With at most a tile per resident wave and no row above 160 entries nothing is split: two launches per
     // block (one in the forward sweep) cost more than the longest tile's extra rounds.  The same steps, cut at 16 / not cut:
     // 2,000 nodes (rows up to 74) 487 / 374 us, 10,000 554 / 415, 20,000 (up to 131) 628 / 560; 40,000 (up to 257) 786 / 856,
-    // 60,000 (up to 371) 877 / 1,096.
-    int64_t longest = g->max_degree;
-    if (!symmetric)
-        for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, t.rp[i + 1] - t.rp[i]);
-    const bool short_rows = (n + 15) / 16 <= (int64_t)4 * full_grid && longest <= 160;
-    const int64_t hub_threshold = options().hub_threshold > 0 ? std::min<int64_t>(options().hub_threshold, INT32_MAX)
-                                  : long_rows ? 1 : short_rows ? 160 : very_few_tiles ? 16 : few_tiles ? 64 : 512;
-    // (the kernels hold both as 32 bits, and a row has fewer than 2^31 entries: more than that means "never cut")
+    // 60,000 (up to 371) 877 / 1,096.  A and A^T each by their own rows: a directed graph may have short fan-ins and nets of
+    // thousands of sinks (60,000 nodes, backward of a layer 166 us with A^T uncut up to 160, 151 cut at 16).
+    auto threshold_of = [&](const HostCsr& m) -> int64_t {
+        if (options().hub_threshold > 0) return std::min<int64_t>(options().hub_threshold, INT32_MAX);
+        if (long_rows) return 1;
+        int64_t longest = 0;
+        for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, m.rp[i + 1] - m.rp[i]);
+        if ((n + 15) / 16 <= (int64_t)4 * full_grid && longest <= 160) return 160;
+        return very_few_tiles ? 16 : few_tiles ? 64 : 512;
+    };
+    const int64_t hub_threshold = threshold_of(a);
+    int64_t t_threshold = symmetric ? hub_threshold : threshold_of(t);
+    if (hub_threshold == 160 && t_threshold == 16) {       // (not beyond what gsr_spmm_noalloc can take)
+        int64_t chunks = 0;
+        for (int64_t i = 0; i < n; ++i) {
+            const int64_t len = t.rp[i + 1] - t.rp[i];
+            chunks += len > 16 ? (len + 63) / 64 : 0;
+        }
+        if (chunks > kNoAllocMaxChunks) t_threshold = 160;
+    }
+    // (the kernels hold thresholds and chunks as 32 bits, and a row has fewer than 2^31 entries: more means "never cut")
     const int64_t hub_chunk = options().hub_chunk > 0 ? std::min<int64_t>(options().hub_chunk, INT32_MAX) : (long_rows ? 512 : 64);      // (long rows, up to 390 entries, the steps above with chunks of 64 / 128 / 256 / 512 / 1,024: two groups of 192 11,358 / 10,332 / 9,787 / 8,971 / 8,965 us)
-    g->hub_threshold = (int32_t)hub_threshold;
     g->hub_chunk = (int32_t)hub_chunk;
     // (with more tiles per wave the tile with the long nets starts early and is hidden: there the first pass is better short)
     const bool grow = few_tiles && !long_rows && options().hub_chunk == 0;
@@ -590,7 +603,7 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, grow, (hipStream_t)stream, &g->a);
     if (st == GSR_OK) {
         if (symmetric) g->at = g->a;
-        else st = upload_csr(t, n, hub_threshold, hub_chunk, grow, (hipStream_t)stream, &g->at);
+        else st = upload_csr(t, n, t_threshold, hub_chunk, grow, (hipStream_t)stream, &g->at);
     }
     if (st == GSR_OK) {
         const size_t chunks = (size_t)std::max(std::max(g->a.hub.n_chunks, g->at.hub.n_chunks), 1);

@@ -90,6 +90,7 @@ struct Csr {
     float* av = nullptr;    // device [nnz]
     uint8_t* er = nullptr;  // device [nnz]  row of the entry modulo 16 (behind av, in its allocation)
     HubPlan hub;
+    int32_t hub_threshold = 512;   // rows longer than this are split
     int32_t* heavy = nullptr;  // device [n_heavy]: the heavy tiles, ascending
     int32_t n_heavy = 0;
     int32_t heavy_ptr[9] = {};   // where the entries of every eighth of the tiles start in the list
@@ -106,7 +107,6 @@ struct gsr_graph {
     bool split_backward = true;   // float32: the backward of a block as inverse kernel + k_dw (large graphs), else fused
     bool long_rows = false;  // the mean row has 64 stored entries or more: nearly every row goes through the first pass
     int hub_values = 0;      // the first pass over float32 records runs as k_hub_values: 0 never, 1 unless they are held as rows, 2 always
-    int32_t hub_threshold = 512;
     int32_t hub_chunk = 64;
     int device = 0;
     int num_cus = 256;
@@ -156,6 +156,9 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g);
 bool records_as_rows(const gsr_config_t* cfg, const gsr_graph_t* g);
 int64_t tie_capacity(const gsr_config_t* cfg);
 constexpr int kTieSub = 16, kTieCounterStride = 32;     // (device code: TIE_SUB, TIE_COUNTER_STRIDE)
+
+// First-pass chunks the fixed scratch of gsr_spmm_noalloc holds.
+constexpr int kNoAllocMaxChunks = 16384;
 
 // Tile counters of the dynamic sweeps (device code: tile_draws): 8 XCDs x 64 queues, 128 bytes apart.
 constexpr int kTileCounters = 8 * 64 * 32;

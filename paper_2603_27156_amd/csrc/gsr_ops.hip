@@ -22,7 +22,7 @@ CsrView make_view(const gsr_graph_t* g, bool transpose) {
     CsrView v;
     v.rp = c.rp; v.ci = c.ci; v.av = c.av; v.er = c.er;
     v.hub_rows = c.hub.rows; v.hub_cptr = c.hub.cptr; v.hub_tile0 = c.hub.tile0; v.n_hub = c.hub.n_hub;
-    v.hub_threshold = g->hub_threshold;
+    v.hub_threshold = c.hub_threshold;
     v.hub_chunk = g->hub_chunk;
     v.heavy = c.heavy; v.n_heavy = c.n_heavy; v.heavy_edges = kHeavyTileEdges;
     for (int x = 0; x < 9; ++x) v.heavy_ptr[x] = c.heavy_ptr[x];
@@ -505,7 +505,6 @@ static gsr_status_t spmm_launch(const gsr_graph_t* g, const float* x, int64_t ld
 // then the first-pass sums of up to kNoAllocMaxChunks chunks of split rows.  Every GPU the library runs on holds its
 // own copy of the array until the process ends; host code reaches it only through the address that
 // hipGetSymbolAddress returns with that GPU current (the array's name is not a device address on the host).
-constexpr int kNoAllocMaxChunks = 16384;
 constexpr int kNoAllocCounterInts = kTileCounters + 9 * 32;
 constexpr size_t kNoAllocCounterBytes = ((size_t)kNoAllocCounterInts * sizeof(int) + 255) / 256 * 256;
 constexpr size_t kNoAllocBytes = kNoAllocCounterBytes + (size_t)kNoAllocMaxChunks * 64 * sizeof(float);

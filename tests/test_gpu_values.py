@@ -153,25 +153,47 @@ def test_short_rows_are_not_split_on_a_small_graph(longest):
     assert (np.abs(y - ref) <= bound).all()
 
 
-@pytest.mark.parametrize("sinks", [160, 161])
-def test_short_rows_of_the_transpose_count_as_well(sinks):
-    """A directed graph: rows of A are short, a net of A^T (a column of A) has `sinks` entries."""
-    n = 500
-    rng = np.random.default_rng(9)
-    rows = [np.sort(rng.choice(np.arange(1, n), size=20, replace=False)) for _ in range(n)]
-    for r in range(sinks):
-        rows[r] = np.concatenate([[0], rows[r][1:]])
-    rowptr, cols = np.arange(n + 1, dtype=np.int32) * 20, np.concatenate(rows).astype(np.int32)
-    vals = rng.standard_normal(len(cols)).astype(np.float32)
-    g = gsr.gsr_graph_create(rowptr, cols, vals, flags=0)
-    assert gsr.gsr_graph_info(g)["n_hub_rows"] == (0 if sinks <= 160 else n)       # not cut, or cut at 16 entries
+def test_short_rows_are_judged_for_the_transpose_on_its_own():
+    """A directed graph: every row of A has 20 entries, a net of A^T (a column of A) has 160 or 161.  Rows of A are never cut;
+    those of A^T are at 16 entries once the net is too long, which shows in the room for partial rows (two arrays)."""
+    import scipy.sparse as sp
+    n, size, longer = 500, {}, {}
+    for sinks in (160, 161):
+        rng = np.random.default_rng(9)
+        rows = [np.sort(rng.choice(np.arange(1, n), size=20, replace=False)) for _ in range(n)]
+        for r in range(sinks):
+            rows[r] = np.concatenate([[0], rows[r][1:]])
+        rowptr, cols = np.arange(n + 1, dtype=np.int32) * 20, np.concatenate(rows).astype(np.int32)
+        vals = rng.standard_normal(len(cols)).astype(np.float32)
+        g = gsr.gsr_graph_create(rowptr, cols, vals, flags=0)
+        assert gsr.gsr_graph_info(g)["n_hub_rows"] == 0
+        size[sinks] = gsr.gsr_workspace_size(g, gsr.Config(n=n, d=128, c=2, k=16))[0]
+        longer[sinks] = int((np.bincount(cols, minlength=n) > 16).sum())
+        x = torch.randn(n, 64, device="cuda")
+        y = torch.empty_like(x)
+        for transpose in (False, True):
+            a = sp.csr_matrix((vals, cols, rowptr), shape=(n, n))
+            a = (a.T if transpose else a).tocsr()
+            ref, bound = sums_and_bound(a.indptr, a.indices, a.data, x.cpu().numpy().astype(np.float64))
+            assert (np.abs(gsr.gsr_spmm(g, x, transpose=transpose).cpu().numpy() - ref) <= bound).all()
+            gsr.gsr_spmm_noalloc(g, x, y, transpose=transpose)
+            assert (np.abs(y.cpu().numpy() - ref) <= bound).all()
+    assert longer[161] > 300 and size[161] - size[160] > 2 * (longer[161] - 8) * 64 * 4
+
+
+def test_transpose_stays_uncut_where_the_fixed_scratch_would_not_hold_its_chunks():
+    """A net of 200, rows of A^T above 16 entries, more than 16,384 of them: gsr_spmm_noalloc takes the graph."""
+    n = 20_000
+    rng = np.random.default_rng(10)
+    cols = np.stack([rng.permutation(n) for _ in range(20)], 1).astype(np.int32)        # every column has 20 entries
+    cols[:200, 0] = cols[0, 0]                                                          # and one of them 200 more
+    rowptr, ci = np.arange(n + 1, dtype=np.int32) * 20, np.sort(cols, 1).reshape(-1)
+    vals = rng.standard_normal(len(ci)).astype(np.float32)
+    g = gsr.gsr_graph_create(rowptr, ci, vals, flags=0)
     x = torch.randn(n, 64, device="cuda")
-    for transpose in (0, 1):
-        import scipy.sparse as sp
-        a = sp.csr_matrix((vals, cols, rowptr), shape=(n, n))
-        a = (a.T if transpose else a).tocsr()
-        ref, bound = sums_and_bound(a.indptr, a.indices, a.data, x.cpu().numpy().astype(np.float64))
-        assert (np.abs(gsr.gsr_spmm(g, x, transpose=bool(transpose)).cpu().numpy() - ref) <= bound).all()
+    y = torch.empty_like(x)
+    gsr.gsr_spmm_noalloc(g, x, y, transpose=True)
+    assert torch.equal(y, gsr.gsr_spmm(g, x, transpose=True))
 
 
 @pytest.mark.parametrize("sinks,width", [(1_024, 64), (1_025, 64), (5_000, 64), (5_000, 16), (2_500, 32)])
