@@ -274,23 +274,24 @@ __device__ __forceinline__ int find_hub(const CsrView& g, int row) {
 // acc + partial rows q .. q1 - 1 of column c, added in chunk order, sixteen requested at a time.  The last batch is a
 // whole one too, with zeros in the places past the end: one partial row after the other it was a round trip to memory
 // each (30k nodes, eight nets of 5,000 sinks in one tile: 54 -> 38 us per launch of a tile kernel).
-template <int DG>
+template <int DG, int NB = 16>
 __device__ __forceinline__ float hub_chunks_sum(const float* __restrict__ part, int q, int q1, int c, float acc) {
-    for (; q < q1; q += 16) {
-        float v[16];
+    for (; q < q1; q += NB) {
+        float v[NB];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = part[(size_t)(q + u < q1 ? q + u : q1 - 1) * DG + c];
+        for (int u = 0; u < NB; ++u) v[u] = part[(size_t)(q + u < q1 ? q + u : q1 - 1) * DG + c];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) acc += q + u < q1 ? v[u] : 0.f;
+        for (int u = 0; u < NB; ++u) acc += q + u < q1 ? v[u] : 0.f;
     }
     return acc;
 }
 
-// sum of the first-pass partial rows of hub row `row`, in chunk order
+// sum of the first-pass partial rows of hub row `row`, in chunk order.  Few partial rows (on graphs of long rows nearly every
+// row is one) are asked for four at a time: whole batches of sixteen took 352 us against 334 for a pass of Algorithm 1 there.
 template <int DG>
 __device__ __forceinline__ float hub_row_sum(const CsrView& g, const float* __restrict__ part, int row, int c) {
-    const int h = find_hub(g, row);
-    return hub_chunks_sum<DG>(part, g.hub_cptr[h], g.hub_cptr[h + 1], c, 0.f);
+    const int h = find_hub(g, row), q = g.hub_cptr[h], q1 = g.hub_cptr[h + 1];
+    return q1 - q <= 4 ? hub_chunks_sum<DG, 4>(part, q, q1, c, 0.f) : hub_chunks_sum<DG>(part, q, q1, c, 0.f);
 }
 
 // ---- 16-row tiles in LDS ---------------------------------------------------------------------------------
