@@ -559,7 +559,12 @@ __device__ __forceinline__ void gather_dense_mfma(const CsrView& g, const T* __r
 #pragma unroll
                 for (int u = 0; u < GB; ++u)
 #pragma unroll
-                    for (int cb = 0; cb < CPL; ++cb) acc[cb][0] = __builtin_fmaf(p[u], word_col<T>(w[u], cb), acc[cb][0]);
+                    for (int cb = 0; cb < CPL; ++cb) {       // (through word_col: 10.6 us per launch against 9.5, 20k nodes, 16 bits)
+                        uint32_t bits;
+                        if constexpr (sizeof(T) == 4) bits = w[u][cb];
+                        else bits = (cb & 1) ? (w[u][cb >> 1] & 0xFFFF0000u) : (w[u][cb >> 1] << 16);
+                        acc[cb][0] = __builtin_fmaf(p[u], __uint_as_float(bits), acc[cb][0]);
+                    }
             } else if constexpr (sizeof(T) == 4) {
 #pragma unroll
                 for (int u = 0; u < GB; ++u)
@@ -1408,7 +1413,6 @@ __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int n
     }
     const float scale = record_scale<DG>(x, norm, eps);
     const int rows = min(16, n - r0);
-    if (!given && out.mask && q == 0 && r < rows) out.mask[r0 + r] = mask;
     if constexpr (FORM == REC_ROWS) {
         constexpr int CPL = DG / 16;
 #pragma unroll
@@ -1424,6 +1428,7 @@ __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int n
             for (int cb = 0; cb < CPL; ++cb) v[cb] = stored<T>(v[cb]);
             if (rr < rows) store_cols<CPL, T, true>(out.vals + (size_t)(r0 + rr) * DG + CPL * r, v);
         }
+        if (!given && out.mask && q == 0 && r < rows) out.mask[r0 + r] = mask;
         return;
     }
     wave_sync();   // every lane holds its quarter: the tile can be reused for the compacted values
@@ -1450,6 +1455,7 @@ __device__ __forceinline__ void emit_tile(float* st, int r0, int n, int k, int n
     }
     if (idx_out)
         for (int i = lane; i < total; i += 64) idx_out[(size_t)r0 * k + i] = ist[i];
+    if (!given && out.mask && q == 0 && r < rows) out.mask[r0 + r] = mask;
 }
 
 // ---- persistent row-tile schedule ---------------------------------------------------------------
