@@ -590,7 +590,9 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
         if (chunks > kNoAllocMaxChunks) t_threshold = 160;
     }
     // (the kernels hold thresholds and chunks as 32 bits, and a row has fewer than 2^31 entries: more means "never cut")
-    const int64_t hub_chunk = options().hub_chunk > 0 ? std::min<int64_t>(options().hub_chunk, INT32_MAX) : (long_rows ? 512 : 64);      // (long rows, up to 390 entries, the steps above with chunks of 64 / 128 / 256 / 512 / 1,024: two groups of 192 11,358 / 10,332 / 9,787 / 8,971 / 8,965 us)
+    // Long rows (up to 390 entries), the steps above of two groups of 192 with chunks of 64 / 128 / 256 / 512 / 1,024: 11,358 /
+    // 10,332 / 9,787 / 8,971 / 8,965 us.
+    const int64_t hub_chunk = options().hub_chunk > 0 ? std::min<int64_t>(options().hub_chunk, INT32_MAX) : (long_rows ? 512 : 64);
     g->hub_chunk = (int32_t)hub_chunk;
     // (with more tiles per wave the tile with the long nets starts early and is hidden: there the first pass is better short)
     const bool grow = few_tiles && !long_rows && options().hub_chunk == 0;
