@@ -997,18 +997,28 @@ __device__ __forceinline__ void mfma_tile(const float* st, const WLds<DG>& wl, f
 // 2^-25.5 and 2^-24); over a row of H W_i the sum's own rounding covers it: Y's error against 64 bits is the float32
 // instructions' or a little less (50k nodes of mean degree 236, groups of 192: 5.5e-8 against 5.6e-8; ten more draws of
 // such graphs and widths: 1 - 5 % less each).  (A long sum over rows, dW, is another matter: see mfma_outer.)
-// v_mfma_f32_16x16x16_bf16 takes 16 K-slots per instruction and, unlike the float32 matrix instructions of this chip, runs beside
-// the vector pipe, so the six products of a 16-deep step cost less than the one float32 instruction sequence they
-// replace and hide under the vector work of the other waves.
+// v_mfma_f32_16x16x32_bf16 takes 32 K-slots per instruction and, unlike the float32 matrix instructions of this chip, runs beside
+// the vector pipe, so the six products of a 32-deep step cost less than the float32 instruction sequence they replace and hide
+// under the vector work of the other waves.  (The 16-deep form takes the same 16 cycles of the pipe for half of the slots; a tile
+// kernel waits for much of a product's chain.  1M nodes, D/C = 64: forward kernel 228 -> 213 us, 100k nodes inverse + dW 45.9 ->
+// 43.3; 200k nodes, groups of 128, X_i - H W_i 98 -> 88 us, 50k long rows, groups of 192, back through W_i^T 57 -> 45.  Its sums lose
+// less: error of layer outputs and gradients against 64 bits with every column kept 5 - 8 % lower, dW up to 64 columns 8 - 9 %.)
 // W is kept in LDS already split and laid out as B operands: entry [term][s][cb][lane] holds, for lane (kk = lane / 16,
-// j = lane % 16), the four bf16 of rows 16 s + 4 kk .. + 3 of column CPL j + cb (of W, or of W^T).
+// j = lane % 16), the eight bf16 of a 32-deep step s in column CPL j + cb (of W, or of W^T).
+// A lane's eight K-slots of a 32-deep step are two times four rows: with h = 0, 1 and u = 0 .. 3, slot 4 h + u of lane group kk is
+// row 32 s + 16 h + 4 kk + u.  v_mfma_f32_16x16x32_bf16 takes as long as its 16-deep form (16 cycles of the pipe): see mfma_tile_b3.
 template <int DG>
 struct WLdsB3 {
-    uint64_t w[3][DG / 16][DG / 16][64];
+    alignas(16) uint64_t w[3][DG / 32][DG / 16][64][2];
 };
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint64_t as_u64(bf16x4 v) { return __builtin_bit_cast(uint64_t, v); }
-__device__ __forceinline__ bf16x4 as_bf16x4(uint64_t v) { return __builtin_bit_cast(bf16x4, v); }
+// two times four bf16 as the operand of a 32-deep step
+__device__ __forceinline__ bf16x8 join8(bf16x4 h0, bf16x4 h1) {
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ f32x4 mfma_k32(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
 template <int DG>
 __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int ldw, bool transposed, WLdsB3<DG>& l) {
@@ -1025,9 +1035,9 @@ __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int l
             for (int u = 0; u < 4; ++u) v[u] = w[col * ldw + 16 * s + 4 * kk + u];
             bf16x4 hi, mid, lo;
             split_p4(v, hi, mid, lo);
-            l.w[0][s][cb][lane] = as_u64(hi);
-            l.w[1][s][cb][lane] = as_u64(mid);
-            l.w[2][s][cb][lane] = as_u64(lo);
+            l.w[0][s >> 1][cb][lane][s & 1] = as_u64(hi);
+            l.w[1][s >> 1][cb][lane][s & 1] = as_u64(mid);
+            l.w[2][s >> 1][cb][lane][s & 1] = as_u64(lo);
         }
         __syncthreads();
         return;
@@ -1052,25 +1062,34 @@ __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int l
                 const int lane = e & 63, cb = (e >> 6) % NB, s = (e >> 6) / NB;
                 bf16x4 hi, mid, lo;
                 split_p4(v[t], hi, mid, lo);
-                l.w[0][s][cb][lane] = as_u64(hi);
-                l.w[1][s][cb][lane] = as_u64(mid);
-                l.w[2][s][cb][lane] = as_u64(lo);
+                l.w[0][s >> 1][cb][lane][s & 1] = as_u64(hi);
+                l.w[1][s >> 1][cb][lane][s & 1] = as_u64(mid);
+                l.w[2][s >> 1][cb][lane][s & 1] = as_u64(lo);
             }
         }
     }
     __syncthreads();
 }
 
-// acc += the six products of one 16-deep step with W's block cb, smallest terms first
+// acc[cb] += the six products of one 32-deep step with W's blocks cb, smallest terms first; two column blocks in turn, so that no
+// instruction waits for the one before it
 template <int DG>
-__device__ __forceinline__ void mfma_b3(bf16x4 ah, bf16x4 am, bf16x4 al, const WLdsB3<DG>& wl, int s, int cb, int lane, f32x4& acc) {
-    const bf16x4 bh = as_bf16x4(wl.w[0][s][cb][lane]), bm = as_bf16x4(wl.w[1][s][cb][lane]), bl = as_bf16x4(wl.w[2][s][cb][lane]);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bm, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bh, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bm, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, acc, 0, 0, 0);
+__device__ __forceinline__ void mfma_b3(bf16x8 ah, bf16x8 am, bf16x8 al, const WLdsB3<DG>& wl, int s, int lane, f32x4 (&acc)[DG / 16]) {
+#pragma unroll
+    for (int c0 = 0; c0 < DG / 16; c0 += 2) {
+        bf16x8 bh[2], bm[2], bl[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            bh[c] = *reinterpret_cast<const bf16x8*>(wl.w[0][s][c0 + c][lane]);
+            bm[c] = *reinterpret_cast<const bf16x8*>(wl.w[1][s][c0 + c][lane]);
+            bl[c] = *reinterpret_cast<const bf16x8*>(wl.w[2][s][c0 + c][lane]);
+        }
+        auto both = [&](bf16x8 a, const bf16x8 (&b)[2]) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[c0 + c] = mfma_k32(a, b[c], acc[c0 + c]);
+        };
+        both(al, bh); both(ah, bl); both(am, bm); both(am, bh); both(ah, bm); both(ah, bh);
+    }
 }
 
 // acc = tile (16 x DG float32, LDS, row stride tile_ld) * W, in the tile register layout of mfma_tile.
@@ -1082,27 +1101,33 @@ __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& 
 #pragma unroll
     for (int cb = 0; cb < CPL; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < DG / 16; ++s) {
-        float a[4];
-        lds_load<4>(st + arow * tile_ld<DG>() + 16 * s + 4 * kk, a);
-        bf16x4 ah, am, al;
-        split_p4(a, ah, am, al);
-#pragma unroll
-        for (int cb = 0; cb < CPL; ++cb) mfma_b3<DG>(ah, am, al, wl, s, cb, lane, acc[cb]);
+    for (int s = 0; s < DG / 32; ++s) {
+        float a[8];
+        lds_load<4>(st + arow * tile_ld<DG>() + 32 * s + 4 * kk, *reinterpret_cast<float(*)[4]>(&a[0]));
+        lds_load<4>(st + arow * tile_ld<DG>() + 32 * s + 16 + 4 * kk, *reinterpret_cast<float(*)[4]>(&a[4]));
+        bf16x4 ah[2], am[2], al[2];
+        split_p4(a, ah[0], am[0], al[0]);
+        split_p4(a + 4, ah[1], am[1], al[1]);
+        mfma_b3<DG>(join8(ah[0], ah[1]), join8(am[0], am[1]), join8(al[0], al[1]), wl, s, lane, acc);
+        __builtin_amdgcn_sched_barrier(0);      // (the next step's operands requested beside this one's: a register spilled in three variants)
     }
 }
 
-// dW += H^T dY over the 16 rows of the tile, as mfma_outer, on the bf16 pipe.  The 16 rows are the 16 K-slots of one
-// instruction; K-slot 4 kk + u stands for tile row 4 u + kk, so that the B operand of lane (kk, j) is what the lane
-// already holds of dY (gy[u][ob], rows 4 u + kk) and the A operand is H[4 u + kk][16 mb + j] from the LDS tile.
-template <int DG>
+// dW += H^T dY over the 16 rows of the tile, as mfma_outer, on the bf16 pipe.  The 16 rows are half of the 32 K-slots of one
+// instruction, so an instruction takes two of the six products at once: slot 4 kk + u of either half stands for tile row 4 u + kk, so
+// that the B operand of lane (kk, j) is what the lane already holds of dY (gy[u][ob], rows 4 u + kk) and the A operand is
+// H[4 u + kk][16 mb + j] from the LDS tile.  Pairs: (lo hi, mid mid), (mid hi, hi mid), (hi lo, hi hi).  Rows of dY held in 16 bits
+// (T) are their own first term and have no others: (lo hi, mid hi), then hi hi alone.
+template <int DG, typename T>
 __device__ __forceinline__ void mfma_outer_b3(const float* st_h, const float (&gy)[4][DG / 16], f32x4 (&acc)[DG / 16][DG / 16]) {
     const int lane = lane_id(), kk = lane >> 4, j = lane & 15;
+    constexpr bool EXACT = sizeof(T) == 2;
     bf16x4 bh[DG / 16], bm[DG / 16], bl[DG / 16];
 #pragma unroll
     for (int ob = 0; ob < DG / 16; ++ob) {
         const float b[4] = {gy[0][ob], gy[1][ob], gy[2][ob], gy[3][ob]};
-        split_p4(b, bh[ob], bm[ob], bl[ob]);
+        if constexpr (EXACT) bh[ob] = pack_upper4(__float_as_uint(b[0]), __float_as_uint(b[1]), __float_as_uint(b[2]), __float_as_uint(b[3]));
+        else split_p4(b, bh[ob], bm[ob], bl[ob]);
     }
 #pragma unroll
     for (int mb = 0; mb < DG / 16; ++mb) {
@@ -1111,14 +1136,18 @@ __device__ __forceinline__ void mfma_outer_b3(const float* st_h, const float (&g
         for (int u = 0; u < 4; ++u) a[u] = st_h[(4 * u + kk) * tile_ld<DG>() + 16 * mb + j];
         bf16x4 ah, am, al;
         split_p4(a, ah, am, al);
+        if constexpr (EXACT) {
 #pragma unroll
-        for (int ob = 0; ob < DG / 16; ++ob) {
-            acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh[ob], acc[mb][ob], 0, 0, 0);
-            acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bm[ob], acc[mb][ob], 0, 0, 0);
-            acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl[ob], acc[mb][ob], 0, 0, 0);
-            acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bh[ob], acc[mb][ob], 0, 0, 0);
-            acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bm[ob], acc[mb][ob], 0, 0, 0);
-            acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh[ob], acc[mb][ob], 0, 0, 0);
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = mfma_k32(join8(al, am), join8(bh[ob], bh[ob]), acc[mb][ob]);
+#pragma unroll
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh[ob], acc[mb][ob], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = mfma_k32(join8(al, am), join8(bh[ob], bm[ob]), acc[mb][ob]);
+#pragma unroll
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = mfma_k32(join8(am, ah), join8(bh[ob], bm[ob]), acc[mb][ob]);
+#pragma unroll
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = mfma_k32(join8(ah, ah), join8(bl[ob], bh[ob]), acc[mb][ob]);
         }
     }
 }

@@ -65,7 +65,7 @@ struct BlockArgs {
 constexpr int block_waves(bool with_dw, bool b3) { return (!with_dw && b3) ? 8 : 4; }
 
 template <int DG, typename T, int SIGN, bool WITH_DW, bool DEAL, bool B3, RecordForm FORM>
-__global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgpu_waves_per_eu(WITH_DW ? 2 : 4))) void k_block(BlockArgs<DG, T> a) {
+__global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgpu_waves_per_eu(WITH_DW && DG == 64 ? 2 : 4))) void k_block(BlockArgs<DG, T> a) {
     static_assert(B3 || (SIGN > 0 && !WITH_DW), "only the forward kernel has a float32 variant");
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     __shared__ WaveLds<DG, true> lds[block_waves(WITH_DW, B3)];
@@ -127,9 +127,9 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         // The tile's own rows (X_i, and dY_i for the weight gradient), in the tile register layout.  Requested before
         // the gather they arrive while it runs, but hold sixteen registers through it; requested after it they arrive
         // during the weight product.  Measured per variant (1M-node workload, float32: forward 232 us early against 241
-        // late, inverse 264 against 257; the fused inverse + dW kernel gains from late rows at D/C = 32 and loses at 64,
-        // the 16-bit forward kernel the other way round).
-        constexpr bool OWN_LATE = WITH_DW ? DG == 32 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
+        // late, inverse 264 against 257; the fused inverse + dW kernel gains from late rows at D/C = 32 in float32 and loses
+        // otherwise (1M nodes, 16 bits, D/C = 32: 152 us early, 159 late), the 16-bit forward kernel gains at 64).
+        constexpr bool OWN_LATE = WITH_DW ? DG == 32 && sizeof(T) == 4 : (sizeof(T) == 4 ? SIGN < 0 : DG == 64);
         float xy[4][CPL], gy[WITH_DW ? 4 : 1][CPL];
         auto own_rows = [&]() {
 #pragma unroll
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         f32x4 acc[CPL];
         if constexpr (B3) {
             mfma_tile_b3<DG>(st_h, wl, acc);               // O = H W_i in the tile register layout
-            if constexpr (WITH_DW) mfma_outer_b3<DG>(st_h, gy, dw);
+            if constexpr (WITH_DW) mfma_outer_b3<DG, T>(st_h, gy, dw);
         } else {
             mfma_tile<DG>(st_h, wl, acc);
         }
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (t < ts.end) request(t);
         wave_sync();
         if constexpr (WIDE && sizeof(T) == 4) mfma_outer<DG>(st, g, dw);
-        else mfma_outer_b3<DG>(st, g, dw);
+        else mfma_outer_b3<DG, T>(st, g, dw);
     }
     // workgroup partial of dW_i: the four waves add their accumulators in wave order
     __shared__ float red[DG * DG];
@@ -867,7 +867,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // The A operands of a 16-row tile's product, straight from a plane of [n][64] floats: row arow, columns 16 s + 4 kk .. of
 // step s, split in three terms (mfma_tile_b3).
 struct PlaneOperand {
-    bf16x4 hi[4], mid[4], lo[4];
+    bf16x8 hi[2], mid[2], lo[2];
 };
 __device__ __forceinline__ void plane_request(const float* __restrict__ plane, int r0, int n, float (&v)[4][4]) {
     const int lane = lane_id(), i = lane & 15, kk = lane >> 4;
@@ -880,9 +880,19 @@ __device__ __forceinline__ void plane_product(const PlaneOperand& p, const WLdsB
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int s = 0; s < 2; ++s) mfma_b3(p.hi[s], p.mid[s], p.lo[s], wl, s, lane, acc);
+}
+// the columns of v (steps s of plane_request) in three terms
+__device__ __forceinline__ void plane_split(const float (&v)[4][4], PlaneOperand& p) {
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) mfma_b3(p.hi[s], p.mid[s], p.lo[s], wl, s, cb, lane, acc[cb]);
+    for (int s = 0; s < 2; ++s) {
+        bf16x4 h[2], m[2], l[2];
+        split_p4(v[2 * s], h[0], m[0], l[0]);
+        split_p4(v[2 * s + 1], h[1], m[1], l[1]);
+        p.hi[s] = join8(h[0], h[1]);
+        p.mid[s] = join8(m[0], m[1]);
+        p.lo[s] = join8(l[0], l[1]);
+    }
 }
 
 // Workgroups of eight waves, a 16-row tile each, sharing W_i's blocks: row mb of blocks (of the transpose: column ob) at a
@@ -913,8 +923,7 @@ __global__ __launch_bounds__(512) void k_wide_product(WideProductArgs<S, T> a) {
 #pragma unroll 1
         for (int ob = 0; ob < S; ++ob) load_w_lds_b3<64>(a.w + (size_t)mb * 64 * (64 * S) + 64 * ob, 64 * S, false, wl[ob]);
         PlaneOperand p;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) split_p4(v[s], p.hi[s], p.mid[s], p.lo[s]);
+        plane_split(v, p);
 #pragma unroll
         for (int ob = 0; ob < S; ++ob) {
             f32x4 acc[4];
@@ -971,8 +980,7 @@ __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
 #pragma unroll 1
         for (int mb = 0; mb < S; ++mb) load_w_lds_b3<64>(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
         PlaneOperand p;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) split_p4(v[s], p.hi[s], p.mid[s], p.lo[s]);
+        plane_split(v, p);
 #pragma unroll
         for (int mb = 0; mb < S; ++mb) {
             f32x4 acc[4];
