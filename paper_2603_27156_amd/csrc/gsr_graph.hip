@@ -265,6 +265,26 @@ static void transpose_host(int64_t n, const HostCsr& a, HostCsr* t) {
         }
 }
 
+// Rows per workgroup of k_band_gather on this matrix, or 0 where a gather of whole rows is better: a workgroup stages every row of
+// the band its rows' neighbours lie in, so what counts is how many entries share a staged row.  Backward layer, gather of whole rows /
+// recorded columns, us, graphs of mean degree 236 in a band of 5,952 rows: 8,000 nodes (32 rows per workgroup, 1.2 entries per staged row)
+// D/C = 32, k = 8 336 / 284, 64, k = 16 398 / 410, 128, k = 42 431 / 447; 12,000 (1.7) 415 / 338, 495 / 473, 560 / 545; 20,000 (2.8)
+// 580 / 445, 693 / 599, 794 / 761; 49,600 (6.6) 1,244 / 848, 1,507 / 1,145, 1,761 / 1,544, two groups of 192, k = 16 1,770 / 1,090.
+static int band_rows_of(const HostCsr& m, int64_t n, int workgroups) {
+    const int64_t rows = std::min<int64_t>(256, std::max<int64_t>(1, (n + workgroups - 1) / workgroups));
+    int64_t staged = 0;
+    for (int64_t r0 = 0; r0 < n; r0 += rows) {
+        int64_t lo = n, hi = 0;
+        for (int64_t r = r0; r < std::min(n, r0 + rows); ++r)
+            if (m.rp[r + 1] > m.rp[r]) {
+                lo = std::min<int64_t>(lo, m.ci[m.rp[r]]);
+                hi = std::max<int64_t>(hi, m.ci[m.rp[r + 1] - 1] + 1);
+            }
+        staged += std::max<int64_t>(0, hi - lo);
+    }
+    return 5 * (int64_t)m.ci.size() >= 8 * staged ? (int)rows : 0;
+}
+
 // The tile counters of a graph's dynamic sweeps and, behind them, the nine counters its waves sign off
 // in.  Both are zero between launches (clear when the graph is created; every launch clears them again).
 void tile_counters(const gsr_graph_t* g, int** set, int** done) {
@@ -289,6 +309,10 @@ bool records_as_rows(const gsr_config_t* cfg, const gsr_graph_t* g) {
     return 2 * cfg->k > dg;
 }
 
+bool band_gradient(const gsr_config_t* cfg, const gsr_graph_t* g) {
+    return g->band_rows > 0 && cfg->k <= std::min(64, cfg->d / cfg->c / 2) && !records_as_rows(cfg, g);
+}
+
 LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
     LayerWs w;
     memset(&w, 0, sizeof(w));
@@ -311,7 +335,8 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
     w.y0 = off;
     off += align_up(n * dg * b);
     w.dh = off;
-    if (S > 1) off += align_up(n * dg * sizeof(float));
+    const bool band = band_gradient(cfg, g);
+    if (S > 1 || band) off += align_up(n * dg * sizeof(float));
     w.dw_partial = off;
     off += align_up((size_t)g->grid * dgs * dgs * sizeof(float) * (size_t)(S * S));      // (wide groups: a set per block of dW_i)
     w.hub_partial = off;
@@ -321,7 +346,7 @@ LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g) {
     if (S == 1) off += align_up(std::max<size_t>(chunks, 1) * dgs * sizeof(float));
     w.h = off;               // (not for 16-bit storage at 32 columns: that backward keeps H on chip)
     if (S > 1) off += align_up(n * dg * sizeof(float));
-    else if ((b == 4 || dgs == 64) && g->split_backward) off += align_up(n * dgs * sizeof(float));
+    else if (((b == 4 || dgs == 64) && g->split_backward) || band) off += align_up(n * dgs * sizeof(float));
     w.total = off;
     return w;
 }
@@ -601,6 +626,8 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
     // 1,304, 130k 1,482 / 1,611.  On long rows either way takes the same time, backward layer of two groups of 64 754 / 755 us,
     // and the fused one less memory)
     g->split_backward = !(long_rows || (n + 15) / 16 < (int64_t)8 * full_grid);
+
+    g->band_rows = long_rows ? band_rows_of(symmetric ? a : t, n, std::min(g->num_cus, full_grid)) : 0;
 
     gsr_status_t st = upload_csr(a, n, hub_threshold, hub_chunk, grow, (hipStream_t)stream, &g->a);
     if (st == GSR_OK) {

@@ -106,6 +106,7 @@ struct gsr_graph {
     bool has_transpose = false;
     bool split_backward = true;   // float32: the backward of a block as inverse kernel + k_dw (large graphs), else fused
     bool long_rows = false;  // the mean row has 64 stored entries or more: nearly every row goes through the first pass
+    int band_rows = 0;       // rows per workgroup of k_band_gather, or 0: the gradient gathers dense rows
     int hub_values = 0;      // the first pass over float32 records runs as k_hub_values: 0 never, 1 unless they are held as rows, 2 always
     int32_t hub_chunk = 64;
     int device = 0;
@@ -131,8 +132,9 @@ struct LayerWs {
     size_t rec_cols[kMaxRecordSlots];  // per slot: column of every value [n][k] bytes (not with rows)
     size_t rec_mask[kMaxRecordSlots];  // per slot and sub-plane: column bit mask    [n] of uint32 (32 columns) / uint64 (64)
     size_t y0;           // Y_0 plane [n][dg] of T (C > 2); wide groups: [S][n][64]
-    size_t h;            // [n][dg] float: H of the block being inverted, for the weight-gradient kernel; wide groups: [S][n][64], H
-    size_t dh;           // wide groups only: [S][n][64] float, Q = A^T dY_i
+    size_t h;            // [n][dg] float: H of the block being inverted, for the weight-gradient kernel; wide groups: [S][n][64], H;
+                         // with band_gradient also [n][k] float, the sums at the recorded positions, once H has been used
+    size_t dh;           // wide groups: [S][n][64] float, Q = A^T dY_i; with band_gradient any group: [n][dg] float, P = dY_i W_i^T
     size_t dw_partial;   // [grid][dg*dg] float; wide groups: [S*S][grid][64*64]
     size_t hub_partial;  // [max(n_chunks A, n_chunks A^T)][dg] float; wide groups: [S][chunks][64]
     size_t hub_partial2; // same size: the backward's two first passes of a block run as one launch (not wide groups)
@@ -154,6 +156,8 @@ struct StepWs {
 LayerWs carve_layer(const gsr_config_t* cfg, const gsr_graph_t* g);
 // Whether the layer and step calls hold the records of (cfg, g) as rows, zeros in the dropped columns.
 bool records_as_rows(const gsr_config_t* cfg, const gsr_graph_t* g);
+// Whether their backward takes dY_i W_i^T before the gather over A^T and gathers the recorded columns of it alone (k_band_gather).
+bool band_gradient(const gsr_config_t* cfg, const gsr_graph_t* g);
 int64_t tie_capacity(const gsr_config_t* cfg);
 constexpr int kTieSub = 16, kTieCounterStride = 32;     // (device code: TIE_SUB, TIE_COUNTER_STRIDE)
 

@@ -1040,6 +1040,317 @@ __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
         }
 }
 
+// ---- gradient on graphs of long rows in a band --------------------------------------------------------------------
+// dH_i = A^T dY_i W_i^T is read only at the k columns recorded for each row (eq. (11)).  A row that gathers its hundreds of
+// neighbours' whole rows of dY_i moves D/C values per entry to use k of D/C sums: 50k nodes of mean degree 236, groups of 192: 3 GB
+// per block of 64 columns from L2 to the compute units, three blocks of 172 us.  Here the product goes first, P = dY_i W_i^T
+// (k_pre_product), and then the entries add a_ij P[j][c] for the recorded c alone (k_band_gather), from LDS: a workgroup takes
+// B adjacent rows, whose neighbours lie in a band, and walks the band in windows of rows of P, every one staged once for all its
+// rows (how many entries share a staged row decides whether that pays: band_rows_of).  k_band_back takes the sums back through GS.
+// Per block of that graph, us: 516 of first passes, 18 of tiles and 45 of the product -> 33 + 178 + 27 (backward layer 1,770 ->
+// 1,086; error of dX against 64 bits, median row, 11 - 14 % lower on five such graphs and widths, dW 0 - 8 %).
+template <int DG, int S, typename T>
+struct PreProductArgs {
+    int n;
+    const T* dy;            // row stride ld; block ob 64 ob columns on
+    int64_t ld;
+    const float* w;         // W_i, row stride DG S
+    float* p;               // [n][DG S]
+};
+// Workgroups of eight waves, a 16-row tile each, sharing column ob of W_i's blocks at a time.  The sums of the matrix instructions
+// are not rounded to nearest but to one side, and a few hundred rows of P are added up: odd rows are multiplied with their sign turned and
+// turned back, so that what one row loses another gains (dW, which adds up the rows of dY: error against 64 bits 1.5e-7 with it,
+// 3.0e-7 without; 30k nodes, groups of 128).
+template <int DG, int S, typename T>
+__global__ __launch_bounds__(512) void k_pre_product(PreProductArgs<DG, S, T> a) {
+    constexpr int CPL = DG / 16, DGW = DG * S;
+    __shared__ WLdsB3<DG> wl[S];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
+    const int r0 = ((int)blockIdx.x * 8 + wave) * 16;
+    const int arow = min(r0 + 4 * (tj & 3) + (tj >> 2), a.n - 1);
+    const uint32_t flip_in = (uint32_t)(tj >> 2 & 1) << 31, flip_out = (uint32_t)(tg & 1) << 31;      // of the odd rows
+    f32x4 acc[S][CPL];
+#pragma unroll
+    for (int mb = 0; mb < S; ++mb)
+#pragma unroll
+        for (int cb = 0; cb < CPL; ++cb) acc[mb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int ob = 0; ob < S; ++ob) {
+        float v[DG / 16][4];
+#pragma unroll
+        for (int s = 0; s < DG / 16; ++s) load_cols<4, T>(a.dy + (size_t)arow * a.ld + 64 * ob + 16 * s + 4 * tg, v[s]);
+#pragma unroll
+        for (int s = 0; s < DG / 16; ++s)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[s][u] = __uint_as_float(__float_as_uint(v[s][u]) ^ flip_in);
+        __syncthreads();        // the blocks before have been read
+#pragma unroll 1
+        for (int mb = 0; mb < S; ++mb) load_w_lds_b3<DG>(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
+        bf16x8 hi[DG / 32], mid[DG / 32], lo[DG / 32];
+#pragma unroll
+        for (int s = 0; s < DG / 32; ++s) {
+            bf16x4 h[2], m[2], l[2];
+            split_p4(v[2 * s], h[0], m[0], l[0]);
+            split_p4(v[2 * s + 1], h[1], m[1], l[1]);
+            hi[s] = join8(h[0], h[1]); mid[s] = join8(m[0], m[1]); lo[s] = join8(l[0], l[1]);
+        }
+#pragma unroll
+        for (int mb = 0; mb < S; ++mb) {
+            f32x4 sum[CPL];          // (from zero for every block, as in k_wide_grad)
+#pragma unroll
+            for (int cb = 0; cb < CPL; ++cb) sum[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < DG / 32; ++s) mfma_b3<DG>(hi[s], mid[s], lo[s], wl[mb], s, lane, sum);
+#pragma unroll
+            for (int cb = 0; cb < CPL; ++cb)
+#pragma unroll
+                for (int reg = 0; reg < 4; ++reg) acc[mb][cb][reg] += sum[cb][reg];
+        }
+    }
+#pragma unroll
+    for (int mb = 0; mb < S; ++mb)
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) {
+            const int row = r0 + 4 * reg + tg;
+            float v[CPL];
+#pragma unroll
+            for (int cb = 0; cb < CPL; ++cb) v[cb] = __uint_as_float(__float_as_uint(acc[mb][cb][reg]) ^ flip_out);
+            if (row < a.n) store_cols<CPL, float, true>(a.p + (size_t)row * DGW + 64 * mb + CPL * tj, v);
+        }
+}
+
+struct BandGatherArgs {
+    CsrView gt;             // A^T
+    int n, rows;            // rows per workgroup, at most 64 BAND_ROWS
+    const float* p;         // [n][DGW]
+    const uint8_t* cols;    // [n][k] recorded columns
+    int k;
+    float* out;             // [n][k]
+};
+constexpr int BAND_ROWS = 4;                    // rows per group of sixteen lanes
+constexpr int BAND_FLOATS = 18432;              // of a window: 73,728 bytes, a whole number of rows of 32, 64, 128, 192 or 256 columns
+// Sixteen waves; a group of sixteen lanes owns rows G, G + 64, .. of the workgroup's, lane l of it the sums of the recorded columns
+// l, l + 16, .. (KQ of them).  Two windows of P in LDS: while the entries of one are added the next is on its way (loads straight
+// into LDS).  The entries of a row are in ascending column order, so those of a window follow those of the one before; sixteen
+// of them at a time sit in the lanes of the group (row_lane hands them out), the next sixteen are requested when it is known how many of these
+// the window took.  A window's entries are summed from zero, eight windows' sums from zero again, which bounds the length of the
+// chains of additions.  Places past the window's entries read a row of zeros.  50k nodes of mean degree 236, 192 columns: 178 us, 94 of them for
+// the windows alone (1.2 GB into LDS) and 139 for the sums alone, which the LDS bounds: a read takes some 13 cycles, its 64 columns
+// collide on banks, and a third of the places are past the end of the shorter of four groups' runs (all rows' first eight
+// places read before the first is added, a quarter more reads: 217).
+template <int DGW, int KQ>
+__global__ __launch_bounds__(1024) void k_band_gather(BandGatherArgs a) {
+    constexpr int WROWS = BAND_FLOATS / DGW, ROWB = 4 * DGW;
+    static_assert(BAND_FLOATS % DGW == 0 && ROWB % 128 == 0, "a window is a whole number of rows");
+    struct Lds {
+        alignas(16) float win[2][BAND_FLOATS];
+        float zero[DGW];
+        int lo, hi;
+    };
+    __shared__ Lds L;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = lane & 15, gi = lane >> 4;
+    // adjacent blocks of rows on one XCD: they share most of their bands
+    const int per = (int)(gridDim.x + 7) / 8, block = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+    const int first = block * a.rows, last = min(first + a.rows, a.n);      // (first may lie past the end: no rows)
+    if (threadIdx.x == 0) { L.lo = a.n; L.hi = 0; }
+    if ((int)threadIdx.x < DGW) L.zero[threadIdx.x] = 0.f;
+    __syncthreads();
+    int ptr[BAND_ROWS], end[BAND_ROWS];
+    uint32_t coff[BAND_ROWS][KQ];
+    float acc[BAND_ROWS][KQ], total[BAND_ROWS][KQ];
+#pragma unroll
+    for (int q = 0; q < BAND_ROWS; ++q) {
+        const int in = 4 * wave + gi + 64 * q, row = first + in;
+        const bool ok = in < a.rows && row < last;
+        ptr[q] = ok ? a.gt.rp[row] : 0;
+        end[q] = ok ? a.gt.rp[row + 1] : 0;
+        if (end[q] > ptr[q] && l == 0) {
+            atomicMin(&L.lo, a.gt.ci[ptr[q]]);
+            atomicMax(&L.hi, a.gt.ci[end[q] - 1] + 1);
+        }
+#pragma unroll
+        for (int w = 0; w < KQ; ++w) {
+            const int t = l + 16 * w;
+            coff[q][w] = ok && t < a.k ? 4u * a.cols[(size_t)row * a.k + t] : 0u;
+            acc[q][w] = total[q][w] = 0.f;
+        }
+    }
+    int j[BAND_ROWS];
+    float av[BAND_ROWS];
+    auto request = [&](int q) {          // the next sixteen entries of row q (past the end: an entry that exists, not used)
+        const int e = ptr[q] + l, ec = e < end[q] ? e : max(end[q] - 1, 0);
+        j[q] = a.gt.ci[ec];
+        av[q] = a.gt.av[ec];
+    };
+#pragma unroll
+    for (int q = 0; q < BAND_ROWS; ++q) request(q);
+    __syncthreads();
+    const int lo = __builtin_amdgcn_readfirstlane(L.lo), hi = __builtin_amdgcn_readfirstlane(L.hi);
+    // window at row w0 on into buffer b: a wave moves 64 pieces of 16 bytes per instruction
+    auto stage = [&](int w0, int b) {
+        const int pieces = min(WROWS, a.n - w0) * (DGW / 4);
+        const char* src = reinterpret_cast<const char*>(a.p + (size_t)w0 * DGW);
+        for (int i = wave; 64 * i < pieces; i += 16) {
+            const int piece = min(64 * i + lane, pieces - 1);
+            __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(src + 16 * (size_t)piece)),
+                                             (__attribute__((address_space(3))) void*)&L.win[b][256 * i], 16, 0, 0);
+        }
+    };
+    const uint32_t zero = (uint32_t)(uintptr_t)(lds_float*)&L.zero[0];
+    if (lo < hi) stage(lo, 0);
+    for (int w0 = lo, step = 0; w0 < hi; w0 += WROWS, ++step) {
+        const int b = step & 1;
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): this wave's pieces of the window have arrived
+        __syncthreads();                         // everyone's have, and nobody reads the other buffer any more
+        if (w0 + WROWS < hi) stage(w0 + WROWS, b ^ 1);
+        const uint32_t base = (uint32_t)(uintptr_t)(lds_float*)&L.win[b][0];
+#pragma unroll
+        for (int q = 0; q < BAND_ROWS; ++q) {
+            float sum[KQ];
+#pragma unroll
+            for (int w = 0; w < KQ; ++w) sum[w] = 0.f;
+            // the entries of the window among the sixteen in the lanes; whether there may be more of them
+            auto pass = [&]() -> bool {
+                const bool mine = ptr[q] + l < end[q] && j[q] < w0 + WROWS;
+                const uint64_t m = ballot(mine);
+                if (m == 0) return false;
+                const uint32_t off = mine ? base + (uint32_t)(j[q] - w0) * ROWB : zero;
+                const uint32_t f = __float_as_uint(mine ? av[q] : 0.f);
+                uint32_t any = (uint32_t)m | (uint32_t)(m >> 32);
+                any = (any | any >> 16) & 0xFFFFu;          // places any of the four groups has an entry in (each a run from place 0)
+                ptr[q] += __popc((uint32_t)(m >> (16 * gi)) & 0xFFFFu);
+                request(q);
+                auto four = [&](auto sc) {
+                    constexpr int S0 = decltype(sc)::value;
+                    float v[4][KQ];
+#pragma unroll
+                    for (int w = 0; w < KQ; ++w) {
+                        v[0][w] = *(lds_float*)(uintptr_t)(row_lane<S0>(off) + coff[q][w]);
+                        v[1][w] = *(lds_float*)(uintptr_t)(row_lane<S0 + 1>(off) + coff[q][w]);
+                        v[2][w] = *(lds_float*)(uintptr_t)(row_lane<S0 + 2>(off) + coff[q][w]);
+                        v[3][w] = *(lds_float*)(uintptr_t)(row_lane<S0 + 3>(off) + coff[q][w]);
+                    }
+#pragma unroll
+                    for (int w = 0; w < KQ; ++w) {
+                        sum[w] = __builtin_fmaf(__uint_as_float(row_lane<S0>(f)), v[0][w], sum[w]);
+                        sum[w] = __builtin_fmaf(__uint_as_float(row_lane<S0 + 1>(f)), v[1][w], sum[w]);
+                        sum[w] = __builtin_fmaf(__uint_as_float(row_lane<S0 + 2>(f)), v[2][w], sum[w]);
+                        sum[w] = __builtin_fmaf(__uint_as_float(row_lane<S0 + 3>(f)), v[3][w], sum[w]);
+                    }
+                };
+                four(std::integral_constant<int, 0>{});
+                if (any >> 4) four(std::integral_constant<int, 4>{});
+                if (any >> 8) four(std::integral_constant<int, 8>{});
+                if (any >> 12) four(std::integral_constant<int, 12>{});
+                return any >> 15;                           // some group has seen sixteen
+            };
+            // (the first pass on its own: its entries arrived before the barrier, those of a further one are waited for, and with them
+            // the window under way)
+            if (pass())
+                while (pass()) {}
+#pragma unroll
+            for (int w = 0; w < KQ; ++w) acc[q][w] += sum[w];
+        }
+        if ((step & 7) == 7 || w0 + WROWS >= hi) {
+#pragma unroll
+            for (int q = 0; q < BAND_ROWS; ++q)
+#pragma unroll
+                for (int w = 0; w < KQ; ++w) {
+                    total[q][w] += acc[q][w];
+                    acc[q][w] = 0.f;
+                }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < BAND_ROWS; ++q) {
+        const int in = 4 * wave + gi + 64 * q, row = first + in;
+        if (in >= a.rows || row >= last) continue;
+#pragma unroll
+        for (int w = 0; w < KQ; ++w) {
+            const int t = l + 16 * w;
+            if (t < a.k) a.out[(size_t)row * a.k + t] = total[q][w];
+        }
+    }
+}
+
+// dst planes += dZ, with g = dH at the recorded positions as k_band_gather left them: dZ_c = [c in I] g_c / r - Z_c (sum_t g_t Z_{I_t}) /
+// (D/C r^3).  A wave takes a 16-row tile; the slot of a recorded column is the number of recorded columns before it.
+template <int DG, int S, typename T>
+struct BandBackArgs {
+    using M = typename MaskOf<DG>::type;
+    int n, tiles;
+    const float* g;                     // [n][k]
+    int k;
+    const M* mask[S];                   // column sets recorded for the block's input
+    const T* z;                         // rows of the block's input (RMS only): row stride ldz, sub-plane s at + s * z_sub
+    int64_t ldz, z_sub;
+    int norm;
+    float eps;
+    T* dst;                             // ndst groups, dst_gs apart, row stride ldd
+    int64_t ldd, dst_gs;
+    int ndst;
+};
+template <int DG, int S, typename T>
+__global__ __launch_bounds__(256) void k_band_back(BandBackArgs<DG, S, T> a) {
+    using M = typename MaskOf<DG>::type;
+    constexpr int CPL = DG / 16, DGW = DG * S;
+    const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
+    const int t = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), r0 = t * 16;
+    if (t >= a.tiles) return;
+#pragma unroll
+    for (int reg = 0; reg < 4; ++reg) {
+        const int row = r0 + 4 * reg + tg, rowc = min(row, a.n - 1);
+        float g[S][CPL];
+        bool bit[S][CPL];
+        int slot = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const M m = a.mask[s][rowc];
+            int at = slot + popc<DG>(m & (((M)1 << (CPL * tj)) - 1));
+            slot += popc<DG>(m);
+#pragma unroll
+            for (int cb = 0; cb < CPL; ++cb) {
+                bit[s][cb] = (m >> (CPL * tj + cb)) & 1u;
+                const float v = a.g[(size_t)rowc * a.k + (at < a.k ? at : a.k - 1)];
+                g[s][cb] = bit[s][cb] ? v : 0.f;
+                at += bit[s][cb] ? 1 : 0;
+            }
+        }
+        if (a.norm == GSR_NORM_RMS) {
+            float z[S][CPL], ss = 0.f, dot = 0.f;
+#pragma unroll
+            for (int s = 0; s < S; ++s) load_cols<CPL, T>(a.z + (size_t)rowc * a.ldz + (size_t)s * a.z_sub + CPL * tj, z[s]);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int cb = 0; cb < CPL; ++cb) {
+                    ss += z[s][cb] * z[s][cb];
+                    dot += g[s][cb] * z[s][cb];
+                }
+            ss = group16_sum(ss);
+            dot = group16_sum(dot);
+            const float rinv = __builtin_amdgcn_rsqf(ss * (1.0f / (float)DGW) + a.eps);
+            const float coef = dot * (rinv * rinv * rinv) * (1.0f / (float)DGW);
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int cb = 0; cb < CPL; ++cb) g[s][cb] = (bit[s][cb] ? g[s][cb] * rinv : 0.f) - z[s][cb] * coef;
+        }
+        for (int d = 0; d < a.ndst; ++d) {
+            T* p = a.dst + (size_t)d * a.dst_gs + (size_t)rowc * a.ldd + CPL * tj;
+            float v[S][CPL];
+#pragma unroll
+            for (int s = 0; s < S; ++s) load_cols<CPL, T>(p + 64 * s, v[s]);
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+#pragma unroll
+                for (int cb = 0; cb < CPL; ++cb) v[s][cb] = stored<T>(v[s][cb] + g[s][cb]);
+                if (row < a.n) store_cols<CPL, T>(p + 64 * s, v[s]);
+            }
+        }
+    }
+}
+
 template <int S, typename T>
 struct WideGsArgs {
     int n;
@@ -1382,6 +1693,7 @@ struct Ctx {
     int tiles;
     int S;          // sub-planes of a group: 1, or D/C / 64 for groups wider than a tile (then DG = 64)
     bool rows;      // records are held as rows (records_as_rows)
+    bool band;      // the gradient goes through a product before the gather (band_gradient)
     M* saved;       // [L+1][C][S][n] column masks kept from the forward sweep, or NULL
     // rows kept because they selected at a near-tie (cfg->save_indices == 2), per segment (layer, slot), or NULL
     int* tie_counts;
@@ -1768,6 +2080,33 @@ static void launch_wide_grad(const Ctx<64, T>& x, const float* wi, int slot, int
     });
 }
 
+// The gradient of block `slot` + 1 on a graph of long rows in a band (see k_pre_product): dst planes += dZ.  P in x.dh(), the sums at the
+// recorded positions in x.hplane().
+template <int DG, int S, typename T>
+static void launch_band_grad(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const float* wi, int slot, int layer, const T* z, int64_t ldz,
+                             int64_t z_sub, T* dst, int64_t ldd, int64_t dst_gs, int ndst) {
+    constexpr int DGW = DG * S;
+    const int n = (int)x.cfg->n, k = x.cfg->k;
+    ProfScope prof(KC_GRAD, x.s);
+    PreProductArgs<DG, S, T> pa{n, dy, ldg, wi, x.dh()};
+    hipLaunchKernelGGL((k_pre_product<DG, S, T>), dim3((unsigned)((x.tiles + 7) / 8)), dim3(512), 0, x.s, pa);
+    BandGatherArgs ga{make_view(x.g, true), n, x.g->band_rows, x.dh(), x.rec(slot, layer).cols, k, x.hplane()};
+    const int blocks = (n + ga.rows - 1) / ga.rows;
+    const dim3 grid((unsigned)((blocks + 7) / 8 * 8));
+    auto gather = [&](auto kq) { hipLaunchKernelGGL((k_band_gather<DGW, decltype(kq)::value>), grid, dim3(1024), 0, x.s, ga); };
+    if (k <= 16) gather(std::integral_constant<int, 1>{});
+    else if constexpr (DGW > 32) {
+        if (k <= 32) gather(std::integral_constant<int, 2>{});
+        else if constexpr (DGW > 64) gather(std::integral_constant<int, 4>{});
+    }
+    BandBackArgs<DG, S, T> ba;
+    ba.n = n; ba.tiles = x.tiles; ba.g = x.hplane(); ba.k = k;
+    for (int s = 0; s < S; ++s) ba.mask[s] = x.rec(slot, layer, s).mask;
+    ba.z = z; ba.ldz = ldz; ba.z_sub = z_sub; ba.norm = x.cfg->norm; ba.eps = x.cfg->eps;
+    ba.dst = dst; ba.ldd = ldd; ba.dst_gs = dst_gs; ba.ndst = ndst;
+    hipLaunchKernelGGL((k_band_back<DG, S, T>), dim3((unsigned)((x.tiles + 3) / 4)), dim3(256), 0, x.s, ba);
+}
+
 template <typename T>
 static void wide_forward(const Ctx<64, T>& x, const float* w, const Planes<T>& p, bool slot0_ready, int layer) {
     const int C = x.cfg->c, dgw = 64 * x.S;
@@ -1825,6 +2164,13 @@ static void wide_backward(const Ctx<64, T>& x, const float* w, const Planes<T>& 
             if (!(in_step && layer == 0)) launch_gs_wide<T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, i, given ? layer - 1 : 0, given);
         } else if (C == 2) {
             launch_gs_wide<T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, 0, layer, given);      // X_2 = Y_0 of this layer
+        }
+        if (x.band) {
+            wide_blocks(S, [&](auto sc) {
+                launch_band_grad<64, decltype(sc)::value, T>(x, dy.grp(i - 1), dy.ld, wi, i - 1, layer, z, ldz, z_sub,
+                                                             dy.grp(i >= 2 ? i - 2 : 1), dy.ld, dy.gs, i >= 2 ? 1 : C - 1);
+            });
+            continue;
         }
         launch_dense_planes<T>(x, true, dy.grp(i - 1), dy.ld, x.dh(), KC_GRAD);       // Q = A^T dY_i
         if (i >= 2) launch_wide_grad<T>(x, wi, i - 1, layer, z, ldz, z_sub, dy.grp(i - 2), dy.ld, dy.gs, 1);
@@ -1903,9 +2249,10 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
             out = x.rec(0, layer);                                                     // X_2 = Y_0 of this layer
             if (in_step) out_tie = x.tie_seg(layer, 0);
         }
-        launch_hub_both<DG, T>(x, x.rec(i - 1, layer), dy.grp(i - 1), dy.ld);
+        if (x.band) launch_hub_records<DG, T>(x, x.rec(i - 1, layer));
+        else launch_hub_both<DG, T>(x, x.rec(i - 1, layer), dy.grp(i - 1), dy.ld);
         unsigned nparts;
-        const bool own_reduce = x.tiles < 4 * 4 * x.g->grid;
+        const bool own_reduce = x.band || x.tiles < 4 * 4 * x.g->grid;
         bool dw_reduced = false;
         if (split_dw<DG, T>(x.g)) {
             // X_i = Y_i - f_i(Y_{i-1}) with H kept for the weight gradient, then dW_i = H^T dY_i
@@ -1930,6 +2277,11 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
                                (int)nparts, DG * DG, dwi, DG, DG);
             dwi = nullptr;
         }
+        if (x.band) {
+            launch_band_grad<DG, 1, T>(x, dy.grp(i - 1), dy.ld, wi, i - 1, layer, z, ldz, 0, dy.grp(i >= 2 ? i - 2 : 1), dy.ld, dy.gs,
+                                       i >= 2 ? 1 : C - 1);
+            continue;
+        }
         const typename MaskOf<DG>::type* own = x.rec(i - 1, layer).mask;
         if (i >= 2) launch_grad<DG, T>(x, dy.grp(i - 1), dy.ld, wi, own, z, ldz, dy.grp(i - 2), dy.ld, dy.gs, 1, (int)nparts, dwi, true);
         else launch_grad<DG, T>(x, dy.grp(0), dy.ld, wi, own, z, ldz, dy.grp(1), dy.ld, dy.gs, C - 1, (int)nparts, dwi, true);
@@ -1943,6 +2295,7 @@ static Ctx<DG, T> make_ctx(const gsr_graph_t* g, const gsr_config_t* cfg, void* 
     x.tiles = (int)((cfg->n + 15) / 16);
     x.S = sub_planes(cfg);
     x.rows = records_as_rows(cfg, g);
+    x.band = band_gradient(cfg, g);
     x.saved = nullptr;
     x.tie_counts = nullptr; x.tie_rows = nullptr; x.tie_masks = nullptr; x.tie_cap = 0;
     return x;
