@@ -53,6 +53,7 @@ struct BlockArgs {
     int* draws_done;
     TieSeg<DG> tie;         // where rows that select at a near-tie are listed (count == NULL: nowhere)
     float* h_out;           // [n][DG] float32: receives H = A scatter(V, I) of the block for k_dw (NULL: not kept)
+    TieSeg<DG> fix;         // rows listed in the forward sweep get their kept column sets (WITH_DW; count == NULL: none, see TieFix)
 };
 
 // B3: the H W_i (and dW_i) products on the bf16 matrix pipe from three-term splits (mfma_tile_b3), with W_i kept
@@ -165,6 +166,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
 #pragma unroll
                 for (int cb = 0; cb < CPL; ++cb) gy[reg][cb] = r0 + 4 * reg + tg < a.n ? gy[reg][cb] : 0.f;   // rows past the end
         }
+        TieFix<DG, WITH_DW> fix{a.fix, t, lane};
         wave_sync();
         if constexpr (!WITH_DW) {
             if (a.h_out) {                                 // H leaves for the weight-gradient kernel, four rows per store
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
         }
         if (a.out.mask) {
             wave_sync();
-            emit_tile<DG, T, FORM>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+            emit_tile<DG, T, FORM>(st_h, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie, fix);
         }
         t = t_next;
         t_end = t_end_next;
@@ -280,9 +282,8 @@ __device__ __forceinline__ void tie_fixup_rows(const TieSeg<DG>& tie, const T* _
 // (Blocks of 64 entries left three quarters of the compute units idle on a 64 x 64 matrix: 18 us per launch.)
 constexpr int DW_REDUCE_ENTRIES = 16;
 __device__ __forceinline__ void dw_reduce_block(int block, const float* __restrict__ partial, int nparts, int elems,
-                                                float* __restrict__ out, int cols, int ld_out) {
-    __shared__ float red[16][DW_REDUCE_ENTRIES];
-    const int j = threadIdx.x & (DW_REDUCE_ENTRIES - 1), seg = threadIdx.x / DW_REDUCE_ENTRIES;
+                                                float* __restrict__ out, int cols, int ld_out, float (&red)[16][DW_REDUCE_ENTRIES]) {
+    const int j = threadIdx.x & (DW_REDUCE_ENTRIES - 1), seg = (threadIdx.x & 255) / DW_REDUCE_ENTRIES;
     const int e = block * DW_REDUCE_ENTRIES + j;
     const int per = (nparts + 15) / 16, p0 = seg * per, p1 = min(nparts, p0 + per);
     float acc = 0.f;
@@ -307,26 +308,11 @@ __device__ __forceinline__ void dw_reduce_block(int block, const float* __restri
     }
 }
 
-// What a launch of k_tie_fixup may take along: the reduction of dW_i's workgroup partials (its workgroups from
-// fix_blocks on do that; out == NULL: nothing), which saves a launch per block on small graphs.
-struct DwReduceJob {
-    const float* partial;
-    int nparts, elems;
-    float* out;
-    int cols, ld_out;
-    int fix_blocks;
-};
-
 template <int DG, typename T>
 __global__ __launch_bounds__(256) void k_tie_fixup(TieSeg<DG> tie, const T* __restrict__ plane, int64_t ld, int k, int norm,
-                                                   float eps, Record<DG, T> out, DwReduceJob red) {
-    if (red.out && (int)blockIdx.x >= red.fix_blocks) {
-        dw_reduce_block((int)blockIdx.x - red.fix_blocks, red.partial, red.nparts, red.elems, red.out, red.cols, red.ld_out);
-        return;
-    }
-    const int blocks = red.out ? red.fix_blocks : (int)gridDim.x;
+                                                   float eps, Record<DG, T> out) {
     tie_fixup_rows<DG, T>(tie, plane, ld, k, norm, eps, out, (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6),
-                          (int)((blocks * blockDim.x) >> 6));
+                          (int)((gridDim.x * blockDim.x) >> 6));
 }
 
 // dW_i = H^T dY_i as a pass of its own over H (left by the inverse kernel) and dY_i: a wave sums over the tiles of a
@@ -443,7 +429,8 @@ __global__ __launch_bounds__(256) void k_dw_reduce(const float* __restrict__ par
                                                    int sets_per_row = 1) {
     partial += (size_t)blockIdx.y * set_stride;
     out += (size_t)(blockIdx.y / sets_per_row) * 64 * ld_out + (size_t)(blockIdx.y % sets_per_row) * 64;
-    dw_reduce_block((int)blockIdx.x, partial, nparts, elems, out, cols, ld_out);
+    __shared__ float red[16][DW_REDUCE_ENTRIES];
+    dw_reduce_block((int)blockIdx.x, partial, nparts, elems, out, cols, ld_out, red);
 }
 
 // ---- block: data gradient ---------------------------------------------------------------------------
@@ -471,6 +458,9 @@ struct GradArgs {
     const float* dw_partial;
     int dw_parts;
     float* dw_out;
+    // On small graphs a second row of workgroups (blockIdx.y = 1) sums them beside the tiles instead, as k_dw_reduce does (NULL: no
+    // such row; not in the variants that deal heavy tiles out)
+    float* beside_out;
 };
 
 // dW_i[e] = sum over the workgroup partials, in a fixed order: a workgroup takes 64 entries at a time; its four
@@ -522,7 +512,19 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
     WaveLds<DG>& L = lds[wave];
     float* st = L.st;
     __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
-    static_assert(GRAD_WAVES >= 4 && sizeof(lds) >= 256 * sizeof(float), "dw_reduce_slices works with the first 256 threads");
+    static_assert(GRAD_WAVES >= 4 && sizeof(lds) >= 64 * GRAD_WAVES * sizeof(float), "dw_reduce_slices works with the first 256 threads");
+    if constexpr (!DEAL) {
+        if (a.beside_out && blockIdx.y == 1) {
+            constexpr int PER = GRAD_WAVES / 4, BLOCKS = DG * DG / DW_REDUCE_ENTRIES;
+            for (int b0 = (int)blockIdx.x * PER; b0 < BLOCKS; b0 += (int)gridDim.x * PER) {       // (the same for every thread of the workgroup)
+                const int half = (int)threadIdx.x >> 8;
+                dw_reduce_block(b0 + half, a.dw_partial, a.dw_parts, DG * DG, a.beside_out, DG, DG,
+                                reinterpret_cast<float(*)[16][DW_REDUCE_ENTRIES]>(lds)[half]);
+                __syncthreads();
+            }
+            return;
+        }
+    }
     if (a.dw_out) dw_reduce_slices<DG * DG>(a.dw_partial, a.dw_parts, a.dw_out, reinterpret_cast<float*>(lds));
     if constexpr (B3) load_w_lds_b3<DG>(a.w, DG, true, wl);
     else load_w_lds<DG>(a.w, true, wl);
@@ -674,6 +676,7 @@ struct SumArgs {
     Record<DG, T> out;
     bool out_given;         // out.mask holds the column sets to use
     TieSeg<DG> tie;         // where rows that select at a near-tie are listed (count == NULL: nowhere)
+    TieSeg<DG> fix;         // as in BlockArgs
 };
 
 __global__ void k_zero_ints(int* p, int count) {
@@ -681,7 +684,7 @@ __global__ void k_zero_ints(int* p, int count) {
     if (i < count) p[i] = 0;
 }
 
-template <int DG, typename T, RecordForm FORM>
+template <int DG, typename T, RecordForm FORM, bool FIX>
 __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
     constexpr int LR = tile_ld<DG>(), CPL = DG / 16;
     __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, REC_COLUMNS>()];
@@ -708,6 +711,7 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
 #pragma unroll
                 for (int cb = 0; cb < CPL; ++cb) y[reg][cb] += v[reg][cb];
         }
+        TieFix<DG, FIX> fix{a.fix, t, lane};
         wave_sync();          // the previous tile's records have left the scratch
 #pragma unroll
         for (int reg = 0; reg < 4; ++reg) {
@@ -721,7 +725,7 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
             lds_store<CPL>(st + rr * LR + CPL * tj, y[reg]);
         }
         wave_sync();
-        emit_tile<DG, T, FORM>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie);
+        emit_tile<DG, T, FORM>(st, r0, a.n, a.k, a.norm, a.eps, a.out, a.out_given, lane, nullptr, nullptr, a.tie, fix);
     }
 }
 
@@ -1744,15 +1748,18 @@ static unsigned persistent_grid(const gsr_graph_t* g, int per_cu) {
 template <int DG, typename T>
 static void launch_sum(const Ctx<DG, T>& x, const T* src, int64_t ld, int64_t gs, int nsrc, T* y0,
                        const Record<DG, T>& out, bool out_given = false,
-                       TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}) {
+                       TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f},
+                       TieSeg<DG> fix = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}) {
     SumArgs<DG, T> a;
     a.tie = tie;
+    a.fix = fix;
     a.n = (int)x.cfg->n; a.src = src; a.ld = ld; a.src_gs = gs; a.nsrc = nsrc; a.y0 = y0;
     a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
     a.out = out; a.out_given = out_given;
     ProfScope prof(KC_SUM, x.s);
-    if (x.rows) hipLaunchKernelGGL((k_sum<DG, T, REC_ROWS>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
-    else hipLaunchKernelGGL((k_sum<DG, T, REC_COLUMNS>), dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a); };
+    if (fix.count) x.rows ? launch(k_sum<DG, T, REC_ROWS, true>) : launch(k_sum<DG, T, REC_COLUMNS, true>);
+    else x.rows ? launch(k_sum<DG, T, REC_ROWS, false>) : launch(k_sum<DG, T, REC_COLUMNS, false>);
 }
 
 template <int DG, typename T>
@@ -1836,10 +1843,12 @@ static bool split_dw(const gsr_graph_t* g) { return (sizeof(T) == 4 || DG == 64)
 template <int DG, typename T>
 static unsigned launch_block(const Ctx<DG, T>& x, int mode, const Record<DG, T>& in, const float* w, T* plane, int64_t ld,
                              const Record<DG, T>& out, bool out_given, const T* dy, int64_t ldg, bool first_pass_done = false,
-                             TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, float* h_out = nullptr) {
+                             TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, float* h_out = nullptr,
+                             TieSeg<DG> fix = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}) {
     if (!first_pass_done) launch_hub_records<DG, T>(x, in);
     BlockArgs<DG, T> a;
     a.tie = tie;
+    a.fix = fix;
     a.h_out = h_out;
     a.g = make_view(x.g, false);
     a.n = (int)x.cfg->n; a.tiles = x.tiles;
@@ -1880,10 +1889,17 @@ static unsigned launch_block(const Ctx<DG, T>& x, int mode, const Record<DG, T>&
 }
 
 template <int DG, typename T>
+static void launch_dw_reduce(const Ctx<DG, T>& x, int parts, float* out) {
+    ProfScope prof(KC_DW_REDUCE, x.s);
+    hipLaunchKernelGGL(k_dw_reduce, dim3((DG * DG + DW_REDUCE_ENTRIES - 1) / DW_REDUCE_ENTRIES), dim3(256), 0, x.s, (const float*)x.dw_partial(),
+                       parts, DG * DG, out, DG, DG);
+}
+
+template <int DG, typename T>
 static void launch_grad(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const float* w,
                         const typename MaskOf<DG>::type* own_mask, const T* z,
                         int64_t ldz, T* dst, int64_t ldd, int64_t dst_gs, int ndst, int dw_parts, float* dw_out,
-                        bool first_pass_done = false) {
+                        bool first_pass_done = false, float* beside_out = nullptr) {
     if (!first_pass_done) launch_hub_dense<DG, T>(x, dy, ldg);
     GradArgs<DG, T> a;
     a.gt = make_view(x.g, true);
@@ -1891,13 +1907,17 @@ static void launch_grad(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const flo
     a.w = w;
     a.own_mask = own_mask; a.z = z; a.ldz = ldz; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
     a.dst = dst; a.ldd = ldd; a.dst_gs = dst_gs; a.ndst = ndst;
-    a.dw_partial = x.dw_partial(); a.dw_parts = dw_parts; a.dw_out = dw_out;
+    a.dw_partial = x.dw_partial(); a.dw_parts = dw_parts; a.dw_out = dw_out; a.beside_out = beside_out;
     tile_counters(x.g, &a.draws, &a.draws_done);
     ProfScope prof(KC_GRAD, x.s);
     auto go = [&](auto plain, auto deal, int per_cu, unsigned threads) {
         const unsigned grid = persistent_grid(x.g, per_cu);
-        if (heavy_first(a.gt.n_heavy, x.tiles, grid * (threads / 64) / 4)) hipLaunchKernelGGL(deal, dim3(grid), dim3(threads), 0, x.s, a);
-        else hipLaunchKernelGGL(plain, dim3(grid), dim3(threads), 0, x.s, a);
+        if (heavy_first(a.gt.n_heavy, x.tiles, grid * (threads / 64) / 4)) {
+            if (beside_out) launch_dw_reduce<DG, T>(x, dw_parts, beside_out);
+            hipLaunchKernelGGL(deal, dim3(grid), dim3(threads), 0, x.s, a);
+        } else {
+            hipLaunchKernelGGL(plain, dim3(grid, beside_out ? 2 : 1), dim3(threads), 0, x.s, a);
+        }
     };
     if (!x.g->long_rows) {
         static const int per_cu = resident_blocks((const void*)k_grad<DG, T, false, true>, 512);
@@ -1911,21 +1931,11 @@ static void launch_grad(const Ctx<DG, T>& x, const T* dy, int64_t ldg, const flo
 // After a record was taken again from rebuilt rows during the inverse sweep: the rows listed for that application of
 // GS in the forward sweep get their kept column sets back (values from the same rebuilt rows).
 template <int DG, typename T>
-// (red: a reduction of dW_i's partials for the launch to take along, or NULL; returns whether it was taken)
-static bool launch_tie_fixup(const Ctx<DG, T>& x, const TieSeg<DG>& tie, const T* plane, int64_t ld, const Record<DG, T>& out,
-                             const DwReduceJob* red = nullptr) {
-    if (!tie.count) return false;
+static void launch_tie_fixup(const Ctx<DG, T>& x, const TieSeg<DG>& tie, const T* plane, int64_t ld, const Record<DG, T>& out) {
+    if (!tie.count) return;
     ProfScope prof(KC_TIE, x.s);
     const unsigned blocks = (unsigned)std::min((TIE_SUB * tie.cap + 63) / 64 / 4 * 4 + 4, 1024);     // 4 waves each: a multiple of TIE_SUB waves
-    DwReduceJob job{nullptr, 0, 0, nullptr, 0, 0, 0};
-    unsigned more = 0;
-    if (red) {
-        job = *red;
-        job.fix_blocks = (int)blocks;
-        more = (unsigned)((job.elems + DW_REDUCE_ENTRIES - 1) / DW_REDUCE_ENTRIES);
-    }
-    hipLaunchKernelGGL((k_tie_fixup<DG, T>), dim3(blocks + more), dim3(256), 0, x.s, tie, plane, ld, x.cfg->k, x.cfg->norm, x.cfg->eps, out, job);
-    return red != nullptr;
+    hipLaunchKernelGGL((k_tie_fixup<DG, T>), dim3(blocks), dim3(256), 0, x.s, tie, plane, ld, x.cfg->k, x.cfg->norm, x.cfg->eps, out);
 }
 
 // dW_i's workgroup partials from H (in x.hplane()) and dY_i; returns their number
@@ -2225,6 +2235,10 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
     }
     const int C = x.cfg->c;
     const bool given = x.saved != nullptr;
+    // With few tiles per wave a launch is worth more than the work it takes along: dW_i's partials are summed beside the gradient's tiles
+    // (first they would delay them: a 49,600-node graph with 3,100 tiles, +80 us on a 405 us kernel), and the rows
+    // listed in the forward sweep get their kept column sets back where the record is taken (TieFix) instead of in a launch after it.
+    const bool few_tiles = x.band || x.tiles < 4 * 4 * x.g->grid;
     if (!slots_ready)
         for (int i = 1; i < C; ++i) launch_sum<DG, T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, x.rec(i, layer), given);
     for (int i = C; i >= 1; --i) {
@@ -2234,8 +2248,9 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
         if (i >= 2) { z = y.grp(i - 2); ldz = y.ld; }
         else if (C == 2) { z = y.grp(1); ldz = y.ld; }      // Y_0 = X_2, rebuilt just before
         else {
-            launch_sum<DG, T>(x, y.grp(1), y.ld, y.gs, C - 1, x.y0(), x.rec(0, layer), given);
-            launch_tie_fixup<DG, T>(x, x.tie_seg(layer, 0), x.y0(), DG, x.rec(0, layer));
+            launch_sum<DG, T>(x, y.grp(1), y.ld, y.gs, C - 1, x.y0(), x.rec(0, layer), given, x.tie_seg(-1, 0),
+                              x.tie_seg(few_tiles ? layer : -1, 0));
+            if (!few_tiles) launch_tie_fixup<DG, T>(x, x.tie_seg(layer, 0), x.y0(), DG, x.rec(0, layer));
             z = x.y0(); ldz = DG;
         }
         Record<DG, T> out = x.rec(-1);
@@ -2252,39 +2267,28 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
         if (x.band) launch_hub_records<DG, T>(x, x.rec(i - 1, layer));
         else launch_hub_both<DG, T>(x, x.rec(i - 1, layer), dy.grp(i - 1), dy.ld);
         unsigned nparts;
-        const bool own_reduce = x.band || x.tiles < 4 * 4 * x.g->grid;
-        bool dw_reduced = false;
+        float* dwi = dw_out + (size_t)(i - 1) * DG * DG;
         if (split_dw<DG, T>(x.g)) {
             // X_i = Y_i - f_i(Y_{i-1}) with H kept for the weight gradient, then dW_i = H^T dY_i
             launch_block<DG, T>(x, 1, x.rec(i - 1, layer), wi, y.grp(i - 1), y.ld, out, given, nullptr, 0, true,
                                 TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, x.hplane());
             nparts = launch_dw<DG, T>(x, dy.grp(i - 1), dy.ld, out_tie, y.grp(i - 1), y.ld, out.mask ? &out : nullptr);
         } else {
-            nparts = launch_block<DG, T>(x, 2, x.rec(i - 1, layer), wi, y.grp(i - 1), y.ld, out, given, dy.grp(i - 1), dy.ld, true);
-            // (on a small graph the launch that restores the listed rows' column sets also sums dW_i's partials)
-            const DwReduceJob job{x.dw_partial(), (int)nparts, DG * DG, dw_out + (size_t)(i - 1) * DG * DG, DG, DG, 0};
-            if (out.mask) dw_reduced = launch_tie_fixup<DG, T>(x, out_tie, y.grp(i - 1), y.ld, out, own_reduce ? &job : nullptr);
+            const bool fix = few_tiles && out.mask;
+            nparts = launch_block<DG, T>(x, 2, x.rec(i - 1, layer), wi, y.grp(i - 1), y.ld, out, given, dy.grp(i - 1), dy.ld, true,
+                                         TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, nullptr, fix ? out_tie : x.tie_seg(-1, 0));
+            if (out.mask && !fix) launch_tie_fixup<DG, T>(x, out_tie, y.grp(i - 1), y.ld, out);
         }
-        // dW_i is summed from the partials by the first job of the gradient kernel that follows, unless that kernel
-        // has so few tiles per wave that it could not make up for the late start of those workgroups (measured on
-        // a 49,600-node graph with 3,100 tiles: +80 us on a 405 us kernel): then by a launch of its own
-        float* dwi = dw_out + (size_t)(i - 1) * DG * DG;
-        if (dw_reduced) {
-            dwi = nullptr;
-        } else if (own_reduce) {
-            ProfScope prof(KC_DW_REDUCE, x.s);
-            hipLaunchKernelGGL(k_dw_reduce, dim3((DG * DG + DW_REDUCE_ENTRIES - 1) / DW_REDUCE_ENTRIES), dim3(256), 0, x.s, (const float*)x.dw_partial(),
-                               (int)nparts, DG * DG, dwi, DG, DG);
-            dwi = nullptr;
-        }
+        if (x.band) launch_dw_reduce<DG, T>(x, (int)nparts, dwi);
         if (x.band) {
             launch_band_grad<DG, 1, T>(x, dy.grp(i - 1), dy.ld, wi, i - 1, layer, z, ldz, 0, dy.grp(i >= 2 ? i - 2 : 1), dy.ld, dy.gs,
                                        i >= 2 ? 1 : C - 1);
             continue;
         }
         const typename MaskOf<DG>::type* own = x.rec(i - 1, layer).mask;
-        if (i >= 2) launch_grad<DG, T>(x, dy.grp(i - 1), dy.ld, wi, own, z, ldz, dy.grp(i - 2), dy.ld, dy.gs, 1, (int)nparts, dwi, true);
-        else launch_grad<DG, T>(x, dy.grp(0), dy.ld, wi, own, z, ldz, dy.grp(1), dy.ld, dy.gs, C - 1, (int)nparts, dwi, true);
+        // (large graphs: the partials are the first job of the gradient kernel's workgroups)
+        launch_grad<DG, T>(x, dy.grp(i - 1), dy.ld, wi, own, z, ldz, dy.grp(i >= 2 ? i - 2 : 1), dy.ld, dy.gs, i >= 2 ? 1 : C - 1, (int)nparts,
+                           few_tiles ? nullptr : dwi, true, few_tiles ? dwi : nullptr);
     }
 }
 
