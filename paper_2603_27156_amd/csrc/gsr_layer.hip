@@ -677,6 +677,7 @@ struct SumArgs {
     bool out_given;         // out.mask holds the column sets to use
     TieSeg<DG> tie;         // where rows that select at a near-tie are listed (count == NULL: nowhere)
     TieSeg<DG> fix;         // as in BlockArgs
+    size_t y_rec, y_mask;   // blockIdx.y: the records of that many planes in one launch, src_gs apart, their records these many bytes apart
 };
 
 __global__ void k_zero_ints(int* p, int count) {
@@ -690,6 +691,12 @@ __global__ __launch_bounds__(256) void k_sum(SumArgs<DG, T> a) {
     __shared__ __attribute__((aligned(16))) float tile[4][emit_floats<DG, REC_COLUMNS>()];
     const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
     float* st = tile[threadIdx.x >> 6];
+    if (blockIdx.y > 0) {
+        a.src += blockIdx.y * a.src_gs;
+        a.out.vals = reinterpret_cast<T*>(reinterpret_cast<char*>(a.out.vals) + blockIdx.y * a.y_rec);
+        if (a.out.cols) a.out.cols += blockIdx.y * a.y_rec;
+        a.out.mask = reinterpret_cast<typename MaskOf<DG>::type*>(reinterpret_cast<char*>(a.out.mask) + blockIdx.y * a.y_mask);
+    }
     const int nwaves = (gridDim.x * blockDim.x) >> 6, tiles = (a.n + 15) / 16;
     for (int t = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; t < tiles; t += nwaves) {
         const int r0 = t * 16;
@@ -1763,17 +1770,28 @@ template <int DG, typename T>
 static void launch_sum(const Ctx<DG, T>& x, const T* src, int64_t ld, int64_t gs, int nsrc, T* y0,
                        const Record<DG, T>& out, bool out_given = false,
                        TieSeg<DG> tie = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f},
-                       TieSeg<DG> fix = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}) {
+                       TieSeg<DG> fix = TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, int planes = 1, size_t y_rec = 0, size_t y_mask = 0) {
     SumArgs<DG, T> a;
     a.tie = tie;
     a.fix = fix;
+    a.y_rec = y_rec; a.y_mask = y_mask;
     a.n = (int)x.cfg->n; a.src = src; a.ld = ld; a.src_gs = gs; a.nsrc = nsrc; a.y0 = y0;
     a.k = x.cfg->k; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
     a.out = out; a.out_given = out_given;
     ProfScope prof(KC_SUM, x.s);
-    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)x.g->grid * 2), dim3(256), 0, x.s, a); };
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)x.g->grid * 2, (unsigned)planes), dim3(256), 0, x.s, a); };
     if (fix.count) x.rows ? launch(k_sum<DG, T, REC_ROWS, true>) : launch(k_sum<DG, T, REC_COLUMNS, true>);
     else x.rows ? launch(k_sum<DG, T, REC_ROWS, false>) : launch(k_sum<DG, T, REC_COLUMNS, false>);
+}
+
+// The records of Y_1 .. Y_{C-1} into slots 1 .. C - 1, in one launch (one each: two launches of 6.9 us on 30k nodes and three groups,
+// so one of 9.6; 1M nodes, eight 16-bit groups, seven launches of 44 us, so one of 304).  A workspace holds the slots evenly spaced.
+template <int DG, typename T>
+static void launch_records(const Ctx<DG, T>& x, const Planes<T>& y, int layer, bool given) {
+    const int C = x.cfg->c;
+    const Record<DG, T> first = x.rec(1, layer), second = x.rec(C > 2 ? 2 : 1, layer);
+    launch_sum<DG, T>(x, y.grp(0), y.ld, y.gs, 1, nullptr, first, given, x.tie_seg(-1, 0), x.tie_seg(-1, 0), C - 1,
+                      (size_t)((char*)second.vals - (char*)first.vals), (size_t)((char*)second.mask - (char*)first.mask));
 }
 
 template <int DG, typename T>
@@ -2227,7 +2245,7 @@ static void layer_inverse_impl(const Ctx<DG, T>& x, const float* w, const Planes
         if (x.S > 1) { wide_inverse<T>(x, w, p); return; }
     }
     const int C = x.cfg->c;
-    for (int i = 1; i < C; ++i) launch_sum<DG, T>(x, p.grp(i - 1), p.ld, p.gs, 1, nullptr, x.rec(i));
+    launch_records<DG, T>(x, p, 0, false);
     for (int i = C; i >= 1; --i) {
         if (i == 1 && C > 2) launch_sum<DG, T>(x, p.grp(1), p.ld, p.gs, C - 1, nullptr, x.rec(0));
         const Record<DG, T> out = (i == 2 && C == 2) ? x.rec(0) : x.rec(-1);
@@ -2253,8 +2271,7 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
     // (first they would delay them: a 49,600-node graph with 3,100 tiles, +80 us on a 405 us kernel), and the rows
     // listed in the forward sweep get their kept column sets back where the record is taken (TieFix) instead of in a launch after it.
     const bool few_tiles = x.band || x.tiles < 4 * 4 * x.g->grid;
-    if (!slots_ready)
-        for (int i = 1; i < C; ++i) launch_sum<DG, T>(x, y.grp(i - 1), y.ld, y.gs, 1, nullptr, x.rec(i, layer), given);
+    if (!slots_ready) launch_records<DG, T>(x, y, layer, given);
     for (int i = C; i >= 1; --i) {
         const float* wi = w + (size_t)(i - 1) * DG * DG;
         const T* z;      // rows of Y_{i-1}
