@@ -954,6 +954,63 @@ __global__ __launch_bounds__(512) void k_wide_product(WideProductArgs<S, T> a) {
         }
 }
 
+// Two column blocks: all four blocks of W_i stay in LDS (98 KB) and a workgroup per compute unit sweeps tiles with them, each wave's next tile
+// on its way while the present one is multiplied.  (Loading and splitting W_i again for every eight tiles was a third of the time: 200k nodes,
+// groups of 128, X_i - H W_i 88 -> 72 us, back through W_i^T 99 -> 84 us; three blocks' W_i does not fit.)
+template <typename T, int SIGN>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_wide_product2(WideProductArgs<2, T> a) {
+    __shared__ WLdsB3<64> wl[2][2];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
+    const int step = (int)gridDim.x * 8;
+    int t = (int)blockIdx.x * 8 + wave;
+    float v[2][4][4], y[2][4][4];
+    auto request = [&](int tile) {
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) plane_request(a.h + (size_t)mb * a.n * 64, tile * 16, a.n, v[mb]);
+#pragma unroll
+        for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) load_cols<4, T>(a.plane + (size_t)min(tile * 16 + 4 * reg + tg, a.n - 1) * a.ld + 64 * ob + 4 * tj, y[ob][reg]);
+    };
+    if (t < a.tiles) request(t);
+#pragma unroll 1
+    for (int b = 0; b < 4; ++b) load_w_lds_b3<64>(a.w + (size_t)(b >> 1) * 64 * 128 + 64 * (b & 1), 128, false, wl[b >> 1][b & 1]);
+    while (t < a.tiles) {
+        const int r0 = t * 16;
+        PlaneOperand p[2];
+        float out[2][4][4];
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) plane_split(v[mb], p[mb]);
+#pragma unroll
+        for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) out[ob][reg][cb] = y[ob][reg][cb];
+        t += step;
+        if (t < a.tiles) request(t);
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int ob = 0; ob < 2; ++ob) {
+                f32x4 acc[4];
+                wave_sync();          // (W_i's operands are read from LDS here, not kept in registers for the whole sweep)
+                plane_product(p[mb], wl[mb][ob], acc);
+#pragma unroll
+                for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) out[ob][reg][cb] = stored<T>(SIGN > 0 ? out[ob][reg][cb] + acc[cb][reg] : out[ob][reg][cb] - acc[cb][reg]);
+            }
+#pragma unroll
+        for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) {
+                const int row = r0 + 4 * reg + tg;
+                if (row < a.n) store_cols<4, T>(a.plane + (size_t)row * a.ld + 64 * ob + 4 * tj, out[ob][reg]);
+            }
+    }
+}
+
 // dH = Q W_i^T, then back through GS and its scale: dZ_c = [c in I] g_c / r - Z_c (sum_t g_t Z_{I_t}) / (D/C r^3) with g = dH
 // at the recorded positions (eq. (11): only those are read); dst planes += dZ.
 template <int S, typename T>
@@ -970,6 +1027,76 @@ struct WideGradArgs {
     int64_t ldd, dst_gs;
     int ndst;
 };
+// What that takes of a 16-row tile beside dH: its own rows and column sets, and (one of them) the rows that receive dZ.
+template <int S>
+struct WideGradRows {
+    float z[4][S][4];
+    uint64_t mask[4][S];
+    float d[4][S][4];
+};
+template <int S, typename T>
+__device__ __forceinline__ void wide_grad_request(const WideGradArgs<S, T>& a, int r0, int reg, bool with_dst, WideGradRows<S>& w) {
+    const int lane = lane_id(), tg = lane >> 4, tj = lane & 15, rowc = min(r0 + 4 * reg + tg, a.n - 1);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        w.mask[reg][s] = a.mask[s][rowc];
+        if (a.norm == GSR_NORM_RMS) load_cols<4, T>(a.z + (size_t)rowc * a.ldz + (size_t)s * a.z_sub + 4 * tj, w.z[reg][s]);
+        if (with_dst) load_cols<4, T>(a.dst + (size_t)rowc * a.ldd + 64 * s + 4 * tj, w.d[reg][s]);
+    }
+}
+// back through GS and its scale: g = dH of the tile -> dZ
+template <int S, typename T>
+__device__ __forceinline__ void wide_grad_back(const WideGradArgs<S, T>& a, float (&g)[S][4][4], int reg, const WideGradRows<S>& w) {
+    constexpr int DGW = 64 * S;
+    const int tj = lane_id() & 15;
+    uint32_t bits[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) bits[s] = (uint32_t)(w.mask[reg][s] >> (4 * tj)) & 15u;
+    if (a.norm == GSR_NORM_RMS) {
+        float ss = 0.f, dot = 0.f;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                ss += w.z[reg][s][cb] * w.z[reg][s][cb];
+                dot += ((bits[s] >> cb) & 1u) ? g[s][reg][cb] * w.z[reg][s][cb] : 0.f;
+            }
+        ss = group16_sum(ss);
+        dot = group16_sum(dot);
+        const float rinv = __builtin_amdgcn_rsqf(ss * (1.0f / (float)DGW) + a.eps);
+        const float coef = dot * (rinv * rinv * rinv) * (1.0f / (float)DGW);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) g[s][reg][cb] = (((bits[s] >> cb) & 1u) ? g[s][reg][cb] * rinv : 0.f) - w.z[reg][s][cb] * coef;
+    } else {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) g[s][reg][cb] = ((bits[s] >> cb) & 1u) ? g[s][reg][cb] : 0.f;
+    }
+}
+// the planes j0 .. ndst - 1 that receive dZ
+template <int S, typename T>
+__device__ __forceinline__ void wide_grad_add(const WideGradArgs<S, T>& a, const float (&g)[S][4][4], int r0, int j0) {
+    const int lane = lane_id(), tg = lane >> 4, tj = lane & 15;
+    for (int j = j0; j < a.ndst; ++j)
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            float d[4][4];
+            T* p = a.dst + (size_t)j * a.dst_gs + 64 * s + 4 * tj;
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) load_cols<4, T>(p + (size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ldd, d[reg]);
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) {
+                const int row = r0 + 4 * reg + tg;
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) d[reg][cb] = stored<T>(d[reg][cb] + g[s][reg][cb]);
+                if (row < a.n) store_cols<4, T>(p + (size_t)row * a.ldd, d[reg]);
+            }
+        }
+}
+
 template <int S, typename T>
 __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
     constexpr int DGW = 64 * S;
@@ -1002,53 +1129,67 @@ __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
                 for (int cb = 0; cb < 4; ++cb) g[mb][reg][cb] += acc[cb][reg];
         }
     }
+    WideGradRows<S> w;
 #pragma unroll
     for (int reg = 0; reg < 4; ++reg) {
-        const int row = r0 + 4 * reg + tg, rowc = min(row, a.n - 1);
-        uint32_t bits[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) bits[s] = (uint32_t)(a.mask[s][rowc] >> (4 * tj)) & 15u;
-        if (a.norm == GSR_NORM_RMS) {
-            float z[S][4], ss = 0.f, dot = 0.f;
-#pragma unroll
-            for (int s = 0; s < S; ++s) load_cols<4, T>(a.z + (size_t)rowc * a.ldz + (size_t)s * a.z_sub + 4 * tj, z[s]);
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) {
-                    ss += z[s][cb] * z[s][cb];
-                    dot += ((bits[s] >> cb) & 1u) ? g[s][reg][cb] * z[s][cb] : 0.f;
-                }
-            ss = group16_sum(ss);
-            dot = group16_sum(dot);
-            const float rinv = __builtin_amdgcn_rsqf(ss * (1.0f / (float)DGW) + a.eps);
-            const float coef = dot * (rinv * rinv * rinv) * (1.0f / (float)DGW);
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) g[s][reg][cb] = (((bits[s] >> cb) & 1u) ? g[s][reg][cb] * rinv : 0.f) - z[s][cb] * coef;
-        } else {
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) g[s][reg][cb] = ((bits[s] >> cb) & 1u) ? g[s][reg][cb] : 0.f;
-        }
+        wide_grad_request<S, T>(a, r0, reg, false, w);
+        wide_grad_back<S, T>(a, g, reg, w);
     }
-    for (int j = 0; j < a.ndst; ++j)
+    wide_grad_add<S, T>(a, g, r0, 0);
+}
+
+// Two column blocks, as k_wide_product2
+template <typename T>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_wide_grad2(WideGradArgs<2, T> a) {
+    __shared__ WLdsB3<64> wl[2][2];          // [ob][mb]
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int step = (int)gridDim.x * 8;
+    int t = (int)blockIdx.x * 8 + wave;
+    float v[2][4][4];
+    auto request = [&](int tile) {
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            float d[4][4];
-            T* p = a.dst + (size_t)j * a.dst_gs + 64 * s + 4 * tj;
+        for (int ob = 0; ob < 2; ++ob) plane_request(a.q + (size_t)ob * a.n * 64, tile * 16, a.n, v[ob]);
+    };
+    if (t < a.tiles) request(t);
+#pragma unroll 1
+    for (int b = 0; b < 4; ++b) load_w_lds_b3<64>(a.w + (size_t)(b & 1) * 64 * 128 + 64 * (b >> 1), 128, true, wl[b >> 1][b & 1]);
+    while (t < a.tiles) {
+        const int r0 = t * 16;
+        PlaneOperand p[2];
+        float g[2][4][4];
 #pragma unroll
-            for (int reg = 0; reg < 4; ++reg) load_cols<4, T>(p + (size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ldd, d[reg]);
+        for (int ob = 0; ob < 2; ++ob) plane_split(v[ob], p[ob]);
+        WideGradRows<2> w;
 #pragma unroll
-            for (int reg = 0; reg < 4; ++reg) {
-                const int row = r0 + 4 * reg + tg;
+        for (int reg = 0; reg < 4; ++reg) wide_grad_request<2, T>(a, r0, reg, true, w);
+        t += step;
+        if (t < a.tiles) request(t);
 #pragma unroll
-                for (int cb = 0; cb < 4; ++cb) d[reg][cb] = stored<T>(d[reg][cb] + g[s][reg][cb]);
-                if (row < a.n) store_cols<4, T>(p + (size_t)row * a.ldd, d[reg]);
+        for (int mb = 0; mb < 2; ++mb) {
+            f32x4 acc[2][4];
+#pragma unroll
+            for (int ob = 0; ob < 2; ++ob) {
+                wave_sync();          // (as in k_wide_product2)
+                plane_product(p[ob], wl[ob][mb], acc[ob]);
+            }
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) g[mb][reg][cb] = acc[0][cb][reg] + acc[1][cb][reg];
+        }
+#pragma unroll
+        for (int reg = 0; reg < 4; ++reg) {
+            const int lane = lane_id(), row = r0 + 4 * reg + (lane >> 4);
+            wide_grad_back<2, T>(a, g, reg, w);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) w.d[reg][s][cb] = stored<T>(w.d[reg][s][cb] + g[s][reg][cb]);
+                if (row < a.n) store_cols<4, T>(a.dst + (size_t)row * a.ldd + 64 * s + 4 * (lane & 15), w.d[reg][s]);
             }
         }
+        wide_grad_add<2, T>(a, g, r0, 1);
+    }
 }
 
 // ---- gradient on graphs of long rows in a band --------------------------------------------------------------------
@@ -2101,8 +2242,14 @@ static void launch_wide_product(const Ctx<64, T>& x, int sign, const float* wi, 
         WideProductArgs<S, T> a;
         a.n = (int)x.cfg->n; a.tiles = x.tiles; a.h = x.hplane(); a.w = wi; a.plane = plane; a.ld = ld;
         const dim3 grid((unsigned)((x.tiles + 7) / 8));
-        if (sign > 0) hipLaunchKernelGGL((k_wide_product<S, T, +1>), grid, dim3(512), 0, x.s, a);
-        else hipLaunchKernelGGL((k_wide_product<S, T, -1>), grid, dim3(512), 0, x.s, a);
+        if constexpr (S == 2) {
+            const dim3 cus((unsigned)std::min({(x.tiles + 7) / 8, x.g->num_cus, x.g->grid}));
+            if (sign > 0) hipLaunchKernelGGL((k_wide_product2<T, +1>), cus, dim3(512), 0, x.s, a);
+            else hipLaunchKernelGGL((k_wide_product2<T, -1>), cus, dim3(512), 0, x.s, a);
+        } else {
+            if (sign > 0) hipLaunchKernelGGL((k_wide_product<S, T, +1>), grid, dim3(512), 0, x.s, a);
+            else hipLaunchKernelGGL((k_wide_product<S, T, -1>), grid, dim3(512), 0, x.s, a);
+        }
     });
 }
 
@@ -2118,7 +2265,9 @@ static void launch_wide_grad(const Ctx<64, T>& x, const float* wi, int slot, int
         for (int s = 0; s < S; ++s) a.mask[s] = x.rec(slot, layer, s).mask;
         a.z = z; a.ldz = ldz; a.z_sub = z_sub; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
         a.dst = dst; a.ldd = ldd; a.dst_gs = dst_gs; a.ndst = ndst;
-        hipLaunchKernelGGL((k_wide_grad<S, T>), dim3((unsigned)((x.tiles + 7) / 8)), dim3(512), 0, x.s, a);
+        const int groups = (x.tiles + 7) / 8;
+        if constexpr (S == 2) hipLaunchKernelGGL((k_wide_grad2<T>), dim3((unsigned)std::min({groups, x.g->num_cus, x.g->grid})), dim3(512), 0, x.s, a);
+        else hipLaunchKernelGGL((k_wide_grad<S, T>), dim3((unsigned)groups), dim3(512), 0, x.s, a);
     });
 }
 

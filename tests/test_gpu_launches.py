@@ -1,0 +1,91 @@
+"""Launch forms at their edges: a wave with several tiles of a two-block group, column packing by four (remainders, refused
+indices), row widths of the head, layout copies of rows that do not start on sixteen bytes."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2603_27156_amd as gsr
+from paper_2603_27156_amd import synth
+from gpu_util import Case, assert_close
+from test_gpu_layer import run_step, ROW, PLANAR
+from test_gpu_wide import wide_case
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("n,c,k,layout", [(1029, 2, 16, ROW), (2051, 3, 32, PLANAR), (100, 2, 128, ROW)])
+def test_two_block_groups_with_several_tiles_per_wave(n, c, k, layout):
+    """Eight workgroups of eight waves: 64 waves for 65, 129 and 7 tiles (the last one ragged)."""
+    gsr.gsr_set_option("max_workgroups", 8)
+    try:
+        cs = wide_case(n, 128 * c, c, k, 1, "rms", layout)
+        w, W = cs.w, cs.inp.weights[0]
+        Wd = torch.from_numpy(W).to(cs.dev)
+        Y = oracle.layer_forward(cs.og, cs.ocfg, W, cs.x0_on_grid())
+        y = cs.to_dev(cs.x0_on_grid())
+        gsr.gsr_layer_forward(cs.gg, cs.gcfg, Wd, y)
+        assert_close("Y", cs.to_host(y), Y)
+        rng = np.random.default_rng(5)
+        dY = (rng.standard_normal((w.n, w.d)) * 1e-3).astype(np.float32).astype(np.float64)
+        X_ref, dX_ref, dW_ref = oracle.layer_backward(cs.og, cs.ocfg, W, Y, dY)
+        yb, dyb = cs.to_dev(Y), cs.to_dev(dY)
+        dW = torch.empty((w.c, w.dg, w.dg), dtype=torch.float32, device=cs.dev)
+        gsr.gsr_layer_backward(cs.gg, cs.gcfg, Wd, yb, dyb, dW)
+        assert_close("X", cs.to_host(yb), X_ref)
+        assert_close("dX", cs.to_host(dyb), dX_ref)
+        assert_close("dW", dW.cpu().numpy(), dW_ref)
+    finally:
+        gsr.gsr_set_option("max_workgroups", 0)
+
+
+@pytest.mark.parametrize("dg,k", [(64, 4), (64, 12), (64, 32), (32, 16), (64, 13)])
+def test_columns_packed_by_four(dg, k):
+    """k / 4 lanes per row (1, 3 of 4, 8, 4), and k that is no multiple of four; any slot order; refused indices write nothing."""
+    w = synth.scaled(synth.workload(2), 3003)
+    rng = np.random.Generator(np.random.PCG64(k))
+    rp, ci = synth.circuit_dag(w, rng)
+    og, gg = oracle.graph_build(rp, ci), gsr.gsr_graph_create(rp, ci)
+    V, I, _ = oracle.gs(rng.standard_normal((w.n, dg)).astype(np.float32).astype(np.float64), k)
+    perm = np.argsort(rng.random((w.n, k)), axis=1)
+    v = torch.from_numpy(np.take_along_axis(V, perm, axis=1).astype(np.float32)).cuda()
+    i = torch.from_numpy(np.take_along_axis(I, perm, axis=1).astype(np.int32)).cuda()
+    got = gsr.gsr_spmm_compressed(gg, v, i, dg)
+    assert_close("A scatter(V, I)", got.cpu().numpy(), oracle.aggregate(og, V, I, dg))
+    store = torch.empty(w.n * k + 1, dtype=torch.int32, device="cuda")          # an index array that starts off sixteen bytes
+    store[1:] = i.reshape(-1)
+    assert torch.equal(gsr.gsr_spmm_compressed(gg, v, store[1:].view(w.n, k), dg), got)
+    for row, slot, value in ((0, 0, -1), (w.n - 1, k - 1, dg), (17, k - 1, 1 << 30), (5, 0, None), (w.n - 2, k - 1, None)):
+        bad = i.clone()
+        bad[row, slot] = bad[row, (slot + 1) % k] if value is None else value   # (None: a column named twice)
+        with pytest.raises(gsr.GsrError):
+            gsr.gsr_spmm_compressed(gg, v, bad, dg)
+
+
+@pytest.mark.parametrize("c,dg,layout", [(3, 32, ROW), (2, 64, PLANAR), (3, 64, ROW), (5, 64, PLANAR)])
+def test_head_widths_and_rows_off_sixteen_bytes(c, dg, layout):
+    """D = 96, 128, 192 and 320: two, two, three and five column pieces of the head; the planes of the call on sixteen bytes and four off."""
+    w = synth.scaled(synth.workload(2), 1003, l=2, d=c * dg, c=c, k=dg // 4)
+    cs = Case(w, 1, layout)
+    ref = oracle.step(cs.og, cs.ocfg, w.l, cs.x0_on_grid(), cs.inp.weights, cs.inp.w_out, cs.inp.b_out, cs.inp.target, variant=2)
+    out = run_step(cs, raw=True, save_indices=1)
+    host = run_step(cs, save_indices=1)
+    assert np.isclose(host["loss"], ref["loss"], rtol=1e-4)
+    for key in ("yhat", "XL", "X0rec", "dW", "dwout", "dX0"):
+        assert_close(key, host[key], ref[key])
+    f32 = dict(dtype=torch.float32, device=cs.dev)
+    cfg = gsr.Config(**{**cs.gcfg.__dict__, "l": w.l, "save_indices": 1})
+    x0 = cs.to_dev(cs.inp.x0)
+
+    def off(like):
+        return torch.empty(like.numel() + 1, **f32)[1:].view(like.shape)
+
+    x, dx0, x0r, xl = off(x0), off(x0), off(x0), off(x0)
+    x.copy_(x0)
+    W = torch.from_numpy(np.ascontiguousarray(cs.inp.weights)).to(cs.dev)
+    loss, db, dW, dwout, yhat = torch.zeros(1, **f32), torch.zeros(1, **f32), torch.empty_like(W), torch.empty(w.d, **f32), torch.empty(w.n, **f32)
+    gsr.gsr_step(cs.gg, cfg, x, W, torch.from_numpy(cs.inp.w_out).to(cs.dev), torch.tensor([cs.inp.b_out], **f32),
+                 torch.from_numpy(cs.inp.target).to(cs.dev), loss, dW, dwout, db, yhat_out=yhat, dx0_out=dx0, x0_rebuilt_out=x0r, xl_out=xl,
+                 workspace=torch.empty(gsr.gsr_workspace_size(cs.gg, cfg)[1], dtype=torch.uint8, device=cs.dev))
+    for key, got in (("loss", loss), ("yhat", yhat), ("dW", dW), ("dwout", dwout), ("dX0", dx0), ("X0rec", x0r), ("XL", xl)):
+        assert torch.equal(got, out[key]), key
