@@ -128,7 +128,8 @@ const char* gsr_version(void);
  *                     k <= 64, D/C < 256 where D/C is above 64).  With 0 and 2, and with 16-bit storage whatever the
  *                     option, records of more than half of the columns are held as rows and summed as rows.  Read
  *                     when a graph is created
- *   "max_workgroups"  workgroups of the persistent kernels, multiple of 8 (0: as many as stay resident, at most 4 per CU)
+ *   "max_workgroups"  workgroups of the persistent kernels, multiple of 8 (0: as many as stay resident, at most 4 per CU, on large
+ *                     graphs 5 where a kernel only gathers)
  *   "profile"         bit mask of kernel classes to time (see gsr_profile_read); read at once */
 gsr_status_t gsr_set_option(const char* key, int64_t value);
 
@@ -217,7 +218,8 @@ gsr_status_t gsr_spmm_compressed(const gsr_graph_t* g, const void* vals, const i
  * Bytes of device workspace the layer / step calls need for (cfg, g).  The layer's figure holds, among others, a record
  * per group: N k values of cfg->dtype and N k bytes naming their columns, or (records held as rows) N D/C values, and the
  * column masks; the partial rows of split rows; and with D/C above 64 always two float32 planes of N D/C (the neighbour
- * sums H and A^T dY), up to 64 one, on graphs large enough that a block's backward runs in two kernels.  gsr_step's figure
+ * sums H and A^T dY), up to 64 one, on graphs large enough that a block's backward runs in two kernels, and two on graphs of long
+ * rows in a band (the mean row has 64 stored entries or more and neighbours lie close: dY_i W_i^T and its gathered columns).  gsr_step's figure
  * includes its activation and gradient arena and does not grow with cfg->l (the reversible
  * scheme's memory is independent of depth, Sections 1 and 2) unless cfg->save_indices is set. */
 gsr_status_t gsr_workspace_size(const gsr_config_t* cfg, const gsr_graph_t* g, size_t* layer_bytes,

@@ -1894,15 +1894,16 @@ struct Ctx {
 
 // Workgroups of 256 threads one CU keeps resident for a kernel, and the persistent grid that
 // fills the chip with them: a multiple of 8 (one share per XCD), never above g->grid, which
-// sizes the per-workgroup partial buffers.
+// sizes the per-workgroup partial buffers, or g->gather_grid where the kernel has none.
 static int resident_blocks(const void* kernel, int threads = 256) {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, threads, 0) != hipSuccess || nb < 1) nb = 1;
     return nb;
 }
-static unsigned persistent_grid(const gsr_graph_t* g, int per_cu) {
+static unsigned persistent_grid(const gsr_graph_t* g, int per_cu, bool gather = false) {
     int grid = g->num_cus * per_cu / 8 * 8;
-    if (grid > g->grid) grid = g->grid;
+    const int most = gather ? g->gather_grid : g->grid;
+    if (grid > most) grid = most;
     if (grid < 8) grid = 8;
     return (unsigned)grid;
 }
@@ -2186,7 +2187,7 @@ static void launch_dense_planes(const Ctx<64, T>& x, bool transpose, const T* sr
     tile_counters(x.g, &a.draws, &a.draws_done);
     ProfScope prof(kc, x.s);
     static const int per_cu = resident_blocks((const void*)k_dense_planes<T, false>);
-    const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu) / (unsigned)x.S / 8 * 8);       // the resident workgroups shared out
+    const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu, true) / (unsigned)x.S / 8 * 8);       // the resident workgroups shared out
     if (heavy_first(a.g.n_heavy, x.tiles, grid)) hipLaunchKernelGGL((k_dense_planes<T, true>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
     else hipLaunchKernelGGL((k_dense_planes<T, false>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
 }
@@ -2229,7 +2230,7 @@ static void launch_gather_wide(const Ctx<64, T>& x, int slot, int layer) {
         a.h = x.hplane();
         tile_counters(x.g, &a.draws, &a.draws_done);
         static const int per_cu = resident_blocks((const void*)k_gather_wide<S, T>);
-        hipLaunchKernelGGL((k_gather_wide<S, T>), dim3(persistent_grid(x.g, per_cu)), dim3(256), 0, x.s, a);
+        hipLaunchKernelGGL((k_gather_wide<S, T>), dim3(persistent_grid(x.g, per_cu, true)), dim3(256), 0, x.s, a);
     });
 }
 

@@ -473,9 +473,10 @@ static gsr_status_t aggregate_impl(const gsr_graph_t* g, const void* vals, const
     }
     int *dn, *dx;
     tile_counters(g, &dn, &dx);
-    const bool deal = heavy_first(v.n_heavy, tiles, (unsigned)g->grid);
+    const unsigned grid = (unsigned)g->gather_grid;
+    const bool deal = heavy_first(v.n_heavy, tiles, grid);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)g->grid), dim3(256), 0, s, v, (int)n, tiles, rec, k, (const float*)part, h_out, dn, dx,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, v, (int)n, tiles, rec, k, (const float*)part, h_out, dn, dx,
                            (const int*)bad);
     };
     if (as_rows) deal ? launch(k_aggregate_tile<DG, T, REC_ROWS, true>) : launch(k_aggregate_tile<DG, T, REC_ROWS, false>);
@@ -519,9 +520,9 @@ static gsr_status_t spmm_launch(const gsr_graph_t* g, const float* x, int64_t ld
             else if (width == 32) hipLaunchKernelGGL((k_hub_dense<32, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
             else hipLaunchKernelGGL((k_hub_dense<16, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
         }
-        const bool deal = heavy_first(view.n_heavy, tiles, (unsigned)g->grid);
+        const bool deal = heavy_first(view.n_heavy, tiles, (unsigned)g->gather_grid);
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)g->grid), dim3(256), 0, s, view, (int)g->n, tiles, x, ldx, y, ldy,
+            hipLaunchKernelGGL(kernel, dim3((unsigned)g->gather_grid), dim3(256), 0, s, view, (int)g->n, tiles, x, ldx, y, ldy,
                                (const float*)hub_part, draws, done);
         };
         if (width == 64) deal ? launch(k_spmm_tile<64, true>) : launch(k_spmm_tile<64, false>);
