@@ -77,3 +77,32 @@ def test_band_backward(n, half, keep, c, dg, k, norm, dtype, layout, workgroups)
     else:
         for name, got, ref in (("X", to_host(y), X_ref), ("dX", to_host(dy), dX_ref), ("dW", dW.cpu().numpy(), dW_ref)):
             assert rel_norm(got, ref) <= BF16_REL, name
+
+
+@pytest.mark.parametrize("c,dg,k,workgroups", [(2, 64, 16, 8), (2, 192, 20, 8), (3, 32, 8, 0)])
+def test_band_backward_on_a_directed_weighted_graph(c, dg, k, workgroups):
+    """Row i reaches i .. i + 99 (cut at the end) with values of its own: the band and its entries are those of A^T."""
+    n = 1300
+    lists = [np.arange(i, min(n, i + 100)) for i in range(n)]
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    ci = np.concatenate(lists).astype(np.int32)
+    rng = np.random.default_rng(8)
+    av = rng.uniform(0.01, 0.03, len(ci)).astype(np.float32)
+    gsr.gsr_set_option("max_workgroups", workgroups)
+    try:
+        gg = gsr.gsr_graph_create(rp, ci, vals=av, flags=0)
+    finally:
+        gsr.gsr_set_option("max_workgroups", 0)
+    og = oracle.graph_from_csr(rp, ci, av)
+    d = c * dg
+    ocfg = oracle.Cfg(d, c, k, oracle.NORM_RMS, 1e-5, oracle.STORE_F32)
+    cfg = gsr.Config(n=n, d=d, c=c, k=k, l=1, norm=gsr.GSR_NORM_RMS, eps=1e-5)
+    W = ((rng.random((c, dg, dg)) * 2 - 1) * np.sqrt(3.0 / dg)).astype(np.float32)
+    Y = rng.standard_normal((n, d)).astype(np.float32)
+    dY = (rng.standard_normal((n, d)) * 1e-3).astype(np.float32)
+    X_ref, dX_ref, dW_ref = oracle.layer_backward(og, ocfg, W, Y.astype(np.float64), dY.astype(np.float64))
+    y, dy, dW = torch.from_numpy(Y).cuda(), torch.from_numpy(dY).cuda(), torch.empty((c, dg, dg), dtype=torch.float32, device="cuda")
+    gsr.gsr_layer_backward(gg, cfg, torch.from_numpy(W).cuda(), y, dy, dW)
+    assert_close("X", y.cpu().numpy(), X_ref)
+    assert_close("dX", dy.cpu().numpy(), dX_ref)
+    assert_close("dW", dW.cpu().numpy(), dW_ref)

@@ -6,9 +6,10 @@ import pytest
 import oracle
 import paper_2603_27156_amd as gsr
 from paper_2603_27156_amd import synth
-from gpu_util import Case, assert_close
+from gpu_util import BF16_REL, Case, assert_close, rel_norm
 from test_gpu_layer import run_step, ROW, PLANAR
 from test_gpu_wide import wide_case
+from test_gpu_band import band_graph
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -89,3 +90,29 @@ def test_head_widths_and_rows_off_sixteen_bytes(c, dg, layout):
                  workspace=torch.empty(gsr.gsr_workspace_size(cs.gg, cfg)[1], dtype=torch.uint8, device=cs.dev))
     for key, got in (("loss", loss), ("yhat", yhat), ("dW", dW), ("dwout", dwout), ("dX0", dx0), ("X0rec", x0r), ("XL", xl)):
         assert torch.equal(got, out[key]), key
+
+
+@pytest.mark.parametrize("dg,dtype", [(64, "f32"), (32, "f32"), (64, "bf16")])
+def test_backward_where_every_tile_is_dealt_out(dg, dtype):
+    """Few tiles, all of them with more than 512 entries: dW's partials are summed in a launch of their own there, not beside the tiles."""
+    n, c, k = 1500, 2, dg // 4
+    rowptr, colidx = band_graph(n, 24, 1.0, 1)
+    og, gg = oracle.graph_build(rowptr, colidx), gsr.gsr_graph_create(rowptr, colidx)
+    info = gsr.gsr_graph_info(gg)
+    assert 40 * n < info["nnz"] < 64 * n and info["n_hub_rows"] == 0
+    f32 = dtype == "f32"
+    d, tdt = c * dg, torch.float32 if f32 else torch.bfloat16
+    ocfg = oracle.Cfg(d, c, k, oracle.NORM_RMS, 1e-5, oracle.STORE_F32 if f32 else oracle.STORE_BF16)
+    cfg = gsr.Config(n=n, d=d, c=c, k=k, l=1, dtype=gsr.GSR_F32 if f32 else gsr.GSR_BF16, norm=gsr.GSR_NORM_RMS, eps=1e-5)
+    rng = np.random.default_rng(4)
+    W = ((rng.random((c, dg, dg)) * 2 - 1) * np.sqrt(3.0 / dg)).astype(np.float32)
+    Y, dY = (torch.from_numpy((rng.standard_normal((n, d)) * s).astype(np.float32)).to(tdt) for s in (1.0, 1e-3))
+    refs = oracle.layer_backward(og, ocfg, W, Y.double().numpy(), dY.double().numpy())
+    y, dy, dW = Y.cuda(), dY.cuda(), torch.empty((c, dg, dg), dtype=torch.float32, device="cuda")
+    gsr.gsr_layer_backward(gg, cfg, torch.from_numpy(W).cuda(), y, dy, dW)
+    for name, got, ref in zip(("X", "dX", "dW"), (y, dy, dW), refs):
+        got = got.double().cpu().numpy()
+        if f32:
+            assert_close(name, got, ref)
+        else:
+            assert rel_norm(got, ref) <= BF16_REL, name
