@@ -1028,25 +1028,39 @@ __device__ __forceinline__ void mfma_tile(const float* st, const WLds<DG>& wl, f
 // kernel waits for much of a product's chain.  1M nodes, D/C = 64: forward kernel 228 -> 213 us, 100k nodes inverse + dW 45.9 ->
 // 43.3; 200k nodes, groups of 128, X_i - H W_i 98 -> 88 us, 50k long rows, groups of 192, back through W_i^T 57 -> 45.  Its sums lose
 // less: error of layer outputs and gradients against 64 bits with every column kept 5 - 8 % lower, dW up to 64 columns 8 - 9 %.)
+// With 16-bit storage the products stay 16-deep (DEEP = false).  The 32-deep form adds in another order, which is below any rounding of
+// the sum itself, but one stored value in thirty thousand then rounds to the neighbouring 16-bit number, a step of 2^-8, and where that value
+// is at the k-th place of its row GS keeps another column: a few rows per pass over 8 planes of 1M nodes (their k-th and next
+// value are one such step apart), whose gradients differ by up to twice the plane's root mean square from what the 16-deep form gives.
 // W is kept in LDS already split and laid out as B operands: entry [term][s][cb][lane] holds, for lane (kk = lane / 16,
 // j = lane % 16), the eight bf16 of a 32-deep step s in column CPL j + cb (of W, or of W^T).
 // A lane's eight K-slots of a 32-deep step are two times four rows: with h = 0, 1 and u = 0 .. 3, slot 4 h + u of lane group kk is
 // row 32 s + 16 h + 4 kk + u.  v_mfma_f32_16x16x32_bf16 takes as long as its 16-deep form (16 cycles of the pipe): see mfma_tile_b3.
-template <int DG>
+// 16-deep steps (DEEP = false) read one of the two at a time and have each in a piece of its own.
+template <int DG, bool DEEP>
 struct WLdsB3 {
-    alignas(16) uint64_t w[3][DG / 32][DG / 16][64][2];
+    alignas(16) uint64_t w[3][DEEP ? DG / 32 : DG / 16][DG / 16][64][DEEP ? 2 : 1];
+    // rows 16 s + 4 kk .. + 3
+    __device__ __forceinline__ uint64_t& at(int term, int s, int cb, int lane) {
+        if constexpr (DEEP) return w[term][s >> 1][cb][lane][s & 1];
+        else return w[term][s][cb][lane][0];
+    }
 };
+// whether the products of a layer in storage type T take 32 K-slots per instruction
+template <typename T>
+constexpr bool deep_products() { return sizeof(T) == 4; }
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint64_t as_u64(bf16x4 v) { return __builtin_bit_cast(uint64_t, v); }
+__device__ __forceinline__ bf16x4 as_bf16x4(uint64_t v) { return __builtin_bit_cast(bf16x4, v); }
 // two times four bf16 as the operand of a 32-deep step
 __device__ __forceinline__ bf16x8 join8(bf16x4 h0, bf16x4 h1) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 __device__ __forceinline__ f32x4 mfma_k32(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
-template <int DG>
-__device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int ldw, bool transposed, WLdsB3<DG>& l) {
+template <int DG, bool DEEP>
+__device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int ldw, bool transposed, WLdsB3<DG, DEEP>& l) {
     constexpr int CPL = DG / 16, NB = DG / 16;
     // (the loads of two of a thread's items in flight at a time, as in load_w_lds; not for the transposed form)
     constexpr int NI = 2, ITEMS = NB * NB * 64;
@@ -1060,9 +1074,9 @@ __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int l
             for (int u = 0; u < 4; ++u) v[u] = w[col * ldw + 16 * s + 4 * kk + u];
             bf16x4 hi, mid, lo;
             split_p4(v, hi, mid, lo);
-            l.w[0][s >> 1][cb][lane][s & 1] = as_u64(hi);
-            l.w[1][s >> 1][cb][lane][s & 1] = as_u64(mid);
-            l.w[2][s >> 1][cb][lane][s & 1] = as_u64(lo);
+            l.at(0, s, cb, lane) = as_u64(hi);
+            l.at(1, s, cb, lane) = as_u64(mid);
+            l.at(2, s, cb, lane) = as_u64(lo);
         }
         __syncthreads();
         return;
@@ -1087,39 +1101,55 @@ __device__ __forceinline__ void load_w_lds_b3(const float* __restrict__ w, int l
                 const int lane = e & 63, cb = (e >> 6) % NB, s = (e >> 6) / NB;
                 bf16x4 hi, mid, lo;
                 split_p4(v[t], hi, mid, lo);
-                l.w[0][s >> 1][cb][lane][s & 1] = as_u64(hi);
-                l.w[1][s >> 1][cb][lane][s & 1] = as_u64(mid);
-                l.w[2][s >> 1][cb][lane][s & 1] = as_u64(lo);
+                l.at(0, s, cb, lane) = as_u64(hi);
+                l.at(1, s, cb, lane) = as_u64(mid);
+                l.at(2, s, cb, lane) = as_u64(lo);
             }
         }
     }
     __syncthreads();
 }
 
+__device__ __forceinline__ bf16x4 half8(bf16x8 v, int h) {
+    return __builtin_bit_cast(bf16x4, h == 0 ? __builtin_shufflevector(v, v, 0, 1, 2, 3) : __builtin_shufflevector(v, v, 4, 5, 6, 7));
+}
+
 // acc[cb] += the six products of one 32-deep step with W's blocks cb, smallest terms first; two column blocks in turn, so that no
-// instruction waits for the one before it
-template <int DG>
-__device__ __forceinline__ void mfma_b3(bf16x8 ah, bf16x8 am, bf16x8 al, const WLdsB3<DG>& wl, int s, int lane, f32x4 (&acc)[DG / 16]) {
+// instruction waits for the one before it.  Not DEEP: as two 16-deep steps.
+template <int DG, bool DEEP>
+__device__ __forceinline__ void mfma_b3(bf16x8 ah, bf16x8 am, bf16x8 al, const WLdsB3<DG, DEEP>& wl, int s, int lane, f32x4 (&acc)[DG / 16]) {
+    if constexpr (DEEP) {
 #pragma unroll
-    for (int c0 = 0; c0 < DG / 16; c0 += 2) {
-        bf16x8 bh[2], bm[2], bl[2];
+        for (int c0 = 0; c0 < DG / 16; c0 += 2) {
+            bf16x8 bh[2], bm[2], bl[2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            bh[c] = *reinterpret_cast<const bf16x8*>(wl.w[0][s][c0 + c][lane]);
-            bm[c] = *reinterpret_cast<const bf16x8*>(wl.w[1][s][c0 + c][lane]);
-            bl[c] = *reinterpret_cast<const bf16x8*>(wl.w[2][s][c0 + c][lane]);
+            for (int c = 0; c < 2; ++c) {
+                bh[c] = *reinterpret_cast<const bf16x8*>(wl.w[0][s][c0 + c][lane]);
+                bm[c] = *reinterpret_cast<const bf16x8*>(wl.w[1][s][c0 + c][lane]);
+                bl[c] = *reinterpret_cast<const bf16x8*>(wl.w[2][s][c0 + c][lane]);
+            }
+            auto both = [&](bf16x8 a, const bf16x8 (&b)[2]) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[c0 + c] = mfma_k32(a, b[c], acc[c0 + c]);
+            };
+            both(al, bh); both(ah, bl); both(am, bm); both(am, bh); both(ah, bm); both(ah, bh);
         }
-        auto both = [&](bf16x8 a, const bf16x8 (&b)[2]) {
+    } else {
 #pragma unroll
-            for (int c = 0; c < 2; ++c) acc[c0 + c] = mfma_k32(a, b[c], acc[c0 + c]);
-        };
-        both(al, bh); both(ah, bl); both(am, bm); both(am, bh); both(ah, bm); both(ah, bh);
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int cb = 0; cb < DG / 16; ++cb) {
+                const bf16x4 bh = as_bf16x4(wl.w[0][2 * s + h][cb][lane][0]), bm = as_bf16x4(wl.w[1][2 * s + h][cb][lane][0]),
+                             bl = as_bf16x4(wl.w[2][2 * s + h][cb][lane][0]);
+                auto add = [&](bf16x8 a, bf16x4 b) { acc[cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(half8(a, h), b, acc[cb], 0, 0, 0); };
+                add(al, bh); add(am, bm); add(ah, bl); add(am, bh); add(ah, bm); add(ah, bh);
+            }
     }
 }
 
 // acc = tile (16 x DG float32, LDS, row stride tile_ld) * W, in the tile register layout of mfma_tile.
-template <int DG>
-__device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& wl, f32x4 (&acc)[DG / 16]) {
+template <int DG, bool DEEP>
+__device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG, DEEP>& wl, f32x4 (&acc)[DG / 16]) {
     constexpr int CPL = DG / 16;
     const int lane = lane_id(), i = lane & 15, kk = lane >> 4;
     const int arow = 4 * (i & 3) + (i >> 2);
@@ -1133,8 +1163,8 @@ __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& 
         bf16x4 ah[2], am[2], al[2];
         split_p4(a, ah[0], am[0], al[0]);
         split_p4(a + 4, ah[1], am[1], al[1]);
-        mfma_b3<DG>(join8(ah[0], ah[1]), join8(am[0], am[1]), join8(al[0], al[1]), wl, s, lane, acc);
-        __builtin_amdgcn_sched_barrier(0);      // (the next step's operands requested beside this one's: a register spilled in three variants)
+        mfma_b3<DG, DEEP>(join8(ah[0], ah[1]), join8(am[0], am[1]), join8(al[0], al[1]), wl, s, lane, acc);
+        if constexpr (DEEP) __builtin_amdgcn_sched_barrier(0);      // (the next step's operands requested beside this one's: a register spilled in three variants)
     }
 }
 
@@ -1142,7 +1172,7 @@ __device__ __forceinline__ void mfma_tile_b3(const float* st, const WLdsB3<DG>& 
 // instruction, so an instruction takes two of the six products at once: slot 4 kk + u of either half stands for tile row 4 u + kk, so
 // that the B operand of lane (kk, j) is what the lane already holds of dY (gy[u][ob], rows 4 u + kk) and the A operand is
 // H[4 u + kk][16 mb + j] from the LDS tile.  Pairs: (lo hi, mid mid), (mid hi, hi mid), (hi lo, hi hi).  Rows of dY held in 16 bits
-// (T) are their own first term and have no others: (lo hi, mid hi), then hi hi alone.
+// (T) are their own first term and have no others: lo hi, mid hi and hi hi one by one, the rows 16 deep (see mfma_tile_b3).
 template <int DG, typename T>
 __device__ __forceinline__ void mfma_outer_b3(const float* st_h, const float (&gy)[4][DG / 16], f32x4 (&acc)[DG / 16][DG / 16]) {
     const int lane = lane_id(), kk = lane >> 4, j = lane & 15;
@@ -1163,7 +1193,9 @@ __device__ __forceinline__ void mfma_outer_b3(const float* st_h, const float (&g
         split_p4(a, ah, am, al);
         if constexpr (EXACT) {
 #pragma unroll
-            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = mfma_k32(join8(al, am), join8(bh[ob], bh[ob]), acc[mb][ob]);
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh[ob], acc[mb][ob], 0, 0, 0);
+#pragma unroll
+            for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, bh[ob], acc[mb][ob], 0, 0, 0);
 #pragma unroll
             for (int ob = 0; ob < DG / 16; ++ob) acc[mb][ob] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh[ob], acc[mb][ob], 0, 0, 0);
         } else {

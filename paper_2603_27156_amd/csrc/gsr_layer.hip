@@ -73,8 +73,8 @@ __global__ __launch_bounds__(64 * block_waves(WITH_DW, B3)) __attribute__((amdgp
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     WaveLds<DG, true>& L = lds[wave];
     float* st_h = L.st;
-    __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
-    if constexpr (B3) load_w_lds_b3<DG>(a.w, DG, false, wl);
+    __shared__ typename std::conditional<B3, WLdsB3<DG, deep_products<T>()>, WLds<DG>>::type wl;
+    if constexpr (B3) load_w_lds_b3(a.w, DG, false, wl);
     else load_w_lds<DG>(a.w, false, wl);
     f32x4 dw[WITH_DW ? DG / 16 : 1][WITH_DW ? DG / 16 : 1];
     if constexpr (WITH_DW) {
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     WaveLds<DG>& L = lds[wave];
     float* st = L.st;
-    __shared__ typename std::conditional<B3, WLdsB3<DG>, WLds<DG>>::type wl;
+    __shared__ typename std::conditional<B3, WLdsB3<DG, deep_products<T>()>, WLds<DG>>::type wl;
     static_assert(GRAD_WAVES >= 4 && sizeof(lds) >= 64 * GRAD_WAVES * sizeof(float), "dw_reduce_slices works with the first 256 threads");
     if constexpr (!DEAL) {
         if (a.beside_out && blockIdx.y == 1) {
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(64 * grad_waves(B3)) __attribute__((amdgpu_waves_pe
         }
     }
     if (a.dw_out) dw_reduce_slices<DG * DG>(a.dw_partial, a.dw_parts, a.dw_out, reinterpret_cast<float*>(lds));
-    if constexpr (B3) load_w_lds_b3<DG>(a.w, DG, true, wl);
+    if constexpr (B3) load_w_lds_b3(a.w, DG, true, wl);
     else load_w_lds<DG>(a.w, true, wl);
     TileDraws td = tile_draws(a.tiles, a.draws, a.draws_done);
     TileDeal deal{0, 0, 0, false};
@@ -886,12 +886,13 @@ __device__ __forceinline__ void plane_request(const float* __restrict__ plane, i
 #pragma unroll
     for (int s = 0; s < 4; ++s) load_cols<4, float>(plane + (size_t)row * 64 + 16 * s + 4 * kk, v[s]);
 }
-__device__ __forceinline__ void plane_product(const PlaneOperand& p, const WLdsB3<64>& wl, f32x4 (&acc)[4]) {
+template <bool DEEP>
+__device__ __forceinline__ void plane_product(const PlaneOperand& p, const WLdsB3<64, DEEP>& wl, f32x4 (&acc)[4]) {
     const int lane = lane_id();
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < 2; ++s) mfma_b3(p.hi[s], p.mid[s], p.lo[s], wl, s, lane, acc);
+    for (int s = 0; s < 2; ++s) mfma_b3<64>(p.hi[s], p.mid[s], p.lo[s], wl, s, lane, acc);
 }
 // the columns of v (steps s of plane_request) in three terms
 __device__ __forceinline__ void plane_split(const float (&v)[4][4], PlaneOperand& p) {
@@ -918,7 +919,7 @@ struct WideProductArgs {
 };
 template <int S, typename T, int SIGN>
 __global__ __launch_bounds__(512) void k_wide_product(WideProductArgs<S, T> a) {
-    __shared__ WLdsB3<64> wl[S];
+    __shared__ WLdsB3<64, deep_products<T>()> wl[S];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     const int t = (int)blockIdx.x * 8 + wave, r0 = t * 16;
     float y[S][4][4];
@@ -932,7 +933,7 @@ __global__ __launch_bounds__(512) void k_wide_product(WideProductArgs<S, T> a) {
         plane_request(a.h + (size_t)mb * a.n * 64, r0, a.n, v);
         __syncthreads();        // the blocks before have been read
 #pragma unroll 1
-        for (int ob = 0; ob < S; ++ob) load_w_lds_b3<64>(a.w + (size_t)mb * 64 * (64 * S) + 64 * ob, 64 * S, false, wl[ob]);
+        for (int ob = 0; ob < S; ++ob) load_w_lds_b3(a.w + (size_t)mb * 64 * (64 * S) + 64 * ob, 64 * S, false, wl[ob]);
         PlaneOperand p;
         plane_split(v, p);
 #pragma unroll
@@ -959,7 +960,7 @@ __global__ __launch_bounds__(512) void k_wide_product(WideProductArgs<S, T> a) {
 // groups of 128, X_i - H W_i 88 -> 72 us, back through W_i^T 99 -> 84 us; three blocks' W_i does not fit.)
 template <typename T, int SIGN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_wide_product2(WideProductArgs<2, T> a) {
-    __shared__ WLdsB3<64> wl[2][2];
+    __shared__ WLdsB3<64, deep_products<T>()> wl[2][2];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     const int step = (int)gridDim.x * 8;
     int t = (int)blockIdx.x * 8 + wave;
@@ -974,7 +975,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     };
     if (t < a.tiles) request(t);
 #pragma unroll 1
-    for (int b = 0; b < 4; ++b) load_w_lds_b3<64>(a.w + (size_t)(b >> 1) * 64 * 128 + 64 * (b & 1), 128, false, wl[b >> 1][b & 1]);
+    for (int b = 0; b < 4; ++b) load_w_lds_b3(a.w + (size_t)(b >> 1) * 64 * 128 + 64 * (b & 1), 128, false, wl[b >> 1][b & 1]);
     while (t < a.tiles) {
         const int r0 = t * 16;
         PlaneOperand p[2];
@@ -1100,7 +1101,7 @@ __device__ __forceinline__ void wide_grad_add(const WideGradArgs<S, T>& a, const
 template <int S, typename T>
 __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
     constexpr int DGW = 64 * S;
-    __shared__ WLdsB3<64> wl[S];
+    __shared__ WLdsB3<64, deep_products<T>()> wl[S];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     const int t = (int)blockIdx.x * 8 + wave, r0 = t * 16;
     float g[S][4][4];
@@ -1116,7 +1117,7 @@ __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
         plane_request(a.q + (size_t)ob * a.n * 64, r0, a.n, v);
         __syncthreads();
 #pragma unroll 1
-        for (int mb = 0; mb < S; ++mb) load_w_lds_b3<64>(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
+        for (int mb = 0; mb < S; ++mb) load_w_lds_b3(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
         PlaneOperand p;
         plane_split(v, p);
 #pragma unroll
@@ -1141,7 +1142,7 @@ __global__ __launch_bounds__(512) void k_wide_grad(WideGradArgs<S, T> a) {
 // Two column blocks, as k_wide_product2
 template <typename T>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_wide_grad2(WideGradArgs<2, T> a) {
-    __shared__ WLdsB3<64> wl[2][2];          // [ob][mb]
+    __shared__ WLdsB3<64, deep_products<T>()> wl[2][2];          // [ob][mb]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int step = (int)gridDim.x * 8;
     int t = (int)blockIdx.x * 8 + wave;
@@ -1152,7 +1153,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     };
     if (t < a.tiles) request(t);
 #pragma unroll 1
-    for (int b = 0; b < 4; ++b) load_w_lds_b3<64>(a.w + (size_t)(b & 1) * 64 * 128 + 64 * (b >> 1), 128, true, wl[b >> 1][b & 1]);
+    for (int b = 0; b < 4; ++b) load_w_lds_b3(a.w + (size_t)(b & 1) * 64 * 128 + 64 * (b >> 1), 128, true, wl[b >> 1][b & 1]);
     while (t < a.tiles) {
         const int r0 = t * 16;
         PlaneOperand p[2];
@@ -1216,7 +1217,7 @@ struct PreProductArgs {
 template <int DG, int S, typename T>
 __global__ __launch_bounds__(512) void k_pre_product(PreProductArgs<DG, S, T> a) {
     constexpr int CPL = DG / 16, DGW = DG * S;
-    __shared__ WLdsB3<DG> wl[S];
+    __shared__ WLdsB3<DG, true> wl[S];
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), tg = lane >> 4, tj = lane & 15;
     const int r0 = ((int)blockIdx.x * 8 + wave) * 16;
     const int arow = min(r0 + 4 * (tj & 3) + (tj >> 2), a.n - 1);
@@ -1237,7 +1238,7 @@ __global__ __launch_bounds__(512) void k_pre_product(PreProductArgs<DG, S, T> a)
             for (int u = 0; u < 4; ++u) v[s][u] = __uint_as_float(__float_as_uint(v[s][u]) ^ flip_in);
         __syncthreads();        // the blocks before have been read
 #pragma unroll 1
-        for (int mb = 0; mb < S; ++mb) load_w_lds_b3<DG>(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
+        for (int mb = 0; mb < S; ++mb) load_w_lds_b3(a.w + (size_t)mb * 64 * DGW + 64 * ob, DGW, true, wl[mb]);
         bf16x8 hi[DG / 32], mid[DG / 32], lo[DG / 32];
 #pragma unroll
         for (int s = 0; s < DG / 32; ++s) {
