@@ -286,7 +286,8 @@ __device__ __forceinline__ float hub_chunks_sum(const float* __restrict__ part, 
     return acc;
 }
 
-// the same for two rows at once, thirty-two requested at a time (30k nodes, eight nets of 5,000 sinks: inverse kernel 18.2 -> 17.0 us)
+// the same for two rows at once, thirty-two requested at a time (30k nodes, eight nets of 5,000 sinks: inverse kernel 18.2 -> 17.0 us; see
+// hub_rows_fill)
 template <int DG>
 __device__ __forceinline__ void hub_chunks_sum2(const float* __restrict__ part, int qa, int qa1, int qb, int qb1, int c, float& a, float& b) {
     constexpr int NB = 16;
@@ -823,13 +824,13 @@ __device__ __forceinline__ void gather_dense_rows(const CsrView& g, const T* __r
     }
 }
 
-template <int DG, bool FAST = true>
+template <int DG, bool FAST, bool PAIRS = true>
 __device__ __forceinline__ void hub_rows_fill(const CsrView& g, const float* __restrict__ hub_part, int r0, const int* s_rp,
                                               float* st, int lane);
 
 // H of the tile into st through a row-wise gather: st (ROWS rows of it) is cleared, the runs of ordinary rows are added into it,
 // split rows receive the sum of their first-pass partial rows afterwards.
-template <int DG, bool FAST = true, int ROWS = 16, typename Range>
+template <int DG, bool FAST = true, int ROWS = 16, bool PAIRS = true, typename Range>
 __device__ __forceinline__ void tile_gather_rows(const CsrView& g, const float* __restrict__ hub_part, bool has_hub, int r0,
                                                  const int* s_rp, float* st, int lane, Range range) {
     static_assert(ROWS * tile_ld<DG>() % 4 == 0, "cleared in pieces of 16 bytes");
@@ -837,7 +838,7 @@ __device__ __forceinline__ void tile_gather_rows(const CsrView& g, const float* 
     wave_sync();
     tile_ranges(g, has_hub, s_rp, range);
     wave_sync();
-    if (has_hub) hub_rows_fill<DG, FAST>(g, hub_part, r0, s_rp, st, lane);
+    if (has_hub) hub_rows_fill<DG, FAST, PAIRS>(g, hub_part, r0, s_rp, st, lane);
 }
 
 // sum of the first-pass partial rows of every split row of the tile into st, each row's in chunk order.  On a graph of
@@ -851,7 +852,10 @@ __device__ __forceinline__ void tile_gather_rows(const CsrView& g, const float* 
 constexpr int HUB_FILL_ROWS = 16;     // rows whose partial rows are requested together
 constexpr int HUB_FILL_DEPTH = 4;     // partial rows per row taken that way (the launch of a long-row graph ends with the
                                       // tile whose rows go on one by one: 26 us against a median of 6)
-template <int DG, bool FAST>
+// PAIRS: rows of more chunks than that go on two at a time, else one by one.  Two at a time shorten
+// the tile of the longest rows, which a launch of few tiles per wave ends with; a kernel that only gathers pays for it in its sweep (93
+// registers for 65, k_spmm_tile of 32 columns: 750k rows 106 us against 98), so the operators take it by their number of tiles.
+template <int DG, bool FAST, bool PAIRS>
 __device__ __forceinline__ void hub_rows_fill(const CsrView& g, const float* __restrict__ hub_part, int r0, const int* s_rp,
                                               float* st, int lane) {
     // (FAST = false: a search per row and the rows one by one - for kernels that have no register to spare; same
@@ -899,7 +903,16 @@ __device__ __forceinline__ void hub_rows_fill(const CsrView& g, const float* __r
             }
         }
     }
-    // rows of more chunks than that go on in pairs, thirty-two loads in flight (an odd one with itself)
+    if constexpr (!PAIRS) {
+        for (int r = 0; r < 16; ++r) {          // sixteen loads in flight
+            const int q = __builtin_amdgcn_readlane(q0v, r) + HUB_FILL_DEPTH, q1 = __builtin_amdgcn_readlane(q1v, r);
+            if (q1 <= q) continue;
+            const float acc = hub_chunks_sum<DG>(hub_part, q, q1, c, st[r * tile_ld<DG>() + c]);
+            if (lane < DG) st[r * tile_ld<DG>() + lane] = acc;
+        }
+        return;
+    }
+    // in pairs, thirty-two loads in flight (an odd one with itself)
     uint64_t more = __builtin_amdgcn_ballot_w64(q1v - q0v > HUB_FILL_DEPTH);
     while (more != 0ull) {
         const int ra = __builtin_ctzll(more);

@@ -181,7 +181,8 @@ __device__ __forceinline__ void store_acc_rows(const f32x4 (&acc)[W / 16], const
 // Widths 32 and 64: the sums of a tile in ordinary arithmetic into an LDS tile (gather_dense_rows: on this chip the
 // float32 matrix instructions do not run beside the vector pipe, and a 16-row product spends fifteen rows of every
 // edge on zeros), rows stored from there; width 16: on the matrix cores, rows stored from the accumulators.
-template <int W, bool DEAL>
+// PAIRS: see hub_rows_fill (width 16 sums split rows itself).
+template <int W, bool DEAL, bool PAIRS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_spmm_tile(CsrView g, int n, int tiles, const float* __restrict__ x, int64_t ldx,
                                                    float* __restrict__ y, int64_t ldy, const float* __restrict__ hub_part,
                                                    int* draws, int* draws_done) {
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const bool has_hub = tile_begin(g, rpv, L.rp, lane);
         if (walk.dealt(g, rpv, L.rp, has_hub)) { walk.next(g); continue; }
         if constexpr (ROWS) {
-            tile_gather_rows<W>(g, hub_part, has_hub, r0, L.rp, Wv.st, lane, [&](int e_a, int e_b) {
+            tile_gather_rows<W, true, 16, PAIRS>(g, hub_part, has_hub, r0, L.rp, Wv.st, lane, [&](int e_a, int e_b) {
                 gather_dense_rows<W, 8>(g, x, ldx, __builtin_amdgcn_readfirstlane(e_a), __builtin_amdgcn_readfirstlane(e_b),
                                         lane, Wv.st);
             });
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // The sums of a tile into an LDS tile (gather_values_rows, or gather_dense_rows where the values were laid out as rows), rows
 // stored from there.  *bad: the indices have been found wanting by the kernel before, nothing is written.
-template <int DG, typename T, RecordForm FORM, bool DEAL>
+template <int DG, typename T, RecordForm FORM, bool DEAL, bool PAIRS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_aggregate_tile(CsrView g, int n, int tiles, Record<DG, T> in, int k,
                                                         const float* __restrict__ hub_part, float* __restrict__ h_out,
                                                         int* draws, int* draws_done, const int* __restrict__ bad) {
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const int rpv = tile_rp_load(g, r0, n, lane);
         const bool has_hub = tile_begin(g, rpv, W.rp, lane);
         if (walk.dealt(g, rpv, W.rp, has_hub)) { walk.next(g); continue; }
-        tile_gather_rows<DG, true, 20>(g, hub_part, has_hub, r0, W.rp, W.st, lane, [&](int e_a, int e_b) {
+        tile_gather_rows<DG, true, 20, PAIRS>(g, hub_part, has_hub, r0, W.rp, W.st, lane, [&](int e_a, int e_b) {
             const int ea = __builtin_amdgcn_readfirstlane(e_a), eb = __builtin_amdgcn_readfirstlane(e_b);
             if constexpr (FORM == REC_ROWS) gather_dense_rows<DG, 8>(g, in.vals, DG, ea, eb, lane, W.st);
             else gather_values_rows<DG, 8, false>(g, in.vals, in.cols, k, ea, eb, lane, W.st);
@@ -474,13 +475,21 @@ static gsr_status_t aggregate_impl(const gsr_graph_t* g, const void* vals, const
     int *dn, *dx;
     tile_counters(g, &dn, &dx);
     const unsigned grid = (unsigned)g->gather_grid;
-    const bool deal = heavy_first(v.n_heavy, tiles, grid);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, v, (int)n, tiles, rec, k, (const float*)part, h_out, dn, dx,
                            (const int*)bad);
     };
-    if (as_rows) deal ? launch(k_aggregate_tile<DG, T, REC_ROWS, true>) : launch(k_aggregate_tile<DG, T, REC_ROWS, false>);
-    else deal ? launch(k_aggregate_tile<DG, T, REC_COLUMNS, true>) : launch(k_aggregate_tile<DG, T, REC_COLUMNS, false>);
+    // Split rows of many chunks two at a time with fewer than eight tiles per wave: 300k rows of 64 columns 133.6 us against 136.5 one by
+    // one, 400k 146.8 / 152.1, 500k 166.1 / 167.7, 600k (nine tiles) 191.0 / 188.2; of 32 columns, k = 8, 111.9 / 114.8, 115.4 / 120.5, 127.2 / 128.6,
+    // 142.2 / 137.5.
+    const bool deal = heavy_first(v.n_heavy, tiles, grid), pairs = tiles < (int64_t)32 * grid;
+    auto of_records = [&](auto r) {
+        constexpr RecordForm FORM = decltype(r)::value;
+        if (pairs) deal ? launch(k_aggregate_tile<DG, T, FORM, true, true>) : launch(k_aggregate_tile<DG, T, FORM, false, true>);
+        else deal ? launch(k_aggregate_tile<DG, T, FORM, true, false>) : launch(k_aggregate_tile<DG, T, FORM, false, false>);
+    };
+    if (as_rows) of_records(std::integral_constant<RecordForm, REC_ROWS>{});
+    else of_records(std::integral_constant<RecordForm, REC_COLUMNS>{});
     GSR_HIP_CHECK(hipGetLastError());
     int bad_h = 0;
     GSR_HIP_CHECK(hipMemcpyAsync(&bad_h, bad, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -520,14 +529,23 @@ static gsr_status_t spmm_launch(const gsr_graph_t* g, const float* x, int64_t ld
             else if (width == 32) hipLaunchKernelGGL((k_hub_dense<32, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
             else hipLaunchKernelGGL((k_hub_dense<16, float>), hg, dim3(256), 0, s, view, hc, x, ldx, hub_part, (float*)nullptr);
         }
-        const bool deal = heavy_first(view.n_heavy, tiles, (unsigned)g->gather_grid);
+        // Split rows of many chunks two at a time with at most two tiles per wave: 60k rows, eight nets of 5,000 sinks, 64 columns 29.2 us against
+        // 30.3 one by one, 110k 44.8 / 45.9, 250k 71.1 / 71.4, 500k 98.8 / 98.2; 32 columns 24.7 / 25.8, 39.6 / 39.8, 58.7 / 56.6, 77.9 / 76.6, 750k
+        // 106.1 / 97.8, 1M 120.8 / 113.0.
+        const bool deal = heavy_first(view.n_heavy, tiles, (unsigned)g->gather_grid), pairs = !deal && tiles <= (int64_t)8 * g->gather_grid;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)g->gather_grid), dim3(256), 0, s, view, (int)g->n, tiles, x, ldx, y, ldy,
                                (const float*)hub_part, draws, done);
         };
-        if (width == 64) deal ? launch(k_spmm_tile<64, true>) : launch(k_spmm_tile<64, false>);
-        else if (width == 32) deal ? launch(k_spmm_tile<32, true>) : launch(k_spmm_tile<32, false>);
-        else deal ? launch(k_spmm_tile<16, true>) : launch(k_spmm_tile<16, false>);
+        auto of_width = [&](auto w) {
+            constexpr int W = decltype(w)::value;
+            if (deal) launch(k_spmm_tile<W, true, false>);
+            else if (pairs) launch(k_spmm_tile<W, false, W != 16>);
+            else launch(k_spmm_tile<W, false, false>);
+        };
+        if (width == 64) of_width(std::integral_constant<int, 64>{});
+        else if (width == 32) of_width(std::integral_constant<int, 32>{});
+        else of_width(std::integral_constant<int, 16>{});
         GSR_HIP_CHECK(hipGetLastError());
         return GSR_OK;
     }

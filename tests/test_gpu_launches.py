@@ -116,3 +116,49 @@ def test_backward_where_every_tile_is_dealt_out(dg, dtype):
             assert_close(name, got, ref)
         else:
             assert rel_norm(got, ref) <= BF16_REL, name
+
+
+def graph_cut_at_64(rp, ci, workgroups):
+    """Rows above 64 entries in chunks of 64, whatever the number of workgroups makes of the graph by itself."""
+    options = {"max_workgroups": workgroups, "hub_threshold": 64, "hub_chunk": 64}
+    try:
+        for key, value in options.items():
+            gsr.gsr_set_option(key, value)
+        return gsr.gsr_graph_create(rp, ci)
+    finally:
+        for key in options:
+            gsr.gsr_set_option(key, 0)
+
+
+def net_graph(n, nets, sinks, seed):
+    """Rows of two neighbours, and `nets` nodes of the second tile wired to `sinks` others each."""
+    rng = np.random.default_rng(seed)
+    rows, cols = np.repeat(np.arange(n), 2), rng.integers(0, n, 2 * n)
+    for h in range(nets):
+        rows, cols = np.concatenate([rows, np.full(sinks, 16 + h)]), np.concatenate([cols, rng.permutation(n)[:sinks]])
+    key = np.unique(rows * n + cols)
+    return np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int32), (key % n).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 4080, 4081])
+def test_rows_of_many_chunks_one_by_one_and_in_pairs(n):
+    """Rows of 600 entries (ten chunks of 64), an odd number of them in one tile, with 32 waves: gsr_spmm adds them up in pairs to 64 tiles,
+    gsr_spmm_compressed below 256.  The additions are the same as with a wave per tile."""
+    rp, ci = net_graph(n, 3, 600, n)
+    og = oracle.graph_build(rp, ci)
+    got = {}
+    for workgroups in (8, 0):
+        g = graph_cut_at_64(rp, ci, workgroups)
+        assert gsr.gsr_graph_info(g)["n_hub_rows"] == 3
+        rng = np.random.default_rng(6)
+        out = []
+        for width in (64, 32, 16):
+            X = rng.standard_normal((n, width)).astype(np.float32)
+            out.append(gsr.gsr_spmm(g, torch.from_numpy(X).cuda()))
+            assert_close("A X", out[-1].cpu().numpy(), oracle.spmm(og, X))
+        for dg, k in ((64, 16), (32, 8), (64, 60)):
+            V, I, _ = oracle.gs(rng.standard_normal((n, dg)).astype(np.float32).astype(np.float64), k)
+            out.append(gsr.gsr_spmm_compressed(g, torch.from_numpy(V.astype(np.float32)).cuda(), torch.from_numpy(I.astype(np.int32)).cuda(), dg))
+            assert_close("A scatter(V, I)", out[-1].cpu().numpy(), oracle.aggregate(og, V, I, dg))
+        got[workgroups] = out
+    assert all(torch.equal(a, b) for a, b in zip(got[8], got[0]))

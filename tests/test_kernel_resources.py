@@ -2,6 +2,7 @@
 import struct
 
 import msgpack
+import pytest
 
 import paper_2603_27156_amd as gsr
 
@@ -43,3 +44,15 @@ def test_no_kernel_spills_registers():
     spilling = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in ks.items()
                 if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not spilling, spilling
+
+
+# Registers that a launch rule or a measured figure counts on (a wave may have 512 / waves per SIMD of them): two workgroups of eight waves
+# beside each other on a compute unit in the products of three column blocks, and the sums over neighbours of 32 columns, whose sweep
+# slowed by a tenth at 93 registers.
+@pytest.mark.parametrize("kernel,most", [
+    ("k_wide_productILi3E", 128), ("k_wide_gradILi3E", 128),
+    ("k_spmm_tileILi32ELb0ELb0E", 80), ("k_spmm_tileILi32ELb1ELb0E", 80),
+])
+def test_registers_that_residency_counts_on(kernel, most):
+    held = {n: k[".vgpr_count"] for n, k in kernels().items() if kernel in n}
+    assert held and max(held.values()) <= most, held
