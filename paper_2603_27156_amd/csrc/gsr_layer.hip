@@ -2235,6 +2235,18 @@ static void launch_gather_wide(const Ctx<64, T>& x, int slot, int layer) {
     });
 }
 
+// Two column blocks: workgroups of a sweep with all of W_i in LDS (k_wide_product2, k_wide_grad2), one per compute unit, or 0 where a workgroup
+// per eight tiles (k_wide_product, k_wide_grad) is better.  The sweep leaves one workgroup resident per unit where the other form has two or three,
+// so one round of eight tiles more than the other form needs costs a whole round: groups of 128, k = 32, forward / backward layer, sweep against
+// other form, us: 16-bit 24k nodes (one round at most) 127.3 / 288.1, 125.3 / 288.6; 50k 188.6 / 401.2, 181.0 / 382.9; 64k (two rounds) 197.3 / 433.2,
+// 190.1 / 416.3; 72k 217.8 / 481.7 against 228 / 499; float32 24k 129.4 / 300.3, 128.9 / 303.9; 50k 189.0 / 429.1, 185.9 / 412.4; 64k 202.7 / 478.3,
+// 205.1 / 472.0.
+template <typename T>
+static unsigned sweep_workgroups(const Ctx<64, T>& x) {
+    const int cus = std::min(x.g->num_cus, x.g->grid), groups = (x.tiles + 7) / 8;
+    return groups > 2 * cus || (groups <= cus && sizeof(T) == 4) ? (unsigned)std::min(groups, cus) : 0u;
+}
+
 // plane (+/-)= H W_i with H in x.hplane()
 template <typename T>
 static void launch_wide_product(const Ctx<64, T>& x, int sign, const float* wi, T* plane, int64_t ld) {
@@ -2245,13 +2257,14 @@ static void launch_wide_product(const Ctx<64, T>& x, int sign, const float* wi, 
         a.n = (int)x.cfg->n; a.tiles = x.tiles; a.h = x.hplane(); a.w = wi; a.plane = plane; a.ld = ld;
         const dim3 grid((unsigned)((x.tiles + 7) / 8));
         if constexpr (S == 2) {
-            const dim3 cus((unsigned)std::min({(x.tiles + 7) / 8, x.g->num_cus, x.g->grid}));
-            if (sign > 0) hipLaunchKernelGGL((k_wide_product2<T, +1>), cus, dim3(512), 0, x.s, a);
-            else hipLaunchKernelGGL((k_wide_product2<T, -1>), cus, dim3(512), 0, x.s, a);
-        } else {
-            if (sign > 0) hipLaunchKernelGGL((k_wide_product<S, T, +1>), grid, dim3(512), 0, x.s, a);
-            else hipLaunchKernelGGL((k_wide_product<S, T, -1>), grid, dim3(512), 0, x.s, a);
+            if (const unsigned cus = sweep_workgroups(x)) {
+                if (sign > 0) hipLaunchKernelGGL((k_wide_product2<T, +1>), dim3(cus), dim3(512), 0, x.s, a);
+                else hipLaunchKernelGGL((k_wide_product2<T, -1>), dim3(cus), dim3(512), 0, x.s, a);
+                return;
+            }
         }
+        if (sign > 0) hipLaunchKernelGGL((k_wide_product<S, T, +1>), grid, dim3(512), 0, x.s, a);
+        else hipLaunchKernelGGL((k_wide_product<S, T, -1>), grid, dim3(512), 0, x.s, a);
     });
 }
 
@@ -2267,9 +2280,13 @@ static void launch_wide_grad(const Ctx<64, T>& x, const float* wi, int slot, int
         for (int s = 0; s < S; ++s) a.mask[s] = x.rec(slot, layer, s).mask;
         a.z = z; a.ldz = ldz; a.z_sub = z_sub; a.norm = x.cfg->norm; a.eps = x.cfg->eps;
         a.dst = dst; a.ldd = ldd; a.dst_gs = dst_gs; a.ndst = ndst;
-        const int groups = (x.tiles + 7) / 8;
-        if constexpr (S == 2) hipLaunchKernelGGL((k_wide_grad2<T>), dim3((unsigned)std::min({groups, x.g->num_cus, x.g->grid})), dim3(512), 0, x.s, a);
-        else hipLaunchKernelGGL((k_wide_grad<S, T>), dim3((unsigned)groups), dim3(512), 0, x.s, a);
+        if constexpr (S == 2) {
+            if (const unsigned cus = sweep_workgroups(x)) {
+                hipLaunchKernelGGL((k_wide_grad2<T>), dim3(cus), dim3(512), 0, x.s, a);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_wide_grad<S, T>), dim3((unsigned)((x.tiles + 7) / 8)), dim3(512), 0, x.s, a);
     });
 }
 

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import paper_2603_27156_amd as gsr
 from paper_2603_27156_amd import synth
-from gpu_util import BF16_REL, Case, assert_close, rel_norm
+from gpu_util import BF16_REL, Case, assert_close, bf16_bar, rel_norm
 from test_gpu_layer import run_step, ROW, PLANAR
 from test_gpu_wide import wide_case
 from test_gpu_band import band_graph
@@ -162,3 +162,34 @@ def test_rows_of_many_chunks_one_by_one_and_in_pairs(n):
             assert_close("A scatter(V, I)", out[-1].cpu().numpy(), oracle.aggregate(og, V, I, dg))
         got[workgroups] = out
     assert all(torch.equal(a, b) for a, b in zip(got[8], got[0]))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 2049])
+def test_two_block_groups_by_sweep_and_by_workgroup(n, dtype):
+    """8 and 9 groups of eight tiles, 16 and 17, for 8 workgroups: a sweep with W_i in LDS, a workgroup per group of tiles, and the sweep again
+    (16-bit storage: the sweep from 17 on).  With 64 workgroups or more these graphs are one round: the same bits either way."""
+    cs = wide_case(n, 256, 2, 32, 1, "rms", ROW, dtype)
+    w, W = cs.w, cs.inp.weights[0]
+    Wd = torch.from_numpy(W).to(cs.dev)
+    dY = (np.random.default_rng(5).standard_normal((w.n, w.d)) * 1e-3).astype(np.float32)
+    dY = torch.from_numpy(dY).to(torch.bfloat16 if dtype == "bf16" else torch.float32).double().numpy()
+    Y = oracle.layer_forward(cs.og, cs.ocfg, W, cs.x0_on_grid())
+    got = []
+    for workgroups in (8, 0):
+        g = graph_cut_at_64(cs.inp.rowptr, cs.inp.colidx, workgroups)
+        y = cs.to_dev(cs.x0_on_grid())
+        gsr.gsr_layer_forward(g, cs.gcfg, Wd, y)
+        x, dy, dW = y.clone(), cs.to_dev(dY), torch.empty((w.c, w.dg, w.dg), dtype=torch.float32, device=cs.dev)
+        gsr.gsr_layer_backward(g, cs.gcfg, Wd, x, dy, dW)
+        got.append((y, x, dy, dW))
+    for a, b in zip(got[0][:3], got[1][:3]):
+        assert torch.equal(a, b)
+    y, x, dy, dW = got[0]
+    if dtype == "bf16":          # the first group's rows follow from identical inputs (16-bit near-ties make later rows select differently)
+        assert not bf16_bar(cs.to_host(y)[:, :w.dg], Y[:, :w.dg]).any()
+        return
+    assert_close("Y", cs.to_host(y), Y)
+    refs = oracle.layer_backward(cs.og, cs.ocfg, W, cs.to_host(y), dY)
+    for name, have, ref in zip(("X", "dX", "dW"), (cs.to_host(x), cs.to_host(dy), dW.cpu().numpy()), refs):
+        assert_close(name, have, ref)

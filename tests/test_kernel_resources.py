@@ -47,10 +47,10 @@ def test_no_kernel_spills_registers():
 
 
 # Registers that a launch rule or a measured figure counts on (a wave may have 512 / waves per SIMD of them): two workgroups of eight waves
-# beside each other on a compute unit in the products of three column blocks, and the sums over neighbours of 32 columns, whose sweep
+# beside each other on a compute unit in the products of two and three column blocks, and the sums over neighbours of 32 columns, whose sweep
 # slowed by a tenth at 93 registers.
 @pytest.mark.parametrize("kernel,most", [
-    ("k_wide_productILi3E", 128), ("k_wide_gradILi3E", 128),
+    ("k_wide_productILi2E", 128), ("k_wide_productILi3E", 128), ("k_wide_gradILi2E", 128), ("k_wide_gradILi3E", 128),
     ("k_spmm_tileILi32ELb0ELb0E", 80), ("k_spmm_tileILi32ELb1ELb0E", 80),
 ])
 def test_registers_that_residency_counts_on(kernel, most):
