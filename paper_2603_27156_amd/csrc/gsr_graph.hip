@@ -584,8 +584,8 @@ static gsr_status_t graph_create_impl(gsr_graph_t** out, int64_t n, int64_t nnz,
         const int64_t by_tiles = std::max<int64_t>(64, ((n + 15) / 16 / 2 + 7) / 8 * 8);
         if (by_tiles < g->grid) g->grid = (int)by_tiles;
     }
-    // The kernels that only gather (gsr_spmm, gsr_spmm_compressed, groups above 64 columns) hold at most 96 registers (two variants 104), so
-    // a fifth workgroup per compute unit stays resident; with many tiles per wave what they wait for is memory, with few the tiles that are
+    // The kernels that only gather (gsr_spmm, gsr_spmm_compressed, groups above 64 columns) hold at most 96 registers, so a fifth workgroup
+    // per compute unit stays resident (but for one variant of k_dense_planes, which gets the workgroups that do); with many tiles per wave what they wait for is memory, with few the tiles that are
     // left over.  Four / five workgroups, us: 1M rows (15 tiles per wave), dense product of 32 columns 137.5 / 126.3, of 64 186.1 / 180.2 (six: 181),
     // gsr_group_sparse and gsr_spmm_compressed, k = 16 283.6 / 280.1, 16 bits 284.4 / 278.8; 400k (6) 71.7 / 73.4, 86.6 / 90.0, 150.9 / 152.7,
     // 149.0 / 151.5; 100k 37.1 / 38.3, 41.8 / 42.6.

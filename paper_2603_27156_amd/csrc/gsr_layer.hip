@@ -2187,10 +2187,11 @@ static void launch_dense_planes(const Ctx<64, T>& x, bool transpose, const T* sr
     a.y_draws = kTileCounterSet;
     tile_counters(x.g, &a.draws, &a.draws_done);
     ProfScope prof(kc, x.s);
-    static const int per_cu = resident_blocks((const void*)k_dense_planes<T, false>);
-    const unsigned grid = std::max(8u, persistent_grid(x.g, per_cu, true) / (unsigned)x.S / 8 * 8);       // the resident workgroups shared out
-    if (heavy_first(a.g.n_heavy, x.tiles, grid)) hipLaunchKernelGGL((k_dense_planes<T, true>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
-    else hipLaunchKernelGGL((k_dense_planes<T, false>), dim3(grid, (unsigned)x.S), dim3(256), 0, x.s, a);
+    static const int plain_per_cu = resident_blocks((const void*)k_dense_planes<T, false>), deal_per_cu = resident_blocks((const void*)k_dense_planes<T, true>);
+    auto grid = [&](int per_cu) { return std::max(8u, persistent_grid(x.g, per_cu, true) / (unsigned)x.S / 8 * 8); };       // the resident workgroups shared out
+    const unsigned dealt = grid(deal_per_cu), plain = grid(plain_per_cu);
+    if (heavy_first(a.g.n_heavy, x.tiles, dealt)) hipLaunchKernelGGL((k_dense_planes<T, true>), dim3(dealt, (unsigned)x.S), dim3(256), 0, x.s, a);
+    else hipLaunchKernelGGL((k_dense_planes<T, false>), dim3(plain, (unsigned)x.S), dim3(256), 0, x.s, a);
 }
 
 // H of block `slot` + 1 into x.hplane(): the first pass over split rows, then the tiles

@@ -51,6 +51,8 @@ def test_no_kernel_spills_registers():
 # slowed by a tenth at 93 registers.
 @pytest.mark.parametrize("kernel,most", [
     ("k_wide_productILi2E", 128), ("k_wide_productILi3E", 128), ("k_wide_gradILi2E", 128), ("k_wide_gradILi3E", 128),
+    # five workgroups of four waves each (k_dense_planes of 16 bits that deals tiles out holds more and is launched with four)
+    ("k_spmm_tile", 96), ("k_aggregate_tile", 96), ("k_gather_wide", 96), ("k_dense_planesIfLb", 96), ("k_dense_planesINS_6bf16_tELb0E", 96),
     ("k_spmm_tileILi32ELb0ELb0E", 80), ("k_spmm_tileILi32ELb1ELb0E", 80),
 ])
 def test_registers_that_residency_counts_on(kernel, most):
