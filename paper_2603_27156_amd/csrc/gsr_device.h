@@ -1429,8 +1429,12 @@ struct TieSeg {
 };
 
 // The rows of a tile that a list names get the column sets kept with them instead of what the search found (see TieSeg), where the
-// record is taken: the tile's sub-list is short on a graph with few tiles per wave (a few dozen rows on 100k nodes), and its first 64 rows
-// are requested ahead with its length.  (As a launch after the record's, 4 us on 2,000 nodes and 6 us on 100k.)
+// record is taken: the tile's sub-list has few rows on a graph with few tiles per wave (a few dozen on 100k nodes), and its first 64 are
+// requested ahead with its length.  (As a launch after the record's, 4 us on 2,000 nodes and 6 us on 100k.)  Every tile walks its whole
+// sub-list, so with room for more than TIE_FIX_MOST rows there the launch stays.  Steps of four layers, two groups of 64, every row at a near-tie
+// so that the lists are full, launch / here, us: 30k nodes, 491 places per sub-list 648 / 625, 1,875 places 662 / 672; 60k, 182 places 871 / 854,
+// 725 places 872 / 888; 100k, 260 places 1,216 / 1,209, 1,038 places 1,225 / 1,286, 6,250 places 1,298 / 1,759.
+constexpr int TIE_FIX_MOST = 320;
 template <int DG, bool ON>
 struct TieFix {
     TieSeg<DG> seg;

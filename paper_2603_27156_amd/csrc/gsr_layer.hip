@@ -2438,8 +2438,9 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
     const bool given = x.saved != nullptr;
     // With few tiles per wave a launch is worth more than the work it takes along: dW_i's partials are summed beside the gradient's tiles
     // (first they would delay them: a 49,600-node graph with 3,100 tiles, +80 us on a 405 us kernel), and the rows
-    // listed in the forward sweep get their kept column sets back where the record is taken (TieFix) instead of in a launch after it.
-    const bool few_tiles = x.band || x.tiles < 4 * 4 * x.g->grid;
+    // listed in the forward sweep get their kept column sets back where the record is taken (TieFix, while the lists are short) instead of in
+    // a launch after it.
+    const bool few_tiles = x.tiles < 4 * 4 * x.g->grid, fix_here = few_tiles && x.tie_cap <= TIE_FIX_MOST;
     if (!slots_ready) launch_records<DG, T>(x, y, layer, given);
     for (int i = C; i >= 1; --i) {
         const float* wi = w + (size_t)(i - 1) * DG * DG;
@@ -2449,8 +2450,8 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
         else if (C == 2) { z = y.grp(1); ldz = y.ld; }      // Y_0 = X_2, rebuilt just before
         else {
             launch_sum<DG, T>(x, y.grp(1), y.ld, y.gs, C - 1, x.y0(), x.rec(0, layer), given, x.tie_seg(-1, 0),
-                              x.tie_seg(few_tiles ? layer : -1, 0));
-            if (!few_tiles) launch_tie_fixup<DG, T>(x, x.tie_seg(layer, 0), x.y0(), DG, x.rec(0, layer));
+                              x.tie_seg(fix_here ? layer : -1, 0));
+            if (!fix_here) launch_tie_fixup<DG, T>(x, x.tie_seg(layer, 0), x.y0(), DG, x.rec(0, layer));
             z = x.y0(); ldz = DG;
         }
         Record<DG, T> out = x.rec(-1);
@@ -2474,7 +2475,7 @@ static void layer_backward_impl(const Ctx<DG, T>& x, const float* w, const Plane
                                 TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, x.hplane());
             nparts = launch_dw<DG, T>(x, dy.grp(i - 1), dy.ld, out_tie, y.grp(i - 1), y.ld, out.mask ? &out : nullptr);
         } else {
-            const bool fix = few_tiles && out.mask;
+            const bool fix = fix_here && out.mask;
             nparts = launch_block<DG, T>(x, 2, x.rec(i - 1, layer), wi, y.grp(i - 1), y.ld, out, given, dy.grp(i - 1), dy.ld, true,
                                          TieSeg<DG>{nullptr, nullptr, nullptr, 0, 0.f}, nullptr, fix ? out_tie : x.tie_seg(-1, 0));
             if (out.mask && !fix) launch_tie_fixup<DG, T>(x, out_tie, y.grp(i - 1), y.ld, out);

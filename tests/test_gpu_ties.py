@@ -119,3 +119,19 @@ def test_workspace_with_near_tie_list():
         gsr.gsr_workspace_size(c.gg, gsr.Config(**{**c.gcfg.__dict__, "save_indices": 2, "tie_tol": -1.0}))
     with pytest.raises(gsr.GsrError):
         gsr.gsr_workspace_size(c.gg, gsr.Config(**{**c.gcfg.__dict__, "save_indices": 3}))
+
+
+@pytest.mark.parametrize("c,dg,k,dtype", [(2, 64, 16, "f32"), (4, 64, 48, "f32"), (3, 32, 8, "f32"), (8, 32, 8, "bf16"), (3, 64, 16, "bf16")])
+def test_listed_rows_restored_with_the_record_and_in_a_launch_of_their_own(c, dg, k, dtype):
+    """Up to 320 places per sub-list the listed rows get their sets back where the record is taken, beyond in a launch after it.  Every row
+    listed (4,001 rows: 256 in most sub-lists, four rounds of 64) both must equal the step that keeps all indices; the room alone chooses."""
+    w = synth.scaled(synth.workload(4 if dtype == "bf16" else 2), 4001, l=3, d=c * dg, c=c, k=k)
+    cs = Case(w, 0, ROW)
+    saved = run_step(cs, raw=True, save_indices=1)
+    for capacity in (16 * 320, 16 * 320 + 1):
+        keep = {}
+        listed = run_step(cs, raw=True, save_indices=2, tie_tol=1e30, tie_capacity=capacity, keep=keep)
+        st = gsr.gsr_step_tie_stats(cs.gg, keep["cfg"], keep["ws"])
+        assert st["dropped"] == 0 and st["max_per_block"] == w.n
+        for key in saved:
+            assert torch.equal(listed[key], saved[key]), (capacity, key)
