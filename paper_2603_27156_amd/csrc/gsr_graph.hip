@@ -270,19 +270,29 @@ static void transpose_host(int64_t n, const HostCsr& a, HostCsr* t) {
 // recorded columns, us, graphs of mean degree 236 in a band of 5,952 rows: 8,000 nodes (32 rows per workgroup, 1.2 entries per staged row)
 // D/C = 32, k = 8 336 / 284, 64, k = 16 398 / 410, 128, k = 42 431 / 447; 12,000 (1.7) 415 / 338, 495 / 473, 560 / 545; 20,000 (2.8)
 // 580 / 445, 693 / 599, 794 / 761; 49,600 (6.6) 1,244 / 848, 1,507 / 1,145, 1,761 / 1,544, two groups of 192, k = 16 1,770 / 1,090.
+// The launch ends with its largest workgroup, so none may stage more than half as much again as the mean, unless all of them at that size
+// would still be the faster form, and no sixteen lanes of one may have more than four times the mean to add up.  The same layers (49,600 / 16,000 nodes, whole rows / recorded
+// columns) with one row that reaches every node: two groups of 192 1,802 / 4,063, 715 / 1,397, four of 64 1,538 / 6,122, 593 / 1,962; one
+// net over the whole graph with 100 sinks: 64 1,493 / 1,640, 565 / 632; a row of 1,000 entries in the band: 64 1,492 / 1,182, 573 / 565, of 2,000:
+// 1,506 / 1,275, 586 / 668, of 4,000: 1,504 / 1,431, 591 / 835 (a group's mean is 714 and 231 entries).
 static int band_rows_of(const HostCsr& m, int64_t n, int workgroups) {
-    const int64_t rows = std::min<int64_t>(256, std::max<int64_t>(1, (n + workgroups - 1) / workgroups));
-    int64_t staged = 0;
+    const int64_t rows = std::min<int64_t>(256, std::max<int64_t>(1, (n + workgroups - 1) / workgroups)), blocks = (n + rows - 1) / rows;
+    int64_t staged = 0, most_staged = 0, most_added = 0;
     for (int64_t r0 = 0; r0 < n; r0 += rows) {
-        int64_t lo = n, hi = 0;
+        int64_t lo = n, hi = 0, added[64] = {};          // (lanes 16 i .. 16 i + 15 of a workgroup own its rows i, i + 64, ..)
         for (int64_t r = r0; r < std::min(n, r0 + rows); ++r)
             if (m.rp[r + 1] > m.rp[r]) {
                 lo = std::min<int64_t>(lo, m.ci[m.rp[r]]);
                 hi = std::max<int64_t>(hi, m.ci[m.rp[r + 1] - 1] + 1);
+                int64_t& sum = added[(r - r0) & 63];
+                most_added = std::max(most_added, sum += m.rp[r + 1] - m.rp[r]);
             }
         staged += std::max<int64_t>(0, hi - lo);
+        most_staged = std::max(most_staged, hi - lo);
     }
-    return 5 * (int64_t)m.ci.size() >= 8 * staged ? (int)rows : 0;
+    const int64_t nnz = (int64_t)m.ci.size();
+    const bool even = 2 * most_staged * blocks <= 3 * staged || 5 * nnz >= 8 * most_staged * std::min<int64_t>(blocks, workgroups);
+    return 5 * nnz >= 8 * staged && even && most_added * blocks * std::min<int64_t>(rows, 64) <= 4 * nnz ? (int)rows : 0;
 }
 
 // The tile counters of a graph's dynamic sweeps and, behind them, the nine counters its waves sign off

@@ -106,3 +106,63 @@ def test_band_backward_on_a_directed_weighted_graph(c, dg, k, workgroups):
     assert_close("X", y.cpu().numpy(), X_ref)
     assert_close("dX", dy.cpu().numpy(), dX_ref)
     assert_close("dW", dW.cpu().numpy(), dW_ref)
+
+
+def graph_of(rowptr, colidx, workgroups=0):
+    gsr.gsr_set_option("max_workgroups", workgroups)
+    try:
+        return gsr.gsr_graph_create(rowptr, colidx)
+    finally:
+        gsr.gsr_set_option("max_workgroups", 0)
+
+
+def with_rows(rowptr, colidx, more):
+    """The graph with further entries: {row: columns}."""
+    n = len(rowptr) - 1
+    key = np.repeat(np.arange(n, dtype=np.int64), np.diff(rowptr)) * n + colidx
+    key = np.unique(np.concatenate([key] + [np.full(len(c), r, dtype=np.int64) * n + c for r, c in more.items()]))
+    return np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))]).astype(np.int32), (key % n).astype(np.int32)
+
+
+def layer_bytes(g, n):
+    """Of a configuration that gathers recorded columns wherever the graph lets it: two float32 planes more where it does."""
+    return gsr.gsr_workspace_size(g, gsr.Config(n=n, d=128, c=2, k=16, l=1))[0]
+
+
+def takes_band(rowptr, colidx, workgroups=0):
+    n = len(rowptr) - 1
+    hub = with_rows(rowptr, colidx, {r: np.arange(r + 1, n) for r in (0, 64, 128)})      # nodes next to every other: whole rows are gathered
+    more = layer_bytes(graph_of(rowptr, colidx, workgroups), n) - layer_bytes(graph_of(*hub, workgroups), n)
+    plane = n * 64 * 4
+    assert abs(more) < plane // 4 or abs(more - 2 * plane) < plane // 4          # (beside them a few rows of chunk sums)
+    return more > plane
+
+
+@pytest.mark.parametrize("workgroups", [0, 8])
+@pytest.mark.parametrize("n,half,keep,seed", [(1201, 60, 1.0, 40), (1537, 50, 1.0, 48), (1300, 70, 0.9, 80), (1205, 80, 1.0, 161), (1900, 300, 0.5, 208),
+                                              (1210, 60, 1.0, 256), (1200, 60, 1.0, 273)])
+def test_the_graphs_above_are_gathered_by_recorded_columns(n, half, keep, seed, workgroups):
+    assert takes_band(*band_graph(n, half, keep, seed), workgroups)
+
+
+def test_graphs_with_a_workgroup_or_a_row_far_above_the_mean_are_gathered_by_whole_rows():
+    """The gather ends with its largest workgroup: a net over the whole graph makes one stage every row, and a row several times as long as the
+    others is added up by sixteen lanes."""
+    n, half = 3000, 300
+    rowptr, colidx = band_graph(n, half, 0.22, 7)
+    rng = np.random.default_rng(2)
+    near = lambda c, count: {c: np.setdiff1d(c - half + rng.permutation(2 * half)[:count], [c])}
+    assert takes_band(rowptr, colidx)
+    assert takes_band(*with_rows(rowptr, colidx, near(1500, 200)))          # (a row of some 300 entries, the mean has 130)
+    assert not takes_band(*with_rows(rowptr, colidx, near(1500, 600)))      # .. of 600
+    assert not takes_band(*with_rows(rowptr, colidx, {20: np.arange(100, n, 200)}))
+    far = with_rows(rowptr, colidx, {20: np.arange(100, n, 200), **near(1500, 600)})
+    og, g = oracle.graph_build(*far), graph_of(*far)
+    c, dg, k = 2, 64, 16
+    W = ((rng.random((c, dg, dg)) * 2 - 1) * np.sqrt(3.0 / dg)).astype(np.float32)
+    Y, dY = rng.standard_normal((n, c * dg)).astype(np.float32), (rng.standard_normal((n, c * dg)) * 1e-3).astype(np.float32)
+    refs = oracle.layer_backward(og, oracle.Cfg(c * dg, c, k, oracle.NORM_RMS, 1e-5, oracle.STORE_F32), W, Y.astype(np.float64), dY.astype(np.float64))
+    y, dy, dW = torch.from_numpy(Y).cuda(), torch.from_numpy(dY).cuda(), torch.empty((c, dg, dg), dtype=torch.float32, device="cuda")
+    gsr.gsr_layer_backward(g, gsr.Config(n=n, d=c * dg, c=c, k=k, l=1, norm=gsr.GSR_NORM_RMS, eps=1e-5), torch.from_numpy(W).cuda(), y, dy, dW)
+    for name, got, ref in zip(("X", "dX", "dW"), (y, dy, dW), refs):
+        assert_close(name, got.cpu().numpy(), ref)
