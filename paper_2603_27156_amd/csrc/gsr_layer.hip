@@ -1260,6 +1260,35 @@ __global__ __launch_bounds__(512) void k_pre_product(PreProductArgs<DG, S, T> a)
                 for (int reg = 0; reg < 4; ++reg) acc[mb][cb][reg] += sum[cb][reg];
         }
     }
+    if constexpr (S == 1) {
+        // The terms of an infinity (inf - inf is one of them) add up to a NaN.  The gather of whole rows multiplies groups of up to 64 columns
+        // by the float32 instructions, which keep it, so what came out as no number is multiplied again in ordinary arithmetic.
+        bool finite = true;
+#pragma unroll
+        for (int cb = 0; cb < CPL; ++cb)
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) finite = finite && __builtin_isfinite(acc[0][cb][reg]);
+        if (ballot(!finite) != 0) {
+            float sum[4][CPL] = {};
+#pragma unroll 1
+            for (int o = 0; o < DG; ++o) {
+                float d[4], w[CPL];
+#pragma unroll
+                for (int reg = 0; reg < 4; ++reg) d[reg] = to_float(a.dy[(size_t)min(r0 + 4 * reg + tg, a.n - 1) * a.ld + o]);
+#pragma unroll
+                for (int cb = 0; cb < CPL; ++cb) w[cb] = a.w[(size_t)(CPL * tj + cb) * DG + o];
+#pragma unroll
+                for (int reg = 0; reg < 4; ++reg)
+#pragma unroll
+                    for (int cb = 0; cb < CPL; ++cb) sum[reg][cb] = __builtin_fmaf(d[reg], w[cb], sum[reg][cb]);
+            }
+#pragma unroll
+            for (int cb = 0; cb < CPL; ++cb)
+#pragma unroll
+                for (int reg = 0; reg < 4; ++reg)
+                    if (!__builtin_isfinite(acc[0][cb][reg])) acc[0][cb][reg] = __uint_as_float(__float_as_uint(sum[reg][cb]) ^ flip_out);
+        }
+    }
 #pragma unroll
     for (int mb = 0; mb < S; ++mb)
 #pragma unroll

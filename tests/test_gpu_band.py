@@ -166,3 +166,37 @@ def test_graphs_with_a_workgroup_or_a_row_far_above_the_mean_are_gathered_by_who
     gsr.gsr_layer_backward(g, gsr.Config(n=n, d=c * dg, c=c, k=k, l=1, norm=gsr.GSR_NORM_RMS, eps=1e-5), torch.from_numpy(W).cuda(), y, dy, dW)
     for name, got, ref in zip(("X", "dX", "dW"), (y, dy, dW), refs):
         assert_close(name, got.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dg,k", [(32, 8), (64, 16)])
+def test_an_infinity_in_the_gradient_stays_one(dg, k, dtype):
+    """dY_2 with one infinite entry: dZ of its neighbours is infinite, with the sign of the weight, at the recorded columns, and a number
+    everywhere else, as in ordinary arithmetic."""
+    n, half, c = 1300, 70, 2
+    rowptr, colidx = band_graph(n, half, 0.9, dg + k)
+    assert takes_band(rowptr, colidx)
+    og, g = oracle.graph_build(rowptr, colidx), graph_of(rowptr, colidx)
+    f32 = dtype == "f32"
+    tdt = torch.float32 if f32 else torch.bfloat16
+    rng = np.random.default_rng(11)
+    W = ((rng.random((c, dg, dg)) * 2 - 1) * np.sqrt(3.0 / dg)).astype(np.float32)
+    W[:, ::2] = np.round(W[:, ::2] * 8) / 8          # (exact in one 16-bit term, the others zero ..
+    W[W == 0] = 0.125                                # .. but no weight is zero)
+    Y = torch.from_numpy(rng.standard_normal((n, c * dg)).astype(np.float32)).to(tdt)
+    dY = torch.from_numpy((rng.standard_normal((n, c * dg)) * 1e-3).astype(np.float32)).to(tdt)
+    dY[601, dg + 5] = float("inf")
+    dY[602, dg + 5] = float("inf")
+    ref = oracle.layer_backward(og, oracle.Cfg(c * dg, c, k, oracle.NORM_NONE, 1e-5, oracle.STORE_F32 if f32 else oracle.STORE_BF16), W,
+                                Y.double().numpy(), dY.double().numpy())[1][:, :dg]
+    dy, dW = dY.cuda(), torch.empty((c, dg, dg), dtype=torch.float32, device="cuda")
+    cfg = gsr.Config(n=n, d=c * dg, c=c, k=k, l=1, dtype=gsr.GSR_F32 if f32 else gsr.GSR_BF16, norm=gsr.GSR_NORM_NONE)
+    gsr.gsr_layer_backward(g, cfg, torch.from_numpy(W).cuda(), Y.cuda(), dy, dW)
+    got = dy.cpu().double().numpy()[:, :dg]          # group 1 has been added to by block 2 alone
+    assert np.isinf(ref).sum() > 1000 and not np.isnan(ref).any()
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+    rest = ~np.isinf(ref)
+    if f32:
+        assert_close("dX", got[rest], ref[rest])
+    else:
+        assert rel_norm(got[rest], ref[rest]) <= BF16_REL
