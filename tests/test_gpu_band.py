@@ -6,7 +6,9 @@ import pytest
 
 import oracle
 import paper_2603_27156_amd as gsr
-from gpu_util import BF16_REL, NORM, assert_close, rel_norm
+from paper_2603_27156_amd import synth
+from gpu_util import BF16_REL, NORM, Case, assert_close, rel_norm
+from test_gpu_layer import run_step
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -166,6 +168,82 @@ def test_graphs_with_a_workgroup_or_a_row_far_above_the_mean_are_gathered_by_who
     gsr.gsr_layer_backward(g, gsr.Config(n=n, d=c * dg, c=c, k=k, l=1, norm=gsr.GSR_NORM_RMS, eps=1e-5), torch.from_numpy(W).cuda(), y, dy, dW)
     for name, got, ref in zip(("X", "dX", "dW"), (y, dy, dW), refs):
         assert_close(name, got.cpu().numpy(), ref)
+
+
+def band_case(n, half, keep, c, dg, k, l=3):
+    """A stack of layers on a band graph: inputs as drawn for the other stacks, the graph in their place."""
+    w = synth.scaled(synth.workload(2), n, l=l, d=c * dg, c=c, k=k)
+    cs = Case(w, 0, gsr.GSR_LAYOUT_ROW_MAJOR)
+    rowptr, colidx = band_graph(n, half, keep, dg + k)
+    assert takes_band(rowptr, colidx)
+    cs.og, cs.gg = oracle.graph_build(rowptr, colidx), graph_of(rowptr, colidx)
+    return cs
+
+
+STACKS = [(1300, 70, 0.9, 2, 64, 16), (1300, 70, 0.9, 3, 64, 16), (1201, 60, 1.0, 2, 32, 8), (1201, 60, 1.0, 4, 32, 8), (1900, 300, 0.5, 2, 192, 16),
+          (1210, 60, 1.0, 3, 128, 20)]
+
+
+@pytest.mark.parametrize("save", [0, 1, 2])
+@pytest.mark.parametrize("n,half,keep,c,dg,k", STACKS)
+def test_step_on_a_band_graph_against_oracle(n, half, keep, c, dg, k, save):
+    """The records of the layer below go into the slots beside those the band gather reads; kept sets come with rebuilt values; the lowest layer
+    leaves no record."""
+    if save == 2 and dg > 64:
+        pytest.skip("the near-tie list is for groups of at most 64 columns")
+    cs, tol = band_case(n, half, keep, c, dg, k), 2.0 ** -6
+    w = cs.w
+    keys = ("yhat", "XL", "X0rec", "dW", "dwout", "dX0")
+    ref = oracle.step(cs.og, cs.ocfg, w.l, cs.x0_on_grid(), cs.inp.weights, cs.inp.w_out, cs.inp.b_out, cs.inp.target, variant={0: 0, 1: 2, 2: 3}[save],
+                      tie_tol=tol, want=keys)
+    more = dict(tie_tol=tol, tie_capacity=16 * 320) if save == 2 else {}
+    out = run_step(cs, save_indices=save, **more)
+    assert np.isclose(out["loss"], ref["loss"], rtol=1e-4)
+    for key in keys:
+        assert_close(key, out[key], ref[key])
+
+
+@pytest.mark.parametrize("n,half,keep,c,dg,k", [s for s in STACKS if s[4] <= 64])
+def test_step_on_a_band_graph_with_every_row_listed(n, half, keep, c, dg, k):
+    """Listed rows restored with the record (up to 320 places per sub-list) and in a launch after it equal the step that keeps all indices."""
+    cs = band_case(n, half, keep, c, dg, k)
+    saved = run_step(cs, raw=True, save_indices=1)
+    for capacity in (16 * 320, 16 * 321):
+        listed = run_step(cs, raw=True, save_indices=2, tie_tol=1e30, tie_capacity=capacity)
+        for key in saved:
+            assert torch.equal(listed[key], saved[key]), (capacity, key)
+
+
+@pytest.mark.parametrize("save,c,dg,k", [(0, 2, 192, 16), (1, 3, 64, 16), (2, 2, 64, 16)])
+def test_step_on_a_band_graph_replays_from_a_graph(save, c, dg, k):
+    """Every replay, with eager work and synchronisations between them, gives the eager step's bits."""
+    cs = band_case(1900 if dg == 192 else 1300, 300 if dg == 192 else 70, 0.5 if dg == 192 else 0.9, c, dg, k)
+    want = run_step(cs, raw=True, save_indices=save)
+    w, dv = cs.w, cs.dev
+    cfg = gsr.Config(**{**cs.gcfg.__dict__, "save_indices": save})
+    one = dict(dtype=torch.float32, device=dv)
+    x0, W = cs.to_dev(cs.inp.x0), torch.from_numpy(np.ascontiguousarray(cs.inp.weights[:w.l])).to(dv)
+    w_out, target, b_out = torch.from_numpy(cs.inp.w_out).to(dv), torch.from_numpy(cs.inp.target).to(dv), torch.tensor([cs.inp.b_out], **one)
+    out = dict(loss=torch.zeros(1, **one), dW=torch.empty_like(W), dwout=torch.empty(w.d, **one), dbout=torch.zeros(1, **one),
+               yhat=torch.empty(w.n, **one), dX0=torch.empty_like(x0), X0rec=torch.empty_like(x0))
+    ws = torch.empty(gsr.gsr_workspace_size(cs.gg, cfg)[1], dtype=torch.uint8, device=dv)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            gsr.gsr_step(cs.gg, cfg, x0, W, w_out, b_out, target, out["loss"], out["dW"], out["dwout"], out["dbout"], yhat_out=out["yhat"],
+                         dx0_out=out["dX0"], x0_rebuilt_out=out["X0rec"], workspace=ws)
+    for rep in range(3):
+        for v in out.values():
+            v.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for key, v in out.items():
+            assert torch.equal(v, want[key]), (rep, key)
+        again = run_step(cs, raw=True, save_indices=save)          # eager work between the replays
+        for key in want:
+            assert torch.equal(again[key], want[key]), (rep, key)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
