@@ -55,6 +55,12 @@ def kernel_class(name: str):
         return "gsr_spmm_compressed"
     if "k_slot_tile<" in name:
         return "slot_block"
+    # groups above 64 columns, and the gradient on graphs of long rows in a band
+    for kernel, kc in (("k_gather_wide<", "wide_gather"), ("k_dense_planes<", "wide_dense_gather"), ("k_wide_product", "wide_product"),
+                       ("k_wide_grad", "wide_grad"), ("k_gs_wide<", "wide_group_sparse"), ("k_pre_product<", "band_product"),
+                       ("k_band_gather<", "band_gather"), ("k_band_back<", "band_back")):
+        if kernel in name:
+            return kc
     return None
 
 
