@@ -1316,9 +1316,9 @@ constexpr int BAND_FLOATS = 18432;              // of a window: 73,728 bytes, a 
 // into LDS).  The entries of a row are in ascending column order, so those of a window follow those of the one before; sixteen
 // of them at a time sit in the lanes of the group (row_lane hands them out), the next sixteen are requested when it is known how many of these
 // the window took.  A window's entries are summed from zero, eight windows' sums from zero again, which bounds the length of the
-// chains of additions.  Places past the window's entries read a row of zeros.  50k nodes of mean degree 236, 192 columns: 178 us, 94 of them for
-// the windows alone (1.2 GB into LDS) and 139 for the sums alone, which the LDS bounds: a read takes some 13 cycles, its 64 columns
-// collide on banks, and a third of the places are past the end of the shorter of four groups' runs (all rows' first eight
+// chains of additions.  Places past the window's entries read a row of zeros.  50k nodes of mean degree 236, 192 columns: 173 us, 94 of them for
+// the windows alone (1.2 GB into LDS) and 139 for the sums alone, which the LDS bounds: 6.1M reads counted, 16 cycles of a compute unit each over the
+// launch, 4.5 of them bank conflicts of the 64 columns; 2.9M would do if the runs of four groups were equally long and whole fours (all rows' first eight
 // places read before the first is added, a quarter more reads: 217).
 template <int DGW, int KQ>
 __global__ __launch_bounds__(1024) void k_band_gather(BandGatherArgs a) {
